@@ -125,7 +125,7 @@ int ee_session_create(ee_model* m, int batch, int max_ctx, int max_rows, int tot
 void ee_session_free(ee_session* s);
 
 /* Context build.  tokens: host, the prompts packed back to back; lens: host [batch], each >= 1.
- * Runs all L_f layers over every prompt in passes of up to 512 rows (64 for EE_F32 models): a long prompt fills
+ * Runs all L_f layers over every prompt in passes of up to 4096 rows (64 for EE_F32 models): a long prompt fills
  * passes by itself, short prompts share one; leaves all group lengths at
  * lens[b], and commits first_token[b] = arg max at L_f of the last prompt position
  * (the "Vanilla generation" step of Sec. 3.1).  first_token: host [batch]. */
@@ -264,7 +264,8 @@ int ee_get_lengths(const ee_session* s, int32_t* len_by_batch);   /* host [batch
 int ee_n_levels(const ee_session* s);   /* verifier exits after L_d: 2 (L_i, L_f) plus the model's extra exits */
 int ee_get_counts(const ee_session* s, int32_t* n_committed, int32_t* n_tentative); /* [batch] each */
 int ee_get_tokens(const ee_session* s, int seq, int32_t* out, int cap, int32_t* n_out); /* T = C||V */
-/* When enabled, every exit-head call also stores full fp32 logits for its rows. */
+/* When enabled, every exit-head call also stores full fp32 logits for its rows.  After a context build the two calls
+ * below report the rows of its last 512-row piece (the tokens of all prompts counted in order; EE_F32: of its last pass). */
 int ee_debug_enable_logits(ee_session* s, int on);
 int ee_debug_last_logits(ee_session* s, float* host_out, int max_rows, int32_t* n_rows);  /* [rows, vocab] */
 int ee_debug_last_hidden(ee_session* s, float* host_out, int max_rows, int32_t* n_rows);  /* [rows, d]     */

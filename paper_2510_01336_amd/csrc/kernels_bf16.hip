@@ -29,16 +29,17 @@ __device__ inline uint32_t pack2(float lo, float hi) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// RMSNorm: fp32 row in, bf16 fragment-layout row out (the next GEMM's B operand)
+// RMSNorm of listed rows: fp32 row idx[r] in, bf16 fragment-layout row r out (the operand of an exit head that serves only
+// the rows that decide a token)
 // ---------------------------------------------------------------------------------------------
 // One workgroup per row; the row is read once as float4 into registers (all loads issued before the
 // first use), reduced, scaled, and written as 8-byte bf16 quads (4 consecutive k share a fragment lane).
 template <int CH>   // float4 chunks per thread: d <= 4 * 256 * CH
-__global__ __launch_bounds__(256) void bf16_rmsnorm_kernel(const float* __restrict__ X, const float* __restrict__ g, float eps,
-                                                           bf16_t* __restrict__ out, int ktiles, int d) {
+__global__ __launch_bounds__(256) void bf16_rmsnorm_kernel(const float* __restrict__ X, const int* __restrict__ idx,
+                                                           const float* __restrict__ g, float eps, bf16_t* __restrict__ out, int ktiles, int d) {
   __shared__ float part[4];
   const int r = blockIdx.x, nch = d >> 2;
-  const float4* x4 = (const float4*)(X + (size_t)r * d);
+  const float4* x4 = (const float4*)(X + (size_t)idx[r] * d);
   const float4* g4 = (const float4*)g;
   float4 xv[CH], gv[CH];
 #pragma unroll
@@ -64,11 +65,11 @@ __global__ __launch_bounds__(256) void bf16_rmsnorm_kernel(const float* __restri
     }
   }
 }
-void bf16_rmsnorm(hipStream_t st, const float* X, const float* g, float eps, bf16_t* out, int ktiles, int M, int d) {
+void bf16_rmsnorm(hipStream_t st, const float* X, const int* idx, const float* g, float eps, bf16_t* out, int ktiles, int M, int d) {
   // d is a multiple of 16 for bf16 models (checked at model load), so float4 access is aligned
-  if (d <= 1024) hipLaunchKernelGGL((bf16_rmsnorm_kernel<1>), dim3(M), dim3(256), 0, st, X, g, eps, out, ktiles, d);
-  else if (d <= 4096) hipLaunchKernelGGL((bf16_rmsnorm_kernel<4>), dim3(M), dim3(256), 0, st, X, g, eps, out, ktiles, d);
-  else hipLaunchKernelGGL((bf16_rmsnorm_kernel<16>), dim3(M), dim3(256), 0, st, X, g, eps, out, ktiles, d);
+  if (d <= 1024) hipLaunchKernelGGL((bf16_rmsnorm_kernel<1>), dim3(M), dim3(256), 0, st, X, idx, g, eps, out, ktiles, d);
+  else if (d <= 4096) hipLaunchKernelGGL((bf16_rmsnorm_kernel<4>), dim3(M), dim3(256), 0, st, X, idx, g, eps, out, ktiles, d);
+  else hipLaunchKernelGGL((bf16_rmsnorm_kernel<16>), dim3(M), dim3(256), 0, st, X, idx, g, eps, out, ktiles, d);
 }
 
 // The first kernel of a pass over layers, one workgroup per row: brings the row into the residual stream X -- from the
@@ -532,21 +533,14 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
   // TMT*16 rows that blockIdx.z names; the deferred-norm factors and the K-share partials are indexed from row0,
   // everything the epilogue touches by the row itself
   constexpr int NB = (EPI == EPI_SWIGLU || EPI == EPI_ROPE) ? 2 : 1;
-  static_assert(TN == 2 || TN == 4 || TN == 8, "weight tiles per wave");
-  // TN = 8 (sixteen weight tiles per workgroup, rows in two blocks): the grid is one-dimensional and workgroups L and
-  // L + 8 are the two row blocks of one column group -- dispatched together and on the same XCD (L mod 8), so the
-  // weights cross HBM once and the second reader finds them in that XCD's L2
-  const int bx = TN == 8 ? (int)(((blockIdx.x >> 4) << 3) | (blockIdx.x & 7)) : (int)blockIdx.x;
-  const int bz = TN == 8 ? (int)((blockIdx.x >> 3) & 1) : (int)blockIdx.z;
-  if (TN == 8 && (bx * (2 * TN) >= ntiles || bz * (TMT * 16) >= M_all)) return;       // whole workgroup
-  const int rbase = bz * (TMT * 16), M = min(M_all - rbase, TMT * 16);
+  static_assert(TN == 2 || TN == 4, "weight tiles per wave");
+  const int bx = blockIdx.x, rbase = blockIdx.z * (TMT * 16), M = min(M_all - rbase, TMT * 16);
   constexpr int TMW = TMT / 4;                      // row tiles per wave
   static_assert(TMT % 4 == 0 && TMT >= 4 && TMT <= 32, "row tiles split four ways");
   constexpr int STAGE = (2 * TN + TMT) * 64;        // 16-byte units: weight tiles first, then row tiles
   constexpr int S = (160 / (2 * TN + TMT)) & ~1;    // stages in the ring: what 160 KiB of LDS holds (even: fragments alternate between two register sets)
   constexpr int XHI = (TMT + 7) / 8;                // row tiles a wave requests per stage at most: wave, wave+8, ...
-  constexpr int WHI = TN == 8 ? 2 : 1;              // weight tiles a wave requests per stage: wave (and wave+8)
-  constexpr int LHI = WHI + XHI;                    // requests per stage at most
+  constexpr int LHI = 1 + XHI;                      // requests per stage at most (one weight tile, XHI row tiles)
   static_assert((S - 1) * LHI < 64, "the load counter has six bits");
   __shared__ u32x4 ring[S][STAGE];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -586,14 +580,12 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
   const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(lptr_t)&ring[0][0]) + 1024u * wave_s;
 #define ROWS_LDS(slot_, tile_) ((lptr_t)(size_t)(lds0 + 16u * ((slot_) * STAGE + (tile_) * 64)))
   const u32x4* wsrc = (const u32x4*)W + (size_t)min(bx * (2 * TN) + wave, ntiles - 1) * ktiles * 64 + lane;
-  const u32x4* wsrc2 = (const u32x4*)W + (size_t)min(bx * (2 * TN) + wave + 8, ntiles - 1) * ktiles * 64 + lane;   // (TN = 8)
   const u32x4* xsrc = (const u32x4*)A + (size_t)(((row0 + rbase) >> 4) + wave) * ktiles * 64 + lane;
-  // (weights: streaming hint, except where a second workgroup is to find them in L2)
+  // (weights: streaming hint)
 #define ROWS_REQUEST(slot_, kt_)                                                                              \
   do {                                                                                                        \
     const size_t k_ = (size_t)min(kt_, last) * 64;                                                            \
     if (wreq) __builtin_amdgcn_global_load_lds((gptr_t)(wsrc + k_), ROWS_LDS(slot_, 0), 16, 0, 2);                \
-    if (TN == 8) __builtin_amdgcn_global_load_lds((gptr_t)(wsrc2 + k_), ROWS_LDS(slot_, 8), 16, 0, 2);        \
     _Pragma("unroll") for (int j = 0; j < XHI - 1; ++j)                                                       \
       __builtin_amdgcn_global_load_lds((gptr_t)(xsrc + (size_t)(8 * j) * ktiles * 64 + k_),                   \
                                        ROWS_LDS(slot_, 2 * TN + 8 * j), 16, 0, 0);                            \
@@ -693,6 +685,147 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
       epi_apply<EPI>(acc[t * NB][mt], acc[t * NB + NB - 1][mt], sc, pre, out, task, row0 + rbase + m, m < M, N, lane);
     }
   }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Blocked GEMM for calls of more than 256 rows (context build, large batches): the ring of direct global->LDS stages of
+// the kernel above, but the rows are cut into blocks of 256 and the weights into groups of 2*TN tiles, and one launch covers
+// all blocks.  blockIdx.x enumerates them so that every XCD (workgroup id mod 8) works on consecutive ones, row blocks
+// fastest: the row blocks of a weight group run side by side and read its weights from one L2.
+// What bounds it: with sixteen weight tiles a k-tile is 1024 clocks of MFMAs per SIMD, 128 KiB of LDS traffic (1000 clocks)
+// and 32 KiB of requests, and the clock gives way under that load: 1365 TFLOP/s on the gate/up matrix at 4096 rows (705 us;
+// passes of 512 rows in the previous form 812 us), 1265 at 2048 rows.  Narrow matrices take 12 or 8 weight tiles so that the
+// blocks of a pass fill the chip without K shares: QKV at 2048 rows 95 us (four passes of 512 rows 174), O 67 (127), down
+// 188 (300).
+// K is never shared out: a row's sums run over K in one order in every form and for every row count, so its result does
+// not depend on the rows beside it (K shares of the down projection would gain 154 -> 127 us at 1096 rows, nothing from 2048).
+// ---------------------------------------------------------------------------------------------
+template <int EPI, int TN, bool FULL>
+__device__ __forceinline__ void gemm_block_body(u32x4* ring, const uint4* __restrict__ W, int ktiles, int ntiles, const uint4* __restrict__ A,
+                                                int row0, int rbase, int M, int N, const GemmOut& out, int bx) {
+  constexpr int NB = (EPI == EPI_SWIGLU || EPI == EPI_ROPE) ? 2 : 1;
+  static_assert(TN % NB == 0, "a task's tiles stay in one wave");
+  constexpr int TMT = 16, WT = 2 * TN, TMW = TMT / 4, TILES = WT + TMT, STAGE = TILES * 64;
+  constexpr int S = (160 / TILES) & ~1;             // stages in the ring (even: fragments alternate between two register sets)
+  constexpr int NJ = (TILES + 7) / 8;               // requests per wave and stage at most: tiles wave, wave + 8, ... (weights first)
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+  const int rq = wave_s >> 1, nh = wave_s & 1;
+  const int rqv = wave >> 1, nhv = wave & 1;      // (the same from the vector register: one address serves all LDS reads)
+  const int nt0 = bx * WT + nh * TN;
+  constexpr int MT_STEP = FULL ? 1 : 4;             // a partly filled block deals its row tiles round, a full one in runs
+  const int mt_first = FULL ? rq * TMW : rq;
+  const int mt_used = FULL ? TMT : (M + 15) >> 4;
+  const int last = ktiles - 1;
+  f32x4 acc[TN][TMW];
+#pragma unroll
+  for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+    for (int mt = 0; mt < TMW; ++mt) acc[tn][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  typedef const __attribute__((address_space(1))) void* gptr_t;
+  typedef __attribute__((address_space(3))) void* lptr_t;
+  const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(lptr_t)ring) + 1024u * wave_s;
+  const u32x4* src[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const int t = wave_s + 8 * j;
+    const size_t tile = t < WT ? (size_t)min(bx * WT + t, ntiles - 1) : (size_t)(((row0 + rbase) >> 4) + t - WT);
+    src[j] = (t < WT ? (const u32x4*)W : (const u32x4*)A) + tile * ktiles * 64 + lane;
+  }
+  // requests of this wave per stage: its tiles that exist and, among the row tiles, hold rows (a prefix of its list)
+  const int have = WT + mt_used;
+  int nreq = 0;
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) nreq += wave_s + 8 * j < have ? 1 : 0;
+#define BLK_REQUEST(slot_, kt_)                                                                               \
+  do {                                                                                                        \
+    const size_t k_ = (size_t)min(kt_, last) * 64;                                                            \
+    _Pragma("unroll") for (int j = 0; j < NJ; ++j)                                                            \
+      if (8 * j + 7 < (FULL ? TILES : WT) || j < nreq)                                                        \
+        __builtin_amdgcn_global_load_lds((gptr_t)(src[j] + k_), (lptr_t)(size_t)(lds0 + 16u * ((slot_) * STAGE + 8 * j * 64)), 16, 0, 0); \
+  } while (0)
+#define BLK_WAIT(stages_)                                                                                     \
+  do {                                                                                                        \
+    if ((FULL && TILES % 8 == 0) || nreq == NJ) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((stages_) * NJ)); \
+    else if (FULL || nreq == NJ - 1) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((stages_) * (NJ - 1)));      \
+    else if (nreq == NJ - 2) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((stages_) * (NJ - 2)));              \
+    else __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));                                                     \
+  } while (0)
+  static_assert((S - 1) * NJ < 64, "the load counter has six bits");
+  const u32x4* wl0 = ring + (nhv * TN) * 64 + lane;
+  const u32x4* xl0 = ring + (WT + (FULL ? rqv * TMW : rqv)) * 64 + lane;
+  u32x4 wf[2][TN], xf[2][TMW];
+#pragma unroll
+  for (int s = 0; s < S - 1; ++s) BLK_REQUEST(s, s);
+  BLK_WAIT(S - 2);
+  __builtin_amdgcn_s_barrier();
+#pragma unroll
+  for (int tn = 0; tn < TN; ++tn) wf[0][tn] = wl0[tn * 64];
+#pragma unroll
+  for (int mt = 0; mt < TMW; ++mt) xf[0][mt] = xl0[mt * MT_STEP * 64];
+#define BLK_STEP(u_, guard_)                                                                                  \
+  do {                                                                                                        \
+    BLK_WAIT(S - 3);                                                                                          \
+    __builtin_amdgcn_s_barrier();                                                                             \
+    const int cb_ = (u_) & 1, nb_ = cb_ ^ 1, ns_ = ((u_) + 1) % S;                                            \
+    BLK_REQUEST(((u_) + S - 1) % S, kt + (u_) + S - 1);                                                       \
+    const u32x4* wl_ = wl0 + ns_ * STAGE;                                                                     \
+    const u32x4* xl_ = xl0 + ns_ * STAGE;                                                                     \
+    const bool on_ = !(guard_) || kt + (u_) < ktiles;                                                            \
+    __builtin_amdgcn_sched_barrier(0);                                                                        \
+    _Pragma("unroll") for (int mt = 0; mt < TMW; ++mt) {                                                      \
+      _Pragma("unroll") for (int tn = mt * TN / TMW; tn < (mt + 1) * TN / TMW; ++tn) wf[nb_][tn] = wl_[tn * 64]; \
+      xf[nb_][mt] = xl_[mt * MT_STEP * 64];                                                                   \
+      if (on_ && (FULL || rq + 4 * mt < mt_used)) {                                                           \
+        _Pragma("unroll") for (int tn = 0; tn < TN; ++tn) acc[tn][mt] = mfma16(wf[cb_][tn], xf[cb_][mt], acc[tn][mt]); \
+      }                                                                                                       \
+      __builtin_amdgcn_sched_barrier(0);                                                                      \
+    }                                                                                                         \
+  } while (0)
+  if (wave_s >= 4) __builtin_amdgcn_s_setprio(2);
+  int kt = 0;
+  for (; kt + S <= ktiles; kt += S) {
+#pragma unroll
+    for (int u = 0; u < S; ++u) BLK_STEP(u, false);
+  }
+  if (kt < ktiles) {
+#pragma unroll
+    for (int u = 0; u < S; ++u) BLK_STEP(u, true);
+  }
+#undef BLK_STEP
+#undef BLK_WAIT
+#undef BLK_REQUEST
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+  const int mc = lane & 15;
+#pragma unroll
+  for (int t = 0; t < TN / NB; ++t) {
+    const int nt = nt0 + t * NB;
+    if (nt >= ntiles) continue;
+    const int task = nt / NB;
+#pragma unroll
+    for (int mt = 0; mt < TMW; ++mt) {
+      const int m = (mt_first + mt * MT_STEP) * 16 + mc;
+      if (mt_first + mt * MT_STEP >= mt_used) continue;
+      const float sc = out.nin.inv_rms ? out.nin.inv_rms[rbase + min(m, M - 1)] : 1.0f;
+      EpiPre pre;
+      epi_prefetch<EPI>(pre, out, task, row0 + rbase + m, m < M, lane);
+      epi_apply<EPI>(acc[t * NB][mt], acc[t * NB + NB - 1][mt], sc, pre, out, task, row0 + rbase + m, m < M, N, lane);
+    }
+  }
+}
+
+template <int EPI, int TN>
+__global__ __launch_bounds__(512) void gemm_block_kernel(const uint4* __restrict__ W, int ktiles, int ntiles, const uint4* __restrict__ A,
+                                                         int row0, int M_all, int N, GemmOut out) {
+  constexpr int TMT = 16, TILES = 2 * TN + TMT;
+  __shared__ u32x4 ring[((160 / TILES) & ~1) * TILES * 64];
+  const int rblocks = (M_all + TMT * 16 - 1) / (TMT * 16), total = ((ntiles + 2 * TN - 1) / (2 * TN)) * rblocks;
+  const int share = (total + 7) >> 3, i = blockIdx.x >> 3, b = (blockIdx.x & 7) * share + i;
+  if (i >= share || b >= total) return;             // whole workgroup
+  const int bx = b / rblocks, rbase = (b % rblocks) * (TMT * 16), M = min(M_all - rbase, TMT * 16);
+  if (M > TMT * 16 - 16) gemm_block_body<EPI, TN, true>(ring, W, ktiles, ntiles, A, row0, rbase, M, N, out, bx);
+  else gemm_block_body<EPI, TN, false>(ring, W, ktiles, ntiles, A, row0, rbase, M, N, out, bx);
 }
 
 // sums the K shares of one (task, row tile) in a fixed order and runs the epilogue; one wave per unit
@@ -826,20 +959,53 @@ static bool launch_gemm_rows_blocks(hipStream_t st, int epi, const uint4* W, int
   return true;
 }
 
-// Wide matrices (gate/up, exit head) at 257..512 rows: sixteen weight tiles per workgroup and the rows in two blocks of
-// up to 256.  Per k-tile a workgroup then moves 16 + 16 KiB through its address path for 256 MFMAs where the
-// one-block form (8 weight tiles x 32 row tiles) moves 8 + 32 KiB for the same 256: a fifth less request time per
-// MFMA, which is what bounds these shapes.  The two blocks of a column group run side by side on one XCD (see the
-// kernel), so the weights still cross HBM once.
-template <int EPI>
-static void launch_gemm_rows_wide(hipStream_t st, const uint4* W, int ntiles, int ktiles, const uint4* A, int row0, int M, int N,
-                                  const GemmOut& out) {
-  const int groups = ceil_div(ntiles, 16);
-  dim3 grid(16 * ceil_div(groups, 8)), blk(512);
+// Forms of the blocked kernel: weight tiles per workgroup (always sixteen row tiles), with the time of one k-tile and of
+// a block's start and end on a chip whose compute units are all busy, in units of 10 ns (from sweeps over 8B shapes on
+// random operands: gate/up at 4096 rows 705 us with 16 weight tiles, 798 with 12, 814 with 8; QKV at 2048 rows 106 / 95 /
+// 117; O 96 / 82 / 67; down 276 / 235 / 188).  Small blocks cost more per product but let narrow matrices fill the chip.
+struct BlockForm { int wt, step, ends; };
+static const BlockForm kBlockForms[3] = {{16, 74, 600}, {12, 68, 600}, {8, 41, 800}};
+constexpr int kCusPerXcd = 32;
+// Time of one launch by list scheduling of one XCD's blocks on its compute units (every XCD works on an equal run of
+// them, see the kernel); a partly filled row block costs its share of the MFMAs plus a third of a step.
+static int block_cost(const BlockForm& f, int ntiles, int ktiles, int M) {
+  const int rblocks = ceil_div(M, 256), n = ceil_div(ceil_div(ntiles, f.wt) * rblocks, 8);
+  const int used = ceil_div(M - (rblocks - 1) * 256, 16);
+  const int full = ktiles * f.step + f.ends, part = ktiles * (f.step / 3 + f.step * 2 * used / 48) + f.ends;
+  int free_at[kCusPerXcd] = {0}, end = 0;
+  for (int i = 0; i < n; ++i) {
+    int c = 0;
+    for (int k = 1; k < kCusPerXcd; ++k)
+      if (free_at[k] < free_at[c]) c = k;
+    free_at[c] += i % rblocks == rblocks - 1 ? part : full;
+    end = max(end, free_at[c]);
+  }
+  return end;
+}
+// Weight tiles per workgroup of a blocked call: the cheapest of the forms (bit i: kBlockForms[i]) by the model above.  A pure
+// function of the sizes, remembered for the last few.
+static int choose_block(int ntiles, int ktiles, int M, int forms) {
+  struct Memo { int ntiles, ktiles, M, forms, wt; };
+  static thread_local Memo memo[8] = {};
+  static thread_local unsigned next = 0;
+  for (const Memo& m : memo)
+    if (m.ntiles == ntiles && m.ktiles == ktiles && m.M == M && m.forms == forms) return m.wt;
+  int wt = 0, least = 0;
+  for (int i = 0; i < 3; ++i) {
+    if (!(forms & (1 << i))) continue;
+    const int cost = block_cost(kBlockForms[i], ntiles, ktiles, M);
+    if (!wt || cost < least) { wt = kBlockForms[i].wt; least = cost; }
+  }
+  memo[next++ & 7] = Memo{ntiles, ktiles, M, forms, wt};
+  return wt;
+}
+
+template <int EPI, int TN>
+static void launch_block(hipStream_t st, const uint4* W, int ntiles, int ktiles, const uint4* A, int row0, int M, int N, const GemmOut& out) {
+  dim3 grid(8 * ceil_div(ceil_div(ntiles, 2 * TN) * ceil_div(M, 256), 8)), blk(512);
   LaunchEvents* ev = g_launch_events;
   g_launch_events = nullptr;
-  if (M == 512) launch_timed(ev, gemm_rows_kernel<16, EPI, true, 8>, grid, blk, st, W, ktiles, ntiles, A, row0, M, N, out, ktiles, (float*)nullptr);
-  else launch_timed(ev, gemm_rows_kernel<16, EPI, false, 8>, grid, blk, st, W, ktiles, ntiles, A, row0, M, N, out, ktiles, (float*)nullptr);
+  launch_timed(ev, gemm_block_kernel<EPI, TN>, grid, blk, st, W, ktiles, ntiles, A, row0, M, N, out);
 }
 int g_rows_wide = 1;               // test and tuning hook: 0 keeps the one-block form for wide matrices
 
@@ -860,13 +1026,19 @@ static int rows_blocks_form(int ntiles, int ktiles, int M) {
   return 0;
 }
 
-// more than 16 rows from row 0 of the operand; out.nin.ssq, if set, is first reduced to per-row factors (per block)
+// more than 16 rows from row 0 of the operand; out.nin.ssq, if set, is first reduced to per-row factors
 void bf16_gemm_rows(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N,
-                    const GemmOut& out0, float* scratch, float* inv_rms) {
+                    const GemmOut& out0, float* scratch, float* inv_rms, int inv_cap) {
   const uint4* Wc = (const uint4*)W;
   const uint4* Ac = (const uint4*)A;
-  // blocks of up to 512 rows, of equal size up to a row tile: calls beyond 512 rows stream the weights once per block
-  const int blk = ceil_div(ceil_div(M, ceil_div(M, 512)), 16) * 16;
+  const bool wide = epi == EPI_SWIGLU || epi == EPI_ARGMAX;
+  // Which calls run blocked: the wide matrices from 257 rows (as the one-launch forms below need two row blocks there, and
+  // measured slower), the narrow ones from 513 (below that their own forms and K shares are quicker for O and QKV: 32 and
+  // 43 us at 512 rows against 51 and 53).  The hooks that force another form keep the 512-row passes.
+  const bool blocked = wide ? g_rows_wide && M > 256 && ntiles >= 1536 : M > 512 && g_rows_blocks_override < 0;
+  // else blocks of up to 512 rows, of equal size up to a row tile: calls beyond 512 rows stream the weights once per block
+  const int parts = blocked ? ceil_div(M, max(512, inv_cap)) : ceil_div(M, 512);
+  const int blk = ceil_div(ceil_div(M, parts), 16) * 16;
   if (M > blk) g_launch_events = nullptr;           // several launches: the caller's bracket times the call
   for (int m0 = 0; m0 < M; m0 += blk) {
     const int mc = min(blk, M - m0);
@@ -876,9 +1048,16 @@ void bf16_gemm_rows(hipStream_t st, int epi, const bf16_t* W, int ntiles, int kt
                          out.nin.inv_d, out.nin.eps, inv_rms, mc);
       out.nin.inv_rms = inv_rms;
     }
-    if (g_rows_wide && mc > 256 && ntiles >= 1536 && (epi == EPI_SWIGLU || epi == EPI_ARGMAX)) {
-      if (epi == EPI_SWIGLU) launch_gemm_rows_wide<EPI_SWIGLU>(st, Wc, ntiles, ktiles, Ac, m0, mc, N, out);
-      else launch_gemm_rows_wide<EPI_ARGMAX>(st, Wc, ntiles, ktiles, Ac, m0, mc, N, out);
+    if (blocked) {
+      const int wt = choose_block(ntiles, ktiles, mc, epi == EPI_ARGMAX ? 1 : (epi == EPI_SWIGLU ? 3 : 7));
+#define BLOCK_LAUNCH(E_, TN_) launch_block<E_, TN_>(st, Wc, ntiles, ktiles, Ac, m0, mc, N, out)
+      switch (epi) {
+        case EPI_ARGMAX: BLOCK_LAUNCH(EPI_ARGMAX, 8); break;
+        case EPI_SWIGLU: if (wt == 16) BLOCK_LAUNCH(EPI_SWIGLU, 8); else BLOCK_LAUNCH(EPI_SWIGLU, 6); break;
+        case EPI_ROPE: if (wt == 16) BLOCK_LAUNCH(EPI_ROPE, 8); else if (wt == 12) BLOCK_LAUNCH(EPI_ROPE, 6); else BLOCK_LAUNCH(EPI_ROPE, 4); break;
+        default: if (wt == 16) BLOCK_LAUNCH(EPI_ADD, 8); else if (wt == 12) BLOCK_LAUNCH(EPI_ADD, 6); else BLOCK_LAUNCH(EPI_ADD, 4); break;
+      }
+#undef BLOCK_LAUNCH
       continue;
     }
     const int bt = rows_blocks_form(ntiles, ktiles, mc);

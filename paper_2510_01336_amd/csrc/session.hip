@@ -34,7 +34,10 @@ struct KTimer { int fam; hipEvent_t a, b; };
 struct ee_session {
   ee_model* m = nullptr;
   hipStream_t st = nullptr;
-  int B = 0, max_ctx = 0, max_rows = 0, pps = 0, n_pages = 0, maxM = 0, Mp = 0, maxQT = 0, chunk = 0;
+  int B = 0, max_ctx = 0, max_rows = 0, pps = 0, n_pages = 0, chunk = 0;
+  int maxM = 0, Mp = 0, maxQT = 0;            // most rows of a pass (a context-build pass or a batch-wide call), padded to whole GEMM passes, most q-tiles
+  int headM = 0, headMp = 0;                  // the same for an exit head (a context build sends it the rows that end a prompt)
+  int ssq_stride = 0, inv_cap = 0;            // row stride of ssq, floats in inv_rms
   char* base = nullptr;
   size_t bytes = 0;
   // device buffers (inside the caller's arena)
@@ -56,17 +59,18 @@ struct ee_session {
   // models, the bf16 operand of the up projection), that operand's unused sum-of-squares partials, unit gains
   float *Z = nullptr, *T = nullptr, *ssq_t = nullptr, *ones = nullptr;
   void* TF = nullptr;
+  void* EN = nullptr;           // bf16: operand of the head over the rows that end a prompt [B rows]
   size_t part_units = 0;        // capacity of the attention split scratch in (q-tile, split) units per KV head
   int* pidx = nullptr;
   int max_splits = 64;
   // host side
   MetaSlot slot[2];
-  size_t meta_ints = 0;
+  size_t meta_ints = 0, meta_cap = 0;   // metadata of the call being built, and of the largest one
   int* out_host = nullptr;    // pinned: n_accept[B], next[B], draft [B*max_rows]
   std::vector<SeqState> seq;
   std::vector<int> free_pages;
   bool debug_logits = false, time_kernels = false;
-  int last_rows = 0;
+  int last_rows = 0, last_row0 = 0;   // rows of X behind the last exit head
   std::vector<KTimer> timers;
   int launches[KF_COUNT] = {0};
   // meta layout (offsets in ints)
@@ -91,14 +95,15 @@ struct Carver {
   }
 };
 
-static void layout_meta(ee_session* s) {
+// offsets of the metadata block of a call with so many rows and q-tiles (a call uploads no more than it uses)
+static void layout_meta(ee_session* s, int rows, int qts) {
   size_t o = 0;
   auto take = [&](size_t n) { size_t r = o; o += (n + 3) / 4 * 4; return r; };
   s->cand_stride = s->max_rows + 1;
-  s->o_row_seq = take(s->maxM); s->o_row_pos = take(s->maxM); s->o_row_tok = take(s->maxM);
-  s->o_row_src = take(s->maxM); s->o_row_dst = take(s->maxM);
+  s->o_row_seq = take(rows); s->o_row_pos = take(rows); s->o_row_tok = take(rows);
+  s->o_row_src = take(rows); s->o_row_dst = take(rows);
   s->o_seq_row0 = take(s->B); s->o_seq_m = take(s->B); s->o_seq_p0 = take(s->B); s->o_seq_qt0 = take(s->B);
-  s->o_qt_seq = take(s->maxQT); s->o_qt_local = take(s->maxQT);
+  s->o_qt_seq = take(qts); s->o_qt_local = take(qts);
   s->o_cand = take((size_t)s->B * s->cand_stride); s->o_n_cand = take(s->B);
   s->o_bt = take((size_t)s->B * s->pps);
   s->meta_ints = o;
@@ -122,13 +127,13 @@ static size_t carve(ee_session* s, char* base) {
   s->AO = bf ? (void*)cv.take<bf16_t>((size_t)Mp * ceil_div(Hq * D, 32) * 32) : (void*)cv.take<float>((size_t)s->maxM * Hq * D);
   s->GU = bf ? nullptr : cv.take<float>((size_t)s->maxM * 2 * m->Fp);
   s->H = bf ? (void*)cv.take<bf16_t>((size_t)Mp * ceil_div(c.d_ffn, 32) * 32) : (void*)cv.take<float>((size_t)s->maxM * c.d_ffn);
-  s->LOGITS = cv.take<float>((size_t)s->maxM * c.vocab);
+  s->LOGITS = cv.take<float>((size_t)s->headM * c.vocab);
   if (c.head_rank > 0) {
-    s->Z = cv.take<float>((size_t)s->maxM * d);
-    s->T = cv.take<float>((size_t)s->maxM * c.head_rank);
+    s->Z = cv.take<float>((size_t)s->headM * d);
+    s->T = cv.take<float>((size_t)s->headM * c.head_rank);
     if (bf) {
-      s->TF = cv.take<bf16_t>((size_t)Mp * c.head_rank);
-      s->ssq_t = cv.take<float>((size_t)ceil_div(c.head_rank, 16) * Mp);
+      s->TF = cv.take<bf16_t>((size_t)s->headMp * c.head_rank);
+      s->ssq_t = cv.take<float>((size_t)ceil_div(c.head_rank, 16) * s->headMp);
       s->ones = cv.take<float>(c.head_rank);
     }
   }
@@ -143,22 +148,23 @@ static size_t carve(ee_session* s, char* base) {
   s->out_dev = cv.take<int>(2 * (size_t)s->B);
   s->page_scratch = cv.take<int>(s->pps);
   if (bf) {
-    // attention split scratch: all 64 splits for verify-sized calls (<= 64 rows), 8 for context-build passes
-    const size_t qt_small = (size_t)ceil_div(std::min(s->maxM, 64) * rep, 16) + s->B;
-    s->part_units = std::max(qt_small * s->max_splits, (size_t)s->maxQT * 8);
+    // attention split scratch: all 64 splits for verify-sized calls (<= 64 rows), 8 at 512 rows and fewer for larger context-build passes
+    const size_t qt_small = (size_t)ceil_div(std::min(s->headM, 64) * rep, 16) + s->B;
+    s->part_units = std::max(qt_small * s->max_splits, (size_t)(ceil_div(s->headM * rep, 16) + s->B) * 8);
     s->part_o = cv.take<float>(s->part_units * Hkv * 16 * D);
     s->part_ml = cv.take<float>(s->part_units * Hkv * 32);
-    s->pmax = cv.take<float>((size_t)m->head.ntiles() * Mp);
-    s->pidx = cv.take<int>((size_t)m->head.ntiles() * Mp);
+    s->pmax = cv.take<float>((size_t)m->head.ntiles() * s->headMp);
+    s->pidx = cv.take<int>((size_t)m->head.ntiles() * s->headMp);
+    s->EN = cv.take<bf16_t>((size_t)(s->B <= 64 ? 64 : ceil_div(s->B, 512) * 512) * ceil_div(d, 32) * 32);
     s->ssq = cv.take<float>((size_t)ceil_div(d, 16) * Mp);            // deferred-RMSNorm partials [d/16][Mp]
     size_t gp = 0;                                                    // K-share scratch of the row-tiled GEMM
     for (const MatLoc* ml : {&m->L[0].qkv, &m->L[0].o, &m->L[0].gu, &m->L[0].down, &m->head, &m->auxA[0], &m->auxB[0]})
       if (ml->Np > 0) gp = std::max(gp, bf16_gemm_rows_scratch_floats(ml->ntiles(), ml->ktiles()));
     s->gemm_part = s->maxM > 64 ? cv.take<float>(gp) : nullptr;
-    s->inv_rms = cv.take<float>(512);
+    s->inv_rms = cv.take<float>(s->inv_cap);
   }
-  s->slot[0].d = cv.take<int>(s->meta_ints);
-  s->slot[1].d = cv.take<int>(s->meta_ints);
+  s->slot[0].d = cv.take<int>(s->meta_cap);
+  s->slot[1].d = cv.take<int>(s->meta_cap);
   (void)rep;
   return align_up(cv.cur, 256);
 }
@@ -172,12 +178,19 @@ static int shape_session(ee_session* s, const ee_model* m, int batch, int max_ct
   s->B = batch; s->max_ctx = max_ctx; s->max_rows = max_rows;
   s->pps = ceil_div(max_ctx, EE_PAGE);
   s->n_pages = total_pages > 0 ? total_pages : batch * s->pps;
-  s->chunk = m->bf16 ? 512 : 64;                        // context-build rows per pass
+  // context-build rows per pass: 4096 give the blocked GEMM whole rounds of 256 x 256 blocks (gate/up at the 8B width: 1365
+  // TFLOP/s against 1265 at 2048 rows and 1150 at 512); no more than the sequences can hold
+  s->chunk = m->bf16 ? std::min(4096, std::max(512, (int)std::min<long>(4096, ((long)batch * max_ctx + 511) / 512 * 512))) : 64;
+  s->headM = std::max(batch * max_rows, m->bf16 ? 512 : 64);
+  s->headMp = s->headM <= 64 ? 64 : ceil_div(s->headM, 512) * 512;
   s->maxM = std::max(batch * max_rows, s->chunk);
   // activation rows padded to whole GEMM passes: 64 rows (skinny kernel), blocks of 512 (the row-tiled kernel requests up to 32 row tiles)
   s->Mp = s->maxM <= 64 ? 64 : ceil_div(s->maxM, 512) * 512;
   s->maxQT = ceil_div(s->maxM * rep, 16) + batch;
-  layout_meta(s);
+  s->ssq_stride = s->Mp;
+  s->inv_cap = std::max(512, s->maxM);
+  layout_meta(s, s->maxM, s->maxQT);                    // (the largest block; every call lays out its own)
+  s->meta_cap = s->meta_ints;
   return EE_OK;
 }
 
@@ -204,7 +217,7 @@ extern "C" int ee_session_create(ee_model* m, int batch, int max_ctx, int max_ro
   const std::vector<float> unit(s->ones ? m->cfg.head_rank : 0, 1.0f);
   if (e == hipSuccess && s->ones) e = hipMemcpyAsync(s->ones, unit.data(), unit.size() * sizeof(float), hipMemcpyHostToDevice, s->st);
   for (int i = 0; i < 2 && e == hipSuccess; ++i) {
-    e = hipHostMalloc((void**)&s->slot[i].h, s->meta_ints * sizeof(int), hipHostMallocDefault);
+    e = hipHostMalloc((void**)&s->slot[i].h, s->meta_cap * sizeof(int), hipHostMallocDefault);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&s->slot[i].copied, hipEventDisableTiming);
   }
   if (e == hipSuccess) e = hipHostMalloc((void**)&s->out_host, (2 * (size_t)batch + (size_t)batch * max_rows) * sizeof(int), hipHostMallocDefault);
@@ -299,6 +312,10 @@ static int build_meta(ee_session* s, int si, CallPlan& p, RowFn row_fn) {
   int* h = sl.h;
   const int rep = s->m->cfg.n_q_heads / s->m->cfg.n_kv_heads;
   int row = 0, qt = 0;
+  for (int b = 0; b < s->B; ++b) { row += p.m[b]; qt += ceil_div(p.m[b] * rep, 16); }
+  if (row > s->maxM || qt > s->maxQT) { ee_set_error("internal: call exceeds work buffers (%d rows)", row); return EE_ERR_CAPACITY; }
+  layout_meta(s, row, qt);
+  row = qt = 0;
   p.M = 0; p.n_active = 0; p.max_m = 0; p.max_kv_end = 0;
   for (int b = 0; b < s->B; ++b) {
     int m = p.m[b];
@@ -316,7 +333,6 @@ static int build_meta(ee_session* s, int si, CallPlan& p, RowFn row_fn) {
     for (int t = 0; t < nqt; ++t, ++qt) { h[s->o_qt_seq + qt] = b; h[s->o_qt_local + qt] = t; }
   }
   p.M = row; p.total_qt = qt;
-  if (row > s->maxM || qt > s->maxQT) { ee_set_error("internal: call exceeds work buffers (%d rows)", row); return EE_ERR_CAPACITY; }
   for (int b = 0; b < s->B; ++b) {
     const SeqState& q = s->seq[b];
     for (size_t i = 0; i < q.pages.size(); ++i) h[s->o_bt + (size_t)b * s->pps + i] = q.pages[i];
@@ -374,11 +390,11 @@ static void reset_accounting(ee_session* s) {
 // ---------------------------------------------------------------------------------------------
 // weights cross HBM once per call: up to 16 rows the skinny kernel, from 33 to 512 the row-tiled one, in
 // between the row-tiled one for matrices of 128 MB and more (measured: the small projections are quicker
-// without its K-share reduction pass); beyond 512 rows the row-tiled kernel goes over the rows in blocks of 512
+// without its K-share reduction pass); beyond 512 rows (wide matrices: 256) the blocked one
 static void gemm(ee_session* s, int epi, const MatLoc& ml, const bf16_t* A, int M, const GemmOut& o) {
   const bf16_t* W = (const bf16_t*)(s->m->base + ml.off);
   const bool big = (size_t)ml.ntiles() * ml.ktiles() * 1024 >= ((size_t)128 << 20);
-  if (M > (big ? 16 : 32)) bf16_gemm_rows(s->st, epi, W, ml.ntiles(), ml.ktiles(), A, M, ml.N, o, s->gemm_part, s->inv_rms);
+  if (M > (big ? 16 : 32)) bf16_gemm_rows(s->st, epi, W, ml.ntiles(), ml.ktiles(), A, M, ml.N, o, s->gemm_part, s->inv_rms, s->inv_cap);
   else bf16_gemm(s->st, epi, W, ml.ntiles(), ml.ktiles(), A, M, ml.N, o);
 }
 
@@ -444,7 +460,7 @@ static void run_layers(ee_session* s, int l0, int l1, const CallPlan& p, const C
     const float* g2 = (const float*)(m->base + L.g2);
     if (m->bf16) {
       // five launches per layer (six with the merge of a split attention); RMSNorm is deferred into the projections (see NormIn / NormOut)
-      const int Mp = s->Mp;
+      const int Mp = s->ssq_stride;
       NormIn nin;         // operand left by the previous EPI_ADD launch
       nin.ssq = s->ssq; nin.n_part = d / 16; nin.stride = Mp; nin.inv_d = 1.0f / (float)d; nin.eps = c.rms_eps;
       NormOut nout;
@@ -490,7 +506,9 @@ static void run_layers(ee_session* s, int l0, int l1, const CallPlan& p, const C
 // Prediction head of exit `which` (0 = L_d, 1 = L_i, ..., n_levels = L_f) + arg max for rows 0..M-1 of X -> vtok.
 // The shared final RMSNorm and LM head (Sec. 3.1); at an early exit of a model with auxiliary heads
 // (App. I) behind that exit's rank-r adapter  z = x + B (A RMSNorm(x; g)),  which leaves X itself alone.
-static void exit_head(ee_session* s, int M, int which) {
+// row0 (a multiple of 16): the rows are row0 .. row0+M-1 of the pass instead (final exit only).  ended: the rows are those
+// listed on the device (the ends of prompts in a context build), normalised here; X's other rows need no head.
+static void exit_head(ee_session* s, int M, int which, int row0 = 0, const int* ended = nullptr) {
   const ee_model* m = s->m;
   const ee_config& c = m->cfg;
   hipStream_t st = s->st;
@@ -499,9 +517,10 @@ static void exit_head(ee_session* s, int M, int which) {
   const bool aux = r > 0 && which < s->n_levels;
   if (m->bf16) {
     // the last down projection of the pass left XN = bf16(x * gain) and the partial sums of squares
-    const int Mp = s->Mp;
+    const int Mp = s->ssq_stride;
+    const bf16_t* operand = (const bf16_t*)s->XN + (size_t)row0 * ceil_div(d, 32) * 32;
     NormIn nin;
-    nin.ssq = s->ssq; nin.n_part = d / 16; nin.stride = Mp; nin.inv_d = 1.0f / (float)d; nin.eps = c.rms_eps;
+    nin.ssq = s->ssq + row0; nin.n_part = d / 16; nin.stride = Mp; nin.inv_d = 1.0f / (float)d; nin.eps = c.rms_eps;
     if (aux) {
       // t = A n(x): rows into T (cleared: the epilogue adds to what it finds) and as the next operand TF;
       // z = x + B t: into a copy of the rows, leaving the shared head's operand XN = bf16(z * gfinal)
@@ -509,19 +528,24 @@ static void exit_head(ee_session* s, int M, int which) {
       (void)hipMemcpyAsync(s->Z, s->X, (size_t)M * d * sizeof(float), hipMemcpyDeviceToDevice, st);
       GemmOut o;
       o.nin = nin; o.Y = s->T; o.ldy = r;
-      o.nout.xn = (bf16_t*)s->TF; o.nout.ktiles = r / 32; o.nout.ssq = s->ssq_t; o.nout.stride = Mp; o.nout.g = s->ones;
+      o.nout.xn = (bf16_t*)s->TF; o.nout.ktiles = r / 32; o.nout.ssq = s->ssq_t; o.nout.stride = s->headMp; o.nout.g = s->ones;
       KF(KF_GEMM_HEAD, gemm(s, EPI_ADD, m->auxA[which], (const bf16_t*)s->XN, M, o));
       o = GemmOut(); o.Y = s->Z; o.ldy = d;
       o.nout.xn = (bf16_t*)s->XN; o.nout.ktiles = ceil_div(d, 32); o.nout.ssq = s->ssq; o.nout.stride = Mp; o.nout.g = gf;
       KF(KF_GEMM_HEAD, gemm(s, EPI_ADD, m->auxB[which], (const bf16_t*)s->TF, M, o));
     }
     GemmOut o;
-    o.nin = nin;
+    if (ended) {
+      KF(KF_NORM, bf16_rmsnorm(st, s->X, ended, gf, c.rms_eps, (bf16_t*)s->EN, ceil_div(d, 32), M, d));
+      operand = (const bf16_t*)s->EN;
+    } else {
+      o.nin = nin;
+    }
     // (max, arg max) partials [row][tile]: the reduction of a row then reads one contiguous strip
     const int pstride = m->head.ntiles();
     o.pmax = s->pmax; o.pidx = s->pidx; o.pstride = pstride;
     if (s->debug_logits || s->need_logits) { o.Y = s->LOGITS; o.ldy = c.vocab; }
-    KF(KF_GEMM_HEAD, gemm(s, EPI_ARGMAX, m->head, (const bf16_t*)s->XN, M, o));
+    KF(KF_GEMM_HEAD, gemm(s, EPI_ARGMAX, m->head, operand, M, o));
     KF(KF_ARGMAX, bf16_argmax_reduce(st, s->pmax, s->pidx, m->head.ntiles(), pstride, M, s->vtok));
   } else {
     const float* hidden = s->X;
@@ -537,7 +561,7 @@ static void exit_head(ee_session* s, int M, int which) {
                               c.vocab, d, false));
     KF(KF_ARGMAX, f32_argmax(st, s->LOGITS, M, c.vocab, s->vtok));
   }
-  s->last_rows = M;
+  s->last_rows = M; s->last_row0 = row0;
 }
 
 static int finish(ee_session* s) {
@@ -595,6 +619,9 @@ static int prefill_impl(ee_session* s, const int32_t* tokens, const int32_t* len
   // Passes of up to `chunk` rows.  A pass takes one contiguous piece of every prompt that still has rows, in
   // sequence order, until it is full: a long prompt fills passes by itself, short prompts share one (the weights
   // cross HBM once per pass).  A sequence's next piece comes in a later pass, after its earlier rows are cached.
+  const bool bf = s->m->bf16;
+  int n_first = 0;                                       // first tokens on their way to out_host so far
+  std::vector<int> end_seq(s->B), end_row(s->B), first_slot(s->B, 0);
   for (int ci = 0;; ++ci) {
     const int si = ci & 1;        // alternate upload slots so the host runs one pass ahead
     CallPlan p;
@@ -607,17 +634,40 @@ static int prefill_impl(ee_session* s, const int32_t* tokens, const int32_t* len
     }
     if (room == s->chunk) break;
     EE_TRY(build_meta(s, si, p, [&](int b, int r, int& tok, int&, int&) { tok = tokens[off0[b] + done[b] + r]; }));
+    int n_end = 0;
+    bool last_pass = true;
+    for (int b = 0, row = 0; b < s->B; row += p.m[b], ++b) {
+      if (done[b] + p.m[b] < lens[b]) last_pass = false;
+      else if (p.m[b]) { end_seq[n_end] = b; end_row[n_end++] = row + p.m[b] - 1; }
+    }
+    std::copy(end_row.begin(), end_row.begin() + n_end, s->slot[si].h + s->o_row_src);     // (no rows are gathered here: the list of ends)
     EE_TRY(upload_meta(s, si));
     CallMeta mt = meta_ptrs(s, s->slot[si].d);
     PassSource from_tokens; from_tokens.tok = mt.row_tok;
     run_layers(s, 0, c.n_layers, p, mt, 0, from_tokens);
-    bool head_done = false;
-    for (int b = 0, row = 0; b < s->B; row += p.m[b], ++b) {
-      if (!p.m[b] || done[b] + p.m[b] < lens[b]) continue;
-      // the prompt ends in this pass: its last row decides the first committed token
-      if (!head_done) { exit_head(s, p.M, s->n_levels); head_done = true; }
-      HIP_TRY(hipMemcpyAsync(s->out_host + b, s->vtok + (row + p.m[b] - 1), sizeof(int), hipMemcpyDeviceToHost, s->st));
+    // The rows that end a prompt decide its first committed token: the head runs over them alone.  What the introspection
+    // calls report of a context build are the rows of its last 512-row piece; with logits kept these get a head as well.
+    if (bf && n_end) {
+      const int r0 = (p.M - 1) / 512 * 512, kept_piece = s->debug_logits && last_pass;
+      int early = 0;                                     // ends in front of that piece (all of them where it gets no head)
+      while (early < n_end && !(kept_piece && end_row[early] >= r0)) ++early;
+      if (early) {
+        exit_head(s, early, s->n_levels, 0, mt.row_src);
+        HIP_TRY(hipMemcpyAsync(s->out_host + n_first, s->vtok, early * sizeof(int), hipMemcpyDeviceToHost, s->st));
+      }
+      if (kept_piece) {
+        exit_head(s, p.M - r0, s->n_levels, r0);
+        for (int e = early; e < n_end; ++e)
+          HIP_TRY(hipMemcpyAsync(s->out_host + n_first + e, s->vtok + (end_row[e] - r0), sizeof(int), hipMemcpyDeviceToHost, s->st));
+      }
+      s->last_rows = p.M - r0; s->last_row0 = r0;
+    } else if (n_end) {
+      exit_head(s, p.M, s->n_levels);
+      for (int e = 0; e < n_end; ++e)
+        HIP_TRY(hipMemcpyAsync(s->out_host + n_first + e, s->vtok + end_row[e], sizeof(int), hipMemcpyDeviceToHost, s->st));
     }
+    for (int e = 0; e < n_end; ++e) first_slot[end_seq[e]] = n_first + e;
+    n_first += n_end;
     for (int b = 0; b < s->B; ++b) done[b] += p.m[b];
   }
   size_t off = 0;
@@ -627,10 +677,10 @@ static int prefill_impl(ee_session* s, const int32_t* tokens, const int32_t* len
     if (lens[b] <= 0) continue;
     SeqState& q = s->seq[b];
     q.C.assign(tokens + off, tokens + off + lens[b]);
-    q.C.push_back(s->out_host[b]);
+    q.C.push_back(s->out_host[first_slot[b]]);
     settle(s, q);
     q.started = true;
-    first_token[b] = s->out_host[b];
+    first_token[b] = s->out_host[first_slot[b]];
     off += lens[b];
   }
   return EE_OK;
@@ -877,11 +927,13 @@ struct ScratchSwap {
   ee_session* s;
   float *part_o, *part_ml, *pmax, *ssq, *gemm_part, *inv_rms;
   int* pidx;
+  int ssq_stride, inv_cap;
   explicit ScratchSwap(ee_session* s_) : s(s_), part_o(s_->part_o), part_ml(s_->part_ml), pmax(s_->pmax), ssq(s_->ssq),
-                                         gemm_part(s_->gemm_part), inv_rms(s_->inv_rms), pidx(s_->pidx) {}
+                                         gemm_part(s_->gemm_part), inv_rms(s_->inv_rms), pidx(s_->pidx),
+                                         ssq_stride(s_->ssq_stride), inv_cap(s_->inv_cap) {}
   ~ScratchSwap() {
     s->part_o = part_o; s->part_ml = part_ml; s->pmax = pmax; s->ssq = ssq; s->gemm_part = gemm_part; s->inv_rms = inv_rms;
-    s->pidx = pidx;
+    s->pidx = pidx; s->ssq_stride = ssq_stride; s->inv_cap = inv_cap;
   }
 };
 
@@ -904,7 +956,8 @@ static int place_scratch_static(ee_session* s, const CallPlan& p) {
   const size_t pstride = (size_t)ceil_div(p.M, 16) * 16;
   float* pmax = cv.take<float>((size_t)m->head.ntiles() * pstride);
   int* pidx = cv.take<int>((size_t)m->head.ntiles() * pstride);
-  float* ssq = cv.take<float>((size_t)ceil_div(c.d_model, 16) * s->Mp);
+  const int stride = p.M <= 64 ? 64 : ceil_div(p.M, 512) * 512;      // whole GEMM passes of this call's rows
+  float* ssq = cv.take<float>((size_t)ceil_div(c.d_model, 16) * stride);
   float* inv_rms = cv.take<float>(512);
   float* gemm_part = nullptr;
   if (p.M > 16) {                                   // the row-tiled GEMM may run: room for its K shares
@@ -919,7 +972,7 @@ static int place_scratch_static(ee_session* s, const CallPlan& p) {
     return EE_ERR_CAPACITY;
   }
   s->part_o = part_o; s->part_ml = part_ml; s->pmax = pmax; s->pidx = pidx; s->ssq = ssq; s->inv_rms = inv_rms;
-  s->gemm_part = gemm_part;
+  s->gemm_part = gemm_part; s->ssq_stride = stride; s->inv_cap = 512;
   return EE_OK;
 }
 
@@ -1292,7 +1345,7 @@ extern "C" int ee_debug_last_logits(ee_session* s, float* host_out, int max_rows
 extern "C" int ee_debug_last_hidden(ee_session* s, float* host_out, int max_rows, int32_t* n_rows) {
   if (!s || !host_out || !n_rows) { ee_set_error("null argument"); return EE_ERR_ARG; }
   int n = std::min(max_rows, s->last_rows);
-  HIP_TRY(hipMemcpy(host_out, s->X, (size_t)n * s->m->cfg.d_model * sizeof(float), hipMemcpyDeviceToHost));
+  HIP_TRY(hipMemcpy(host_out, s->X + (size_t)s->last_row0 * s->m->cfg.d_model, (size_t)n * s->m->cfg.d_model * sizeof(float), hipMemcpyDeviceToHost));
   *n_rows = n;
   return EE_OK;
 }

@@ -548,3 +548,40 @@ def test_read_floor_times_plain_reads():
     assert sizes[1] / (us[1] * 1e-6) < 8.0e12
     with pytest.raises(hs.EEError):
         hs.ee_debug_read_floor(buf.data_ptr() + 4, sizes, 5, 0)
+
+
+@pytest.mark.parametrize("rows", [257, 512, 513, 767, 1025])
+@pytest.mark.parametrize("name", ["bf16_wide", "bf16_d128"])
+def test_context_build_in_blocks_matches_the_512_row_passes(name, rows):
+    """Context builds of more than 256 / 512 rows run the blocked GEMMs (256-row blocks, 16 / 12 / 8 weight tiles);
+    the hooks force the forms used up to there (K shares, one row block, split attention).  The rows around
+    the block edges, a ragged last block and matrices whose tiles do not fill the last group: both ways within the bf16 bound
+    of each other and the same first token, on a prompt whose last row clears the margin."""
+    import paper_2510_01336_amd as hs
+    # 2 * d_ffn / 16 weight tiles: 1546 (the wide form's floor is 1536, 1546 = 96 * 16 + 10) with few k-tiles, or narrow only
+    cfg = bf16_small(d_ffn=12368, sigma=0.02) if name == "bf16_wide" else bf16_d128()
+    model = hs.Model(cfg, 31)
+    sess = hs.Session(model, 2, rows + 40, 12)
+    sess.enable_logits(True)
+    for seed in range(12):
+        prompts = [synth.gen_prompt(cfg.vocab, n, 70 + seed + n) for n in (rows - 30, 30)]       # (two sequences share the pass)
+        first = sess.prefill(prompts)
+        got, hid = sess.last_logits()[-1:].astype(np.float64), sess.last_hidden()[-1:].copy()
+        if eo.top2_margin(got)[0] > 4 * MARGIN:
+            break
+    else:
+        raise AssertionError("no prompt cleared the margin")
+    step = sess.decode_ar(1)
+    after = sess.last_logits(2).astype(np.float64)
+    hs.ee_debug_gemm_row_blocks(0); hs.ee_debug_gemm_row_blocks(1000); hs.ee_debug_attention_split_pages(4)
+    try:
+        assert sess.prefill(prompts)[1] == first[1]
+        ref = sess.last_logits()[-1:].astype(np.float64)
+        assert max_rel(got, ref) <= TOL["bf16"] and max_rel(hid, sess.last_hidden()[-1:].astype(np.float64)) <= TOL["bf16"]
+        if int(first[0]) == int(sess.tokens(0)[-1]):            # (the first sequence's token may be a near-tie)
+            sess.decode_ar(1)
+            assert max_rel(after, sess.last_logits(2).astype(np.float64)) <= TOL["bf16"]           # every cached row enters here
+    finally:
+        hs.ee_debug_gemm_row_blocks(-1); hs.ee_debug_attention_split_pages(0)
+    assert step.shape == (2, 1)
+    sess.close(); model.close()
