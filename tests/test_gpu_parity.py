@@ -553,8 +553,8 @@ def test_read_floor_times_plain_reads():
 @pytest.mark.parametrize("rows", [257, 512, 513, 767, 1025])
 @pytest.mark.parametrize("name", ["bf16_wide", "bf16_d128"])
 def test_context_build_in_blocks_matches_the_512_row_passes(name, rows):
-    """Context builds of more than 256 / 512 rows run the blocked GEMMs (256-row blocks, 16 / 12 / 8 weight tiles);
-    the hooks force the forms used up to there (K shares, one row block, split attention).  The rows around
+    """Context builds of more than 256 / 512 rows run the blocked GEMMs (256-row blocks, 16 / 12 / 8 weight tiles) and the
+    block attention; the hooks force the forms used up to there (K shares, one row block, split attention).  The rows around
     the block edges, a ragged last block and matrices whose tiles do not fill the last group: both ways within the bf16 bound
     of each other and the same first token, on a prompt whose last row clears the margin."""
     import paper_2510_01336_amd as hs
