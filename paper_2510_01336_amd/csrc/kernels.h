@@ -92,20 +92,22 @@ void bf16_begin_pass(hipStream_t st, const bf16_t* emb, const int* tok, const fl
                      const float* g, float eps, bf16_t* out, int ktiles, int M, int d, const CallMeta& mt, int pos_add,
                      const double* inv_freq, float2* cs, int half, int pps, int4* rowinfo);
 struct AttnScratch { float* part_o; float* part_ml; int max_splits; };
-// pages each KV split takes, chosen from the call's sequence ends (kv_end[b] = first position past the
-// block, 0 for a sequence not taking part) so that a ragged batch is cut into equal workgroups
-int bf16_attention_pages_per_split(const int* kv_end, const int* seq_m, int B, int Hq, int Hkv, int max_splits);
-// per = pages per KV split (ceil(max pages / per) must not exceed scr.max_splits)
-void bf16_attention(hipStream_t st, const bf16_t* Q, const bf16_t* kv, const CallMeta& meta, int pos_add, int B, int max_m,
-                    int total_qt, int max_kv_end, int Hq, int Hkv, int D, int layer, int n_pages, int pages_per_seq,
-                    const AttnScratch& scr, bf16_t* out, int out_ktiles, int per);
+// Attention kernel and KV splits of a call (the same for all its layers), chosen from the sequence ends (kv_end[b] = first
+// position past the block, 0 for a sequence not taking part): every split takes `per` pages, the longest sequence has nsplit.
+enum { ATTN_RING = 0, ATTN_BLOCK, ATTN_TILE };
+struct AttnPlan { int kind, per, nsplit; };
+AttnPlan bf16_attention_plan(const int* kv_end, const int* seq_m, int B, int Hq, int Hkv, int max_splits);
+void bf16_attention(hipStream_t st, const AttnPlan& plan, const bf16_t* Q, const bf16_t* kv, const CallMeta& meta, int pos_add, int B,
+                    int max_m, int total_qt, int Hq, int Hkv, int D, int layer, int n_pages, int pages_per_seq, const AttnScratch& scr,
+                    bf16_t* out, int out_ktiles);
 void bf16_argmax_reduce(hipStream_t st, const float* pmax, const int* pidx, int ntiles, int pstride, int M, int* v);
 
 // ---- rejection-sampling acceptance (kernels_sample.hip) ----
-void k_softmax_rows(hipStream_t st, const float* in, size_t in_stride, float* out, const int* out_idx, int out_add, int M, int vocab);
+// out (and out2, if set) <- softmax of the rows of `in`; k_softmax_draw also draws one token per row from it
+void k_softmax_rows(hipStream_t st, const float* in, float* out, const int* out_idx, int out_add, float* out2, const int* out2_idx, int M, int vocab);
+void k_softmax_draw(hipStream_t st, const float* in, float* out, const int* out_idx, int out_add, int M, int vocab, const float* u, int u_stride,
+                    int j, const int* row_seq, int* tok_next, int* draft_out, int stride);
 void k_rs_accept(hipStream_t st, const float* Pt, const float* Pd, int pd_rows_per_seq, int vocab, const CallMeta& meta,
                  int cand_stride, int B, const float* u_acc, int u_stride, int* n_accept);
-void k_draw_rows(hipStream_t st, const float* P, int rows_per_seq, int j, int vocab, const float* u, int u_stride,
-                 const int* row_seq, int M, int* tok_next, int* draft_out, int stride);
 void k_rs_draw(hipStream_t st, const float* Pt, const float* Pd, int pd_rows_per_seq, int vocab, const CallMeta& meta, int B,
                const int* n_accept, const float* u_res, int* next_tok);

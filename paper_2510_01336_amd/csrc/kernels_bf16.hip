@@ -1673,6 +1673,145 @@ __global__ __launch_bounds__(512) void attn_block_kernel(const uint4* __restrict
   }
 }
 
+// ---------------------------------------------------------------------------------------------
+// The same attention for few query rows over short contexts (drafted and catch-up rows, verify blocks of a batch): latency,
+// not bytes, bounds these calls.  A workgroup takes one q-tile of one KV head and a run of `per` pages; its eight waves take
+// every eighth page each, straight from HBM / L2 into registers (no LDS staging, no barrier per page: 256 KiB in flight per
+// compute unit), and meet once in LDS at the end.  The q-tiles of a KV head read the same pages from one L2 (blockIdx.x is
+// the KV head).  Up to a few pages per wave the call is then one launch, where the kernel above needs KV splits and a merge.
+// ---------------------------------------------------------------------------------------------
+template <int D>
+__global__ __launch_bounds__(512) void attn_tile_kernel(const uint4* __restrict__ Q, const bf16_t* __restrict__ kv, const int* seq_m,
+                                                        const int* seq_p0, const int* seq_row0, const int* qt_seq, const int* qt_local,
+                                                        const int* block_table, int pos_add, int rep, int Hkv, int layer, int n_pages,
+                                                        int pps, int nsplit, int per, float* part_o, float* part_ml,
+                                                        bf16_t* __restrict__ out, int out_ktiles) {
+  constexpr int DS = D / 32, DT = D / 16, KCH = 4 * DS;
+  __shared__ f32x4 lo[8][DT][64];
+  __shared__ float2 ml[8][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4, qc = lane & 15;
+  const int kvh = blockIdx.x, gqt = blockIdx.y, sp = blockIdx.z;
+  const int b = qt_seq[gqt], qt = qt_local[gqt], total_qt = gridDim.y;
+  const int m = seq_m[b], p0 = seq_p0[b] + pos_add, row0 = seq_row0[b], nq = m * rep, kv_end = p0 + m;
+  const int npages = (kv_end + EE_PAGE - 1) / EE_PAGE, pg0 = sp * per, pg1 = min(npages, pg0 + per);
+  if (pg0 >= npages) return;                            // whole workgroup; the merge pass knows this sequence's split count
+  const int* bt = block_table + b * pps;
+  const int qrow = qt * 16 + qc, limit = qrow < nq ? p0 + qrow / rep : -1;
+  u32x4 qf[DS];
+#pragma unroll
+  for (int s = 0; s < DS; ++s) qf[s] = ((const u32x4*)Q)[(((size_t)kvh * total_qt + gqt) * DS + s) * 64 + lane];
+  const float sc2 = 1.4426950408889634f / sqrtf((float)D);         // scores in base-2 units, as above
+  const u32x4 ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+  float mrun = -INFINITY;
+  f32x4 o[DT], lacc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  u32x4 kf[KCH], vf[2 * DT];
+  auto page_ptr = [&](int pg) __attribute__((always_inline)) {
+    return (const u32x4*)(kv + kv_slab(layer, bt[pg], kvh, n_pages, Hkv, D)) + lane;
+  };
+  int pg = pg0 + wave;
+  const u32x4* src = page_ptr(min(pg, pg1 - 1));
+  if (pg < pg1) {
+#pragma unroll
+    for (int c = 0; c < KCH; ++c) kf[c] = __builtin_nontemporal_load(src + c * 64);
+#pragma unroll
+    for (int c = 0; c < 2 * DT; ++c) vf[c] = __builtin_nontemporal_load(src + (KCH + c) * 64);
+  }
+  for (; pg < pg1; pg += 8) {
+    const int base = pg * EE_PAGE + 16 * g;             // this lane group holds positions base .. base+15
+    // (the next page's fragments are requested as soon as this page's are consumed; past the end the last page again, unused)
+    const u32x4* nsrc = page_ptr(min(pg + 8, pg1 - 1));
+    f32x4 s4[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) s4[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < DS; ++s)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) s4[t] = mfma16(kf[t * DS + s], qf[s], s4[t]);
+    if (pg + 8 < pg1) {
+#pragma unroll
+      for (int c = 0; c < KCH; ++c) kf[c] = __builtin_nontemporal_load(nsrc + c * 64);
+    }
+    const bool masked = (pg + 1) * EE_PAGE > p0;        // reaches into the block or past the end (uniform)
+    float tmax = -INFINITY;
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        if (base + 4 * t + v > limit) s4[t][v] = -INFINITY;
+        tmax = fmaxf(tmax, s4[t][v]);
+      }
+    tmax = colmax4(tmax * sc2);
+    const float mnew = fmaxf(mrun, tmax);
+    const float msafe = mnew == -INFINITY ? 0.f : mnew;
+    const float alpha = __builtin_amdgcn_exp2f(mrun - msafe), nm = -msafe;
+    mrun = mnew;
+    uint32_t pk[8];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      pk[2 * t] = pack2(__builtin_amdgcn_exp2f(fmaf(s4[t][0], sc2, nm)), __builtin_amdgcn_exp2f(fmaf(s4[t][1], sc2, nm)));
+      pk[2 * t + 1] = pack2(__builtin_amdgcn_exp2f(fmaf(s4[t][2], sc2, nm)), __builtin_amdgcn_exp2f(fmaf(s4[t][3], sc2, nm)));
+    }
+    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) { o[dt][0] *= alpha; o[dt][1] *= alpha; o[dt][2] *= alpha; o[dt][3] *= alpha; }
+      lacc[0] *= alpha; lacc[1] *= alpha; lacc[2] *= alpha; lacc[3] *= alpha;
+    }
+    const u32x4 P[2] = {u32x4{pk[0], pk[1], pk[2], pk[3]}, u32x4{pk[4], pk[5], pk[6], pk[7]}};
+    if (masked) {      // dead positions (>= kv_end) may hold anything: zero their V
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int pa = base + 8 * ks + 2 * j;
+          const uint32_t keep = pa + 1 < kv_end ? 0xffffffffu : (pa < kv_end ? 0xffffu : 0u);
+#pragma unroll
+          for (int dt = 0; dt < DT; ++dt) vf[dt * 2 + ks][j] &= keep;
+        }
+    }
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      lacc = mfma16(ones, P[ks], lacc);
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) o[dt] = mfma16(vf[dt * 2 + ks], P[ks], o[dt]);
+    }
+    if (pg + 8 < pg1) {
+#pragma unroll
+      for (int c = 0; c < 2 * DT; ++c) vf[c] = __builtin_nontemporal_load(nsrc + (KCH + c) * 64);
+    }
+  }
+  ml[wave][lane] = make_float2(mrun, lacc[0]);
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) lo[wave][dt][lane] = o[dt];
+  __syncthreads();
+  if (wave >= DT) return;                               // wave w finishes d-tile w, in a fixed order over the waves
+  float mall = -INFINITY, f[8], l = 0.f;
+#pragma unroll
+  for (int w = 0; w < 8; ++w) mall = fmaxf(mall, ml[w][lane].x);
+  const float msafe = mall == -INFINITY ? 0.f : mall;
+  f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int w = 0; w < 8; ++w) {
+    const float2 t = ml[w][lane];
+    f[w] = __builtin_amdgcn_exp2f(t.x - msafe);
+    l += f[w] * t.y;
+    const f32x4 x = lo[w][wave][lane];
+    acc[0] += f[w] * x[0]; acc[1] += f[w] * x[1]; acc[2] += f[w] * x[2]; acc[3] += f[w] * x[3];
+  }
+  if (nsplit == 1) {
+    if (qrow < nq) {
+      const float inv = 1.0f / l;
+      const int row = row0 + qrow / rep, col = (kvh * rep + qrow % rep) * D + wave * 16 + 4 * g;
+      *(uint2*)(out + frag_offset(row, col, out_ktiles)) = make_uint2(pack2(acc[0] * inv, acc[1] * inv), pack2(acc[2] * inv, acc[3] * inv));
+    }
+  } else {
+    const size_t slot = ((size_t)gqt * Hkv + kvh) * nsplit + sp;
+    if (wave == 0 && g == 0) *(float2*)(part_ml + slot * 32 + qc * 2) = make_float2(mall, l);
+    ((f32x4*)part_o)[(slot * DT + wave) * 64 + lane] = acc;
+  }
+}
+
 // merge the KV splits of one (q-tile, KV head) and emit the bf16 attention output in fragment layout
 // (O-projection operand).  Workgroup = (q-tile, KV head, pair of d-tiles); its four waves share out the
 // splits (wave w takes w, w+4, ...), each folding its share with all loads of a batch of eight splits in
@@ -1758,14 +1897,11 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
   }
 }
 
-// Pages per KV split.  Every split of every sequence takes the same number of pages, so that a ragged
-// batch is cut into workgroups of equal length; the count is the smallest one (>= 4, the software
-// pipeline's depth) that keeps the launch within one workgroup per compute unit (the LDS ring admits
-// one resident workgroup, so a second round would start cold).  kv_end[b] = 0: sequence not taking part.
-int bf16_attention_pages_per_split(const int* kv_end, const int* seq_m, int B, int Hq, int Hkv, int max_splits) {
-  const int rep = Hq / Hkv;
-  int max_pages = 1;
-  for (int b = 0; b < B; ++b) max_pages = max(max_pages, ceil_div(kv_end[b], EE_PAGE));
+// Pages per KV split of attn_kernel.  Every split of every sequence takes the same number of pages, so that a ragged
+// batch is cut into workgroups of equal length; the count is the smallest one that keeps the launch within one workgroup
+// per compute unit (the LDS ring admits one resident workgroup, so a second round would start cold).  kv_end[b] = 0: sequence
+// not taking part.
+static int ring_pages_per_split(const int* kv_end, const int* seq_m, int B, int rep, int Hkv, int max_pages, int max_splits) {
   int per = max(2, ceil_div(max_pages, max(1, min(max_splits, EE_MAX_SPLITS))));
   if (g_attn_pages_override > 0) return min(max(per, g_attn_pages_override), max_pages);   // (never more splits than the scratch holds)
   for (; per < max_pages; ++per) {
@@ -1778,45 +1914,79 @@ int bf16_attention_pages_per_split(const int* kv_end, const int* seq_m, int B, i
   return min(per, max_pages);
 }
 
-template <int D, int QPW>
-static void launch_attn(hipStream_t st, dim3 grid, const bf16_t* Q, const bf16_t* kv, const CallMeta& meta, int pos_add, int rep,
-                        int total_qt, int Hkv, int layer, int n_pages, int pps, int nsplit, int per, const AttnScratch& scr,
-                        bf16_t* out, int out_ktiles) {
-  hipLaunchKernelGGL((attn_kernel<D, QPW>), grid, dim3(64 * EE_ATTN_WAVES), 0, st, (const uint4*)Q, kv, meta.seq_m, meta.seq_p0,
-                     meta.seq_qt0, meta.seq_row0, meta.block_table, pos_add, rep, total_qt, Hkv, layer, n_pages, pps, nsplit, per,
-                     scr.part_o, scr.part_ml, out, out_ktiles);
+// Kernel and split length of a call.  Long blocks that fill the chip unsplit take attn_block_kernel; else the cheaper of the
+// ring kernel and the tile kernel by what they measured (8B head shapes, microseconds; a merge launch adds 5.8):
+//   ring: 3 + 1.5 per page of a split                       (one sequence, 9 rows, 2 pages a split: 11.1 with the merge)
+//   tile: 3.9 + 0.52 per page a workgroup reads -- one compute unit takes in no more than about 60 GB/s; more workgroups than
+//         compute units take their sum over the chip and 30 % (2 pages 4.6, 8 pages 7.7, 16 pages 12.3; 384 workgroups of 16
+//         pages on average 26.9)
+// and neither quicker than the bytes at 6.5 TB/s.  Eight requests of ~1000 tokens, one row each: ring 16.9, tile 12.7; one
+// request, 500 tokens, 9 rows: 9.7 / 7.6; one request, 2048 tokens, 9 rows: 11.1 / 11.8.  The tile kernel never takes more
+// splits than the ring kernel would, so the scratch of a call does not grow, and has to promise 5 %.  A pinned split length (test hook) keeps every
+// call in the ring kernel, so that a sequence is cut alike alone and in a batch.
+AttnPlan bf16_attention_plan(const int* kv_end, const int* seq_m, int B, int Hq, int Hkv, int max_splits) {
+  const int rep = Hq / Hkv;
+  int max_pages = 1, max_qt = 0;
+  long pages = 0;
+  for (int b = 0; b < B; ++b) {
+    if (kv_end[b] <= 0) continue;
+    const int n = ceil_div(kv_end[b], EE_PAGE);
+    max_pages = max(max_pages, n); max_qt = max(max_qt, ceil_div(seq_m[b] * rep, 16));
+    pages += n;
+  }
+  AttnPlan ring{ATTN_RING, ring_pages_per_split(kv_end, seq_m, B, rep, Hkv, max_pages, max_splits), 1};
+  ring.nsplit = ceil_div(max_pages, ring.per);
+  if (g_attn_pages_override > 0) return ring;
+  if (ring.nsplit == 1 && max_qt > EE_ATTN_COMPUTE) return AttnPlan{ATTN_BLOCK, max_pages, 1};
+  const float floor_us = pages * Hkv * (EE_PAGE * 128 * 4.0f) / 6.5e6f, merge_us = 5.8f;
+  float least = max(3.0f + 1.5f * ring.per, floor_us) + (ring.nsplit > 1 ? merge_us : 0.f);
+  AttnPlan best = ring;
+  for (int per = 8;; per += 8) {
+    per = min(per, max_pages);
+    const int nsplit = ceil_div(max_pages, per);
+    if (nsplit <= ring.nsplit) {
+      long wgs = 0, reads = 0;                         // workgroups, pages they read
+      for (int b = 0; b < B; ++b) {
+        if (kv_end[b] <= 0) continue;
+        const int n = ceil_div(kv_end[b], EE_PAGE), q = ceil_div(seq_m[b] * rep, 16) * Hkv;
+        wgs += (long)ceil_div(n, per) * q; reads += (long)n * q;
+      }
+      const float whole = (3.9f * wgs + 0.52f * reads) / 256.0f;
+      const float us = max(max(3.9f + 0.52f * per, wgs > 256 ? 1.3f * whole : 0.f), floor_us) + (nsplit > 1 ? merge_us : 0.f);
+      if (us < 0.95f * least) { least = us; best = AttnPlan{ATTN_TILE, per, nsplit}; }
+    }
+    if (per >= max_pages) break;
+  }
+  return best;
 }
 
-void bf16_attention(hipStream_t st, const bf16_t* Q, const bf16_t* kv, const CallMeta& meta, int pos_add, int B, int max_m,
-                    int total_qt, int max_kv_end, int Hq, int Hkv, int D, int layer, int n_pages, int pages_per_seq,
-                    const AttnScratch& scr, bf16_t* out, int out_ktiles, int per) {
-  const int rep = Hq / Hkv;
-  const int max_qt = ceil_div(max_m * rep, 16);
-  const int qt_groups = ceil_div(max_qt, EE_ATTN_COMPUTE);
-  const int max_pages = ceil_div(max_kv_end, EE_PAGE);
-  per = max(1, min(per, max_pages));
-  const int nsplit = ceil_div(max_pages, per);       // grid width and stride of the partial slots
-  dim3 grid(nsplit, Hkv * qt_groups, B);
-  // Blocks of more than six q-tiles whose workgroups fill the chip without KV splits (context build); a pinned split length
-  // keeps every call in the kernel that splits, so that a sequence is cut alike alone and in a batch
-  if (nsplit == 1 && max_qt > EE_ATTN_COMPUTE && g_attn_pages_override <= 0) {
-    dim3 bgrid(Hkv, ceil_div(max_qt, 8), B);
-    if (D == 128)
-      hipLaunchKernelGGL((attn_block_kernel<128>), bgrid, dim3(512), 0, st, (const uint4*)Q, kv, meta.seq_m, meta.seq_p0, meta.seq_qt0,
-                         meta.seq_row0, meta.block_table, pos_add, rep, total_qt, Hkv, layer, n_pages, pages_per_seq, out, out_ktiles);
-    else
-      hipLaunchKernelGGL((attn_block_kernel<64>), bgrid, dim3(512), 0, st, (const uint4*)Q, kv, meta.seq_m, meta.seq_p0, meta.seq_qt0,
-                         meta.seq_row0, meta.block_table, pos_add, rep, total_qt, Hkv, layer, n_pages, pages_per_seq, out, out_ktiles);
+template <int D>
+static void launch_attn(hipStream_t st, const AttnPlan& plan, const bf16_t* Q, const bf16_t* kv, const CallMeta& meta, int pos_add, int B,
+                        int max_qt, int rep, int total_qt, int Hkv, int layer, int n_pages, int pps, const AttnScratch& scr, bf16_t* out,
+                        int out_ktiles) {
+  if (plan.kind == ATTN_BLOCK) {
+    hipLaunchKernelGGL((attn_block_kernel<D>), dim3(Hkv, ceil_div(max_qt, 8), B), dim3(512), 0, st, (const uint4*)Q, kv, meta.seq_m,
+                       meta.seq_p0, meta.seq_qt0, meta.seq_row0, meta.block_table, pos_add, rep, total_qt, Hkv, layer, n_pages, pps, out,
+                       out_ktiles);
     return;
   }
-  if (D == 128) launch_attn<128, 1>(st, grid, Q, kv, meta, pos_add, rep, total_qt, Hkv, layer, n_pages, pages_per_seq, nsplit, per, scr, out, out_ktiles);
-  else launch_attn<64, 1>(st, grid, Q, kv, meta, pos_add, rep, total_qt, Hkv, layer, n_pages, pages_per_seq, nsplit, per, scr, out, out_ktiles);
-  if (nsplit > 1) {
-    if (D == 128)
-      hipLaunchKernelGGL((attn_merge_kernel<128>), dim3(total_qt, Hkv, 4), dim3(256), 0, st, scr.part_o, scr.part_ml, meta.qt_seq,
-                         meta.qt_local, meta.seq_m, meta.seq_p0, meta.seq_row0, pos_add, rep, Hkv, nsplit, per, out, out_ktiles);
-    else
-      hipLaunchKernelGGL((attn_merge_kernel<64>), dim3(total_qt, Hkv, 2), dim3(256), 0, st, scr.part_o, scr.part_ml, meta.qt_seq,
-                         meta.qt_local, meta.seq_m, meta.seq_p0, meta.seq_row0, pos_add, rep, Hkv, nsplit, per, out, out_ktiles);
-  }
+  if (plan.kind == ATTN_TILE)
+    hipLaunchKernelGGL((attn_tile_kernel<D>), dim3(Hkv, total_qt, plan.nsplit), dim3(512), 0, st, (const uint4*)Q, kv, meta.seq_m,
+                       meta.seq_p0, meta.seq_row0, meta.qt_seq, meta.qt_local, meta.block_table, pos_add, rep, Hkv, layer, n_pages, pps,
+                       plan.nsplit, plan.per, scr.part_o, scr.part_ml, out, out_ktiles);
+  else
+    hipLaunchKernelGGL((attn_kernel<D, 1>), dim3(plan.nsplit, Hkv * ceil_div(max_qt, EE_ATTN_COMPUTE), B), dim3(64 * EE_ATTN_WAVES), 0, st,
+                       (const uint4*)Q, kv, meta.seq_m, meta.seq_p0, meta.seq_qt0, meta.seq_row0, meta.block_table, pos_add, rep,
+                       total_qt, Hkv, layer, n_pages, pps, plan.nsplit, plan.per, scr.part_o, scr.part_ml, out, out_ktiles);
+  if (plan.nsplit > 1)
+    hipLaunchKernelGGL((attn_merge_kernel<D>), dim3(total_qt, Hkv, D / 32), dim3(256), 0, st, scr.part_o, scr.part_ml, meta.qt_seq,
+                       meta.qt_local, meta.seq_m, meta.seq_p0, meta.seq_row0, pos_add, rep, Hkv, plan.nsplit, plan.per, out, out_ktiles);
+}
+
+void bf16_attention(hipStream_t st, const AttnPlan& plan, const bf16_t* Q, const bf16_t* kv, const CallMeta& meta, int pos_add, int B,
+                    int max_m, int total_qt, int Hq, int Hkv, int D, int layer, int n_pages, int pages_per_seq, const AttnScratch& scr,
+                    bf16_t* out, int out_ktiles) {
+  const int rep = Hq / Hkv, max_qt = ceil_div(max_m * rep, 16);
+  if (D == 128) launch_attn<128>(st, plan, Q, kv, meta, pos_add, B, max_qt, rep, total_qt, Hkv, layer, n_pages, pages_per_seq, scr, out, out_ktiles);
+  else launch_attn<64>(st, plan, Q, kv, meta, pos_add, B, max_qt, rep, total_qt, Hkv, layer, n_pages, pages_per_seq, scr, out, out_ktiles);
 }

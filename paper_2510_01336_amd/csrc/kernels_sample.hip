@@ -24,26 +24,178 @@ __device__ inline float block_reduce_sum(float v, float* sh) {
   return r;
 }
 
-// p = softmax(logits) per row; row r of `in` (stride in_stride floats) -> row out_idx[r] (or r) + out_add of `out`
-// (rows of `vocab` floats).  In place when in == out with the same row mapping.
-__global__ __launch_bounds__(EE_SAMPLE_THREADS) void softmax_rows_kernel(const float* in, size_t in_stride, float* out,
-                                                                        const int* out_idx, int out_add, int vocab) {
+// ---- rows of a vocabulary: who reads what ----
+// One workgroup of sixteen waves per row; wave w owns the contiguous tokens [w*R, (w+1)*R), R a multiple of 256, and walks them
+// 256 at a time, four per lane (one 16-byte load where the rows allow it).  For the inverse CDF a wave keeps the weight of each
+// of its (up to 64 groups of) chunks in the lane of that number, so the chunk that holds a draw is found with shuffles and only
+// that chunk is read again.  One compute unit takes in about 60 GB/s, which is what bounds these kernels (32000 tokens: 128
+// KB, 2 us); the first version let every thread walk a contiguous strip of its own (uncoalesced) and one thread add up
+// 1024 strip sums: 67 us a draw at 32000 tokens.
+struct RowSpan { int i0, i1, per; };       // this wave's tokens, chunks per group
+__device__ inline RowSpan row_span(int vocab) {
+  const int w = threadIdx.x >> 6, R = ((vocab + 16 * 256 - 1) / (16 * 256)) * 256;
+  RowSpan r;
+  r.i0 = min(vocab, w * R); r.i1 = min(vocab, (w + 1) * R);
+  r.per = (R / 256 + 63) / 64;
+  return r;
+}
+// four consecutive elements from i (those below n; the others 0); VEC: i and the row are 16-byte aligned
+template <bool VEC>
+__device__ inline float4 load4(const float* __restrict__ x, int i, int n) {
+  if (VEC && i + 3 < n) return *(const float4*)(x + i);
+  return make_float4(i < n ? x[i] : 0.f, i + 1 < n ? x[i + 1] : 0.f, i + 2 < n ? x[i + 2] : 0.f, i + 3 < n ? x[i + 3] : 0.f);
+}
+__device__ inline float wave_sum(float v) {
+  for (int s = 1; s < 64; s <<= 1) v += __shfl_xor(v, s, 64);
+  return v;
+}
+// inclusive sum over the lanes below and this one
+__device__ inline float wave_scan(float v) {
+  const int lane = threadIdx.x & 63;
+  for (int s = 1; s < 64; s <<= 1) {
+    const float o = __shfl_up(v, s, 64);
+    if (lane >= s) v += o;
+  }
+  return v;
+}
+// The draw: first token whose cumulative weight exceeds u * (sum of weights).  group: the weight of chunk group `lane` of this
+// wave, last: this thread's last token with weight (-1: none); weight(i) gives four consecutive weights.
+struct DrawShared { float tot[16]; int last[16]; int tok; };
+template <typename W>
+__device__ inline int draw_token(const RowSpan& sp, float group, int last, float u, DrawShared& sh, W weight) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const float incl = wave_scan(group);
+  for (int s = 1; s < 64; s <<= 1) last = max(last, __shfl_xor(last, s, 64));
+  if (lane == 63) { sh.tot[w] = incl; sh.last[w] = last; }
+  if (threadIdx.x == 0) sh.tok = -1;
+  __syncthreads();
+  float total = 0.f;
+  int end = -1;
+  for (int k = 0; k < 16; ++k) { total += sh.tot[k]; end = max(end, sh.last[k]); }
+  const float target = u * total;
+  float pre = 0.f;
+  int h = -1;
+  for (int k = 0; k < 16 && h < 0; ++k) {
+    if (pre + sh.tot[k] > target) h = k;
+    else pre += sh.tot[k];
+  }
+  if (h == w) {
+    const unsigned long long over = __ballot(pre + incl > target);
+    const int gl = over ? __ffsll((long long)over) - 1 : 63;
+    float run = pre + (gl ? __shfl(incl, gl - 1, 64) : 0.f);
+    int tok = -1, seen = -1;                            // (seen: the group's last token with weight, should rounding pass the target by)
+    for (int c = 0; c < sp.per && tok < 0; ++c) {
+      const int i = sp.i0 + (gl * sp.per + c) * 256 + 4 * lane;
+      if (i - 4 * lane >= sp.i1) break;
+      const float4 x = weight(i);
+      const float s0 = x.x, s1 = s0 + x.y, s2 = s1 + x.z, s3 = s2 + x.w;
+      const float inc = wave_scan(s3), base = run + (inc - s3);
+      const int k = base + s0 > target ? 0 : (base + s1 > target ? 1 : (base + s2 > target ? 2 : (base + s3 > target ? 3 : 4)));
+      const unsigned long long hit = __ballot(k < 4);
+      if (hit) {
+        const int l = __ffsll((long long)hit) - 1;
+        tok = __shfl(i + k, l, 64);
+      }
+      const int mine = x.w > 0.f ? i + 3 : (x.z > 0.f ? i + 2 : (x.y > 0.f ? i + 1 : (x.x > 0.f ? i : -1)));
+      seen = max(seen, mine);
+      run += __shfl(inc, 63, 64);
+    }
+    for (int s = 1; s < 64; s <<= 1) seen = max(seen, __shfl_xor(seen, s, 64));
+    if (lane == 0) sh.tok = tok >= 0 ? tok : seen;
+  }
+  __syncthreads();
+  return sh.tok >= 0 ? sh.tok : end;                     // rounding at the very end of the interval: the last token with weight
+}
+
+// p = softmax(logits) per row; row r of `in` (stride vocab floats) -> row out_idx[r] (or r) + out_add of `out`, and of `out2` if
+// set.  In place when in == out with the same row mapping.  DRAW: also draws the row's token from p with u[row_seq[r]*u_stride + j].
+template <bool VEC, bool DRAW>
+__global__ __launch_bounds__(EE_SAMPLE_THREADS) void softmax_rows_kernel(const float* in, float* out, const int* out_idx, int out_add,
+                                                                        float* out2, const int* out2_idx, int vocab,
+                                                                        const float* __restrict__ u, int u_stride, int j,
+                                                                        const int* __restrict__ row_seq, int* tok_next, int* draft_out,
+                                                                        int stride) {
   __shared__ float sh[EE_SAMPLE_THREADS / 64];
-  const int r = blockIdx.x;
-  const float* x = in + (size_t)r * in_stride;
+  __shared__ DrawShared ds;
+  const int r = blockIdx.x, lane = threadIdx.x & 63;
+  const float* x = in + (size_t)r * vocab;
   float* y = out + (size_t)((out_idx ? out_idx[r] : r) + out_add) * vocab;
+  float* y2 = out2 ? out2 + (size_t)out2_idx[r] * vocab : nullptr;
+  const RowSpan sp = row_span(vocab);
   float mx = -INFINITY;
-  for (int i = threadIdx.x; i < vocab; i += EE_SAMPLE_THREADS) mx = fmaxf(mx, x[i]);
+#pragma unroll 4
+  for (int i = sp.i0 + 4 * lane; i < sp.i1; i += 256) {
+    const float4 v = load4<VEC>(x, i, sp.i1);
+    mx = fmaxf(mx, fmaxf(fmaxf(v.x, i + 1 < sp.i1 ? v.y : v.x), fmaxf(i + 2 < sp.i1 ? v.z : v.x, i + 3 < sp.i1 ? v.w : v.x)));
+  }
   mx = block_reduce_max(mx, sh);
   float sum = 0.f;
-  for (int i = threadIdx.x; i < vocab; i += EE_SAMPLE_THREADS) sum += __expf(x[i] - mx);
+#pragma unroll 4
+  for (int i = sp.i0 + 4 * lane; i < sp.i1; i += 256) {
+    const float4 v = load4<VEC>(x, i, sp.i1);
+    sum += (__expf(v.x - mx) + (i + 1 < sp.i1 ? __expf(v.y - mx) : 0.f)) + ((i + 2 < sp.i1 ? __expf(v.z - mx) : 0.f) + (i + 3 < sp.i1 ? __expf(v.w - mx) : 0.f));
+  }
   sum = block_reduce_sum(sum, sh);
   const float inv = 1.0f / sum;
-  for (int i = threadIdx.x; i < vocab; i += EE_SAMPLE_THREADS) y[i] = __expf(x[i] - mx) * inv;
+  float group = 0.f;
+  int last = -1, chunk = 0;
+  for (int c0 = sp.i0; c0 < sp.i1; c0 += 1024) {              // four chunks in flight; the whole wave walks every one (the sums use all lanes)
+    float4 v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = load4<VEC>(x, c0 + 256 * q + 4 * lane, sp.i1);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = c0 + 256 * q + 4 * lane;
+      float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (i < sp.i1) p.x = __expf(v[q].x - mx) * inv;
+      if (i + 1 < sp.i1) p.y = __expf(v[q].y - mx) * inv;
+      if (i + 2 < sp.i1) p.z = __expf(v[q].z - mx) * inv;
+      if (i + 3 < sp.i1) p.w = __expf(v[q].w - mx) * inv;
+      if (VEC && i + 3 < sp.i1) {
+        *(float4*)(y + i) = p;
+        if (y2) *(float4*)(y2 + i) = p;
+      } else {
+        const float e[4] = {p.x, p.y, p.z, p.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (i + k < sp.i1) { y[i + k] = e[k]; if (y2) y2[i + k] = e[k]; }
+      }
+      if (DRAW) {
+        const float sm = wave_sum((p.x + p.y) + (p.z + p.w));
+        if (chunk / sp.per == lane) group += sm;
+        last = p.w > 0.f ? i + 3 : (p.z > 0.f ? i + 2 : (p.y > 0.f ? i + 1 : (p.x > 0.f ? i : last)));
+        ++chunk;
+      }
+    }
+  }
+  if (DRAW) {
+    __syncthreads();                                     // (and the row is complete: a chunk of it is read again)
+    const int b = row_seq[r];
+    const int tok = draw_token(sp, group, last, u[(size_t)b * u_stride + j], ds, [&](int i) { return load4<VEC>(y, i, sp.i1); });
+    if (threadIdx.x == 0) { tok_next[r] = tok; draft_out[b * stride + j] = tok; }
+  }
 }
-void k_softmax_rows(hipStream_t st, const float* in, size_t in_stride, float* out, const int* out_idx, int out_add, int M, int vocab) {
+static bool rows_aligned(int vocab, const float* a, const float* b, const float* c) {
+  return vocab % 4 == 0 && (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c) & 15) == 0;
+}
+void k_softmax_rows(hipStream_t st, const float* in, float* out, const int* out_idx, int out_add, float* out2, const int* out2_idx, int M, int vocab) {
   if (M <= 0) return;
-  hipLaunchKernelGGL(softmax_rows_kernel, dim3(M), dim3(EE_SAMPLE_THREADS), 0, st, in, in_stride, out, out_idx, out_add, vocab);
+  if (rows_aligned(vocab, in, out, out2))
+    hipLaunchKernelGGL((softmax_rows_kernel<true, false>), dim3(M), dim3(EE_SAMPLE_THREADS), 0, st, in, out, out_idx, out_add, out2, out2_idx,
+                       vocab, nullptr, 0, 0, nullptr, nullptr, nullptr, 0);
+  else
+    hipLaunchKernelGGL((softmax_rows_kernel<false, false>), dim3(M), dim3(EE_SAMPLE_THREADS), 0, st, in, out, out_idx, out_add, out2, out2_idx,
+                       vocab, nullptr, 0, 0, nullptr, nullptr, nullptr, 0);
+}
+void k_softmax_draw(hipStream_t st, const float* in, float* out, const int* out_idx, int out_add, int M, int vocab, const float* u, int u_stride,
+                    int j, const int* row_seq, int* tok_next, int* draft_out, int stride) {
+  if (M <= 0) return;
+  if (rows_aligned(vocab, in, out, nullptr))
+    hipLaunchKernelGGL((softmax_rows_kernel<true, true>), dim3(M), dim3(EE_SAMPLE_THREADS), 0, st, in, out, out_idx, out_add, nullptr, nullptr,
+                       vocab, u, u_stride, j, row_seq, tok_next, draft_out, stride);
+  else
+    hipLaunchKernelGGL((softmax_rows_kernel<false, true>), dim3(M), dim3(EE_SAMPLE_THREADS), 0, st, in, out, out_idx, out_add, nullptr, nullptr,
+                       vocab, u, u_stride, j, row_seq, tok_next, draft_out, stride);
 }
 
 // The accept tests of one block per sequence (one wavefront each): candidate j, drawn from row
@@ -76,92 +228,54 @@ void k_rs_accept(hipStream_t st, const float* Pt, const float* Pd, int pd_rows_p
                      meta.cand, meta.n_cand, cand_stride, u_acc, u_stride, n_accept);
 }
 
-// One draw per workgroup by inverse CDF: the first token whose cumulative weight exceeds u * (sum of weights).
-// Thread t owns the contiguous tokens [t*C, (t+1)*C); chunk sums meet in LDS, one thread walks them and the
-// owner of the hit chunk walks its tokens.  weight(i) = max(0, A[i] - B[i]) with B optional.
-__device__ inline int draw_token(const float* __restrict__ A, const float* __restrict__ B, int vocab, float u, float* chunk, int* hit) {
-  const int t = threadIdx.x, C = (vocab + EE_SAMPLE_THREADS - 1) / EE_SAMPLE_THREADS;
-  const int i0 = t * C, i1 = min(vocab, i0 + C);
-  float local = 0.f;
-  int last_pos = -1;
-  for (int i = i0; i < i1; ++i) {
-    const float w = B ? fmaxf(0.f, A[i] - B[i]) : A[i];
-    local += w;
-    if (w > 0.f) last_pos = i;
-  }
-  chunk[t] = local;
-  if (t == 0) { hit[0] = -1; hit[1] = -1; }
-  __syncthreads();
-  atomicMax(&hit[1], last_pos);                 // last token with weight (integer maximum: order-free)
-  __shared__ float s_target, s_prefix;
-  if (t == 0) {
-    float total = 0.f;
-    for (int c = 0; c < EE_SAMPLE_THREADS; ++c) total += chunk[c];
-    const float target = u * total;
-    float pre = 0.f;
-    int h = -1;
-    for (int c = 0; c < EE_SAMPLE_THREADS; ++c) {
-      if (pre + chunk[c] > target) { h = c; break; }
-      pre += chunk[c];
-    }
-    hit[0] = h; s_target = target; s_prefix = pre;
-  }
-  __syncthreads();
-  __shared__ int s_tok;
-  if (t == 0) s_tok = -1;
-  __syncthreads();
-  if (t == hit[0]) {
-    float run = s_prefix;
-    int tok = -1;
-    for (int i = i0; i < i1; ++i) {
-      run += B ? fmaxf(0.f, A[i] - B[i]) : A[i];
-      if (run > s_target) { tok = i; break; }
-    }
-    s_tok = tok;
-  }
-  __syncthreads();
-  const int tok = s_tok >= 0 ? s_tok : hit[1];  // rounding at the very end of the interval: the last token with weight
-  __syncthreads();
-  return tok;
-}
-
-// drafting: token of sequence b ~ row b*rows_per_seq + j of P (the distribution just stored there)
-__global__ __launch_bounds__(EE_SAMPLE_THREADS) void draw_rows_kernel(const float* __restrict__ P, int rows_per_seq, int j, int vocab,
-                                                                      const float* __restrict__ u, int u_stride,
-                                                                      const int* __restrict__ row_seq, int* tok_next,
-                                                                      int* draft_out, int stride) {
-  __shared__ float chunk[EE_SAMPLE_THREADS];
-  __shared__ int hit[2];
-  const int r = blockIdx.x, b = row_seq[r];            // one row per drafting sequence
-  const int tok = draw_token(P + ((size_t)b * rows_per_seq + j) * vocab, nullptr, vocab, u[(size_t)b * u_stride + j], chunk, hit);
-  if (threadIdx.x == 0) { tok_next[r] = tok; draft_out[b * stride + j] = tok; }
-}
-void k_draw_rows(hipStream_t st, const float* P, int rows_per_seq, int j, int vocab, const float* u, int u_stride,
-                 const int* row_seq, int M, int* tok_next, int* draft_out, int stride) {
-  hipLaunchKernelGGL(draw_rows_kernel, dim3(M), dim3(EE_SAMPLE_THREADS), 0, st, P, rows_per_seq, j, vocab, u, u_stride, row_seq,
-                     tok_next, draft_out, stride);
-}
-
 // after the accept tests: the replacement from the residual distribution at the first rejected position, or,
 // when every candidate was accepted and the block has one more row, the target's own next token
+// -- one inverse-CDF draw per sequence; weight(i) = max(0, target - draft) or the target's own probability
+template <bool VEC>
 __global__ __launch_bounds__(EE_SAMPLE_THREADS) void rs_draw_kernel(const float* __restrict__ Pt, const float* __restrict__ Pd,
                                                                     int pd_rows_per_seq, int vocab, const int* seq_row0,
                                                                     const int* seq_m, const int* n_cand, const int* n_accept,
                                                                     const float* __restrict__ u_res, int* next_tok) {
-  __shared__ float chunk[EE_SAMPLE_THREADS];
-  __shared__ int hit[2];
-  const int b = blockIdx.x;
+  __shared__ DrawShared ds;
+  const int b = blockIdx.x, lane = threadIdx.x & 63;
   const int m = seq_m[b];
   if (m == 0) { if (threadIdx.x == 0) next_tok[b] = -1; return; }
   const int a = n_accept[b], nc = n_cand[b];
   if (a >= m) { if (threadIdx.x == 0) next_tok[b] = -1; return; }      // all accepted and no further row
   const float* A = Pt + (size_t)(seq_row0[b] + a) * vocab;
   const float* Bd = a < nc ? Pd + ((size_t)b * pd_rows_per_seq + a) * vocab : nullptr;
-  const int tok = draw_token(A, Bd, vocab, u_res[b], chunk, hit);
+  const RowSpan sp = row_span(vocab);
+  auto weight = [&](int i) {
+    float4 x = load4<VEC>(A, i, sp.i1);
+    if (Bd) {
+      const float4 q = load4<VEC>(Bd, i, sp.i1);
+      x = make_float4(fmaxf(0.f, x.x - q.x), fmaxf(0.f, x.y - q.y), fmaxf(0.f, x.z - q.z), fmaxf(0.f, x.w - q.w));
+    }
+    return x;
+  };
+  float group = 0.f;
+  int last = -1, chunk = 0;
+  for (int c0 = sp.i0; c0 < sp.i1; c0 += 1024) {         // four chunks in flight
+    float4 x[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) x[q] = weight(c0 + 256 * q + 4 * lane);      // (0 past the end)
+#pragma unroll
+    for (int q = 0; q < 4; ++q, ++chunk) {
+      const int i = c0 + 256 * q + 4 * lane;
+      const float sm = wave_sum((x[q].x + x[q].y) + (x[q].z + x[q].w));
+      if (chunk / sp.per == lane) group += sm;
+      last = x[q].w > 0.f ? i + 3 : (x[q].z > 0.f ? i + 2 : (x[q].y > 0.f ? i + 1 : (x[q].x > 0.f ? i : last)));
+    }
+  }
+  const int tok = draw_token(sp, group, last, u_res[b], ds, weight);
   if (threadIdx.x == 0) next_tok[b] = tok;
 }
 void k_rs_draw(hipStream_t st, const float* Pt, const float* Pd, int pd_rows_per_seq, int vocab, const CallMeta& meta, int B,
                const int* n_accept, const float* u_res, int* next_tok) {
-  hipLaunchKernelGGL(rs_draw_kernel, dim3(B), dim3(EE_SAMPLE_THREADS), 0, st, Pt, Pd, pd_rows_per_seq, vocab, meta.seq_row0,
-                     meta.seq_m, meta.n_cand, n_accept, u_res, next_tok);
+  if (rows_aligned(vocab, Pt, Pd, nullptr))
+    hipLaunchKernelGGL((rs_draw_kernel<true>), dim3(B), dim3(EE_SAMPLE_THREADS), 0, st, Pt, Pd, pd_rows_per_seq, vocab, meta.seq_row0,
+                       meta.seq_m, meta.n_cand, n_accept, u_res, next_tok);
+  else
+    hipLaunchKernelGGL((rs_draw_kernel<false>), dim3(B), dim3(EE_SAMPLE_THREADS), 0, st, Pt, Pd, pd_rows_per_seq, vocab, meta.seq_row0,
+                       meta.seq_m, meta.n_cand, n_accept, u_res, next_tok);
 }

@@ -407,21 +407,14 @@ static size_t closing_gain(const ee_model* m, int l1) {
   return m->gfinal;
 }
 
-// attention split plan of a call (the same for all its layers): pages per KV split and the scratch handed to the
-// kernels; nsplit_out = KV splits of the longest sequence = stride of the partial slots
-static int attention_plan(const ee_session* s, const CallPlan& p, int pos_add, AttnScratch& scr, int* nsplit_out) {
+// attention plan of a call (the same for all its layers) and the scratch handed to the kernels
+static AttnPlan attention_plan(const ee_session* s, const CallPlan& p, int pos_add, AttnScratch& scr) {
   const ee_config& c = s->m->cfg;
   scr = AttnScratch{s->part_o, s->part_ml, (int)std::min<size_t>(s->max_splits, s->part_units / std::max(1, p.total_qt))};
-  int per = 1;
-  if (s->m->bf16) {
-    std::vector<int> kv_end(s->B);
-    for (int b = 0; b < s->B; ++b) kv_end[b] = p.m[b] > 0 ? p.p0[b] + p.m[b] + pos_add : 0;
-    per = bf16_attention_pages_per_split(kv_end.data(), p.m.data(), s->B, c.n_q_heads, c.n_kv_heads, scr.max_splits);
-  }
-  const int max_pages = ceil_div(p.max_kv_end + pos_add, EE_PAGE);
-  per = std::max(1, std::min(per, max_pages));
-  if (nsplit_out) *nsplit_out = ceil_div(max_pages, per);
-  return per;
+  if (!s->m->bf16) return AttnPlan{ATTN_RING, 1, 1};
+  std::vector<int> kv_end(s->B);
+  for (int b = 0; b < s->B; ++b) kv_end[b] = p.m[b] > 0 ? p.p0[b] + p.m[b] + pos_add : 0;
+  return bf16_attention_plan(kv_end.data(), p.m.data(), s->B, c.n_q_heads, c.n_kv_heads, scr.max_splits);
 }
 
 // where the rows of a pass come from: the embedding of tokens (a1 of a pass that starts at layer 0), kept hidden rows
@@ -453,7 +446,7 @@ static void run_layers(ee_session* s, int l0, int l1, const CallPlan& p, const C
     KF(KF_ROPE, k_rope_table(st, mt, pos_add, m->inv_freq, s->cs, M, D / 2, s->pps, s->rowinfo));
   }
   AttnScratch scr;
-  const int per = attention_plan(s, p, pos_add, scr, nullptr);
+  const AttnPlan attn = attention_plan(s, p, pos_add, scr);
   for (int l = l0; l < l1; ++l) {
     const LayerLoc& L = m->L[l];
     const float* g1 = (const float*)(m->base + L.g1);
@@ -471,8 +464,8 @@ static void run_layers(ee_session* s, int l0, int l1, const CallPlan& p, const C
       R.cs = s->cs; R.rowinfo = s->rowinfo; R.Hq = Hq; R.Hkv = Hkv; R.D = D; R.layer = l;
       R.n_pages = s->n_pages; R.total_qt = p.total_qt; R.Q = (bf16_t*)s->Qb; R.kv = (bf16_t*)s->kv;
       KF(KF_GEMM_QKV, gemm(s, EPI_ROPE, L.qkv, (const bf16_t*)s->XN, M, o));
-      KF(KF_ATTN, bf16_attention(st, (const bf16_t*)s->Qb, (const bf16_t*)s->kv, mt, pos_add, s->B, p.max_m, p.total_qt,
-                                 p.max_kv_end + pos_add, Hq, Hkv, D, l, s->n_pages, s->pps, scr, (bf16_t*)s->AO, L.o.ktiles(), per));
+      KF(KF_ATTN, bf16_attention(st, attn, (const bf16_t*)s->Qb, (const bf16_t*)s->kv, mt, pos_add, s->B, p.max_m, p.total_qt,
+                                 Hq, Hkv, D, l, s->n_pages, s->pps, scr, (bf16_t*)s->AO, L.o.ktiles()));
       o = GemmOut(); o.Y = s->X; o.ldy = d; o.nout = nout; o.nout.g = g2;
       KF(KF_GEMM_O, gemm(s, EPI_ADD, L.o, (const bf16_t*)s->AO, M, o));
       o = GemmOut(); o.H = (bf16_t*)s->H; o.h_ktiles = L.down.ktiles(); o.nin = nin;
@@ -824,8 +817,8 @@ static int draft_impl(ee_session* s, int k, int32_t* draft, const float* u) {
     if (j < k) {
       exit_head(s, p.M, 0);
       if (u) {      // p_{L_d} of this position into the draft-distribution store, then the draw
-        KF(KF_MISC, k_softmax_rows(s->st, s->LOGITS, c.vocab, s->Pd, mt.row_dst, j, p.M, c.vocab));
-        KF(KF_MISC, k_draw_rows(s->st, s->Pd, s->max_rows, j, c.vocab, s->u_dev, k, mt.row_seq, p.M, s->tok_next, s->draft_dev, s->max_rows));
+        KF(KF_MISC, k_softmax_draw(s->st, s->LOGITS, s->Pd, mt.row_dst, j, p.M, c.vocab, s->u_dev, k, j, mt.row_seq, s->tok_next,
+                                   s->draft_dev, s->max_rows));
       } else {
         KF(KF_MISC, k_take_token(s->st, s->vtok, mt.row_seq, p.M, s->tok_next, s->draft_dev, s->max_rows, j));
       }
@@ -947,8 +940,7 @@ static int place_scratch_static(ee_session* s, const CallPlan& p) {
   char* base = nullptr;
   EE_TRY(static_scratch_base(&base));
   AttnScratch scr;
-  int nsplit = 1;
-  (void)attention_plan(s, p, 0, scr, &nsplit);
+  const int nsplit = attention_plan(s, p, 0, scr).nsplit;
   Carver cv{base};
   const size_t slots = (size_t)p.total_qt * c.n_kv_heads * nsplit;
   float* part_o = cv.take<float>(slots * 16 * c.head_dim);
@@ -1033,11 +1025,11 @@ static int verify_intermediate_impl(ee_session* s, int32_t* n_accept, int32_t* n
   exit_head(s, p.M, 1);
   s->need_logits = false;
   if (rs) {
-    KF(KF_MISC, k_softmax_rows(s->st, s->LOGITS, c.vocab, s->LOGITS, nullptr, 0, p.M, c.vocab));          // p_{L_i}, in place
+    // p_{L_i} in place, and kept for the rows that may stay
+    KF(KF_MISC, k_softmax_rows(s->st, s->LOGITS, s->LOGITS, nullptr, 0, s->Pi, mt.row_dst, p.M, c.vocab));
     KF(KF_ACCEPT, k_rs_accept(s->st, s->LOGITS, s->Pd, s->max_rows, c.vocab, mt, s->cand_stride, s->B, s->u_dev, s->max_rows, s->out_dev));
     KF(KF_ACCEPT, k_rs_draw(s->st, s->LOGITS, s->Pd, s->max_rows, c.vocab, mt, s->B, s->out_dev, s->u_dev + (size_t)s->B * s->max_rows,
                             s->out_dev + s->B));
-    KF(KF_COPY, k_copy_rows(s->st, s->Pi, mt.row_dst, 0, s->LOGITS, nullptr, p.M, c.vocab));  // p_{L_i} of the rows that may stay
   } else {
     KF(KF_ACCEPT, k_accept(s->st, s->vtok, mt, s->cand_stride, s->B, s->out_dev, s->out_dev + s->B));
   }
@@ -1183,12 +1175,11 @@ static int verify_upper_impl(ee_session* s, int level, const uint8_t* active, in
   s->need_logits = false;
   if (rs) {      // a further stage of App. G: the buffer below, distributed as exit j-1's p, is the draft; exit j's p the target
     const float* q_below = level_dist(s, j - 1);
-    KF(KF_MISC, k_softmax_rows(s->st, s->LOGITS, c.vocab, s->LOGITS, nullptr, 0, p.M, c.vocab));
+    // exit j's distributions in place and, below L_f, kept for the rows that may stay: the law of the tokens that wait for exit j+1
+    KF(KF_MISC, k_softmax_rows(s->st, s->LOGITS, s->LOGITS, nullptr, 0, j < n ? level_dist(s, j) : nullptr, mt.row_dst, p.M, c.vocab));
     KF(KF_ACCEPT, k_rs_accept(s->st, s->LOGITS, q_below, s->max_rows, c.vocab, mt, s->cand_stride, s->B, s->u_dev, s->max_rows, s->out_dev));
     KF(KF_ACCEPT, k_rs_draw(s->st, s->LOGITS, q_below, s->max_rows, c.vocab, mt, s->B, s->out_dev, s->u_dev + (size_t)s->B * s->max_rows,
                             s->out_dev + s->B));
-    // exit j's distributions of the rows that may stay: the law of the tokens that wait for exit j+1
-    if (j < n) KF(KF_COPY, k_copy_rows(s->st, level_dist(s, j), mt.row_dst, 0, s->LOGITS, nullptr, p.M, c.vocab));
   } else {
     KF(KF_ACCEPT, k_accept(s->st, s->vtok, mt, s->cand_stride, s->B, s->out_dev, s->out_dev + s->B));
   }

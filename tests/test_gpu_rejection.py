@@ -287,3 +287,51 @@ def test_chain_loop_under_the_sampling_rule_runs_on_the_gpu():
         streams.append(toks)
         sess.close(); model.close()
     assert np.array_equal(streams[0], streams[1])
+
+
+@pytest.mark.parametrize("vocab", [2, 255, 1023, 4100, 32001, 262400, 300003])
+def test_rows_and_draws_at_the_edges_of_the_vocabulary_walk(vocab):
+    """Distributions and draws at vocabularies around the walk's pieces (a wave's chunk of 256 tokens, 16 waves, more than
+    64 chunks per wave from 262145 on, rows that are not 16-byte aligned): the distribution against a float64 softmax of the
+    logits (fp32 exponentials and sums: a few 1e-6), every drawn token's CDF interval against its uniform number, within
+    4e-6 of the total (fp32 partial sums of a dozen levels, 2^-24 each, on both sides of the interval)."""
+    import paper_2510_01336_amd as hs
+    cfg = synth.EEConfig(n_layers=3, d_model=32, n_q_heads=1, n_kv_heads=1, head_dim=32, d_ffn=32, vocab=vocab, exit_draft=1,
+                         exit_inter=2, dtype="f32", sigma=0.4)
+    B, k = 2, 3
+    model = hs.Model(cfg, 5)
+    sess = hs.Session(model, B, 64, 12)
+    sess.enable_sampling(); sess.enable_logits(True)
+    sess.prefill([synth.gen_prompt(vocab, n, n) for n in (9, 17)])
+    sess.draft(1)
+    logits = sess.last_logits(B).astype(np.float64)
+    for b, n in enumerate((9, 17)):
+        sess.rollback(b, 0b111, n)
+
+    def inside(w, tok, u):
+        c = np.cumsum(np.asarray(w, np.float64))
+        return w[tok] > 0 and (c[tok - 1] if tok else 0.0) - 4e-6 * c[-1] <= u * c[-1] <= c[tok] + 4e-6 * c[-1]
+
+    rng = np.random.default_rng(vocab)
+    for rnd in range(4):
+        u_d, u_a, u_r = rng.random((B, k), np.float32), rng.random((B, k), np.float32), rng.random(B, np.float32)
+        if rnd == 0:
+            u_d[:, 0] = (0.0, np.nextafter(np.float32(1), np.float32(0)))       # both ends of the interval
+        S = sess.draft_sample(k, u_d)
+        Pd = [sess.read_dist(0, b, 0, k).astype(np.float64) for b in range(B)]
+        a, nxt = sess.verify_intermediate_rs(u_a, u_r)
+        Pt = sess.last_logits(B * (k + 1)).astype(np.float64)
+        for b in range(B):
+            if rnd == 0:
+                ref = eo.softmax_rows(logits[b:b + 1])[0]
+                assert np.max(np.abs(Pd[b][0] - ref)) <= 5e-6 * np.max(ref)
+            assert all(inside(Pd[b][j], int(S[b, j]), float(u_d[b, j])) for j in range(k)), (rnd, b)
+            pt, n = Pt[b * (k + 1):(b + 1) * (k + 1)], int(a[b])
+            ratio = [pt[j, S[b, j]] / Pd[b][j, S[b, j]] for j in range(k)]
+            assert all(float(u_a[b, j]) <= ratio[j] * (1 + 1e-6) for j in range(n)) and (n == k or float(u_a[b, n]) >= min(1.0, ratio[n]) * (1 - 1e-6))
+            w = pt[n] if n == k else np.maximum(0.0, (pt[n].astype(np.float32) - Pd[b][n].astype(np.float32)).astype(np.float64))
+            assert inside(w, int(nxt[b]), float(u_r[b])), (rnd, b)
+            assert np.array_equal(sess.read_dist(1, b, 0, n + 1).astype(np.float64), pt[:n + 1])
+        for b, n in enumerate((9, 17)):
+            sess.rollback(b, 0b111, n)
+    sess.close(); model.close()
