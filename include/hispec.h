@@ -229,7 +229,7 @@ int kv_rollback(ee_session* s, int seq, int group_mask, int new_len);
  * rule again with V as the draft and its stored p_{L_i} rows as q.  All uniform numbers are inputs: host
  * arrays of floats in [0, 1) (EE_ERR_ARG otherwise).  Draws are by inverse CDF over the token ids in order.
  * The distributions are kept in a caller-owned device arena of ee_sampling_bytes() bytes (one store of batch *
- * max_rows * vocab floats per exit below L_f -- two for Alg. 2 -- and the uniform numbers), attached once per session;
+ * max_rows * vocab floats per exit below L_f -- two for Alg. 2), attached once per session;
  * 256-byte aligned.
  * The sampling calls and the arg max calls may not be mixed within one round (EE_ERR_STATE). */
 size_t ee_sampling_bytes(const ee_session* s);

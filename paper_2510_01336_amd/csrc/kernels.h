@@ -3,18 +3,19 @@
 #include "common.h"
 
 // ---- dtype-independent ---------------------------------------------------------------------
-// X[r][:] = float(emb[tok[r]][:])
-void k_embed(hipStream_t st, bool bf16, const void* emb, const int* tok, float* X, int M, int d);
 // dst[dst_idx[r]][:] = src[src_idx[r]][:]   (null index = identity)
 void k_copy_rows(hipStream_t st, float* dst, const int* dst_idx, int dst_add, const float* src, const int* src_idx, int M, int d);
 // per sequence: a = number of leading j < n_cand[b] with cand[b][j] == v[row0[b]+j];
 // next = v[row0+a] if a < m[b] else -1.  Sequences with m[b] == 0 report (-1, -1).
 void k_accept(hipStream_t st, const int* v, const CallMeta& meta, int cand_stride, int B, int* n_accept, int* next_tok);
-// sequential drafting, one row per sequence: tok_next[r] = v[r]; draft_out[row_seq[r]*stride + j] = v[r]
-void k_take_token(hipStream_t st, const int* v, const int* row_seq, int M, int* tok_next, int* draft_out, int stride, int j);
-// cos/sin table for the rows of this call: cs[r][i] = (cos, sin)(pos_r * inv_freq[i]), evaluated in double
-void k_rope_table(hipStream_t st, const CallMeta& mt, int pos_add, const double* inv_freq, float2* cs, int M, int half, int pps,
-                  int4* rowinfo);   // rowinfo[r] = (first q-tile of the row's sequence, row inside the sequence, KV page, slot in page)
+// Sequential drafting and decoding, one row per sequence: the arg max kernels hand a row's token on as the next input
+// (tok_next[r]) and to the caller (draft_out[row_seq[r]*stride + j]); tok_next == null: nothing to hand on.
+struct TakeToken { int* tok_next = nullptr; int* draft_out = nullptr; const int* row_seq = nullptr; int stride = 0, j = 0; };
+__device__ inline void take_token(const TakeToken& t, int r, int tok) {
+  if (!t.tok_next) return;
+  t.tok_next[r] = tok;
+  t.draft_out[t.row_seq[r] * t.stride + t.j] = tok;
+}
 void k_fill_nan_dead_kv(hipStream_t st, bool bf16, void* kv, const int* pages, int n_owned_pages, int len,
                         int layer0, int layer1, int n_pages, int n_kv, int D);
 void k_read_kv(hipStream_t st, bool bf16, const void* kv, const int* pages, int layer, int pos0, int n,
@@ -23,15 +24,28 @@ void k_write_kv(hipStream_t st, bool bf16, void* kv, const int* pages, int layer
                 const float* k_in, const float* v_in);
 
 // ---- fp32 reference-precision path (EE_F32 models) -----------------------------------------
-void f32_rmsnorm(hipStream_t st, const float* X, const float* g, float eps, float* out, int M, int d);
-// Y[m][n] (+)= sum_k A[m][k] W[n][k];  A row-major lda, W row-major [N][K], Y row-major ldy
-void f32_gemm(hipStream_t st, const float* A, int lda, const float* W, float* Y, int ldy, int M, int N, int K, bool add);
-void f32_rope_append(hipStream_t st, const float* QKV, int ldq, const float2* cs, const CallMeta& meta, int pos_add, int M,
-                     int Hq, int Hkv, int D, int layer, int n_pages, int pages_per_seq, float* Q, float* kv);
+// rows of a pass into X (embedding of tok, rows[row_idx], or as they stand), cs[r][i] = (cos, sin)(pos_r * inv_freq[i]), rowinfo[r] =
+// (first q-tile of the row's sequence, row inside the sequence, KV page, slot in page)
+void f32_begin_pass(hipStream_t st, const float* emb, const int* tok, const float* rows, const int* row_idx, float* X, int M, int d,
+                    const CallMeta& mt, int pos_add, const double* inv_freq, float2* cs, int half, int pps, int4* rowinfo);
+struct F32Out {
+  float* Y = nullptr; int ldy = 0;                                    // target rows (F_QKV: Q rows [M][Hq][D])
+  float* Y2 = nullptr; const int* y2_idx = nullptr; int y2_add = 0;   // F_ADD: the new rows also go to Y2[y2_idx[row] + y2_add]
+  const float2* cs = nullptr; const int4* rowinfo = nullptr;          // F_QKV
+  int Hq = 0, Hkv = 0, D = 0, layer = 0, n_pages = 0;
+  float* kv = nullptr;
+};
+// Every projection reads X through an RMSNorm with gain g (null: as it is); W row-major [N][K].
+// Y[m][n] (+)= sum_k x[m][k] W[n][k]
+void f32_gemm(hipStream_t st, const float* X, int ldx, const float* g, float eps, const float* W, float* Y, int ldy, int M, int N, int K, bool add,
+              float* Y2 = nullptr, const int* y2_idx = nullptr, int y2_add = 0);
+// H = silu(gate) * up; W: gate and up rows in alternating blocks of 16
+void f32_gate_up(hipStream_t st, const float* X, const float* g, float eps, const float* W, float* H, int M, int F, int d);
+// fused QKV: rotated Q rows, rotated K and V into their cache pages
+void f32_qkv(hipStream_t st, const float* X, const float* g, float eps, const float* W, int M, int d, const F32Out& out);
 void f32_attention(hipStream_t st, const float* Q, const float* kv, const CallMeta& meta, int pos_add, int M, int Hq, int Hkv,
                    int D, int layer, int n_pages, int pages_per_seq, int max_ctx, float* out);
-void f32_silu_mul(hipStream_t st, const float* GU, int ldg, float* H, int M, int F);
-void f32_argmax(hipStream_t st, const float* logits, int M, int V, int* v);
+void f32_argmax(hipStream_t st, const float* logits, int M, int V, int* v, const TakeToken& take);
 
 // ---- bf16 MFMA path (EE_BF16 models) ---------------------------------------------------------
 enum { EPI_ADD = 0, EPI_SWIGLU = 1, EPI_ARGMAX = 2, EPI_ROPE = 3 };
@@ -87,7 +101,7 @@ void bf16_gemm_rows(hipStream_t st, int epi, const bf16_t* W, int ntiles, int kt
 // out row r (GEMM operand) <- RMSNorm of row idx[r] of X with gain g
 void bf16_rmsnorm(hipStream_t st, const float* X, const int* idx, const float* g, float eps, bf16_t* out, int ktiles, int M, int d);
 // Opens a pass over layers in one launch: row r of X <- embedding of tok[r] (emb set), rows[row_idx[r]] (rows set) or
-// itself; out <- its RMSNorm with gain g as a GEMM operand; cs / rowinfo as k_rope_table fills them.
+// itself; out <- its RMSNorm with gain g as a GEMM operand; cs / rowinfo as f32_begin_pass fills them.
 void bf16_begin_pass(hipStream_t st, const bf16_t* emb, const int* tok, const float* rows, const int* row_idx, float* X,
                      const float* g, float eps, bf16_t* out, int ktiles, int M, int d, const CallMeta& mt, int pos_add,
                      const double* inv_freq, float2* cs, int half, int pps, int4* rowinfo);
@@ -100,7 +114,7 @@ AttnPlan bf16_attention_plan(const int* kv_end, const int* seq_m, int B, int Hq,
 void bf16_attention(hipStream_t st, const AttnPlan& plan, const bf16_t* Q, const bf16_t* kv, const CallMeta& meta, int pos_add, int B,
                     int max_m, int total_qt, int Hq, int Hkv, int D, int layer, int n_pages, int pages_per_seq, const AttnScratch& scr,
                     bf16_t* out, int out_ktiles);
-void bf16_argmax_reduce(hipStream_t st, const float* pmax, const int* pidx, int ntiles, int pstride, int M, int* v);
+void bf16_argmax_reduce(hipStream_t st, const float* pmax, const int* pidx, int ntiles, int pstride, int M, int* v, const TakeToken& take);
 
 // ---- rejection-sampling acceptance (kernels_sample.hip) ----
 // out (and out2, if set) <- softmax of the rows of `in`; k_softmax_draw also draws one token per row from it
@@ -110,4 +124,4 @@ void k_softmax_draw(hipStream_t st, const float* in, float* out, const int* out_
 void k_rs_accept(hipStream_t st, const float* Pt, const float* Pd, int pd_rows_per_seq, int vocab, const CallMeta& meta,
                  int cand_stride, int B, const float* u_acc, int u_stride, int* n_accept);
 void k_rs_draw(hipStream_t st, const float* Pt, const float* Pd, int pd_rows_per_seq, int vocab, const CallMeta& meta, int B,
-               const int* n_accept, const float* u_res, int* next_tok);
+               const int* n_accept, const float* u_res, int* result);   // result: n_accept [B], then the drawn tokens [B]

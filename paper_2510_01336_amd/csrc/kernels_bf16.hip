@@ -74,8 +74,9 @@ void bf16_rmsnorm(hipStream_t st, const float* X, const int* idx, const float* g
 
 // The first kernel of a pass over layers, one workgroup per row: brings the row into the residual stream X -- from the
 // embedding table by token, from a buffer of kept hidden rows by index, or leaves it where it is --, writes its
-// RMSNorm as the first projection's operand, and fills the row's rotary table and epilogue lookups (what
-// rope_table_kernel does) on the side.  One launch where the pass used to open with three.
+// RMSNorm as the first projection's operand, and fills the row's rotary table and epilogue lookups on the side: first q-tile
+// of its sequence, row inside the sequence, KV page and slot of its position, so that the QKV epilogue of every layer finds
+// them with one row-indexed load instead of a chain of dependent ones.  One launch where the pass used to open with three.
 template <int CH>
 __global__ __launch_bounds__(256) void bf16_begin_pass_kernel(const bf16_t* __restrict__ emb, const int* __restrict__ tok,
                                                               const float* __restrict__ rows, const int* __restrict__ row_idx,
@@ -111,7 +112,7 @@ __global__ __launch_bounds__(256) void bf16_begin_pass_kernel(const bf16_t* __re
     gv[i] = c < nch ? g4[c] : make_float4(0.f, 0.f, 0.f, 0.f);
   }
   const int pos = row_pos[r] + pos_add;
-  for (int f = threadIdx.x; f < half; f += 256) {     // rotary angles in double, as in rope_table_kernel
+  for (int f = threadIdx.x; f < half; f += 256) {     // rotary angles in double: at position 32768 an fp32 product pos*freq is off by ~2e-3 rad
     double sn, cn;
     sincos((double)pos * inv_freq[f], &sn, &cn);
     cs[(size_t)r * half + f] = make_float2((float)cn, (float)sn);
@@ -1136,7 +1137,7 @@ void bf16_gemm(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles,
 // one workgroup of 1024 threads per row; the row's partials lie side by side ([row][tile]), so a wave's load is one
 // contiguous 256 bytes; eight independent partials per thread are requested at once
 __global__ __launch_bounds__(1024) void bf16_argmax_reduce_kernel(const float* __restrict__ pmax, const int* __restrict__ pidx,
-                                                                   int ntiles, int pstride, int* v) {
+                                                                   int ntiles, int pstride, int* v, TakeToken take) {
   __shared__ float bv[16];
   __shared__ int bi[16];
   const int m = blockIdx.x;
@@ -1165,11 +1166,11 @@ __global__ __launch_bounds__(1024) void bf16_argmax_reduce_kernel(const float* _
       const float o = __shfl_xor(best, sh, 64); const int oi = __shfl_xor(idx, sh, 64);
       if (o > best || (o == best && oi < idx)) { best = o; idx = oi; }
     }
-    if (threadIdx.x == 0) v[m] = idx;
+    if (threadIdx.x == 0) { v[m] = idx; take_token(take, m, idx); }
   }
 }
-void bf16_argmax_reduce(hipStream_t st, const float* pmax, const int* pidx, int ntiles, int pstride, int M, int* v) {
-  hipLaunchKernelGGL(bf16_argmax_reduce_kernel, dim3(M), dim3(1024), 0, st, pmax, pidx, ntiles, pstride, v);
+void bf16_argmax_reduce(hipStream_t st, const float* pmax, const int* pidx, int ntiles, int pstride, int M, int* v, const TakeToken& take) {
+  hipLaunchKernelGGL(bf16_argmax_reduce_kernel, dim3(M), dim3(1024), 0, st, pmax, pidx, ntiles, pstride, v, take);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -1,6 +1,6 @@
-// Dtype-independent helper kernels and the plain fp32 path used by EE_F32 models.
-// The fp32 kernels favour clarity over speed: EE_F32 exists for the small reference-precision
-// configuration; the bandwidth-critical work is in kernels_bf16.hip.
+// Dtype-independent helper kernels and the fp32 path used by EE_F32 models.  EE_F32 exists for the small
+// reference-precision configuration: its calls are bound by launches and latency, so a layer is five launches (norms, the
+// rotary embedding, the KV append and the activation sit in the projections) and every kernel is a short chain.
 #include "kernels.h"
 #include <hip/hip_ext.h>
 #include <algorithm>
@@ -12,16 +12,6 @@
 __device__ inline float wave_sum(float v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
   return v;
-}
-
-__global__ void embed_kernel(const void* emb, int bf16, const int* tok, float* X, int M, int d) {
-  int r = blockIdx.x;
-  size_t base = (size_t)tok[r] * d;
-  for (int c = threadIdx.x; c < d; c += blockDim.x)
-    X[(size_t)r * d + c] = bf16 ? bf16_to_f32(((const bf16_t*)emb)[base + c]) : ((const float*)emb)[base + c];
-}
-void k_embed(hipStream_t st, bool bf16, const void* emb, const int* tok, float* X, int M, int d) {
-  hipLaunchKernelGGL(embed_kernel, dim3(M), dim3(256), 0, st, emb, (int)bf16, tok, X, M, d);
 }
 
 __global__ void copy_rows_kernel(float* dst, const int* dst_idx, int dst_add, const float* src, const int* src_idx, int d) {
@@ -56,42 +46,6 @@ __global__ void accept_kernel(const int* v, const int* seq_row0, const int* seq_
 void k_accept(hipStream_t st, const int* v, const CallMeta& meta, int cand_stride, int B, int* n_accept, int* next_tok) {
   hipLaunchKernelGGL(accept_kernel, dim3(B), dim3(64), 0, st, v, meta.seq_row0, meta.seq_m, meta.cand, meta.n_cand,
                      cand_stride, n_accept, next_tok);
-}
-
-__global__ void take_token_kernel(const int* v, const int* row_seq, int M, int* tok_next, int* draft_out, int stride, int j) {
-  int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= M) return;
-  tok_next[r] = v[r];
-  draft_out[row_seq[r] * stride + j] = v[r];
-}
-void k_take_token(hipStream_t st, const int* v, const int* row_seq, int M, int* tok_next, int* draft_out, int stride, int j) {
-  hipLaunchKernelGGL(take_token_kernel, dim3(ceil_div(M, 64)), dim3(64), 0, st, v, row_seq, M, tok_next, draft_out, stride, j);
-}
-
-// Rotary angles are formed in double: at position 32768 an fp32 product pos*freq is off by ~2e-3 rad.
-// The thread of a row's first pair also resolves the row's lookups once for all layers of the call -- first q-tile of
-// its sequence, row index inside the sequence, KV page and slot of its position -- so that the QKV epilogue of every
-// layer finds them with one row-indexed load instead of a chain of dependent ones.
-__global__ void rope_table_kernel(const int* row_pos, int pos_add, const double* inv_freq, float2* cs, int M, int half,
-                                  const int* row_seq, const int* seq_row0, const int* seq_qt0, const int* block_table, int pps,
-                                  int4* rowinfo) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= M * half) return;
-  int r = i / half, f = i % half;
-  const int pos = row_pos[r] + pos_add;
-  double ang = (double)pos * inv_freq[f];
-  double s, c;
-  sincos(ang, &s, &c);
-  cs[i] = make_float2((float)c, (float)s);
-  if (f == 0 && rowinfo) {
-    const int sq = row_seq[r];
-    rowinfo[r] = make_int4(seq_qt0[sq], r - seq_row0[sq], block_table[sq * pps + pos / EE_PAGE], pos % EE_PAGE);
-  }
-}
-void k_rope_table(hipStream_t st, const CallMeta& mt, int pos_add, const double* inv_freq, float2* cs, int M, int half, int pps,
-                  int4* rowinfo) {
-  hipLaunchKernelGGL(rope_table_kernel, dim3(ceil_div(M * half, 256)), dim3(256), 0, st, mt.row_pos, pos_add, inv_freq, cs, M, half,
-                     mt.row_seq, mt.seq_row0, mt.seq_qt0, mt.block_table, pps, rowinfo);
 }
 
 __global__ void fill_nan_dead_kv_kernel(void* kv, int bf16, const int* pages, int n_owned, int len, int layer0, int layer1,
@@ -235,163 +189,290 @@ extern "C" int ee_debug_read_floor(const void* buf_dev, const size_t* sizes, int
 // ---------------------------------------------------------------------------------------------
 // fp32 path
 // ---------------------------------------------------------------------------------------------
-__global__ void f32_rmsnorm_kernel(const float* X, const float* g, float eps, float* out, int d) {
-  __shared__ float part[4];
-  int r = blockIdx.x;
-  const float* x = X + (size_t)r * d;
-  float ss = 0.f;
-  for (int c = threadIdx.x; c < d; c += blockDim.x) ss += x[c] * x[c];
-  ss = wave_sum(ss);
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
-  __syncthreads();
-  float tot = part[0] + part[1] + part[2] + part[3];
-  float inv = 1.0f / sqrtf(tot / (float)d + eps);
-  for (int c = threadIdx.x; c < d; c += blockDim.x) out[(size_t)r * d + c] = x[c] * inv * g[c];
-}
-void f32_rmsnorm(hipStream_t st, const float* X, const float* g, float eps, float* out, int M, int d) {
-  hipLaunchKernelGGL(f32_rmsnorm_kernel, dim3(M), dim3(256), 0, st, X, g, eps, out, d);
-}
-
-// one wavefront per output element
-__global__ void f32_gemm_kernel(const float* A, int lda, const float* W, float* Y, int ldy, int M, int N, int K, int add) {
-  int lane = threadIdx.x & 63;
-  long o = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (o >= (long)M * N) return;
-  int m = (int)(o / N), n = (int)(o % N);
-  const float* a = A + (size_t)m * lda;
-  const float* w = W + (size_t)n * K;
-  float acc = 0.f;
-  for (int k = lane; k < K; k += 64) acc += a[k] * w[k];
-  acc = wave_sum(acc);
-  if (lane == 0) {
-    size_t i = (size_t)m * ldy + n;
-    Y[i] = add ? Y[i] + acc : acc;
+// Opens a pass, one workgroup per row: the row into X (embedding of tok[r], rows[row_idx[r]], or as it stands), its rotary
+// table and its lookups for the QKV epilogue.  Rotary angles are formed in double: at position 32768 an fp32 product
+// pos*freq is off by ~2e-3 rad.
+__global__ __launch_bounds__(256) void f32_begin_pass_kernel(const float* __restrict__ emb, const int* __restrict__ tok,
+                                                             const float* __restrict__ rows, const int* __restrict__ row_idx,
+                                                             float* __restrict__ X, int d, const int* row_pos, int pos_add,
+                                                             const double* inv_freq, float2* cs, int half, const int* row_seq,
+                                                             const int* seq_row0, const int* seq_qt0, const int* block_table, int pps,
+                                                             int4* rowinfo) {
+  const int r = blockIdx.x, pos = row_pos[r] + pos_add;
+  const float* src = emb ? emb + (size_t)tok[r] * d : (rows ? rows + (size_t)row_idx[r] * d : nullptr);
+  if (src)
+    for (int c = threadIdx.x; c < d; c += 256) X[(size_t)r * d + c] = src[c];
+  for (int f = threadIdx.x; f < half; f += 256) {
+    double sn, cn;
+    sincos((double)pos * inv_freq[f], &sn, &cn);
+    cs[(size_t)r * half + f] = make_float2((float)cn, (float)sn);
+  }
+  if (threadIdx.x == 0) {
+    const int sq = row_seq[r];
+    rowinfo[r] = make_int4(seq_qt0[sq], r - seq_row0[sq], block_table[sq * pps + pos / EE_PAGE], pos % EE_PAGE);
   }
 }
-void f32_gemm(hipStream_t st, const float* A, int lda, const float* W, float* Y, int ldy, int M, int N, int K, bool add) {
-  long outs = (long)M * N;
-  hipLaunchKernelGGL(f32_gemm_kernel, dim3((unsigned)((outs + 3) / 4)), dim3(256), 0, st, A, lda, W, Y, ldy, M, N, K, (int)add);
+void f32_begin_pass(hipStream_t st, const float* emb, const int* tok, const float* rows, const int* row_idx, float* X, int M, int d,
+                    const CallMeta& mt, int pos_add, const double* inv_freq, float2* cs, int half, int pps, int4* rowinfo) {
+  hipLaunchKernelGGL(f32_begin_pass_kernel, dim3(M), dim3(256), 0, st, emb, tok, rows, row_idx, X, d, mt.row_pos, pos_add, inv_freq, cs,
+                     half, mt.row_seq, mt.seq_row0, mt.seq_qt0, mt.block_table, pps, rowinfo);
 }
 
-__global__ void f32_rope_append_kernel(const float* QKV, int ldq, const float2* cs, const int* row_seq, const int* row_pos,
-                                       const int* block_table, int pos_add, int M, int Hq, int Hkv, int D, int layer,
-                                       int n_pages, int pps, float* Q, float* kv) {
-  int half = D >> 1, heads = Hq + 2 * Hkv;
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= M * heads * half) return;
-  int f = i % half, h = (i / half) % heads, r = i / (half * heads);
-  const float* src = QKV + (size_t)r * ldq + (size_t)h * D;
-  float a = src[f], b = src[f + half];
-  float2 c = cs[r * half + f];
-  if (h < Hq) {
-    Q[(size_t)r * Hq * D + h * D + f] = a * c.x - b * c.y;
-    Q[(size_t)r * Hq * D + h * D + f + half] = b * c.x + a * c.y;
-    return;
+// y[m][unit] = sum_k x[m][k] w[k], optionally behind an RMSNorm of x (g set: (sum_k x g w) / rms(x), the factor from the same
+// walk over x).  One wave per unit and R rows, so a weight row is read once for R rows of x; a unit is one output, or the pair
+// an epilogue needs at once:
+//   F_ADD   Y += product (and the new rows into the second destination)
+//   F_SET   Y  = product
+//   F_GU    H  = silu(gate) * up            (rows of the interleaved gate/up matrix)
+//   F_QKV   rotary pair of a Q, K or V head -> Q rows, cache pages
+enum { F_ADD = 0, F_SET, F_GU, F_QKV };
+template <int EPI, int R, bool VEC>
+__global__ __launch_bounds__(256) void f32_gemm_kernel(const float* __restrict__ X, int ldx, const float* __restrict__ g, float eps,
+                                                       const float* __restrict__ W, int M, int units, int K, F32Out out) {
+  constexpr int NB = EPI == F_GU || EPI == F_QKV ? 2 : 1;
+  const int lane = threadIdx.x & 63, m0 = blockIdx.y * R;
+  const int unit = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (unit >= units) return;
+  const int half = EPI == F_QKV ? out.D >> 1 : 1;
+  const int h = unit / half, f = unit % half;            // F_QKV: head and pair
+  int n[NB];
+  if (EPI == F_GU) { n[0] = ((unit >> 4) * 2) * 16 + (unit & 15); n[NB - 1] = n[0] + 16; }
+  else if (EPI == F_QKV) { n[0] = h * out.D + f; n[NB - 1] = n[0] + half; }
+  else n[0] = unit;
+  float acc[NB][R], ss[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    ss[r] = 0.f;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[b][r] = 0.f;
   }
-  int pos = row_pos[r] + pos_add;
-  int page = block_table[row_seq[r] * pps + pos / EE_PAGE], pp = pos % EE_PAGE;
-  if (h < Hq + Hkv) {
-    size_t slab = kv_slab(layer, page, h - Hq, n_pages, Hkv, D);
-    kv[slab + k_page_off(pp, f, D)] = a * c.x - b * c.y;
-    kv[slab + k_page_off(pp, f + half, D)] = b * c.x + a * c.y;
+  const float* xr[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) xr[r] = X + (size_t)min(m0 + r, M - 1) * ldx;
+  const bool norm = g != nullptr;
+  if (VEC) {
+#pragma unroll 2
+    for (int k = lane * 4; k < K; k += 256) {
+      float4 w[NB];
+#pragma unroll
+      for (int b = 0; b < NB; ++b) w[b] = *(const float4*)(W + (size_t)n[b] * K + k);
+      const float4 gv = norm ? *(const float4*)(g + k) : make_float4(1.f, 1.f, 1.f, 1.f);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const float4 x = *(const float4*)(xr[r] + k);
+        ss[r] += (x.x * x.x + x.y * x.y) + (x.z * x.z + x.w * x.w);
+        const float4 t = make_float4(x.x * gv.x, x.y * gv.y, x.z * gv.z, x.w * gv.w);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[b][r] += (t.x * w[b].x + t.y * w[b].y) + (t.z * w[b].z + t.w * w[b].w);
+      }
+    }
   } else {
-    size_t slab = kv_slab(layer, page, h - Hq - Hkv, n_pages, Hkv, D) + EE_PAGE * D;
-    kv[slab + v_page_off(pp, f, D)] = a;
-    kv[slab + v_page_off(pp, f + half, D)] = b;
+    for (int k = lane; k < K; k += 64) {
+      const float gv = norm ? g[k] : 1.f;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const float x = xr[r][k];
+        ss[r] += x * x;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[b][r] += x * gv * W[(size_t)n[b] * K + k];
+      }
+    }
+  }
+  // every lane ends up with every sum; lane r finishes row r
+  float y0 = 0.f, y1 = 0.f, sq = 0.f;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+#pragma unroll
+    for (int s = 1; s < 64; s <<= 1) {
+#pragma unroll
+      for (int b = 0; b < NB; ++b) acc[b][r] += __shfl_xor(acc[b][r], s, 64);
+      if (norm) ss[r] += __shfl_xor(ss[r], s, 64);
+    }
+    if (lane == r) { y0 = acc[0][r]; y1 = acc[NB - 1][r]; sq = ss[r]; }
+  }
+  const int m = m0 + lane;
+  if (lane >= R || m >= M) return;
+  if (norm) {
+    const float inv = 1.0f / sqrtf(sq / (float)K + eps);
+    y0 *= inv; y1 *= inv;
+  }
+  if (EPI == F_ADD) {
+    float* y = out.Y + (size_t)m * out.ldy + unit;
+    y0 += *y;
+    *y = y0;
+    if (out.Y2) out.Y2[(size_t)(out.y2_idx[m] + out.y2_add) * out.ldy + unit] = y0;
+  } else if (EPI == F_SET) {
+    out.Y[(size_t)m * out.ldy + unit] = y0;
+  } else if (EPI == F_GU) {
+    out.Y[(size_t)m * out.ldy + unit] = y0 / (1.0f + expf(-y0)) * y1;
+  } else {
+    const int D = out.D;
+    const float2 c = h < out.Hq + out.Hkv ? out.cs[(size_t)m * half + f] : make_float2(1.f, 0.f);
+    const float lo = y0 * c.x - y1 * c.y, hi = y1 * c.x + y0 * c.y;
+    if (h < out.Hq) {
+      float* q = out.Y + ((size_t)m * out.Hq + h) * D + f;
+      q[0] = lo; q[half] = hi;
+      return;
+    }
+    const int4 ri = out.rowinfo[m];
+    const int page = ri.z, pp = ri.w;
+    if (h < out.Hq + out.Hkv) {
+      float* slab = out.kv + kv_slab(out.layer, page, h - out.Hq, out.n_pages, out.Hkv, D);
+      slab[k_page_off(pp, f, D)] = lo;
+      slab[k_page_off(pp, f + half, D)] = hi;
+    } else {
+      float* slab = out.kv + kv_slab(out.layer, page, h - out.Hq - out.Hkv, out.n_pages, out.Hkv, D) + EE_PAGE * D;
+      slab[v_page_off(pp, f, D)] = y0;
+      slab[v_page_off(pp, f + half, D)] = y1;
+    }
   }
 }
-void f32_rope_append(hipStream_t st, const float* QKV, int ldq, const float2* cs, const CallMeta& meta, int pos_add, int M,
-                     int Hq, int Hkv, int D, int layer, int n_pages, int pages_per_seq, float* Q, float* kv) {
-  int total = M * (Hq + 2 * Hkv) * (D / 2);
-  hipLaunchKernelGGL(f32_rope_append_kernel, dim3(ceil_div(total, 256)), dim3(256), 0, st, QKV, ldq, cs, meta.row_seq,
-                     meta.row_pos, meta.block_table, pos_add, M, Hq, Hkv, D, layer, n_pages, pages_per_seq, Q, kv);
+template <int EPI>
+static void launch_f32_gemm(hipStream_t st, const float* X, int ldx, const float* g, float eps, const float* W, int M, int units, int K,
+                            const F32Out& out) {
+  // 16-byte loads where every row of x, w and g starts on a 16-byte boundary
+  const bool vec = K % 4 == 0 && ldx % 4 == 0 && (((uintptr_t)X | (uintptr_t)W | (uintptr_t)g) & 15) == 0;
+#define F32_LAUNCH(R_)                                                                                                                  \
+  do {                                                                                                                                  \
+    if (vec) hipLaunchKernelGGL((f32_gemm_kernel<EPI, R_, true>), dim3(ceil_div(units, 4), ceil_div(M, R_)), dim3(256), 0, st, X, ldx, g, eps, W, M, units, K, out); \
+    else hipLaunchKernelGGL((f32_gemm_kernel<EPI, R_, false>), dim3(ceil_div(units, 4), ceil_div(M, R_)), dim3(256), 0, st, X, ldx, g, eps, W, M, units, K, out);    \
+  } while (0)
+  if (M == 1) F32_LAUNCH(1);
+  else F32_LAUNCH(4);          // (more rows per wave lengthen the chain of a small call more than they save)
+#undef F32_LAUNCH
+}
+void f32_gemm(hipStream_t st, const float* X, int ldx, const float* g, float eps, const float* W, float* Y, int ldy, int M, int N, int K, bool add,
+              float* Y2, const int* y2_idx, int y2_add) {
+  F32Out o;
+  o.Y = Y; o.ldy = ldy; o.Y2 = Y2; o.y2_idx = y2_idx; o.y2_add = y2_add;
+  if (add) launch_f32_gemm<F_ADD>(st, X, ldx, g, eps, W, M, N, K, o);
+  else launch_f32_gemm<F_SET>(st, X, ldx, g, eps, W, M, N, K, o);
+}
+void f32_gate_up(hipStream_t st, const float* X, const float* g, float eps, const float* W, float* H, int M, int F, int d) {
+  F32Out o;
+  o.Y = H; o.ldy = F;
+  launch_f32_gemm<F_GU>(st, X, d, g, eps, W, M, F, d, o);
+}
+void f32_qkv(hipStream_t st, const float* X, const float* g, float eps, const float* W, int M, int d, const F32Out& out) {
+  launch_f32_gemm<F_QKV>(st, X, d, g, eps, W, M, (out.Hq + 2 * out.Hkv) * (out.D / 2), d, out);
 }
 
-// one workgroup per (row, query head): scores over positions 0..pos in LDS, two-pass softmax
-__global__ void f32_attention_kernel(const float* Q, const float* kv, const int* row_seq, const int* row_pos,
+// One workgroup per (row, query head): scores over positions 0..pos in LDS, two-pass softmax.  Four neighbouring threads share a
+// position (each a quarter of the head's dimensions, eight at a time as the page stores them), and in the second product
+// the threads of a dimension share out the positions in runs of eight; at a few dozen positions both products are one short
+// chain (the one-thread-per-position form took 10 us at 37 positions).  W8: head_dim is a multiple of 32.
+template <bool W8>
+__global__ __launch_bounds__(256) void f32_attention_kernel(const float* __restrict__ Q, const float* __restrict__ kv, const int* row_seq, const int* row_pos,
                                      const int* block_table, int pos_add, int Hq, int Hkv, int D, int layer, int n_pages,
-                                     int pps, float* out) {
+                                     int pps, float* __restrict__ out) {
   extern __shared__ float sm[];
-  float* q = sm;            // [D]
-  float* red = sm + D;      // [8]
-  float* sc = sm + D + 8;   // [n]
-  int r = blockIdx.x, h = blockIdx.y, kvh = h / (Hq / Hkv);
-  int n = row_pos[r] + pos_add + 1;
+  float* q = sm;                       // [D]
+  float* red = sm + D;                 // [8]
+  float* part = sm + D + 8;            // [256]
+  float* sc = sm + D + 8 + 256;        // [n]
+  const int r = blockIdx.x, h = blockIdx.y, kvh = h / (Hq / Hkv);
+  const int n = row_pos[r] + pos_add + 1;
   const int* bt = block_table + row_seq[r] * pps;
   for (int d = threadIdx.x; d < D; d += blockDim.x) q[d] = Q[(size_t)r * Hq * D + h * D + d];
   __syncthreads();
-  float scale = 1.0f / sqrtf((float)D);
+  const float scale = 1.0f / sqrtf((float)D);
   float mx = -INFINITY;
-  for (int j = threadIdx.x; j < n; j += blockDim.x) {
-    size_t slab = kv_slab(layer, bt[j / EE_PAGE], kvh, n_pages, Hkv, D);
-    float s = 0.f;
-    for (int d = 0; d < D; ++d) s += q[d] * kv[slab + k_page_off(j % EE_PAGE, d, D)];
-    s *= scale;
-    sc[j] = s;
-    mx = fmaxf(mx, s);
+  if (W8) {
+    const int quarter = threadIdx.x & 3;
+    for (int j = threadIdx.x >> 2; j < (n + 63) / 64 * 64; j += 64) {      // (whole waves: the quarters meet by shuffle)
+      const int jj = min(j, n - 1);
+      const float* slab = kv + kv_slab(layer, bt[jj / EE_PAGE], kvh, n_pages, Hkv, D);
+      float s = 0.f;
+      for (int d = quarter * 8; d < D; d += 32) {
+        const float4* k4 = (const float4*)(slab + k_page_off(jj % EE_PAGE, d, D));
+        const float4 a = k4[0], b = k4[1];
+        s += (q[d] * a.x + q[d + 1] * a.y + q[d + 2] * a.z + q[d + 3] * a.w) + (q[d + 4] * b.x + q[d + 5] * b.y + q[d + 6] * b.z + q[d + 7] * b.w);
+      }
+      s += __shfl_xor(s, 1, 64);
+      s += __shfl_xor(s, 2, 64);
+      s *= scale;
+      if (j < n) { if (quarter == 0) sc[j] = s; mx = fmaxf(mx, s); }
+    }
+  } else {
+    for (int j = threadIdx.x; j < n; j += blockDim.x) {
+      const size_t slab = kv_slab(layer, bt[j / EE_PAGE], kvh, n_pages, Hkv, D);
+      float s = 0.f;
+      for (int d = 0; d < D; ++d) s += q[d] * kv[slab + k_page_off(j % EE_PAGE, d, D)];
+      s *= scale;
+      sc[j] = s;
+      mx = fmaxf(mx, s);
+    }
   }
   for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_down(mx, o, 64));
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
   __syncthreads();
   mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-  __syncthreads();
   float sum = 0.f;
   for (int j = threadIdx.x; j < n; j += blockDim.x) { float p = expf(sc[j] - mx); sc[j] = p; sum += p; }
   sum = wave_sum(sum);
   if ((threadIdx.x & 63) == 0) red[4 + (threadIdx.x >> 6)] = sum;
   __syncthreads();
   sum = red[4] + red[5] + red[6] + red[7];
-  for (int d = threadIdx.x; d < D; d += blockDim.x) {
+  const int phases = max(1, 256 / D);                     // threads that share a dimension
+  for (int d0 = 0; d0 < D; d0 += 256) {
+    const int d = d0 + (int)threadIdx.x % min(D, 256), ph = (int)threadIdx.x / min(D, 256);
     float acc = 0.f;
-    for (int j = 0; j < n; ++j) {
-      size_t slab = kv_slab(layer, bt[j / EE_PAGE], kvh, n_pages, Hkv, D) + EE_PAGE * D;
-      acc += sc[j] * kv[slab + v_page_off(j % EE_PAGE, d, D)];
+    if (d < D && ph < phases)
+      for (int j = ph * 8; j < n; j += phases * 8) {      // eight positions lie side by side in a page
+        const float* v = kv + kv_slab(layer, bt[j / EE_PAGE], kvh, n_pages, Hkv, D) + EE_PAGE * D + v_page_off(j % EE_PAGE, d, D);
+        if (j + 8 <= n) {
+          const float4 a = ((const float4*)v)[0], b = ((const float4*)v)[1];
+          acc += (sc[j] * a.x + sc[j + 1] * a.y + sc[j + 2] * a.z + sc[j + 3] * a.w) + (sc[j + 4] * b.x + sc[j + 5] * b.y + sc[j + 6] * b.z + sc[j + 7] * b.w);
+        } else {
+          for (int i = 0; j + i < n; ++i) acc += sc[j + i] * v[i];
+        }
+      }
+    part[threadIdx.x] = acc;
+    __syncthreads();
+    if (ph == 0 && d < D) {
+      for (int i = 1; i < phases; ++i) acc += part[i * min(D, 256) + threadIdx.x];
+      out[(size_t)r * Hq * D + h * D + d] = acc / sum;
     }
-    out[(size_t)r * Hq * D + h * D + d] = acc / sum;
+    __syncthreads();
   }
 }
 void f32_attention(hipStream_t st, const float* Q, const float* kv, const CallMeta& meta, int pos_add, int M, int Hq, int Hkv,
                    int D, int layer, int n_pages, int pages_per_seq, int max_ctx, float* out) {
-  size_t smem = (size_t)(D + 8 + max_ctx) * sizeof(float);
-  hipLaunchKernelGGL(f32_attention_kernel, dim3(M, Hq), dim3(256), smem, st, Q, kv, meta.row_seq, meta.row_pos,
-                     meta.block_table, pos_add, Hq, Hkv, D, layer, n_pages, pages_per_seq, out);
+  const size_t smem = (size_t)(D + 8 + 256 + max_ctx) * sizeof(float);
+  if (D % 32 == 0)
+    hipLaunchKernelGGL((f32_attention_kernel<true>), dim3(M, Hq), dim3(256), smem, st, Q, kv, meta.row_seq, meta.row_pos,
+                       meta.block_table, pos_add, Hq, Hkv, D, layer, n_pages, pages_per_seq, out);
+  else
+    hipLaunchKernelGGL((f32_attention_kernel<false>), dim3(M, Hq), dim3(256), smem, st, Q, kv, meta.row_seq, meta.row_pos,
+                       meta.block_table, pos_add, Hq, Hkv, D, layer, n_pages, pages_per_seq, out);
 }
 
-// GU columns follow the physical row order of the interleaved gate/up matrix
-__global__ void f32_silu_mul_kernel(const float* GU, int ldg, float* H, int M, int F) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= M * F) return;
-  int m = i / F, f = i % F;
-  int gc = ((f >> 4) * 2) * 16 + (f & 15);
-  float g = GU[(size_t)m * ldg + gc], u = GU[(size_t)m * ldg + gc + 16];
-  H[(size_t)m * F + f] = g / (1.0f + expf(-g)) * u;
-}
-void f32_silu_mul(hipStream_t st, const float* GU, int ldg, float* H, int M, int F) {
-  hipLaunchKernelGGL(f32_silu_mul_kernel, dim3(ceil_div(M * F, 256)), dim3(256), 0, st, GU, ldg, H, M, F);
-}
-
-// arg max of each row; the lowest index wins ties
-__global__ void f32_argmax_kernel(const float* logits, int V, int* v) {
-  __shared__ float bv[256];
-  __shared__ int bi[256];
-  int r = blockIdx.x;
+// arg max of each row; the lowest index wins ties.  Sixteen waves, eight values per thread in flight.
+__global__ __launch_bounds__(1024) void f32_argmax_kernel(const float* __restrict__ logits, int V, int* v, TakeToken take) {
+  __shared__ float bv[16];
+  __shared__ int bi[16];
+  const int r = blockIdx.x;
   const float* x = logits + (size_t)r * V;
   float best = -INFINITY; int idx = 0x7fffffff;
-  for (int c = threadIdx.x; c < V; c += blockDim.x) {
-    float t = x[c];
+#pragma unroll 8
+  for (int c = threadIdx.x; c < V; c += 1024) {
+    const float t = x[c];
     if (t > best) { best = t; idx = c; }
   }
-  bv[threadIdx.x] = best; bi[threadIdx.x] = idx;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) {
-      float o = bv[threadIdx.x + s]; int oi = bi[threadIdx.x + s];
-      if (o > bv[threadIdx.x] || (o == bv[threadIdx.x] && oi < bi[threadIdx.x])) { bv[threadIdx.x] = o; bi[threadIdx.x] = oi; }
-    }
-    __syncthreads();
+  for (int s = 32; s > 0; s >>= 1) {
+    const float o = __shfl_xor(best, s, 64); const int oi = __shfl_xor(idx, s, 64);
+    if (o > best || (o == best && oi < idx)) { best = o; idx = oi; }
   }
-  if (threadIdx.x == 0) v[r] = bi[0];
+  if ((threadIdx.x & 63) == 0) { bv[threadIdx.x >> 6] = best; bi[threadIdx.x >> 6] = idx; }
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  best = threadIdx.x < 16 ? bv[threadIdx.x] : -INFINITY; idx = threadIdx.x < 16 ? bi[threadIdx.x] : 0x7fffffff;
+  for (int s = 8; s > 0; s >>= 1) {
+    const float o = __shfl_xor(best, s, 64); const int oi = __shfl_xor(idx, s, 64);
+    if (o > best || (o == best && oi < idx)) { best = o; idx = oi; }
+  }
+  if (threadIdx.x == 0) { v[r] = idx; take_token(take, r, idx); }
 }
-void f32_argmax(hipStream_t st, const float* logits, int M, int V, int* v) {
-  hipLaunchKernelGGL(f32_argmax_kernel, dim3(M), dim3(256), 0, st, logits, V, v);
+void f32_argmax(hipStream_t st, const float* logits, int M, int V, int* v, const TakeToken& take) {
+  hipLaunchKernelGGL(f32_argmax_kernel, dim3(M), dim3(1024), 0, st, logits, V, v, take);
 }

@@ -235,12 +235,13 @@ template <bool VEC>
 __global__ __launch_bounds__(EE_SAMPLE_THREADS) void rs_draw_kernel(const float* __restrict__ Pt, const float* __restrict__ Pd,
                                                                     int pd_rows_per_seq, int vocab, const int* seq_row0,
                                                                     const int* seq_m, const int* n_cand, const int* n_accept,
-                                                                    const float* __restrict__ u_res, int* next_tok) {
+                                                                    const float* __restrict__ u_res, int* __restrict__ result) {
   __shared__ DrawShared ds;
   const int b = blockIdx.x, lane = threadIdx.x & 63;
-  const int m = seq_m[b];
+  const int m = seq_m[b], a = n_accept[b], nc = n_cand[b];
+  int* next_tok = result + gridDim.x;
+  if (threadIdx.x == 0) result[b] = a;                   // (-1 for a sequence that takes no part)
   if (m == 0) { if (threadIdx.x == 0) next_tok[b] = -1; return; }
-  const int a = n_accept[b], nc = n_cand[b];
   if (a >= m) { if (threadIdx.x == 0) next_tok[b] = -1; return; }      // all accepted and no further row
   const float* A = Pt + (size_t)(seq_row0[b] + a) * vocab;
   const float* Bd = a < nc ? Pd + ((size_t)b * pd_rows_per_seq + a) * vocab : nullptr;
@@ -271,11 +272,11 @@ __global__ __launch_bounds__(EE_SAMPLE_THREADS) void rs_draw_kernel(const float*
   if (threadIdx.x == 0) next_tok[b] = tok;
 }
 void k_rs_draw(hipStream_t st, const float* Pt, const float* Pd, int pd_rows_per_seq, int vocab, const CallMeta& meta, int B,
-               const int* n_accept, const float* u_res, int* next_tok) {
+               const int* n_accept, const float* u_res, int* result) {
   if (rows_aligned(vocab, Pt, Pd, nullptr))
     hipLaunchKernelGGL((rs_draw_kernel<true>), dim3(B), dim3(EE_SAMPLE_THREADS), 0, st, Pt, Pd, pd_rows_per_seq, vocab, meta.seq_row0,
-                       meta.seq_m, meta.n_cand, n_accept, u_res, next_tok);
+                       meta.seq_m, meta.n_cand, n_accept, u_res, result);
   else
     hipLaunchKernelGGL((rs_draw_kernel<false>), dim3(B), dim3(EE_SAMPLE_THREADS), 0, st, Pt, Pd, pd_rows_per_seq, vocab, meta.seq_row0,
-                       meta.seq_m, meta.n_cand, n_accept, u_res, next_tok);
+                       meta.seq_m, meta.n_cand, n_accept, u_res, result);
 }

@@ -42,16 +42,16 @@ struct ee_session {
   size_t bytes = 0;
   // device buffers (inside the caller's arena)
   void* kv = nullptr;
-  float *X = nullptr, *QKV = nullptr, *GU = nullptr, *LOGITS = nullptr, *Hd = nullptr, *Hi = nullptr;
+  float *X = nullptr, *LOGITS = nullptr, *Hd = nullptr, *Hi = nullptr;
   float* Hup[4] = {nullptr, nullptr, nullptr, nullptr};   // hidden rows buffered at the further verifier exits (levels 2..n-1)
   int n_levels = 2;             // verifier levels: exits after L_d (2 = Alg. 2: L_i and L_f)
   void *XN = nullptr, *Qb = nullptr, *AO = nullptr, *H = nullptr;
   float2* cs = nullptr;
   int4* rowinfo = nullptr;    // [maxM] per-row lookups of the QKV epilogue, resolved once per call
-  int *vtok = nullptr, *tok_next = nullptr, *draft_dev = nullptr, *out_dev = nullptr, *page_scratch = nullptr;
+  int *vtok = nullptr, *tok_next = nullptr, *out_dev = nullptr, *page_scratch = nullptr;
   // rejection-sampling acceptance (attached separately): the distributions the draft tokens were drawn from,
-  // the L_i distributions of the tokens in V (rows [batch][max_rows][vocab]), and the call's uniform numbers
-  float *Pd = nullptr, *Pi = nullptr, *u_dev = nullptr;
+  // the L_i distributions of the tokens in V (rows [batch][max_rows][vocab])
+  float *Pd = nullptr, *Pi = nullptr;
   float* Pup[4] = {nullptr, nullptr, nullptr, nullptr};   // the same for the buffers of levels 2..n-1
   bool need_logits = false;
   float *part_o = nullptr, *part_ml = nullptr, *pmax = nullptr, *ssq = nullptr, *gemm_part = nullptr, *inv_rms = nullptr;
@@ -66,7 +66,7 @@ struct ee_session {
   // host side
   MetaSlot slot[2];
   size_t meta_ints = 0, meta_cap = 0;   // metadata of the call being built, and of the largest one
-  int* out_host = nullptr;    // pinned: n_accept[B], next[B], draft [B*max_rows]
+  int* out_host = nullptr;    // pinned, written by the kernels that decide them: n_accept[B], next[B], draft [B*max_rows]
   std::vector<SeqState> seq;
   std::vector<int> free_pages;
   bool debug_logits = false, time_kernels = false;
@@ -75,7 +75,7 @@ struct ee_session {
   int launches[KF_COUNT] = {0};
   // meta layout (offsets in ints)
   size_t o_row_seq, o_row_pos, o_row_tok, o_row_src, o_row_dst, o_seq_row0, o_seq_m, o_seq_p0, o_seq_qt0, o_qt_seq,
-      o_qt_local, o_cand, o_n_cand, o_bt;
+      o_qt_local, o_cand, o_n_cand, o_bt, o_u;
   int cand_stride = 0;
 };
 
@@ -96,7 +96,7 @@ struct Carver {
 };
 
 // offsets of the metadata block of a call with so many rows and q-tiles (a call uploads no more than it uses)
-static void layout_meta(ee_session* s, int rows, int qts) {
+static void layout_meta(ee_session* s, int rows, int qts, int uniforms) {
   size_t o = 0;
   auto take = [&](size_t n) { size_t r = o; o += (n + 3) / 4 * 4; return r; };
   s->cand_stride = s->max_rows + 1;
@@ -106,6 +106,7 @@ static void layout_meta(ee_session* s, int rows, int qts) {
   s->o_qt_seq = take(qts); s->o_qt_local = take(qts);
   s->o_cand = take((size_t)s->B * s->cand_stride); s->o_n_cand = take(s->B);
   s->o_bt = take((size_t)s->B * s->pps);
+  s->o_u = take(uniforms);                              // (floats)
   s->meta_ints = o;
 }
 
@@ -120,12 +121,9 @@ static size_t carve(ee_session* s, char* base) {
   const int Mp = s->Mp;
   s->kv = cv.take<char>((size_t)c.n_layers * s->n_pages * Hkv * 2 * EE_PAGE * D * es);
   s->X = cv.take<float>((size_t)s->maxM * d);
-  s->XN = bf ? (void*)cv.take<bf16_t>((size_t)Mp * ceil_div(d, 32) * 32) : (void*)cv.take<float>((size_t)s->maxM * d);
-  const int nqkv = (Hq + 2 * Hkv) * D, nqkv_p = bf ? ceil_div(nqkv, 16) * 16 : nqkv;
-  s->QKV = bf ? nullptr : cv.take<float>((size_t)s->maxM * nqkv_p);
+  s->XN = bf ? (void*)cv.take<bf16_t>((size_t)Mp * ceil_div(d, 32) * 32) : nullptr;
   s->Qb = bf ? (void*)cv.take<bf16_t>((size_t)Hkv * s->maxQT * 16 * D) : (void*)cv.take<float>((size_t)s->maxM * Hq * D);
   s->AO = bf ? (void*)cv.take<bf16_t>((size_t)Mp * ceil_div(Hq * D, 32) * 32) : (void*)cv.take<float>((size_t)s->maxM * Hq * D);
-  s->GU = bf ? nullptr : cv.take<float>((size_t)s->maxM * 2 * m->Fp);
   s->H = bf ? (void*)cv.take<bf16_t>((size_t)Mp * ceil_div(c.d_ffn, 32) * 32) : (void*)cv.take<float>((size_t)s->maxM * c.d_ffn);
   s->LOGITS = cv.take<float>((size_t)s->headM * c.vocab);
   if (c.head_rank > 0) {
@@ -144,8 +142,7 @@ static size_t carve(ee_session* s, char* base) {
   s->rowinfo = cv.take<int4>((size_t)s->maxM);
   s->vtok = cv.take<int>(s->maxM);
   s->tok_next = cv.take<int>(s->maxM);
-  s->draft_dev = cv.take<int>((size_t)s->B * s->max_rows);
-  s->out_dev = cv.take<int>(2 * (size_t)s->B);
+  s->out_dev = cv.take<int>(s->B);                                    // (sampling: accept counts on their way to the draw)
   s->page_scratch = cv.take<int>(s->pps);
   if (bf) {
     // attention split scratch: all 64 splits for verify-sized calls (<= 64 rows), 8 at 512 rows and fewer for larger context-build passes
@@ -189,7 +186,7 @@ static int shape_session(ee_session* s, const ee_model* m, int batch, int max_ct
   s->maxQT = ceil_div(s->maxM * rep, 16) + batch;
   s->ssq_stride = s->Mp;
   s->inv_cap = std::max(512, s->maxM);
-  layout_meta(s, s->maxM, s->maxQT);                    // (the largest block; every call lays out its own)
+  layout_meta(s, s->maxM, s->maxQT, s->B * s->max_rows + s->B);   // (the largest block; every call lays out its own)
   s->meta_cap = s->meta_ints;
   return EE_OK;
 }
@@ -306,7 +303,7 @@ static CallMeta meta_ptrs(const ee_session* s, const int* d) {
 // Fill slot `si` from the plan: rows are packed sequence by sequence.  The callbacks give the
 // per-row token / gather source / scatter destination; candidates are filled by the caller.
 template <class RowFn>
-static int build_meta(ee_session* s, int si, CallPlan& p, RowFn row_fn) {
+static int build_meta(ee_session* s, int si, CallPlan& p, RowFn row_fn, int uniforms = 0) {
   MetaSlot& sl = s->slot[si];
   if (sl.in_flight) { HIP_TRY(hipEventSynchronize(sl.copied)); sl.in_flight = false; }
   int* h = sl.h;
@@ -314,7 +311,7 @@ static int build_meta(ee_session* s, int si, CallPlan& p, RowFn row_fn) {
   int row = 0, qt = 0;
   for (int b = 0; b < s->B; ++b) { row += p.m[b]; qt += ceil_div(p.m[b] * rep, 16); }
   if (row > s->maxM || qt > s->maxQT) { ee_set_error("internal: call exceeds work buffers (%d rows)", row); return EE_ERR_CAPACITY; }
-  layout_meta(s, row, qt);
+  layout_meta(s, row, qt, uniforms);
   row = qt = 0;
   p.M = 0; p.n_active = 0; p.max_m = 0; p.max_kv_end = 0;
   for (int b = 0; b < s->B; ++b) {
@@ -435,15 +432,14 @@ static void run_layers(ee_session* s, int l0, int l1, const CallPlan& p, const C
   const ee_config& c = m->cfg;
   const int d = c.d_model, D = c.head_dim, Hq = c.n_q_heads, Hkv = c.n_kv_heads, M = p.M;
   hipStream_t st = s->st;
-  if (m->bf16 && l0 < l1) {
+  if (m->bf16) {
     // one launch: rows into the stream, the first layer's operand, the rotary table and the epilogue lookups
     KF(KF_NORM, bf16_begin_pass(st, src.tok ? (const bf16_t*)(m->base + m->emb) : nullptr, src.tok, src.rows, src.row_idx, s->X,
                                 (const float*)(m->base + m->L[l0].g1), c.rms_eps, (bf16_t*)s->XN, m->L[l0].qkv.ktiles(), M, d, mt,
                                 pos_add, m->inv_freq, s->cs, D / 2, s->pps, s->rowinfo));
   } else {
-    if (src.tok) KF(KF_EMBED, k_embed(st, m->bf16, m->base + m->emb, src.tok, s->X, M, d));
-    else if (src.rows) KF(KF_COPY, k_copy_rows(st, s->X, nullptr, 0, src.rows, src.row_idx, M, d));
-    KF(KF_ROPE, k_rope_table(st, mt, pos_add, m->inv_freq, s->cs, M, D / 2, s->pps, s->rowinfo));
+    KF(KF_EMBED, f32_begin_pass(st, src.tok ? (const float*)(m->base + m->emb) : nullptr, src.tok, src.rows, src.row_idx, s->X, M, d, mt,
+                                pos_add, m->inv_freq, s->cs, D / 2, s->pps, s->rowinfo));
   }
   AttnScratch scr;
   const AttnPlan attn = attention_plan(s, p, pos_add, scr);
@@ -481,19 +477,20 @@ static void run_layers(ee_session* s, int l0, int l1, const CallPlan& p, const C
       const float* Wo = (const float*)(m->base + L.o.off);
       const float* Wgu = (const float*)(m->base + L.gu.off);
       const float* Wd = (const float*)(m->base + L.down.off);
-      KF(KF_NORM, f32_rmsnorm(st, s->X, g1, c.rms_eps, (float*)s->XN, M, d));
-      KF(KF_GEMM_QKV, f32_gemm(st, (const float*)s->XN, d, Wqkv, s->QKV, L.qkv.N, M, L.qkv.N, d, false));
-      KF(KF_ROPE, f32_rope_append(st, s->QKV, L.qkv.N, s->cs, mt, pos_add, M, Hq, Hkv, D, l, s->n_pages, s->pps, (float*)s->Qb, (float*)s->kv));
+      // five launches per layer: norms, rotary embedding, KV append and activation sit in the projections
+      const bool end = l + 1 == l1;
+      F32Out o;
+      o.Y = (float*)s->Qb; o.cs = s->cs; o.rowinfo = s->rowinfo; o.Hq = Hq; o.Hkv = Hkv; o.D = D; o.layer = l; o.n_pages = s->n_pages;
+      o.kv = (float*)s->kv;
+      KF(KF_GEMM_QKV, f32_qkv(st, s->X, g1, c.rms_eps, Wqkv, M, d, o));
       KF(KF_ATTN, f32_attention(st, (const float*)s->Qb, (const float*)s->kv, mt, pos_add, M, Hq, Hkv, D, l, s->n_pages, s->pps,
                                 s->max_ctx, (float*)s->AO));
-      KF(KF_GEMM_O, f32_gemm(st, (const float*)s->AO, Hq * D, Wo, s->X, d, M, d, Hq * D, true));
-      KF(KF_NORM, f32_rmsnorm(st, s->X, g2, c.rms_eps, (float*)s->XN, M, d));
-      KF(KF_GEMM_GU, f32_gemm(st, (const float*)s->XN, d, Wgu, s->GU, 2 * m->Fp, M, 2 * m->Fp, d, false));
-      KF(KF_GEMM_GU, f32_silu_mul(st, s->GU, 2 * m->Fp, (float*)s->H, M, c.d_ffn));
-      KF(KF_GEMM_DOWN, f32_gemm(st, (const float*)s->H, c.d_ffn, Wd, s->X, d, M, d, c.d_ffn, true));
+      KF(KF_GEMM_O, f32_gemm(st, (const float*)s->AO, Hq * D, nullptr, 0.f, Wo, s->X, d, M, d, Hq * D, true));
+      KF(KF_GEMM_GU, f32_gate_up(st, s->X, g2, c.rms_eps, Wgu, (float*)s->H, M, c.d_ffn, d));
+      KF(KF_GEMM_DOWN, f32_gemm(st, (const float*)s->H, c.d_ffn, nullptr, 0.f, Wd, s->X, d, M, d, c.d_ffn, true, end ? sink.rows : nullptr,
+                                sink.row_idx, sink.add));
     }
   }
-  if (sink.rows && (!m->bf16 || l0 >= l1)) KF(KF_COPY, k_copy_rows(st, sink.rows, sink.row_idx, sink.add, s->X, nullptr, M, d));
 }
 
 // Prediction head of exit `which` (0 = L_d, 1 = L_i, ..., n_levels = L_f) + arg max for rows 0..M-1 of X -> vtok.
@@ -501,7 +498,8 @@ static void run_layers(ee_session* s, int l0, int l1, const CallPlan& p, const C
 // (App. I) behind that exit's rank-r adapter  z = x + B (A RMSNorm(x; g)),  which leaves X itself alone.
 // row0 (a multiple of 16): the rows are row0 .. row0+M-1 of the pass instead (final exit only).  ended: the rows are those
 // listed on the device (the ends of prompts in a context build), normalised here; X's other rows need no head.
-static void exit_head(ee_session* s, int M, int which, int row0 = 0, const int* ended = nullptr) {
+// take: hand every row's token on (drafting, decoding).
+static void exit_head(ee_session* s, int M, int which, int row0 = 0, const int* ended = nullptr, const TakeToken& take = TakeToken()) {
   const ee_model* m = s->m;
   const ee_config& c = m->cfg;
   hipStream_t st = s->st;
@@ -539,20 +537,18 @@ static void exit_head(ee_session* s, int M, int which, int row0 = 0, const int* 
     o.pmax = s->pmax; o.pidx = s->pidx; o.pstride = pstride;
     if (s->debug_logits || s->need_logits) { o.Y = s->LOGITS; o.ldy = c.vocab; }
     KF(KF_GEMM_HEAD, gemm(s, EPI_ARGMAX, m->head, operand, M, o));
-    KF(KF_ARGMAX, bf16_argmax_reduce(st, s->pmax, s->pidx, m->head.ntiles(), pstride, M, s->vtok));
+    KF(KF_ARGMAX, bf16_argmax_reduce(st, s->pmax, s->pidx, m->head.ntiles(), pstride, M, s->vtok, take));
   } else {
     const float* hidden = s->X;
     if (aux) {
-      KF(KF_NORM, f32_rmsnorm(st, s->X, (const float*)(m->base + m->auxg[which]), c.rms_eps, (float*)s->XN, M, d));
-      KF(KF_GEMM_HEAD, f32_gemm(st, (const float*)s->XN, d, (const float*)(m->base + m->auxA[which].off), s->T, r, M, r, d, false));
+      KF(KF_GEMM_HEAD, f32_gemm(st, s->X, d, (const float*)(m->base + m->auxg[which]), c.rms_eps, (const float*)(m->base + m->auxA[which].off),
+                                s->T, r, M, r, d, false));
       (void)hipMemcpyAsync(s->Z, s->X, (size_t)M * d * sizeof(float), hipMemcpyDeviceToDevice, st);
-      KF(KF_GEMM_HEAD, f32_gemm(st, (const float*)s->T, r, (const float*)(m->base + m->auxB[which].off), s->Z, d, M, d, r, true));
+      KF(KF_GEMM_HEAD, f32_gemm(st, s->T, r, nullptr, 0.f, (const float*)(m->base + m->auxB[which].off), s->Z, d, M, d, r, true));
       hidden = s->Z;
     }
-    KF(KF_NORM, f32_rmsnorm(st, hidden, gf, c.rms_eps, (float*)s->XN, M, d));
-    KF(KF_GEMM_HEAD, f32_gemm(st, (const float*)s->XN, d, (const float*)(m->base + m->head.off), s->LOGITS, c.vocab, M,
-                              c.vocab, d, false));
-    KF(KF_ARGMAX, f32_argmax(st, s->LOGITS, M, c.vocab, s->vtok));
+    KF(KF_GEMM_HEAD, f32_gemm(st, hidden, d, gf, c.rms_eps, (const float*)(m->base + m->head.off), s->LOGITS, c.vocab, M, c.vocab, d, false));
+    KF(KF_ARGMAX, f32_argmax(st, s->LOGITS, M, c.vocab, s->vtok, take));
   }
   s->last_rows = M; s->last_row0 = row0;
 }
@@ -736,14 +732,12 @@ extern "C" int ee_decode_ar(ee_session* s, int n, int32_t* out) {
   EE_TRY(build_meta(s, 0, p, [&](int b, int, int& tok, int&, int&) { tok = s->seq[b].C.back(); }));
   EE_TRY(upload_meta(s, 0));
   CallMeta mt = meta_ptrs(s, s->slot[0].d);
+  int* dh = s->out_host + 2 * s->B;   // (pinned: the kernels store the tokens there)
   for (int j = 0; j < n; ++j) {       // the next token stays on the device; positions advance through pos_add
     PassSource from_tokens; from_tokens.tok = j == 0 ? mt.row_tok : s->tok_next;
     run_layers(s, 0, c.n_layers, p, mt, j, from_tokens);
-    exit_head(s, p.M, s->n_levels);
-    KF(KF_MISC, k_take_token(s->st, s->vtok, mt.row_seq, p.M, s->tok_next, s->draft_dev, s->max_rows, j));
+    exit_head(s, p.M, s->n_levels, 0, nullptr, TakeToken{s->tok_next, dh, mt.row_seq, s->max_rows, j});
   }
-  int* dh = s->out_host + 2 * s->B;
-  HIP_TRY(hipMemcpyAsync(dh, s->draft_dev, (size_t)s->B * s->max_rows * sizeof(int), hipMemcpyDeviceToHost, s->st));
   EE_TRY(finish(s));
   for (int b = 0; b < s->B; ++b) {
     SeqState& q = s->seq[b];
@@ -774,13 +768,22 @@ static int draft_precheck(ee_session* s, int k, int rows) {
   return check_capacity(s, want);
 }
 
-// uniform numbers of a call: host -> the session's device buffer (sampling attached)
-static int upload_uniforms(ee_session* s, const float* u, size_t n, size_t at) {
+static int check_uniforms(const float* u, size_t n) {
   for (size_t i = 0; i < n; ++i)
     if (!(u[i] >= 0.0f && u[i] < 1.0f)) { ee_set_error("uniform numbers must lie in [0, 1)"); return EE_ERR_ARG; }
-  HIP_TRY(hipMemcpyAsync(s->u_dev + at, u, n * sizeof(float), hipMemcpyHostToDevice, s->st));
   return EE_OK;
 }
+// The uniform numbers of a call travel in its metadata block: acc [B][max_rows] (stride numbers of each participating
+// sequence), then one more per sequence (res; null: none).
+static void put_uniforms(ee_session* s, const CallPlan& p, const float* acc, int stride, const float* res) {
+  float* u = (float*)(s->slot[0].h + s->o_u);
+  for (int b = 0; b < s->B; ++b) {
+    if (!p.m[b]) continue;
+    std::copy(acc + (size_t)b * stride, acc + (size_t)b * stride + std::min(stride, s->max_rows), u + (size_t)b * s->max_rows);
+    if (res) u[(size_t)s->B * s->max_rows + b] = res[b];
+  }
+}
+static const float* uniforms(const ee_session* s) { return (const float*)(s->slot[0].d + s->o_u); }
 
 // u == null: arg max of p_{L_d} (Alg. 2); otherwise token j of sequence b is drawn from p_{L_d} with u[b*k + j] (App. G)
 static int draft_impl(ee_session* s, int k, int32_t* draft, const float* u) {
@@ -791,7 +794,7 @@ static int draft_impl(ee_session* s, int k, int32_t* draft, const float* u) {
   EE_TRY(draft_precheck(s, k, rows));
   if (u)
     for (int b = 0; b < s->B; ++b)      // an idle slot's numbers are neither read nor checked
-      if (s->seq[b].started) EE_TRY(upload_uniforms(s, u + (size_t)b * k, k, (size_t)b * k));
+      if (s->seq[b].started) EE_TRY(check_uniforms(u + (size_t)b * k, k));
   reset_accounting(s);
   s->need_logits = u != nullptr;
   CallPlan p;
@@ -807,26 +810,23 @@ static int draft_impl(ee_session* s, int k, int32_t* draft, const float* u) {
     const SeqState& q = s->seq[b];
     tok = q.V.empty() ? q.C.back() : q.V.back();
     dst = b * s->max_rows;
-  }));
+  }, u ? s->B * s->max_rows : 0));
+  if (u) put_uniforms(s, p, u, k, nullptr);
   EE_TRY(upload_meta(s, 0));
   CallMeta mt = meta_ptrs(s, s->slot[0].d);
+  int* dh = s->out_host + 2 * s->B;   // (pinned: the kernels store the tokens there)
   for (int j = 0; j < rows; ++j) {
     PassSource from_tokens; from_tokens.tok = j == 0 ? mt.row_tok : s->tok_next;
     PassSink keep; keep.rows = s->Hd; keep.row_idx = mt.row_dst; keep.add = j;
     run_layers(s, 0, c.exit_draft, p, mt, j, from_tokens, keep);
     if (j < k) {
-      exit_head(s, p.M, 0);
-      if (u) {      // p_{L_d} of this position into the draft-distribution store, then the draw
-        KF(KF_MISC, k_softmax_draw(s->st, s->LOGITS, s->Pd, mt.row_dst, j, p.M, c.vocab, s->u_dev, k, j, mt.row_seq, s->tok_next,
-                                   s->draft_dev, s->max_rows));
-      } else {
-        KF(KF_MISC, k_take_token(s->st, s->vtok, mt.row_seq, p.M, s->tok_next, s->draft_dev, s->max_rows, j));
-      }
+      exit_head(s, p.M, 0, 0, nullptr, u ? TakeToken() : TakeToken{s->tok_next, dh, mt.row_seq, s->max_rows, j});
+      if (u)      // p_{L_d} of this position into the draft-distribution store, then the draw
+        KF(KF_MISC, k_softmax_draw(s->st, s->LOGITS, s->Pd, mt.row_dst, j, p.M, c.vocab, uniforms(s), s->max_rows, j, mt.row_seq, s->tok_next,
+                                   dh, s->max_rows));
     }
   }
   s->need_logits = false;
-  int* dh = s->out_host + 2 * s->B;
-  HIP_TRY(hipMemcpyAsync(dh, s->draft_dev, (size_t)s->B * s->max_rows * sizeof(int), hipMemcpyDeviceToHost, s->st));
   EE_TRY(finish(s));
   for (int b = 0; b < s->B; ++b) {
     SeqState& q = s->seq[b];
@@ -999,15 +999,16 @@ static int verify_intermediate_impl(ee_session* s, int32_t* n_accept, int32_t* n
     for (int b = 0; b < s->B; ++b) {                         // idle sequences' numbers are neither read nor checked
       if (!p.m[b]) continue;
       if ((int)s->seq[b].S.size() > u_stride) { ee_set_error("sequence %d: %d draft tokens need as many uniform numbers (u_stride %d)", b, (int)s->seq[b].S.size(), u_stride); return EE_ERR_ARG; }
-      EE_TRY(upload_uniforms(s, u_acc + (size_t)b * u_stride, u_stride, (size_t)b * s->max_rows));
-      EE_TRY(upload_uniforms(s, u_res + b, 1, (size_t)s->B * s->max_rows + b));
+      EE_TRY(check_uniforms(u_acc + (size_t)b * u_stride, u_stride));
+      EE_TRY(check_uniforms(u_res + b, 1));
     }
   }
   reset_accounting(s);
   EE_TRY(build_meta(s, 0, p, [&](int b, int r, int&, int& src, int& dst) {
     src = b * s->max_rows + r;                               // H_d row
     dst = b * s->max_rows + (int)s->seq[b].V.size() + r;     // H_i row
-  }));
+  }, rs ? s->B * s->max_rows + s->B : 0));
+  if (rs) put_uniforms(s, p, u_acc, u_stride, u_res);
   if (static_scratch) EE_TRY(place_scratch_static(s, p));
   int* h = s->slot[0].h;
   for (int b = 0; b < s->B; ++b) {
@@ -1027,13 +1028,12 @@ static int verify_intermediate_impl(ee_session* s, int32_t* n_accept, int32_t* n
   if (rs) {
     // p_{L_i} in place, and kept for the rows that may stay
     KF(KF_MISC, k_softmax_rows(s->st, s->LOGITS, s->LOGITS, nullptr, 0, s->Pi, mt.row_dst, p.M, c.vocab));
-    KF(KF_ACCEPT, k_rs_accept(s->st, s->LOGITS, s->Pd, s->max_rows, c.vocab, mt, s->cand_stride, s->B, s->u_dev, s->max_rows, s->out_dev));
-    KF(KF_ACCEPT, k_rs_draw(s->st, s->LOGITS, s->Pd, s->max_rows, c.vocab, mt, s->B, s->out_dev, s->u_dev + (size_t)s->B * s->max_rows,
-                            s->out_dev + s->B));
+    KF(KF_ACCEPT, k_rs_accept(s->st, s->LOGITS, s->Pd, s->max_rows, c.vocab, mt, s->cand_stride, s->B, uniforms(s), s->max_rows, s->out_dev));
+    KF(KF_ACCEPT, k_rs_draw(s->st, s->LOGITS, s->Pd, s->max_rows, c.vocab, mt, s->B, s->out_dev, uniforms(s) + (size_t)s->B * s->max_rows,
+                            s->out_host));
   } else {
-    KF(KF_ACCEPT, k_accept(s->st, s->vtok, mt, s->cand_stride, s->B, s->out_dev, s->out_dev + s->B));
+    KF(KF_ACCEPT, k_accept(s->st, s->vtok, mt, s->cand_stride, s->B, s->out_host, s->out_host + s->B));
   }
-  HIP_TRY(hipMemcpyAsync(s->out_host, s->out_dev, 2 * (size_t)s->B * sizeof(int), hipMemcpyDeviceToHost, s->st));
   EE_TRY(finish(s));
   for (int b = 0; b < s->B; ++b) {
     SeqState& q = s->seq[b];
@@ -1122,8 +1122,8 @@ static int verify_upper_impl(ee_session* s, int level, const uint8_t* active, in
     for (int b = 0; b < s->B; ++b) {                         // idle sequences' numbers are neither read nor checked
       if (!act[b]) continue;
       if (m_src[b] > u_stride) { ee_set_error("sequence %d: %d tentative tokens need as many uniform numbers (u_stride %d)", b, m_src[b], u_stride); return EE_ERR_ARG; }
-      EE_TRY(upload_uniforms(s, u_acc + (size_t)b * u_stride, u_stride, (size_t)b * s->max_rows));
-      EE_TRY(upload_uniforms(s, u_res + b, 1, (size_t)s->B * s->max_rows + b));
+      EE_TRY(check_uniforms(u_acc + (size_t)b * u_stride, u_stride));
+      EE_TRY(check_uniforms(u_res + b, 1));
     }
   }
   auto src_tok = [&](int b, int i) { const SeqState& q = s->seq[b]; return j == 2 ? q.V[i] : q.C[q.cut[j] + i]; };
@@ -1157,7 +1157,8 @@ static int verify_upper_impl(ee_session* s, int level, const uint8_t* active, in
   EE_TRY(build_meta(s, 0, p, [&](int b, int r, int&, int& src, int& dst) {
     src = b * s->max_rows + r;
     dst = b * s->max_rows + (j < n ? s->seq[b].cut[j] - s->seq[b].cut[j + 1] : 0) + r;     // row of level j's own buffer
-  }));
+  }, rs ? s->B * s->max_rows + s->B : 0));
+  if (rs) put_uniforms(s, p, u_acc, u_stride, u_res);
   int* h = s->slot[0].h;
   for (int b = 0; b < s->B; ++b) {
     if (!act[b]) continue;
@@ -1177,13 +1178,12 @@ static int verify_upper_impl(ee_session* s, int level, const uint8_t* active, in
     const float* q_below = level_dist(s, j - 1);
     // exit j's distributions in place and, below L_f, kept for the rows that may stay: the law of the tokens that wait for exit j+1
     KF(KF_MISC, k_softmax_rows(s->st, s->LOGITS, s->LOGITS, nullptr, 0, j < n ? level_dist(s, j) : nullptr, mt.row_dst, p.M, c.vocab));
-    KF(KF_ACCEPT, k_rs_accept(s->st, s->LOGITS, q_below, s->max_rows, c.vocab, mt, s->cand_stride, s->B, s->u_dev, s->max_rows, s->out_dev));
-    KF(KF_ACCEPT, k_rs_draw(s->st, s->LOGITS, q_below, s->max_rows, c.vocab, mt, s->B, s->out_dev, s->u_dev + (size_t)s->B * s->max_rows,
-                            s->out_dev + s->B));
+    KF(KF_ACCEPT, k_rs_accept(s->st, s->LOGITS, q_below, s->max_rows, c.vocab, mt, s->cand_stride, s->B, uniforms(s), s->max_rows, s->out_dev));
+    KF(KF_ACCEPT, k_rs_draw(s->st, s->LOGITS, q_below, s->max_rows, c.vocab, mt, s->B, s->out_dev, uniforms(s) + (size_t)s->B * s->max_rows,
+                            s->out_host));
   } else {
-    KF(KF_ACCEPT, k_accept(s->st, s->vtok, mt, s->cand_stride, s->B, s->out_dev, s->out_dev + s->B));
+    KF(KF_ACCEPT, k_accept(s->st, s->vtok, mt, s->cand_stride, s->B, s->out_host, s->out_host + s->B));
   }
-  HIP_TRY(hipMemcpyAsync(s->out_host, s->out_dev, 2 * (size_t)s->B * sizeof(int), hipMemcpyDeviceToHost, s->st));
   EE_TRY(finish(s));
   for (int b = 0; b < s->B; ++b) {
     SeqState& q = s->seq[b];
@@ -1239,7 +1239,7 @@ extern "C" int ee_verify_full_rs(ee_session* s, const uint8_t* active, const flo
 // ---------------------------------------------------------------------------------------------
 static size_t sampling_floats(const ee_session* s) {
   const size_t rows = (size_t)s->B * s->max_rows;
-  return (size_t)s->n_levels * rows * s->m->cfg.vocab + rows + s->B + 64;     // one store per level below L_f, and the uniform numbers
+  return (size_t)s->n_levels * rows * s->m->cfg.vocab + 64;     // one store per level below L_f
 }
 extern "C" size_t ee_sampling_bytes(const ee_session* s) { return s ? sampling_floats(s) * sizeof(float) : 0; }
 
@@ -1251,7 +1251,6 @@ extern "C" int ee_sampling_attach(ee_session* s, void* dev_arena, size_t arena_b
   const size_t store = rows * s->m->cfg.vocab;
   s->Pd = f; s->Pi = f + store;
   for (int j = 2; j < s->n_levels; ++j) s->Pup[j - 2] = f + (size_t)j * store;
-  s->u_dev = f + (size_t)s->n_levels * store;
   return EE_OK;
 }
 

@@ -585,3 +585,18 @@ def test_context_build_in_blocks_matches_the_512_row_passes(name, rows):
         hs.ee_debug_gemm_row_blocks(-1); hs.ee_debug_attention_split_pages(0)
     assert step.shape == (2, 1)
     sess.close(); model.close()
+
+
+@pytest.mark.parametrize("d,ffn,heads,vocab", [(66, 70, (2, 1), 130), (68, 41, (4, 2), 1001), (256, 100, (3, 3), 77)])
+def test_fp32_projections_at_odd_widths_match_oracle(d, ffn, heads, vocab):
+    """The fused fp32 projections where their 16-byte loads do not apply (widths that are no multiple of four), at row counts
+    around the four rows of a wave and with unit counts that leave waves idle: against the oracle, fp32 bound."""
+    cfg = synth.EEConfig(n_layers=4, d_model=d, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=32, d_ffn=ffn, vocab=vocab,
+                         exit_draft=1, exit_inter=2, dtype="f32", sigma=0.1, gamma=(1.0, 0.3, 0.3))
+    tol, k = TOL["f32"], 4
+    O, model, sess, first, gfirst = _setup(cfg, 5, [9, 66], 3 * (k + 1) + 2)
+    assert gfirst.tolist() == first.tolist()
+    assert max_rel(sess.last_logits()[-1:], O.o.last_logits) <= tol
+    rng = np.random.default_rng(8)
+    _round(O, sess, k, 0.8, rng, True, tol)
+    sess.close(); model.close()
