@@ -96,7 +96,8 @@ extern int g_attn_pages_override;   // <= 0: pages per KV split chosen from the 
 extern int g_rows_wide;              // 1: gate/up and exit head at 257..512 rows run sixteen weight tiles per workgroup in two row blocks; 0: eight in one
 extern int g_rows_blocks_override;   // -1: built-in choice between K shares and row blocks; else 0, or row tiles per block (+100: eight weight tiles per workgroup)
 size_t bf16_gemm_rows_scratch_floats(int ntiles, int ktiles);
-void bf16_gemm_rows(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N,
+// Returns how many partial sums of squares per row an EPI_ADD call with nout left (n_part of the next NormIn).
+int bf16_gemm_rows(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N,
                     const GemmOut& out, float* scratch, float* inv_rms, int inv_cap);
 // out row r (GEMM operand) <- RMSNorm of row idx[r] of X with gain g
 void bf16_rmsnorm(hipStream_t st, const float* X, const int* idx, const float* g, float eps, bf16_t* out, int ktiles, int M, int d);

@@ -218,10 +218,49 @@ __device__ inline void epi_prefetch(EpiPre& p, const GemmOut& out, int task, int
   }
 }
 
+// Deferred RMSNorm factors sc[i] of rows row0 + 16 * step * i + lane % 16 (row0 a multiple of 16; i < n of NT) from the
+// producer's partial sums of squares [partial][row], in a fixed order: a lane loads four rows (lane % 4) of every 16th partial
+// (lane / 4), a butterfly over the lanes adds them up.  The row tiles go side by side, so the chain is one tile's.
+template <int NT>
+__device__ inline void norm_factors(float (&sc)[NT], const NormIn& nin, int row0, int step, int n, int lane) {
+  const float* p = nin.ssq + row0 + 4 * (lane & 3);
+  float4 sv[NT];
+#pragma unroll
+  for (int i = 0; i < NT; ++i) sv[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int c0 = lane >> 2; c0 < nin.n_part; c0 += 64) {
+    float4 t[NT][4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int i = 0; i < NT; ++i)
+        t[i][j] = *(const float4*)(p + (size_t)min(c0 + 16 * j, nin.n_part - 1) * nin.stride + 16 * step * min(i, n - 1));
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (c0 + 16 * j < nin.n_part) {
+#pragma unroll
+        for (int i = 0; i < NT; ++i) { sv[i].x += t[i][j].x; sv[i].y += t[i][j].y; sv[i].z += t[i][j].z; sv[i].w += t[i][j].w; }
+      }
+  }
+#pragma unroll
+  for (int sh = 4; sh < 64; sh <<= 1)
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      sv[i].x += __shfl_xor(sv[i].x, sh, 64); sv[i].y += __shfl_xor(sv[i].y, sh, 64);
+      sv[i].z += __shfl_xor(sv[i].z, sh, 64); sv[i].w += __shfl_xor(sv[i].w, sh, 64);
+    }
+  const int mc = lane & 15;          // lanes with lane % 4 == q now hold rows 4q .. 4q+3
+#pragma unroll
+  for (int i = 0; i < NT; ++i) {
+    const float a = __shfl(sv[i].x, mc >> 2, 64), b = __shfl(sv[i].y, mc >> 2, 64), c = __shfl(sv[i].z, mc >> 2, 64), e = __shfl(sv[i].w, mc >> 2, 64);
+    const float ss = (mc & 2) ? ((mc & 1) ? e : c) : ((mc & 1) ? b : a);
+    sc[i] = 1.0f / sqrtf(ss * nin.inv_d + nin.eps);
+  }
+}
+
 // sc: the row's deferred RMSNorm factor (1 when the operand was already normalised)
 template <int EPI>
 __device__ inline void epi_apply(const f32x4& acc0, const f32x4& acc1, float sc, const EpiPre& p, const GemmOut& out, int task,
-                                 int row, bool ok, int N, int lane) {
+                                 int row, bool ok, int N, int lane, float* ss_out = nullptr) {
   const int g = lane >> 4;
   if (EPI == EPI_ADD) {
     const int n = task * 16 + 4 * g;
@@ -235,7 +274,8 @@ __device__ inline void epi_apply(const f32x4& acc0, const f32x4& acc1, float sc,
       float ss = ok ? (r.x * r.x + r.y * r.y) + (r.z * r.z + r.w * r.w) : 0.f;
       ss += __shfl_xor(ss, 16, 64);
       ss += __shfl_xor(ss, 32, 64);
-      if (g == 0) out.nout.ssq[(size_t)task * out.nout.stride + row] = ss;
+      if (ss_out) *ss_out = ss;                // (the caller adds up several tiles)
+      else if (g == 0) out.nout.ssq[(size_t)task * out.nout.stride + row] = ss;
     }
   } else if (EPI == EPI_SWIGLU) {
     const int f = task * 16 + 4 * g;     // h[m][f..f+3] = silu(gate) * up
@@ -671,6 +711,14 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
     }
     return;
   }
+  float sc[TMW];        // the rows' deferred RMSNorm factors: reduced beforehand, or here from the producer's partial sums
+#pragma unroll
+  for (int mt = 0; mt < TMW; ++mt) {
+    sc[mt] = 1.0f;
+    if (out.nin.inv_rms && mt_first + mt * MT_STEP < mt_used) sc[mt] = out.nin.inv_rms[rbase + min((mt_first + mt * MT_STEP) * 16 + mc, M - 1)];
+  }
+  const int mt_own = (mt_used - mt_first + MT_STEP - 1) / MT_STEP;      // row tiles of this wave that hold rows
+  if (!out.nin.inv_rms && out.nin.ssq && mt_own > 0) norm_factors<TMW>(sc, out.nin, row0 + rbase + mt_first * 16, MT_STEP, min(mt_own, TMW), lane);
 #pragma unroll
   for (int t = 0; t < TN / NB; ++t) {
     const int nt = nt0 + t * NB;
@@ -680,10 +728,9 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
     for (int mt = 0; mt < TMW; ++mt) {
       const int m = (mt_first + mt * MT_STEP) * 16 + mc;
       if (mt_first + mt * MT_STEP >= mt_used) continue;
-      const float sc = out.nin.inv_rms ? out.nin.inv_rms[rbase + min(m, M - 1)] : 1.0f;
       EpiPre pre;
       epi_prefetch<EPI>(pre, out, task, row0 + rbase + m, m < M, lane);
-      epi_apply<EPI>(acc[t * NB][mt], acc[t * NB + NB - 1][mt], sc, pre, out, task, row0 + rbase + m, m < M, N, lane);
+      epi_apply<EPI>(acc[t * NB][mt], acc[t * NB + NB - 1][mt], sc[mt], pre, out, task, row0 + rbase + m, m < M, N, lane);
     }
   }
 }
@@ -829,35 +876,49 @@ __global__ __launch_bounds__(512) void gemm_block_kernel(const uint4* __restrict
   else gemm_block_body<EPI, TN, false>(ring, W, ktiles, ntiles, A, row0, rbase, M, N, out, bx);
 }
 
-// sums the K shares of one (task, row tile) in a fixed order and runs the epilogue; one wave per unit
+// Sums the K shares of a row tile and runs the epilogue, one wave per task; the four waves of a workgroup take four tasks of
+// the same row tile and leave one partial sum of squares per row for the four of them, so that the next projection finds a
+// quarter of the partials and reads its factors itself (a launch of its own for that took 4.5 us).
+#define EE_REDUCE_TASKS 4
 template <int EPI>
-__global__ __launch_bounds__(256) void gemm_rows_reduce_kernel(const float* __restrict__ partial, int ksplit, int ntiles, int TMT,
-                                                               int row0, int M, int N, GemmOut out) {
+__global__ __launch_bounds__(64 * EE_REDUCE_TASKS) void gemm_rows_reduce_kernel(const float* __restrict__ partial, int ksplit, int ntiles,
+                                                                                int TMT, int row0, int M, int N, GemmOut out) {
   constexpr int NB = (EPI == EPI_SWIGLU || EPI == EPI_ROPE) ? 2 : 1;
-  const int lane = threadIdx.x & 63, mc = lane & 15;
+  __shared__ float ssq[EE_REDUCE_TASKS][16];
+  const int lane = threadIdx.x & 63, mc = lane & 15, wave = threadIdx.x >> 6;
   const int mtiles = (M + 15) >> 4;
-  const int unit = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int task = unit / mtiles, mt = unit % mtiles;
-  if (task * NB >= ntiles) return;
+  const int mt = blockIdx.x % mtiles, group = blockIdx.x / mtiles, task = group * EE_REDUCE_TASKS + wave;
+  const bool active = task * NB < ntiles;
   const int m = mt * 16 + mc;
-  EpiPre pre;
-  epi_prefetch<EPI>(pre, out, task, row0 + m, m < M, lane);
-  const float sc = out.nin.inv_rms ? out.nin.inv_rms[min(m, M - 1)] : 1.0f;
-  f32x4 acc[NB];
+  float ss = 0.f;
+  if (active) {
+    EpiPre pre;
+    epi_prefetch<EPI>(pre, out, task, row0 + m, m < M, lane);
+    float sc[1] = {out.nin.inv_rms ? out.nin.inv_rms[min(m, M - 1)] : 1.0f};
+    f32x4 acc[NB];
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const f32x4* pp = (const f32x4*)partial + ((size_t)(task * NB + nb) * TMT + mt) * 64 + lane;
-    for (int s0 = 0; s0 < ksplit; s0 += 8) {
-      f32x4 t[8];
+    for (int nb = 0; nb < NB; ++nb) {
+      acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      const f32x4* pp = (const f32x4*)partial + ((size_t)(task * NB + nb) * TMT + mt) * 64 + lane;
+      for (int s0 = 0; s0 < ksplit; s0 += 8) {
+        f32x4 t[8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) t[i] = __builtin_nontemporal_load(pp + (size_t)min(s0 + i, ksplit - 1) * ntiles * TMT * 64);
+        for (int i = 0; i < 8; ++i) t[i] = __builtin_nontemporal_load(pp + (size_t)min(s0 + i, ksplit - 1) * ntiles * TMT * 64);
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
-        if (s0 + i < ksplit) acc[nb] += t[i];
+        for (int i = 0; i < 8; ++i)
+          if (s0 + i < ksplit) acc[nb] += t[i];
+      }
     }
+    if (!out.nin.inv_rms && out.nin.ssq) norm_factors<1>(sc, out.nin, row0 + mt * 16, 1, 1, lane);
+    epi_apply<EPI>(acc[0], acc[NB - 1], sc[0], pre, out, task, row0 + m, m < M, N, lane, &ss);
   }
-  epi_apply<EPI>(acc[0], acc[NB - 1], sc, pre, out, task, row0 + m, m < M, N, lane);
+  if (EPI == EPI_ADD && out.nout.xn) {
+    if (lane < 16) ssq[wave][lane] = ss;
+    __syncthreads();
+    if (threadIdx.x < 16)
+      out.nout.ssq[(size_t)group * out.nout.stride + row0 + mt * 16 + threadIdx.x] =
+          (ssq[0][threadIdx.x] + ssq[1][threadIdx.x]) + (ssq[2][threadIdx.x] + ssq[3][threadIdx.x]);
+  }
 }
 
 // per-row factor rsqrt(mean(x^2) + eps) from the producer's per-tile partial sums of squares, in a fixed order:
@@ -902,11 +963,12 @@ static void launch_timed(LaunchEvents* ev, K kernel, dim3 grid, dim3 blk, hipStr
   }
 }
 
+// returns whether the K shares took a reduction pass
 template <int TMT>
-static void launch_gemm_rows(hipStream_t st, int epi, const uint4* W, int ntiles, int ktiles, const uint4* A, int row0, int M, int N,
+static bool launch_gemm_rows(hipStream_t st, int epi, const uint4* W, int ntiles, int ktiles, const uint4* A, int row0, int M, int N,
                              const GemmOut& out, float* scratch) {
   const int ks = rows_ksplit(ntiles, ktiles), per = ceil_div(ktiles, ks);
-  dim3 grid(ceil_div(ntiles, 2 * EE_ROWS_TN), ceil_div(ktiles, per)), blk(512), rblk(256);
+  dim3 grid(ceil_div(ntiles, 2 * EE_ROWS_TN), ceil_div(ktiles, per)), blk(512), rblk(64 * EE_REDUCE_TASKS);
   const int ksr = grid.y;
   // every row tile holds rows; with 32 row tiles the kernel has no register to spare for the other variant
   const bool full = M > TMT * 16 - 16 || TMT == 32;
@@ -927,8 +989,7 @@ static void launch_gemm_rows(hipStream_t st, int epi, const uint4* W, int ntiles
 #undef ROWS_LAUNCH
   if (ksr > 1) {
     const int nb = (epi == EPI_SWIGLU || epi == EPI_ROPE) ? 2 : 1;
-    const int units = (ntiles / nb) * ceil_div(M, 16);
-    dim3 rgrid(ceil_div(units, 4));
+    dim3 rgrid(ceil_div(ntiles / nb, EE_REDUCE_TASKS) * ceil_div(M, 16));
     switch (epi) {
       case EPI_ADD: hipLaunchKernelGGL((gemm_rows_reduce_kernel<EPI_ADD>), rgrid, rblk, 0, st, scratch, ksr, ntiles, TMT, row0, M, N, out); break;
       case EPI_SWIGLU: hipLaunchKernelGGL((gemm_rows_reduce_kernel<EPI_SWIGLU>), rgrid, rblk, 0, st, scratch, ksr, ntiles, TMT, row0, M, N, out); break;
@@ -936,6 +997,7 @@ static void launch_gemm_rows(hipStream_t st, int epi, const uint4* W, int ntiles
       default: hipLaunchKernelGGL((gemm_rows_reduce_kernel<EPI_ARGMAX>), rgrid, rblk, 0, st, scratch, ksr, ntiles, TMT, row0, M, N, out); break;
     }
   }
+  return ksr > 1;
 }
 
 // Narrow matrices (few workgroup columns) without K shares: four weight tiles per workgroup and the rows cut into
@@ -1027,8 +1089,8 @@ static int rows_blocks_form(int ntiles, int ktiles, int M) {
   return 0;
 }
 
-// more than 16 rows from row 0 of the operand; out.nin.ssq, if set, is first reduced to per-row factors
-void bf16_gemm_rows(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N,
+// more than 16 rows from row 0 of the operand; returns how many partial sums of squares per row an EPI_ADD call left
+int bf16_gemm_rows(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N,
                     const GemmOut& out0, float* scratch, float* inv_rms, int inv_cap) {
   const uint4* Wc = (const uint4*)W;
   const uint4* Ac = (const uint4*)A;
@@ -1041,10 +1103,13 @@ void bf16_gemm_rows(hipStream_t st, int epi, const bf16_t* W, int ntiles, int kt
   const int parts = blocked ? ceil_div(M, max(512, inv_cap)) : ceil_div(M, 512);
   const int blk = ceil_div(ceil_div(M, parts), 16) * 16;
   if (M > blk) g_launch_events = nullptr;           // several launches: the caller's bracket times the call
+  int parts_left = ntiles;                          // (all row blocks of a call take the same form)
   for (int m0 = 0; m0 < M; m0 += blk) {
     const int mc = min(blk, M - m0);
     GemmOut out = out0;
-    if (out.nin.ssq) {
+    // Deferred norm factors: up to 192 rows every consumer sums the few partials of its own rows (see gemm_rows_reduce_kernel);
+    // beyond, too many workgroups would each read too many, and one launch reduces them to factors
+    if (out.nin.ssq && mc > 192) {
       hipLaunchKernelGGL(norm_factor_kernel, dim3(ceil_div(mc, 4)), dim3(256), 0, st, out.nin.ssq + m0, out.nin.n_part, out.nin.stride,
                          out.nin.inv_d, out.nin.eps, inv_rms, mc);
       out.nin.inv_rms = inv_rms;
@@ -1067,13 +1132,16 @@ void bf16_gemm_rows(hipStream_t st, int epi, const bf16_t* W, int ntiles, int kt
     if (bt == 16 && launch_gemm_rows_blocks<16, 2>(st, epi, Wc, ntiles, ktiles, Ac, m0, mc, N, out)) continue;
     if (bt == 104 && launch_gemm_rows_blocks<4, 4>(st, epi, Wc, ntiles, ktiles, Ac, m0, mc, N, out)) continue;
     if (bt == 108 && launch_gemm_rows_blocks<8, 4>(st, epi, Wc, ntiles, ktiles, Ac, m0, mc, N, out)) continue;
-    if (mc <= 64) launch_gemm_rows<4>(st, epi, Wc, ntiles, ktiles, Ac, m0, mc, N, out, scratch);
-    else if (mc <= 128) launch_gemm_rows<8>(st, epi, Wc, ntiles, ktiles, Ac, m0, mc, N, out, scratch);
-    else if (mc <= 192) launch_gemm_rows<12>(st, epi, Wc, ntiles, ktiles, Ac, m0, mc, N, out, scratch);
-    else if (mc <= 256) launch_gemm_rows<16>(st, epi, Wc, ntiles, ktiles, Ac, m0, mc, N, out, scratch);
-    else if (mc <= 384) launch_gemm_rows<24>(st, epi, Wc, ntiles, ktiles, Ac, m0, mc, N, out, scratch);
-    else launch_gemm_rows<32>(st, epi, Wc, ntiles, ktiles, Ac, m0, mc, N, out, scratch);
+    bool reduced;
+    if (mc <= 64) reduced = launch_gemm_rows<4>(st, epi, Wc, ntiles, ktiles, Ac, m0, mc, N, out, scratch);
+    else if (mc <= 128) reduced = launch_gemm_rows<8>(st, epi, Wc, ntiles, ktiles, Ac, m0, mc, N, out, scratch);
+    else if (mc <= 192) reduced = launch_gemm_rows<12>(st, epi, Wc, ntiles, ktiles, Ac, m0, mc, N, out, scratch);
+    else if (mc <= 256) reduced = launch_gemm_rows<16>(st, epi, Wc, ntiles, ktiles, Ac, m0, mc, N, out, scratch);
+    else if (mc <= 384) reduced = launch_gemm_rows<24>(st, epi, Wc, ntiles, ktiles, Ac, m0, mc, N, out, scratch);
+    else reduced = launch_gemm_rows<32>(st, epi, Wc, ntiles, ktiles, Ac, m0, mc, N, out, scratch);
+    if (reduced) parts_left = ceil_div(ntiles, EE_REDUCE_TASKS);
   }
+  return parts_left;
 }
 
 template <int MT, int U>

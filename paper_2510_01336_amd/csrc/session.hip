@@ -38,6 +38,7 @@ struct ee_session {
   int maxM = 0, Mp = 0, maxQT = 0;            // most rows of a pass (a context-build pass or a batch-wide call), padded to whole GEMM passes, most q-tiles
   int headM = 0, headMp = 0;                  // the same for an exit head (a context build sends it the rows that end a prompt)
   int ssq_stride = 0, inv_cap = 0;            // row stride of ssq, floats in inv_rms
+  int ssq_parts = 0;                          // partial sums of squares per row that the last down projection left
   char* base = nullptr;
   size_t bytes = 0;
   // device buffers (inside the caller's arena)
@@ -388,11 +389,13 @@ static void reset_accounting(ee_session* s) {
 // weights cross HBM once per call: up to 16 rows the skinny kernel, from 33 to 512 the row-tiled one, in
 // between the row-tiled one for matrices of 128 MB and more (measured: the small projections are quicker
 // without its K-share reduction pass); beyond 512 rows (wide matrices: 256) the blocked one
-static void gemm(ee_session* s, int epi, const MatLoc& ml, const bf16_t* A, int M, const GemmOut& o) {
+// returns the number of partial sums of squares per row that an EPI_ADD call with a next operand leaves
+static int gemm(ee_session* s, int epi, const MatLoc& ml, const bf16_t* A, int M, const GemmOut& o) {
   const bf16_t* W = (const bf16_t*)(s->m->base + ml.off);
   const bool big = (size_t)ml.ntiles() * ml.ktiles() * 1024 >= ((size_t)128 << 20);
-  if (M > (big ? 16 : 32)) bf16_gemm_rows(s->st, epi, W, ml.ntiles(), ml.ktiles(), A, M, ml.N, o, s->gemm_part, s->inv_rms, s->inv_cap);
-  else bf16_gemm(s->st, epi, W, ml.ntiles(), ml.ktiles(), A, M, ml.N, o);
+  if (M > (big ? 16 : 32)) return bf16_gemm_rows(s->st, epi, W, ml.ntiles(), ml.ktiles(), A, M, ml.N, o, s->gemm_part, s->inv_rms, s->inv_cap);
+  bf16_gemm(s->st, epi, W, ml.ntiles(), ml.ktiles(), A, M, ml.N, o);
+  return ml.ntiles();
 }
 
 // offset of the gain that normalises the hidden state behind layer l1: the adapter's own gain at an early exit
@@ -451,7 +454,7 @@ static void run_layers(ee_session* s, int l0, int l1, const CallPlan& p, const C
       // five launches per layer (six with the merge of a split attention); RMSNorm is deferred into the projections (see NormIn / NormOut)
       const int Mp = s->ssq_stride;
       NormIn nin;         // operand left by the previous EPI_ADD launch
-      nin.ssq = s->ssq; nin.n_part = d / 16; nin.stride = Mp; nin.inv_d = 1.0f / (float)d; nin.eps = c.rms_eps;
+      nin.ssq = s->ssq; nin.n_part = s->ssq_parts; nin.stride = Mp; nin.inv_d = 1.0f / (float)d; nin.eps = c.rms_eps;
       NormOut nout;
       nout.xn = (bf16_t*)s->XN; nout.ktiles = ceil_div(d, 32); nout.ssq = s->ssq; nout.stride = Mp;
       GemmOut o;
@@ -463,7 +466,7 @@ static void run_layers(ee_session* s, int l0, int l1, const CallPlan& p, const C
       KF(KF_ATTN, bf16_attention(st, attn, (const bf16_t*)s->Qb, (const bf16_t*)s->kv, mt, pos_add, s->B, p.max_m, p.total_qt,
                                  Hq, Hkv, D, l, s->n_pages, s->pps, scr, (bf16_t*)s->AO, L.o.ktiles()));
       o = GemmOut(); o.Y = s->X; o.ldy = d; o.nout = nout; o.nout.g = g2;
-      KF(KF_GEMM_O, gemm(s, EPI_ADD, L.o, (const bf16_t*)s->AO, M, o));
+      KF(KF_GEMM_O, nin.n_part = gemm(s, EPI_ADD, L.o, (const bf16_t*)s->AO, M, o));
       o = GemmOut(); o.H = (bf16_t*)s->H; o.h_ktiles = L.down.ktiles(); o.nin = nin;
       KF(KF_GEMM_GU, gemm(s, EPI_SWIGLU, L.gu, (const bf16_t*)s->XN, M, o));
       // the down projection leaves the operand of whatever reads the stream next: the next layer's QKV
@@ -471,7 +474,7 @@ static void run_layers(ee_session* s, int l0, int l1, const CallPlan& p, const C
       o = GemmOut(); o.Y = s->X; o.ldy = d; o.nout = nout;
       o.nout.g = l + 1 < l1 ? (const float*)(m->base + m->L[l + 1].g1) : (const float*)(m->base + closing_gain(m, l1));
       if (l + 1 == l1) { o.Y2 = sink.rows; o.y2_idx = sink.row_idx; o.y2_add = sink.add; }
-      KF(KF_GEMM_DOWN, gemm(s, EPI_ADD, L.down, (const bf16_t*)s->H, M, o));
+      KF(KF_GEMM_DOWN, s->ssq_parts = gemm(s, EPI_ADD, L.down, (const bf16_t*)s->H, M, o));
     } else {
       const float* Wqkv = (const float*)(m->base + L.qkv.off);
       const float* Wo = (const float*)(m->base + L.o.off);
@@ -511,7 +514,7 @@ static void exit_head(ee_session* s, int M, int which, int row0 = 0, const int* 
     const int Mp = s->ssq_stride;
     const bf16_t* operand = (const bf16_t*)s->XN + (size_t)row0 * ceil_div(d, 32) * 32;
     NormIn nin;
-    nin.ssq = s->ssq + row0; nin.n_part = d / 16; nin.stride = Mp; nin.inv_d = 1.0f / (float)d; nin.eps = c.rms_eps;
+    nin.ssq = s->ssq + row0; nin.n_part = s->ssq_parts; nin.stride = Mp; nin.inv_d = 1.0f / (float)d; nin.eps = c.rms_eps;
     if (aux) {
       // t = A n(x): rows into T (cleared: the epilogue adds to what it finds) and as the next operand TF;
       // z = x + B t: into a copy of the rows, leaving the shared head's operand XN = bf16(z * gfinal)
@@ -523,7 +526,7 @@ static void exit_head(ee_session* s, int M, int which, int row0 = 0, const int* 
       KF(KF_GEMM_HEAD, gemm(s, EPI_ADD, m->auxA[which], (const bf16_t*)s->XN, M, o));
       o = GemmOut(); o.Y = s->Z; o.ldy = d;
       o.nout.xn = (bf16_t*)s->XN; o.nout.ktiles = ceil_div(d, 32); o.nout.ssq = s->ssq; o.nout.stride = Mp; o.nout.g = gf;
-      KF(KF_GEMM_HEAD, gemm(s, EPI_ADD, m->auxB[which], (const bf16_t*)s->TF, M, o));
+      KF(KF_GEMM_HEAD, nin.n_part = gemm(s, EPI_ADD, m->auxB[which], (const bf16_t*)s->TF, M, o));
     }
     GemmOut o;
     if (ended) {
