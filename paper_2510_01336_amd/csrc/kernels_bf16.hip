@@ -1027,7 +1027,7 @@ static bool launch_gemm_rows_blocks(hipStream_t st, int epi, const uint4* W, int
 // random operands: gate/up at 4096 rows 705 us with 16 weight tiles, 798 with 12, 814 with 8; QKV at 2048 rows 106 / 95 /
 // 117; O 96 / 82 / 67; down 276 / 235 / 188).  Small blocks cost more per product but let narrow matrices fill the chip.
 struct BlockForm { int wt, step, ends; };
-static const BlockForm kBlockForms[3] = {{16, 74, 600}, {12, 68, 600}, {8, 41, 800}};
+static const BlockForm kBlockForms[3] = {{16, 74, 600}, {12, 62, 600}, {8, 41, 600}};
 constexpr int kCusPerXcd = 32;
 // Time of one launch by list scheduling of one XCD's blocks on its compute units (every XCD works on an equal run of
 // them, see the kernel); a partly filled row block costs its share of the MFMAs plus a third of a step.
