@@ -600,3 +600,43 @@ def test_fp32_projections_at_odd_widths_match_oracle(d, ffn, heads, vocab):
     rng = np.random.default_rng(8)
     _round(O, sess, k, 0.8, rng, True, tol)
     sess.close(); model.close()
+
+
+@pytest.mark.parametrize("heads,dim,k,ctx", [
+    ((8, 2), 64, 8, [1, 63, 64, 65]), ((8, 2), 64, 16, [447, 448, 449, 0, 512, 513]), ((8, 1), 128, 1, [575, 576, 577]),
+    ((8, 1), 128, 8, [832, 0, 130, 1]), ((8, 8), 64, 8, [700, 2500, 90, 2561, 2300, 0, 2496, 2559, 2560])],
+    ids=["one_page", "eight_pages", "nine_pages_d128", "ragged_d128", "split"])
+def test_few_rows_over_short_contexts_match_the_split_kernel(heads, dim, k, ctx):
+    """The attention of few rows over short contexts (a wave per page, one launch) against the ring kernel with its KV splits
+    and merge, on the same cache: contexts whose last position lies at, before and behind a page edge, fewer pages than waves
+    and more, several q-tiles, an idle slot (context 0) and a batch long and wide enough that this form is split too.  The
+    two sum a row's softmax in another order and agree to bf16 accuracy."""
+    import paper_2510_01336_amd as hs
+    cfg = bf16_small(n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=dim)
+    B, rows = len(ctx), k + 1
+    model = hs.Model(cfg, 91)
+    rng = np.random.default_rng(3)
+    drafts = rng.integers(0, cfg.vocab, (B, k)).astype(np.int32)
+    # ctx counts the positions behind the block: prompt, first token, drafts
+    prompts = [synth.gen_prompt(cfg.vocab, max(1, n - rows if n > rows else n), 40 + b) for b, n in enumerate(ctx)]
+    got = {}
+    try:
+        for form in (0, 4):                                     # 0: the form the call itself chooses
+            hs.ee_debug_attention_split_pages(4)
+            sess = hs.Session(model, B, max(ctx) + 4 * rows, B * (rows + 2))
+            sess.enable_logits(True)
+            for b, p in enumerate(prompts):
+                if ctx[b]:
+                    sess.prefill_seq(b, p)
+            sess.draft_inject(drafts)
+            hs.ee_debug_attention_split_pages(form)
+            a, _ = sess.verify_intermediate()
+            assert ((a >= 0) == (np.array(ctx) > 0)).all()
+            got[form] = sess.last_logits().astype(np.float64)
+            assert got[form].shape[0] == rows * sum(n > 0 for n in ctx)
+            sess.close()
+    finally:
+        hs.ee_debug_attention_split_pages(0)
+    assert np.isfinite(got[0]).all() and max_rel(got[0], got[4]) <= TOL["bf16"]
+    assert not np.array_equal(got[0], got[4])                   # (the forms differ, or the choice never left the ring kernel)
+    model.close()
