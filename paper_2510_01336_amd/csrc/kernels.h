@@ -83,22 +83,22 @@ struct GemmOut {
 void bf16_gemm(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N, const GemmOut& out);
 void bf16_gemm_cfg(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N,
                    const GemmOut& out, int nw, int ksplit, int U);
-// Row-tiled variant for more than 16 rows (rows start at row 0 of the operand; the kernels read whole row tiles up to the
-// next of 64, 128, 192, 256, 384, 512 rows, beyond 512 up to the next row tile, which the operand buffer must hold).
-// scratch: bf16_gemm_rows_scratch_floats() floats for this shape (may be null when that is 0); inv_rms: inv_cap (at least
-// 512) floats of scratch for the deferred RMSNorm factors; a call of more rows is cut into parts of that size.
 // Launch timing: while this points to a pair of events, the next skinny-GEMM launch attaches them to the dispatch
 // itself (hipExtLaunchKernelGGL), so that they hold the kernel's own start and end rather than the times at which
 // two marker packets around it were processed; the launcher sets `used`.
 struct LaunchEvents { hipEvent_t start, stop; bool used; };
 extern LaunchEvents* g_launch_events;
 extern int g_attn_pages_override;   // <= 0: pages per KV split chosen from the call's shape; else that many (test hook: batch and solo runs then cut their contexts alike)
-extern int g_rows_wide;              // 1: gate/up and exit head at 257..512 rows run sixteen weight tiles per workgroup in two row blocks; 0: eight in one
+extern int g_rows_wide;              // 1: gate/up and exit head beyond 256 rows run in blocks of 256 rows; 0: in passes of up to 512 rows (test hook)
 extern int g_rows_blocks_override;   // -1: built-in choice between K shares and row blocks; else 0, or row tiles per block (+100: eight weight tiles per workgroup)
 size_t bf16_gemm_rows_scratch_floats(int ntiles, int ktiles);
+// Row-tiled variant for more than 16 rows (rows start at row 0 of the operand; the kernels read whole row tiles up to the
+// next of 64, 128, 192, 256, 384, 512 rows, beyond 512 up to the next row tile, which the operand buffer must hold).
+// scratch: bf16_gemm_rows_scratch_floats() floats for this shape (may be null when that is 0); inv_rms: inv_cap (at least
+// 512) floats of scratch for the deferred RMSNorm factors; a call of more rows is cut into parts of that size.
 // Returns how many partial sums of squares per row an EPI_ADD call with nout left (n_part of the next NormIn).
 int bf16_gemm_rows(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N,
-                    const GemmOut& out, float* scratch, float* inv_rms, int inv_cap);
+                   const GemmOut& out, float* scratch, float* inv_rms, int inv_cap);
 // out row r (GEMM operand) <- RMSNorm of row idx[r] of X with gain g
 void bf16_rmsnorm(hipStream_t st, const float* X, const int* idx, const float* g, float eps, bf16_t* out, int ktiles, int M, int d);
 // Opens a pass over layers in one launch: row r of X <- embedding of tok[r] (emb set), rows[row_idx[r]] (rows set) or

@@ -1070,7 +1070,7 @@ static void launch_block(hipStream_t st, const uint4* W, int ntiles, int ktiles,
   g_launch_events = nullptr;
   launch_timed(ev, gemm_block_kernel<EPI, TN>, grid, blk, st, W, ktiles, ntiles, A, row0, M, N, out);
 }
-int g_rows_wide = 1;               // test and tuning hook: 0 keeps the one-block form for wide matrices
+int g_rows_wide = 1;               // test and tuning hook: 0 keeps wide matrices in passes of up to 512 rows
 
 // Form of the launch above for a call of M rows: row tiles per block, plus 100 with eight weight tiles per workgroup
 // (TN = 4) instead of four; 0: use the K-share kernel (wide matrices, and shapes where it measured faster).
@@ -1558,8 +1558,10 @@ __global__ __launch_bounds__(64 * EE_ATTN_WAVES) void attn_kernel(const uint4* _
 // global->LDS loads into two slots of two pages each; a step is one pair of pages, with one barrier, and requests the next
 // pair while it works.  The two parities of a q-tile meet in LDS at the end.  Nothing is split over workgroups, so a row's
 // result depends on its own sequence alone.  8B width: 2048 rows without a context 61 us a layer (136 in four 512-row passes of
-// the kernel above), the 4096-row passes of an 8190-token prompt 383 us on average, 720 TFLOP/s (695).  blockIdx.x is the KV head (with eight of them each XCD keeps one head's pages in its L2), the
-// blocks with the most pages come first.
+// the kernel above), the 4096-row passes of an 8190-token prompt 383 us on average, 720 TFLOP/s (695).  A step of two pages
+// takes about 6000 clocks against 2100-2400 each of MFMAs, vector arithmetic and LDS reads; the P.V product of the previous
+// page under this page's softmax inside each wave, as in the kernel above, only lengthened it (411 us).  blockIdx.x is the KV
+// head (with eight of them each XCD keeps one head's pages in its L2), the blocks with the most pages come first.
 // ---------------------------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(512) void attn_block_kernel(const uint4* __restrict__ Q, const bf16_t* __restrict__ kv, const int* seq_m,
@@ -1991,8 +1993,8 @@ static int ring_pages_per_split(const int* kv_end, const int* seq_m, int B, int 
 //         pages on average 26.9)
 // and neither quicker than the bytes at 6.5 TB/s.  Eight requests of ~1000 tokens, one row each: ring 16.9, tile 12.7; one
 // request, 500 tokens, 9 rows: 9.7 / 7.6; one request, 2048 tokens, 9 rows: 11.1 / 11.8.  The tile kernel never takes more
-// splits than the ring kernel would, so the scratch of a call does not grow, and has to promise 5 %.  A pinned split length (test hook) keeps every
-// call in the ring kernel, so that a sequence is cut alike alone and in a batch.
+// splits than the ring kernel would, so the scratch of a call does not grow, and has to promise 5 %.  A pinned split length
+// (test hook) keeps every call in the ring kernel, so that a sequence is cut alike alone and in a batch.
 AttnPlan bf16_attention_plan(const int* kv_end, const int* seq_m, int B, int Hq, int Hkv, int max_splits) {
   const int rep = Hq / Hkv;
   int max_pages = 1, max_qt = 0;
