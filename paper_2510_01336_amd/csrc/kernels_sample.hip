@@ -1,6 +1,7 @@
 // Rejection-sampling acceptance (App. G): exit distributions, the accept test and the draws.
 // All random numbers are inputs (uniform in [0, 1)); nothing here generates any.
 #include "kernels.h"
+#include "draw.h"
 
 #define EE_SAMPLE_THREADS 1024
 
@@ -58,7 +59,7 @@ __device__ inline float wave_scan(float v) {
   }
   return v;
 }
-// The draw: first token whose cumulative weight exceeds u * (sum of weights).  group: the weight of chunk group `lane` of this
+// The draw: first token with weight whose cumulative weight exceeds u * (sum of weights).  group: the weight of chunk group `lane` of this
 // wave, last: this thread's last token with weight (-1: none); weight(i) gives four consecutive weights.
 struct DrawShared { float tot[16]; int last[16]; int tok; };
 template <typename W>
@@ -80,24 +81,24 @@ __device__ inline int draw_token(const RowSpan& sp, float group, int last, float
     else pre += sh.tot[k];
   }
   if (h == w) {
-    const unsigned long long over = __ballot(pre + incl > target);
-    const int gl = over ? __ffsll((long long)over) - 1 : 63;
+    const unsigned long long over = __ballot(draw_admits_group(pre + incl, group, target)), held = __ballot(group > 0.f);
+    // (none: the wave's own sum passes the target but no group's prefix does -- its last group with weight)
+    const int gl = over ? __ffsll((long long)over) - 1 : 63 - __clzll((long long)held);
     float run = pre + (gl ? __shfl(incl, gl - 1, 64) : 0.f);
     int tok = -1, seen = -1;                            // (seen: the group's last token with weight, should rounding pass the target by)
     for (int c = 0; c < sp.per && tok < 0; ++c) {
       const int i = sp.i0 + (gl * sp.per + c) * 256 + 4 * lane;
       if (i - 4 * lane >= sp.i1) break;
       const float4 x = weight(i);
-      const float s0 = x.x, s1 = s0 + x.y, s2 = s1 + x.z, s3 = s2 + x.w;
-      const float inc = wave_scan(s3), base = run + (inc - s3);
-      const int k = base + s0 > target ? 0 : (base + s1 > target ? 1 : (base + s2 > target ? 2 : (base + s3 > target ? 3 : 4)));
+      const float s3 = ((x.x + x.y) + x.z) + x.w, inc = wave_scan(s3);
+      const int k = draw_among_four(run + (inc - s3), x, target);
       const unsigned long long hit = __ballot(k < 4);
       if (hit) {
         const int l = __ffsll((long long)hit) - 1;
         tok = __shfl(i + k, l, 64);
       }
-      const int mine = x.w > 0.f ? i + 3 : (x.z > 0.f ? i + 2 : (x.y > 0.f ? i + 1 : (x.x > 0.f ? i : -1)));
-      seen = max(seen, mine);
+      const int mine = draw_last_of_four(x);
+      if (mine >= 0) seen = i + mine;
       run += __shfl(inc, 63, 64);
     }
     for (int s = 1; s < 64; s <<= 1) seen = max(seen, __shfl_xor(seen, s, 64));

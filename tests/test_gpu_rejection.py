@@ -335,3 +335,103 @@ def test_rows_and_draws_at_the_edges_of_the_vocabulary_walk(vocab):
         for b, n in enumerate((9, 17)):
             sess.rollback(b, 0b111, n)
     sess.close(); model.close()
+
+
+def _lane_edges(w, want, rng):
+    """Uniform numbers whose target lies at the start of a lane whose first token weighs nothing, where the wave's scan puts
+    that start above everything the lanes before it reach: the sums of a residual draw (kernels_sample.hip) in float32."""
+    f = np.float32
+    vocab = len(w)
+    R = -(-vocab // 4096) * 256
+    x = np.zeros((16, R // 256, 64, 4), f)
+    x.reshape(-1)[:vocab] = w
+
+    def scan(v):
+        v = v.copy()
+        for s in (1, 2, 4, 8, 16, 32):
+            o = np.zeros_like(v)
+            o[..., s:] = v[..., :-s]
+            v = np.where(np.arange(64) >= s, v + o, v)
+        return v
+
+    def butterfly(v):
+        for s in (1, 2, 4, 8, 16, 32):
+            v = v + v[..., np.arange(64) ^ s]
+        return v[..., 0]
+
+    assert R // 256 <= 64                                       # one chunk per group
+    group = np.zeros((16, 64), f)
+    group[:, :R // 256] = butterfly((x[..., 0] + x[..., 1]) + (x[..., 2] + x[..., 3]))
+    incl = scan(group)
+    total = f(0)
+    pre = np.zeros(16, f)
+    for k in range(16):
+        pre[k] = total
+        total = f(total + incl[k, 63])
+    s3 = ((x[..., 0] + x[..., 1]) + x[..., 2]) + x[..., 3]
+    inc = scan(s3)
+    out = []
+    for wv, c in rng.permutation([(a, b) for a in range(16) for b in range(R // 256)]):
+        run = f(pre[wv] + (incl[wv, c - 1] if c else f(0)))
+        base = run + (inc[wv, c] - s3[wv, c])
+        reach = np.maximum.accumulate(base + s3[wv, c])
+        for l in range(1, 64):
+            if x[wv, c, l, 0] == 0 and s3[wv, c, l] > 0 and base[l] > reach[l - 1] >= run:
+                u = f(reach[l - 1] / total)
+                for _ in range(8):                              # the first number whose target is not below what was reached
+                    t = f(u * total)
+                    if reach[l - 1] <= t < base[l]:
+                        out.append(u)
+                        break
+                    u = np.nextafter(u, f(1) if t < reach[l - 1] else f(0))
+        if len(out) >= want:
+            break
+    return out[:want]
+
+
+@pytest.mark.parametrize("vocab", [32000, 128256])
+def test_residual_draws_at_lane_edges_return_weighted_tokens(vocab):
+    """Replacement draws with uniform numbers placed where the rounding of a wave's scan puts the start of a lane above the end
+    of the lane before it: the token drawn there must carry weight in max(0, p - q), and its interval must hold the number."""
+    import paper_2510_01336_amd as hs
+    cfg = synth.EEConfig(n_layers=3, d_model=32, n_q_heads=1, n_kv_heads=1, head_dim=32, d_ffn=32, vocab=vocab, exit_draft=1,
+                         exit_inter=2, dtype="f32", sigma=0.4)
+    B, k, tries = 4, 3, 6
+    model = hs.Model(cfg, 5)
+    sess = hs.Session(model, B, 64, 12)
+    sess.enable_sampling(); sess.enable_logits(True)
+    lens = [9, 17, 26, 40]
+    sess.prefill([synth.gen_prompt(vocab, n, n) for n in lens])
+    rng = np.random.default_rng(vocab)
+    u_a = np.full((B, k), np.nextafter(np.float32(1), np.float32(0)))          # every token with p < q is rejected
+    checked = 0
+    for rnd in range(4):
+        u_d = rng.random((B, k), np.float32)
+
+        def draw(u_r):
+            sess.draft_sample(k, u_d)
+            Pd = [sess.read_dist(0, b, 0, k) for b in range(B)]
+            a, nxt = sess.verify_intermediate_rs(u_a, np.asarray(u_r, np.float32))
+            Pt = sess.last_logits(B * (k + 1)).reshape(B, k + 1, vocab)
+            for b, n in enumerate(lens):
+                sess.rollback(b, 0b111, n)
+            w = [np.maximum(np.float32(0), Pt[b, a[b]] - Pd[b][a[b]]) if a[b] < k else None for b in range(B)]
+            return a.copy(), nxt.copy(), w
+
+        a, _, w = draw(np.full(B, 0.5))
+        edges = [_lane_edges(w[b], tries, rng) if w[b] is not None else [] for b in range(B)]
+        for i in range(max(len(e) for e in edges)):
+            u_r = [e[i] if i < len(e) else 0.5 for e in edges]
+            a2, nxt, w2 = draw(u_r)
+            assert np.array_equal(a2, a)
+            for b in range(B):
+                if i >= len(edges[b]):
+                    continue
+                assert np.array_equal(w2[b], w[b])
+                c, tok, at = np.cumsum(w[b].astype(np.float64)), int(nxt[b]), float(u_r[b])
+                assert w[b][tok] > 0, (rnd, b, tok, at)
+                # (partial sums of a dozen levels on both sides, 2^-24 each)
+                assert (c[tok - 1] if tok else 0.0) - 4e-6 * c[-1] <= at * c[-1] <= c[tok] + 4e-6 * c[-1], (rnd, b, tok, at)
+                checked += 1
+    assert checked >= 20, checked
+    sess.close(); model.close()
