@@ -66,20 +66,23 @@ __host__ __device__ inline size_t frag_offset(int r, int k, int ktiles) {
 //   V part: [dt=D/16][ks=2][lane][8] with d -> dt = d/16, lane row r = d%16,
 //                                          pos%64 -> lane group pos/16, ks = (pos%16)/8, element pos%8
 // (K serves as the A operand of S^T = K Q^T; V as the A operand of O^T = V^T P^T.)
+// A page holds whole tiles of 32 dimensions: heads of other sizes (EE_F32 models only) are padded to kv_page_dim(D), and
+// the padding keeps the zeros that the session's arena is created with.
 // ---------------------------------------------------------------------------------------------
+__host__ __device__ inline int kv_page_dim(int D) { return (D + 31) & ~31; }
 __host__ __device__ inline int k_page_off(int pos, int d, int D) {
   int t = (pos & 15) >> 2, r = ((pos >> 4) << 2) | (pos & 3);
   int s = d >> 5, g = (d & 31) >> 3, e = d & 7;
-  return ((t * (D >> 5) + s) * 64 + g * 16 + r) * 8 + e;
+  return ((t * (kv_page_dim(D) >> 5) + s) * 64 + g * 16 + r) * 8 + e;
 }
-__host__ __device__ inline int v_page_off(int pos, int d, int D) {
+__host__ __device__ inline int v_page_off(int pos, int d) {
   int dt = d >> 4, r = d & 15;
   int g = pos >> 4, ks = (pos & 15) >> 3, j = pos & 7;
   return ((dt * 2 + ks) * 64 + g * 16 + r) * 8 + j;
 }
 // element offset of the (layer, page, kv head) slab inside the KV arena; K first, then V
 __host__ __device__ inline size_t kv_slab(int layer, int page, int kvh, int n_pages, int n_kv, int D) {
-  return (((size_t)layer * n_pages + page) * n_kv + kvh) * (size_t)(2 * EE_PAGE * D);
+  return (((size_t)layer * n_pages + page) * n_kv + kvh) * (size_t)(2 * EE_PAGE * kv_page_dim(D));
 }
 
 // ---------------------------------------------------------------------------------------------

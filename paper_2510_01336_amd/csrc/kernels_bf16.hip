@@ -325,8 +325,8 @@ __device__ inline void epi_apply(const f32x4& acc0, const f32x4& acc1, float sc,
           const uint32_t wl[2] = {plo.x, plo.y}, wh[2] = {phi.x, phi.y};
 #pragma unroll
           for (int v = 0; v < 4; ++v) {
-            slab[v_page_off(pp, f + v, D)] = (bf16_t)(wl[v >> 1] >> (16 * (v & 1)));
-            slab[v_page_off(pp, f + half + v, D)] = (bf16_t)(wh[v >> 1] >> (16 * (v & 1)));
+            slab[v_page_off(pp, f + v)] = (bf16_t)(wl[v >> 1] >> (16 * (v & 1)));
+            slab[v_page_off(pp, f + half + v)] = (bf16_t)(wh[v >> 1] >> (16 * (v & 1)));
           }
         }
       }

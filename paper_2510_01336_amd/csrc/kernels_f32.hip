@@ -60,7 +60,7 @@ __global__ void fill_nan_dead_kv_kernel(void* kv, int bf16, const int* pages, in
     int pi = t % n_owned; int layer = layer0 + (int)(t / n_owned);
     if (pi * EE_PAGE + pp < len) continue;
     size_t slab = kv_slab(layer, pages[pi], kvh, n_pages, n_kv, D);
-    size_t ko = slab + k_page_off(pp, d, D), vo = slab + EE_PAGE * D + v_page_off(pp, d, D);
+    size_t ko = slab + k_page_off(pp, d, D), vo = slab + EE_PAGE * kv_page_dim(D) + v_page_off(pp, d);
     if (bf16) { ((bf16_t*)kv)[ko] = 0x7fc0; ((bf16_t*)kv)[vo] = 0x7fc0; }
     else { ((float*)kv)[ko] = __builtin_nanf(""); ((float*)kv)[vo] = __builtin_nanf(""); }
   }
@@ -78,7 +78,7 @@ __global__ void read_kv_kernel(const void* kv, int bf16, const int* pages, int l
   if (i >= n * n_kv * D) return;
   int d = i % D, kvh = (i / D) % n_kv, p = pos0 + i / (D * n_kv);
   size_t slab = kv_slab(layer, pages[p / EE_PAGE], kvh, n_pages, n_kv, D);
-  size_t ko = slab + k_page_off(p % EE_PAGE, d, D), vo = slab + EE_PAGE * D + v_page_off(p % EE_PAGE, d, D);
+  size_t ko = slab + k_page_off(p % EE_PAGE, d, D), vo = slab + EE_PAGE * kv_page_dim(D) + v_page_off(p % EE_PAGE, d);
   k_out[i] = bf16 ? bf16_to_f32(((const bf16_t*)kv)[ko]) : ((const float*)kv)[ko];
   v_out[i] = bf16 ? bf16_to_f32(((const bf16_t*)kv)[vo]) : ((const float*)kv)[vo];
 }
@@ -95,7 +95,7 @@ __global__ void write_kv_kernel(void* kv, int bf16, const int* pages, int layer,
   if (i >= n * n_kv * D) return;
   int d = i % D, kvh = (i / D) % n_kv, p = pos0 + i / (D * n_kv);
   size_t slab = kv_slab(layer, pages[p / EE_PAGE], kvh, n_pages, n_kv, D);
-  size_t ko = slab + k_page_off(p % EE_PAGE, d, D), vo = slab + EE_PAGE * D + v_page_off(p % EE_PAGE, d, D);
+  size_t ko = slab + k_page_off(p % EE_PAGE, d, D), vo = slab + EE_PAGE * kv_page_dim(D) + v_page_off(p % EE_PAGE, d);
   if (bf16) { ((bf16_t*)kv)[ko] = f32_to_bf16(k_in[i]); ((bf16_t*)kv)[vo] = f32_to_bf16(v_in[i]); }
   else { ((float*)kv)[ko] = k_in[i]; ((float*)kv)[vo] = v_in[i]; }
 }
@@ -321,9 +321,9 @@ __global__ __launch_bounds__(256) void f32_gemm_kernel(const float* __restrict__
       slab[k_page_off(pp, f, D)] = lo;
       slab[k_page_off(pp, f + half, D)] = hi;
     } else {
-      float* slab = out.kv + kv_slab(out.layer, page, h - out.Hq - out.Hkv, out.n_pages, out.Hkv, D) + EE_PAGE * D;
-      slab[v_page_off(pp, f, D)] = y0;
-      slab[v_page_off(pp, f + half, D)] = y1;
+      float* slab = out.kv + kv_slab(out.layer, page, h - out.Hq - out.Hkv, out.n_pages, out.Hkv, D) + EE_PAGE * kv_page_dim(D);
+      slab[v_page_off(pp, f)] = y0;
+      slab[v_page_off(pp, f + half)] = y1;
     }
   }
 }
@@ -360,48 +360,38 @@ void f32_qkv(hipStream_t st, const float* X, const float* g, float eps, const fl
 // One workgroup per (row, query head): scores over positions 0..pos in LDS, two-pass softmax.  Four neighbouring threads share a
 // position (each a quarter of the head's dimensions, eight at a time as the page stores them), and in the second product
 // the threads of a dimension share out the positions in runs of eight; at a few dozen positions both products are one short
-// chain (the one-thread-per-position form took 10 us at 37 positions).  W8: head_dim is a multiple of 32.
-template <bool W8>
+// chain (the one-thread-per-position form took 10 us at 37 positions).  A head whose size is no multiple of 32 is padded as in
+// the pages, with zeros on both sides.
 __global__ __launch_bounds__(256) void f32_attention_kernel(const float* __restrict__ Q, const float* __restrict__ kv, const int* row_seq, const int* row_pos,
                                      const int* block_table, int pos_add, int Hq, int Hkv, int D, int layer, int n_pages,
                                      int pps, float* __restrict__ out) {
   extern __shared__ float sm[];
-  float* q = sm;                       // [D]
-  float* red = sm + D;                 // [8]
-  float* part = sm + D + 8;            // [256]
-  float* sc = sm + D + 8 + 256;        // [n]
+  const int Dp = kv_page_dim(D);
+  float* q = sm;                       // [Dp]
+  float* red = sm + Dp;                // [8]
+  float* part = sm + Dp + 8;           // [256]
+  float* sc = sm + Dp + 8 + 256;       // [n]
   const int r = blockIdx.x, h = blockIdx.y, kvh = h / (Hq / Hkv);
   const int n = row_pos[r] + pos_add + 1;
   const int* bt = block_table + row_seq[r] * pps;
-  for (int d = threadIdx.x; d < D; d += blockDim.x) q[d] = Q[(size_t)r * Hq * D + h * D + d];
+  for (int d = threadIdx.x; d < Dp; d += blockDim.x) q[d] = d < D ? Q[(size_t)r * Hq * D + h * D + d] : 0.f;
   __syncthreads();
   const float scale = 1.0f / sqrtf((float)D);
   float mx = -INFINITY;
-  if (W8) {
-    const int quarter = threadIdx.x & 3;
-    for (int j = threadIdx.x >> 2; j < (n + 63) / 64 * 64; j += 64) {      // (whole waves: the quarters meet by shuffle)
-      const int jj = min(j, n - 1);
-      const float* slab = kv + kv_slab(layer, bt[jj / EE_PAGE], kvh, n_pages, Hkv, D);
-      float s = 0.f;
-      for (int d = quarter * 8; d < D; d += 32) {
-        const float4* k4 = (const float4*)(slab + k_page_off(jj % EE_PAGE, d, D));
-        const float4 a = k4[0], b = k4[1];
-        s += (q[d] * a.x + q[d + 1] * a.y + q[d + 2] * a.z + q[d + 3] * a.w) + (q[d + 4] * b.x + q[d + 5] * b.y + q[d + 6] * b.z + q[d + 7] * b.w);
-      }
-      s += __shfl_xor(s, 1, 64);
-      s += __shfl_xor(s, 2, 64);
-      s *= scale;
-      if (j < n) { if (quarter == 0) sc[j] = s; mx = fmaxf(mx, s); }
+  const int quarter = threadIdx.x & 3;
+  for (int j = threadIdx.x >> 2; j < (n + 63) / 64 * 64; j += 64) {        // (whole waves: the quarters meet by shuffle)
+    const int jj = min(j, n - 1);
+    const float* slab = kv + kv_slab(layer, bt[jj / EE_PAGE], kvh, n_pages, Hkv, D);
+    float s = 0.f;
+    for (int d = quarter * 8; d < Dp; d += 32) {
+      const float4* k4 = (const float4*)(slab + k_page_off(jj % EE_PAGE, d, D));
+      const float4 a = k4[0], b = k4[1];
+      s += (q[d] * a.x + q[d + 1] * a.y + q[d + 2] * a.z + q[d + 3] * a.w) + (q[d + 4] * b.x + q[d + 5] * b.y + q[d + 6] * b.z + q[d + 7] * b.w);
     }
-  } else {
-    for (int j = threadIdx.x; j < n; j += blockDim.x) {
-      const size_t slab = kv_slab(layer, bt[j / EE_PAGE], kvh, n_pages, Hkv, D);
-      float s = 0.f;
-      for (int d = 0; d < D; ++d) s += q[d] * kv[slab + k_page_off(j % EE_PAGE, d, D)];
-      s *= scale;
-      sc[j] = s;
-      mx = fmaxf(mx, s);
-    }
+    s += __shfl_xor(s, 1, 64);
+    s += __shfl_xor(s, 2, 64);
+    s *= scale;
+    if (j < n) { if (quarter == 0) sc[j] = s; mx = fmaxf(mx, s); }
   }
   for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_down(mx, o, 64));
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
@@ -419,7 +409,7 @@ __global__ __launch_bounds__(256) void f32_attention_kernel(const float* __restr
     float acc = 0.f;
     if (d < D && ph < phases)
       for (int j = ph * 8; j < n; j += phases * 8) {      // eight positions lie side by side in a page
-        const float* v = kv + kv_slab(layer, bt[j / EE_PAGE], kvh, n_pages, Hkv, D) + EE_PAGE * D + v_page_off(j % EE_PAGE, d, D);
+        const float* v = kv + kv_slab(layer, bt[j / EE_PAGE], kvh, n_pages, Hkv, D) + EE_PAGE * kv_page_dim(D) + v_page_off(j % EE_PAGE, d);
         if (j + 8 <= n) {
           const float4 a = ((const float4*)v)[0], b = ((const float4*)v)[1];
           acc += (sc[j] * a.x + sc[j + 1] * a.y + sc[j + 2] * a.z + sc[j + 3] * a.w) + (sc[j + 4] * b.x + sc[j + 5] * b.y + sc[j + 6] * b.z + sc[j + 7] * b.w);
@@ -438,13 +428,9 @@ __global__ __launch_bounds__(256) void f32_attention_kernel(const float* __restr
 }
 void f32_attention(hipStream_t st, const float* Q, const float* kv, const CallMeta& meta, int pos_add, int M, int Hq, int Hkv,
                    int D, int layer, int n_pages, int pages_per_seq, int max_ctx, float* out) {
-  const size_t smem = (size_t)(D + 8 + 256 + max_ctx) * sizeof(float);
-  if (D % 32 == 0)
-    hipLaunchKernelGGL((f32_attention_kernel<true>), dim3(M, Hq), dim3(256), smem, st, Q, kv, meta.row_seq, meta.row_pos,
-                       meta.block_table, pos_add, Hq, Hkv, D, layer, n_pages, pages_per_seq, out);
-  else
-    hipLaunchKernelGGL((f32_attention_kernel<false>), dim3(M, Hq), dim3(256), smem, st, Q, kv, meta.row_seq, meta.row_pos,
-                       meta.block_table, pos_add, Hq, Hkv, D, layer, n_pages, pages_per_seq, out);
+  const size_t smem = (size_t)(kv_page_dim(D) + 8 + 256 + max_ctx) * sizeof(float);
+  hipLaunchKernelGGL(f32_attention_kernel, dim3(M, Hq), dim3(256), smem, st, Q, kv, meta.row_seq, meta.row_pos, meta.block_table, pos_add,
+                     Hq, Hkv, D, layer, n_pages, pages_per_seq, out);
 }
 
 // arg max of each row; the lowest index wins ties.  Sixteen waves, eight values per thread in flight.

@@ -120,7 +120,7 @@ static size_t carve(ee_session* s, char* base) {
   Carver cv{base};
   const size_t es = bf ? 2 : 4;
   const int Mp = s->Mp;
-  s->kv = cv.take<char>((size_t)c.n_layers * s->n_pages * Hkv * 2 * EE_PAGE * D * es);
+  s->kv = cv.take<char>((size_t)c.n_layers * s->n_pages * Hkv * 2 * EE_PAGE * kv_page_dim(D) * es);
   s->X = cv.take<float>((size_t)s->maxM * d);
   s->XN = bf ? (void*)cv.take<bf16_t>((size_t)Mp * ceil_div(d, 32) * 32) : nullptr;
   s->Qb = bf ? (void*)cv.take<bf16_t>((size_t)Hkv * s->maxQT * 16 * D) : (void*)cv.take<float>((size_t)s->maxM * Hq * D);

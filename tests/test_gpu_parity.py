@@ -602,6 +602,28 @@ def test_fp32_projections_at_odd_widths_match_oracle(d, ffn, heads, vocab):
     sess.close(); model.close()
 
 
+@pytest.mark.parametrize("dim", [2, 16, 40, 48, 80, 254])
+def test_fp32_heads_of_any_even_size_match_oracle(dim):
+    """fp32 heads whose size is no multiple of the page's tiles of 32 dimensions (padded there): rounds against the oracle over
+    a page edge, and every cached K and V entry, with the dead ones poisoned."""
+    cfg = synth.EEConfig(n_layers=4, d_model=64, n_q_heads=4, n_kv_heads=2, head_dim=dim, d_ffn=96, vocab=300, exit_draft=1,
+                         exit_inter=2, dtype="f32", sigma=0.1, gamma=(1.0, 0.3, 0.3))
+    tol, k = TOL["f32"], 4
+    O, model, sess, first, gfirst = _setup(cfg, 5, [61, 130], 3 * (k + 1) + 2)
+    assert gfirst.tolist() == first.tolist()
+    rng = np.random.default_rng(8)
+    for do_full in (False, True, True):
+        for b in range(2):
+            sess.poison_dead_kv(b)
+        _round(O, sess, k, 0.8, rng, do_full, tol)
+    for b, s in enumerate(O.seqs):
+        for l in range(cfg.n_layers):
+            n = s.len[0 if l < 1 else (1 if l < 2 else 2)]
+            gk, gv = sess.read_kv(b, l, 0, n)
+            assert max_rel(gk, s.cache.K[l, :n]) <= tol and max_rel(gv, s.cache.V[l, :n]) <= tol, (b, l)
+    sess.close(); model.close()
+
+
 @pytest.mark.parametrize("heads,dim,k,ctx", [
     ((8, 2), 64, 8, [1, 63, 64, 65]), ((8, 2), 64, 16, [447, 448, 449, 0, 512, 513]), ((8, 1), 128, 1, [575, 576, 577]),
     ((8, 1), 128, 8, [832, 0, 130, 1]), ((8, 8), 64, 8, [700, 2500, 90, 2561, 2300, 0, 2496, 2559, 2560])],
