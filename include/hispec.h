@@ -118,14 +118,19 @@ void ee_model_free(ee_model* m);   /* frees host bookkeeping only; the arena is 
  *   max_ctx  : largest number of positions any one sequence may hold (incl. speculative rows)
  *   max_rows : largest number of rows one sequence contributes to one call, also the capacity
  *              of H_d / H_i / V per sequence (>= rounds_between_full_verifies*(k+1) + 1)
- *   total_pages : size of the shared page pool, 0 = batch * ceil(max_ctx/64)               */
+ *   total_pages : size of the shared page pool, 0 = batch * ceil(max_ctx/64)
+ * ee_session_bytes() counts the work buffers of context-build passes of up to 4096 rows (EE_BF16; no more than the
+ * sequences or the page pool can hold).  ee_session_create() also takes a smaller arena and then makes the passes
+ * shorter, in steps of 512 rows down to 512 (EE_ERR_CAPACITY below that).  A row of a pass costs about 70 KB at
+ * d_model 4096 / d_ffn 14336 and 140 KB at 8192 / 28672: passes of 512 rows need 0.25 and 0.5 GB less than passes of
+ * 4096; a long context build then takes up to half as long again.          */
 size_t ee_session_bytes(const ee_model* m, int batch, int max_ctx, int max_rows, int total_pages);
 int ee_session_create(ee_model* m, int batch, int max_ctx, int max_rows, int total_pages,
                       void* dev_arena, size_t arena_bytes, void* stream, ee_session** out);
 void ee_session_free(ee_session* s);
 
 /* Context build.  tokens: host, the prompts packed back to back; lens: host [batch], each >= 1.
- * Runs all L_f layers over every prompt in passes of up to 4096 rows (64 for EE_F32 models): a long prompt fills
+ * Runs all L_f layers over every prompt in passes of up to 4096 rows (64 for EE_F32 models; fewer in a small arena): a long prompt fills
  * passes by itself, short prompts share one; leaves all group lengths at
  * lens[b], and commits first_token[b] = arg max at L_f of the last prompt position
  * (the "Vanilla generation" step of Sec. 3.1).  first_token: host [batch]. */

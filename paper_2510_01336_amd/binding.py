@@ -481,9 +481,11 @@ class Model:
 class Session:
     """Owns the device arena of one session; methods forward to the C entry points."""
 
-    def __init__(self, model: Model, batch: int, max_ctx: int, max_rows: int, total_pages: int = 0):
+    def __init__(self, model: Model, batch: int, max_ctx: int, max_rows: int, total_pages: int = 0, arena_bytes: Optional[int] = None):
+        """arena_bytes: size of the device arena, default ee_session_bytes (a smaller one gets shorter context-build passes)."""
         self.model, self.batch, self.max_ctx, self.max_rows = model, batch, max_ctx, max_rows
-        self.nbytes = ee_session_bytes(model.handle, batch, max_ctx, max_rows, total_pages)
+        self.handle = None
+        self.nbytes = arena_bytes or ee_session_bytes(model.handle, batch, max_ctx, max_rows, total_pages)
         self._buf, ptr = _arena(self.nbytes)
         self.handle = ee_session_create(model.handle, batch, max_ctx, max_rows, total_pages, ptr, self.nbytes, model.stream)
 

@@ -60,7 +60,6 @@ struct ee_session {
   // models, the bf16 operand of the up projection), that operand's unused sum-of-squares partials, unit gains
   float *Z = nullptr, *T = nullptr, *ssq_t = nullptr, *ones = nullptr;
   void* TF = nullptr;
-  void* EN = nullptr;           // bf16: operand of the head over the rows that end a prompt [B rows]
   size_t part_units = 0;        // capacity of the attention split scratch in (q-tile, split) units per KV head
   int* pidx = nullptr;
   int max_splits = 64;
@@ -143,7 +142,7 @@ static size_t carve(ee_session* s, char* base) {
   s->rowinfo = cv.take<int4>((size_t)s->maxM);
   s->vtok = cv.take<int>(s->maxM);
   s->tok_next = cv.take<int>(s->maxM);
-  s->out_dev = cv.take<int>(s->B);                                    // (sampling: accept counts on their way to the draw)
+  s->out_dev = s->tok_next;                                           // (sampling: accept counts on their way to the draw; no drafting in that call)
   s->page_scratch = cv.take<int>(s->pps);
   if (bf) {
     // attention split scratch: all 64 splits for verify-sized calls (<= 64 rows), 8 at 512 rows and fewer for larger context-build passes
@@ -153,7 +152,6 @@ static size_t carve(ee_session* s, char* base) {
     s->part_ml = cv.take<float>(s->part_units * Hkv * 32);
     s->pmax = cv.take<float>((size_t)m->head.ntiles() * s->headMp);
     s->pidx = cv.take<int>((size_t)m->head.ntiles() * s->headMp);
-    s->EN = cv.take<bf16_t>((size_t)(s->B <= 64 ? 64 : ceil_div(s->B, 512) * 512) * ceil_div(d, 32) * 32);
     s->ssq = cv.take<float>((size_t)ceil_div(d, 16) * Mp);            // deferred-RMSNorm partials [d/16][Mp]
     size_t gp = 0;                                                    // K-share scratch of the row-tiled GEMM
     for (const MatLoc* ml : {&m->L[0].qkv, &m->L[0].o, &m->L[0].gu, &m->L[0].down, &m->head, &m->auxA[0], &m->auxB[0]})
@@ -162,12 +160,15 @@ static size_t carve(ee_session* s, char* base) {
     s->inv_rms = cv.take<float>(s->inv_cap);
   }
   s->slot[0].d = cv.take<int>(s->meta_cap);
-  s->slot[1].d = cv.take<int>(s->meta_cap);
+  s->slot[1].d = cv.take<int>(s->meta_cap - s->B * (s->max_rows + 1));     // (no uniform numbers there)
   (void)rep;
   return align_up(cv.cur, 256);
 }
 
-static int shape_session(ee_session* s, const ee_model* m, int batch, int max_ctx, int max_rows, int total_pages) {
+// most_rows: upper bound of the rows of a context-build pass (a multiple of 512; bf16).  At the least one no buffer is larger
+// than a session with passes of 512 rows ever needed: batch-wide calls of more rows then run their GEMMs in parts.
+static const int kMostPassRows = 4096, kLeastPassRows = 512;
+static int shape_session(ee_session* s, const ee_model* m, int batch, int max_ctx, int max_rows, int total_pages, int most_rows = kMostPassRows) {
   if (!m || batch < 1 || max_ctx < 2 || max_rows < 2) { ee_set_error("bad session shape"); return EE_ERR_ARG; }
   if (!m->bf16 && max_ctx > 8192) { ee_set_error("EE_F32 sessions support max_ctx <= 8192"); return EE_ERR_ARG; }
   const int rep = m->cfg.n_q_heads / m->cfg.n_kv_heads;
@@ -177,8 +178,9 @@ static int shape_session(ee_session* s, const ee_model* m, int batch, int max_ct
   s->pps = ceil_div(max_ctx, EE_PAGE);
   s->n_pages = total_pages > 0 ? total_pages : batch * s->pps;
   // context-build rows per pass: 4096 give the blocked GEMM whole rounds of 256 x 256 blocks (gate/up at the 8B width: 1365
-  // TFLOP/s against 1265 at 2048 rows and 1150 at 512); no more than the sequences can hold
-  s->chunk = m->bf16 ? std::min(4096, std::max(512, (int)std::min<long>(4096, ((long)batch * max_ctx + 511) / 512 * 512))) : 64;
+  // TFLOP/s against 1265 at 2048 rows and 1150 at 512); no more than the sequences and the page pool can hold
+  const long held = std::min((long)batch * max_ctx, (long)s->n_pages * EE_PAGE);
+  s->chunk = m->bf16 ? (int)std::max<long>(kLeastPassRows, std::min<long>(most_rows, (held + 511) / 512 * 512)) : 64;
   s->headM = std::max(batch * max_rows, m->bf16 ? 512 : 64);
   s->headMp = s->headM <= 64 ? 64 : ceil_div(s->headM, 512) * 512;
   s->maxM = std::max(batch * max_rows, s->chunk);
@@ -186,7 +188,7 @@ static int shape_session(ee_session* s, const ee_model* m, int batch, int max_ct
   s->Mp = s->maxM <= 64 ? 64 : ceil_div(s->maxM, 512) * 512;
   s->maxQT = ceil_div(s->maxM * rep, 16) + batch;
   s->ssq_stride = s->Mp;
-  s->inv_cap = std::max(512, s->maxM);
+  s->inv_cap = most_rows > kLeastPassRows ? std::max(512, s->maxM) : 512;
   layout_meta(s, s->maxM, s->maxQT, s->B * s->max_rows + s->B);   // (the largest block; every call lays out its own)
   s->meta_cap = s->meta_ints;
   return EE_OK;
@@ -206,7 +208,11 @@ extern "C" int ee_session_create(ee_model* m, int batch, int max_ctx, int max_ro
   if (rc != EE_OK) { delete s; return rc; }
   s->st = (hipStream_t)stream;
   s->base = (char*)dev_arena;
-  s->bytes = carve(s, s->base);
+  // an arena short of ee_session_bytes() gets shorter passes, as long as one of them fits
+  for (int most = kMostPassRows; (s->bytes = carve(s, s->base)) > arena_bytes && most > kLeastPassRows;) {
+    most = std::max(kLeastPassRows, s->chunk - 512);
+    shape_session(s, m, batch, max_ctx, max_rows, total_pages, most);
+  }
   if (arena_bytes < s->bytes) {
     ee_set_error("session arena too small: %zu < %zu", arena_bytes, s->bytes);
     delete s; return EE_ERR_CAPACITY;
@@ -530,8 +536,8 @@ static void exit_head(ee_session* s, int M, int which, int row0 = 0, const int* 
     }
     GemmOut o;
     if (ended) {
-      KF(KF_NORM, bf16_rmsnorm(st, s->X, ended, gf, c.rms_eps, (bf16_t*)s->EN, ceil_div(d, 32), M, d));
-      operand = (const bf16_t*)s->EN;
+      // (XN's first rows: the pass is over, and a piece that gets a head of its own lies behind the rows that end in front of it)
+      KF(KF_NORM, bf16_rmsnorm(st, s->X, ended, gf, c.rms_eps, (bf16_t*)s->XN, ceil_div(d, 32), M, d));
     } else {
       o.nin = nin;
     }

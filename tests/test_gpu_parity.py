@@ -587,6 +587,48 @@ def test_context_build_in_blocks_matches_the_512_row_passes(name, rows):
     sess.close(); model.close()
 
 
+# bytes of the session arenas of these shapes where a context-build pass never had more than 512 rows
+@pytest.mark.parametrize("batch,max_ctx,max_rows,nbytes", [(2, 3000, 20, 24127744), (64, 100, 12, 66178816)])
+def test_arena_of_512_row_passes_is_accepted(batch, max_ctx, max_rows, nbytes):
+    """An arena too small for passes of 4096 rows gets shorter ones: the context build of prompts that take several of them
+    (rows behind cached ones, prompts cut by a pass) against the build in passes of 4096, then a block of all rows at once
+    (more than 512 for the larger batch) and a vanilla step; an arena that holds no pass at all is refused."""
+    import paper_2510_01336_amd as hs
+    cfg = synth.EEConfig(n_layers=3, d_model=256, n_q_heads=8, n_kv_heads=2, head_dim=64, d_ffn=688, vocab=1000, exit_draft=1, exit_inter=2,
+                         dtype="bf16", sigma=0.05, gamma=(1.0, 0.2, 0.2))
+    model = hs.Model(cfg, 31)
+    assert hs.ee_session_bytes(model.handle, batch, max_ctx, max_rows, 0) > nbytes
+    rng = np.random.default_rng(2)
+    k = max_rows - 3
+    lens = [1500, 1190] if batch == 2 else [max_ctx - 2 * max_rows - 1 - b % 7 for b in range(batch)]
+    prompts = [synth.gen_prompt(cfg.vocab, n, 40 + b) for b, n in enumerate(lens)]
+    drafts = rng.integers(0, cfg.vocab, (batch, k)).astype(np.int32)
+    got = []
+    for size in (None, nbytes):
+        sess = hs.Session(model, batch, max_ctx, max_rows, arena_bytes=size)
+        sess.enable_logits(True)
+        first = sess.prefill(prompts)
+        last = sess.last_hidden()
+        sess.draft_inject(drafts)
+        sess.verify_intermediate()
+        block = sess.last_logits().astype(np.float64)
+        kv = [sess.read_kv(b, 0, 0, lens[b]) for b in (0, batch - 1)]
+        got.append((first, last, block, kv))
+        sess.close()
+    (f0, l0, b0, kv0), (f1, l1, b1, kv1) = got
+    assert len(l0) == len(l1) == (sum(lens) - 1) % 512 + 1
+    assert max_rel(l1, l0.astype(np.float64)) <= TOL["bf16"]
+    assert np.mean(f0 == f1) >= 0.9                       # (a near-tie may fall either way)
+    same = np.repeat(f0 == f1, k + 1)                     # the block starts with the first token
+    assert max_rel(b1[same], b0[same]) <= TOL["bf16"]
+    for (k0, v0), (k1, v1) in zip(kv0, kv1):
+        assert max_rel(k1, k0.astype(np.float64)) <= TOL["bf16"] and max_rel(v1, v0.astype(np.float64)) <= TOL["bf16"]
+    with pytest.raises(hs.EEError) as e:
+        hs.Session(model, batch, max_ctx, max_rows, arena_bytes=nbytes // 2)
+    assert e.value.code == -3 and "arena too small" in str(e.value)
+    model.close()
+
+
 @pytest.mark.parametrize("d,ffn,heads,vocab", [(66, 70, (2, 1), 130), (68, 41, (4, 2), 1001), (256, 100, (3, 3), 77)])
 def test_fp32_projections_at_odd_widths_match_oracle(d, ffn, heads, vocab):
     """The fused fp32 projections where their 16-byte loads do not apply (widths that are no multiple of four), at row counts
