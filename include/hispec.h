@@ -299,6 +299,11 @@ int ee_debug_kernel_times(ee_session* s, int32_t* n_families, const char** names
  * EE_ERR_ARG for any other value. */
 int ee_debug_gemm_row_blocks(int row_tiles);
 
+/* Test support, process-wide: 8, 12 or 16 runs every projection of more than 16 rows (32 for matrices under 128 MB) in
+ * blocks of 256 rows with that many 16-row weight tiles per workgroup (gate/up: 12 or 16, the exit head: 16), whatever
+ * its size; 0 restores the built-in choice.  The three give bit-identical results.  EE_ERR_ARG for any other value. */
+int ee_debug_gemm_block_tiles(int weight_tiles);
+
 /* Test support, process-wide: by default the attention kernel of a call (KV splits with a merge, a wave per page, or unsplit blocks
  * of 128 query rows) and the length of its KV splits follow the shape of the batch, and with them the order in which a
  * row's softmax partials are summed.  pages > 0 keeps every call in the splitting kernel and fixes the split length to that many 64-position pages for every call (raised where the split scratch would not

@@ -1071,6 +1071,7 @@ static void launch_block(hipStream_t st, const uint4* W, int ntiles, int ktiles,
   launch_timed(ev, gemm_block_kernel<EPI, TN>, grid, blk, st, W, ktiles, ntiles, A, row0, M, N, out);
 }
 int g_rows_wide = 1;               // test and tuning hook: 0 keeps wide matrices in passes of up to 512 rows
+int g_block_tiles = 0;             // test hook: > 0 runs every call of more than 16 rows blocked, with so many weight tiles per workgroup
 
 // Form of the launch above for a call of M rows: row tiles per block, plus 100 with eight weight tiles per workgroup
 // (TN = 4) instead of four; 0: use the K-share kernel (wide matrices, and shapes where it measured faster).
@@ -1098,7 +1099,7 @@ int bf16_gemm_rows(hipStream_t st, int epi, const bf16_t* W, int ntiles, int kti
   // Which calls run blocked: the wide matrices from 257 rows (as the one-launch forms below need two row blocks there, and
   // measured slower), the narrow ones from 513 (below that their own forms and K shares are quicker for O and QKV: 32 and
   // 43 us at 512 rows against 51 and 53).  The hooks that force another form keep the 512-row passes.
-  const bool blocked = wide ? g_rows_wide && M > 256 && ntiles >= 1536 : M > 512 && g_rows_blocks_override < 0;
+  const bool blocked = g_block_tiles > 0 || (wide ? g_rows_wide && M > 256 && ntiles >= 1536 : M > 512 && g_rows_blocks_override < 0);
   // else blocks of up to 512 rows, of equal size up to a row tile: calls beyond 512 rows stream the weights once per block
   const int parts = blocked ? ceil_div(M, max(512, inv_cap)) : ceil_div(M, 512);
   const int blk = ceil_div(ceil_div(M, parts), 16) * 16;
@@ -1108,14 +1109,16 @@ int bf16_gemm_rows(hipStream_t st, int epi, const bf16_t* W, int ntiles, int kti
     const int mc = min(blk, M - m0);
     GemmOut out = out0;
     // Deferred norm factors: up to 192 rows every consumer sums the few partials of its own rows (see gemm_rows_reduce_kernel);
-    // beyond, too many workgroups would each read too many, and one launch reduces them to factors
-    if (out.nin.ssq && mc > 192) {
+    // beyond, too many workgroups would each read too many, and one launch reduces them to factors.  The blocked kernel reads
+    // factors only, and a part of a blocked call may be as short as one row
+    if (out.nin.ssq && (mc > 192 || blocked)) {
       hipLaunchKernelGGL(norm_factor_kernel, dim3(ceil_div(mc, 4)), dim3(256), 0, st, out.nin.ssq + m0, out.nin.n_part, out.nin.stride,
                          out.nin.inv_d, out.nin.eps, inv_rms, mc);
       out.nin.inv_rms = inv_rms;
     }
     if (blocked) {
-      const int wt = choose_block(ntiles, ktiles, mc, epi == EPI_ARGMAX ? 1 : (epi == EPI_SWIGLU ? 3 : 7));
+      const int forms = epi == EPI_ARGMAX ? 1 : (epi == EPI_SWIGLU ? 3 : 7);
+      const int wt = g_block_tiles > 0 ? g_block_tiles : choose_block(ntiles, ktiles, mc, forms);
 #define BLOCK_LAUNCH(E_, TN_) launch_block<E_, TN_>(st, Wc, ntiles, ktiles, Ac, m0, mc, N, out)
       switch (epi) {
         case EPI_ARGMAX: BLOCK_LAUNCH(EPI_ARGMAX, 8); break;

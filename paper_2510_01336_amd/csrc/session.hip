@@ -1436,6 +1436,15 @@ extern "C" int ee_debug_gemm_row_blocks(int row_tiles) {
   return EE_OK;
 }
 
+extern "C" int ee_debug_gemm_block_tiles(int weight_tiles) {
+  if (weight_tiles != 0 && weight_tiles != 8 && weight_tiles != 12 && weight_tiles != 16) {
+    ee_set_error("weight_tiles must be 0, 8, 12 or 16");
+    return EE_ERR_ARG;
+  }
+  g_block_tiles = weight_tiles;
+  return EE_OK;
+}
+
 extern "C" int ee_debug_attention_split_pages(int pages) {
   if (pages < 0 || pages > 65536) { ee_set_error("pages per split must be 0 (built-in choice) or positive"); return EE_ERR_ARG; }
   g_attn_pages_override = pages;

@@ -101,6 +101,15 @@ def test_gemm_form_selector_checks_its_argument(lib):
     assert lib.ee_debug_gemm_row_blocks(-1) == 0
 
 
+def test_block_tile_selector_checks_its_argument(lib):
+    lib.ee_last_error.restype = ctypes.c_char_p
+    for ok in (8, 12, 16, 0):
+        assert lib.ee_debug_gemm_block_tiles(ok) == 0, ok
+    for bad in (-1, 4, 10, 32):
+        assert lib.ee_debug_gemm_block_tiles(bad) == -1 and b"weight_tiles" in lib.ee_last_error(), bad
+    assert lib.ee_debug_gemm_block_tiles(0) == 0
+
+
 def test_attention_split_selector_checks_its_argument(lib):
     lib.ee_last_error.restype = ctypes.c_char_p
     for ok in (2, 1, 17, 0):

@@ -587,6 +587,66 @@ def test_context_build_in_blocks_matches_the_512_row_passes(name, rows):
     sess.close(); model.close()
 
 
+_BLOCK_CFGS = {
+    # weight tiles: QKV 48, O / down 16, gate/up 1546 (96 * 16 + 10); down over 387 k-tiles
+    "long_k": lambda: bf16_small(d_ffn=12368, sigma=0.02),
+    # QKV 80, O / down 32, head 128
+    "d128": lambda: bf16_d128(),
+    # QKV 40, O / down 17 over 12 and 4 k-tiles (fewer than the stages of the ring), gate/up 14, head 1537; adapters of rank 32
+    "ragged": lambda: bf16_small(d_model=272, n_q_heads=6, d_ffn=100, vocab=24592, sigma=0.1, head_rank=32),
+}
+
+
+@pytest.mark.parametrize("rows", [40, 177, 256, 257, 497, 512, 785])
+@pytest.mark.parametrize("name", list(_BLOCK_CFGS))
+def test_blocked_gemm_in_every_form(name, rows):
+    """The blocked GEMM with 8, 12 and 16 weight tiles per workgroup, every epilogue in every form it is built with, at row
+    blocks that are full, partly filled and hold one row, groups of weight tiles that are not, and parts short enough for
+    norm factors to be left to the consumer elsewhere: the forms sum K in one order, so logits, hidden rows and cached K and V
+    are the same bits; against the row-tiled forms they agree to bf16 accuracy."""
+    import paper_2510_01336_amd as hs
+    cfg = _BLOCK_CFGS[name]()
+    model = hs.Model(cfg, 31)
+    k = 40 if rows < 300 else 8
+    lens = [rows - 17, 17]
+    drafts = np.random.default_rng(rows).integers(0, cfg.vocab, (2, k)).astype(np.int32)
+    for seed in range(12):
+        prompts = [synth.gen_prompt(cfg.vocab, n, 70 + seed + n) for n in lens]
+        got = {}
+        hs.ee_debug_attention_split_pages(4)
+        try:
+            for form in ("rows", 8, 12, 16):
+                hs.ee_debug_gemm_block_tiles(0 if form == "rows" else form)
+                if form == "rows":
+                    hs.ee_debug_gemm_row_blocks(0); hs.ee_debug_gemm_row_blocks(1000)
+                else:
+                    hs.ee_debug_gemm_row_blocks(-1)
+                sess = hs.Session(model, 2, rows + 2 * k + 40, 2 * k + 6)
+                sess.enable_logits(True)
+                first = sess.prefill(prompts)
+                out = [sess.last_logits(), sess.last_hidden()]
+                sess.draft_inject(drafts)
+                sess.verify_intermediate()
+                out += [sess.last_logits(), sess.last_hidden()]
+                for b in range(2):
+                    for l in range(cfg.n_layers):
+                        out += list(sess.read_kv(b, l, 0, lens[b]))
+                got[form] = (first, out)
+                sess.close()
+        finally:
+            hs.ee_debug_gemm_block_tiles(0); hs.ee_debug_gemm_row_blocks(-1); hs.ee_debug_attention_split_pages(0)
+        if np.array_equal(got["rows"][0], got[16][0]):         # (else a first token is a near-tie: another prompt)
+            break
+    else:
+        raise AssertionError("no prompt whose first tokens are decided clearly")
+    for form in (8, 12):
+        for i, (x, y) in enumerate(zip(got[form][1], got[16][1])):
+            assert np.array_equal(x, y), (form, i)
+    for i, (x, y) in enumerate(zip(got[16][1], got["rows"][1])):
+        assert np.isfinite(x).all() and max_rel(x, y.astype(np.float64)) <= TOL["bf16"], i
+    model.close()
+
+
 # bytes of the session arenas of these shapes where a context-build pass never had more than 512 rows
 @pytest.mark.parametrize("batch,max_ctx,max_rows,nbytes", [(2, 3000, 20, 24127744), (64, 100, 12, 66178816)])
 def test_arena_of_512_row_passes_is_accepted(batch, max_ctx, max_rows, nbytes):
