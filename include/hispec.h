@@ -312,6 +312,12 @@ int ee_debug_gemm_block_tiles(int weight_tiles);
  * choice.  EE_ERR_ARG for a negative value. */
 int ee_debug_attention_split_pages(int pages);
 
+/* Test support, process-wide: the attention kernel of every bf16 call -- 0 KV splits with a merge, 1 blocks of 128 query rows,
+ * 2 a wave per page (1 and 2 unsplit; all three serve any call) -- or -1, the built-in choice.  EE_ERR_ARG for any other
+ * value.  ee_debug_last_attention returns the one that the session's last pass took (-1 before the first and for fp32). */
+int ee_debug_attention_form(int form);
+int ee_debug_last_attention(const ee_session* s);
+
 /* Plain device-to-device streaming copy on `stream` (pointers and size multiples of 16 bytes; not
  * synchronised).  A kernel of exactly known traffic -- `bytes` read, `bytes` written -- used to
  * calibrate hardware byte counters when the HBM traffic of the other kernels is measured. */

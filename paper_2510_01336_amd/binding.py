@@ -18,7 +18,7 @@ __all__ = [
     "ee_verify_intermediate", "ee_verify_intermediate_static", "ee_verify_full", "ee_verify_level", "ee_n_levels", "kv_rollback", "ee_sampling_bytes", "ee_sampling_attach",
     "ee_draft_sample", "ee_verify_intermediate_rs", "ee_verify_full_rs", "ee_verify_level_rs", "ee_debug_read_dist", "ee_get_lengths", "ee_get_counts", "ee_get_tokens",
     "ee_debug_enable_logits", "ee_debug_last_logits", "ee_debug_last_hidden", "ee_debug_read_kv", "ee_debug_write_kv",
-    "ee_debug_poison_dead_kv", "ee_debug_time_kernels", "ee_debug_kernel_times", "ee_debug_gemm_row_blocks", "ee_debug_gemm_block_tiles", "ee_debug_attention_split_pages", "ee_debug_stream_copy", "ee_debug_read_floor", "ee_last_error",
+    "ee_debug_poison_dead_kv", "ee_debug_time_kernels", "ee_debug_kernel_times", "ee_debug_gemm_row_blocks", "ee_debug_gemm_block_tiles", "ee_debug_attention_split_pages", "ee_debug_attention_form", "ee_debug_last_attention", "ee_debug_stream_copy", "ee_debug_read_floor", "ee_last_error",
     "EE_F32", "EE_BF16", "TENSOR_IDS", "EXPORTED_SYMBOLS",
 ]
 
@@ -33,7 +33,7 @@ EXPORTED_SYMBOLS = [
     "ee_verify_intermediate", "ee_verify_intermediate_static", "ee_verify_full", "ee_verify_level", "ee_n_levels", "kv_rollback", "ee_sampling_bytes", "ee_sampling_attach",
     "ee_draft_sample", "ee_verify_intermediate_rs", "ee_verify_full_rs", "ee_verify_level_rs", "ee_debug_read_dist", "ee_get_lengths", "ee_get_counts", "ee_get_tokens",
     "ee_debug_enable_logits", "ee_debug_last_logits", "ee_debug_last_hidden", "ee_debug_read_kv", "ee_debug_write_kv",
-    "ee_debug_poison_dead_kv", "ee_debug_time_kernels", "ee_debug_kernel_times", "ee_debug_gemm_row_blocks", "ee_debug_gemm_block_tiles", "ee_debug_attention_split_pages", "ee_debug_stream_copy", "ee_debug_read_floor", "ee_last_error",
+    "ee_debug_poison_dead_kv", "ee_debug_time_kernels", "ee_debug_kernel_times", "ee_debug_gemm_row_blocks", "ee_debug_gemm_block_tiles", "ee_debug_attention_split_pages", "ee_debug_attention_form", "ee_debug_last_attention", "ee_debug_stream_copy", "ee_debug_read_floor", "ee_last_error",
 ]
 
 
@@ -107,6 +107,8 @@ def _load():
         "ee_debug_gemm_row_blocks": (C.c_int, [C.c_int]),
         "ee_debug_gemm_block_tiles": (C.c_int, [C.c_int]),
         "ee_debug_attention_split_pages": (C.c_int, [C.c_int]),
+        "ee_debug_attention_form": (C.c_int, [C.c_int]),
+        "ee_debug_last_attention": (C.c_int, [vp]),
         "ee_debug_kernel_times": (C.c_int, [vp, i32p, C.POINTER(C.c_char_p), f32p, i32p]),
         "ee_debug_stream_copy": (C.c_int, [vp, vp, C.c_size_t, vp]),
         "ee_debug_read_floor": (C.c_int, [vp, C.POINTER(C.c_size_t), C.c_int, C.c_int, C.POINTER(C.c_float), vp]),
@@ -425,6 +427,14 @@ def ee_debug_gemm_block_tiles(weight_tiles: int) -> None:
 
 def ee_debug_attention_split_pages(pages: int) -> None:
     _chk(lib.ee_debug_attention_split_pages(int(pages)))
+
+
+def ee_debug_attention_form(form: int) -> None:
+    _chk(lib.ee_debug_attention_form(form))
+
+
+def ee_debug_last_attention(session: int) -> int:
+    return lib.ee_debug_last_attention(session)
 
 
 def ee_debug_time_kernels(session: int, on: bool) -> None:

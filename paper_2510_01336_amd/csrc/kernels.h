@@ -89,6 +89,7 @@ void bf16_gemm_cfg(hipStream_t st, int epi, const bf16_t* W, int ntiles, int kti
 struct LaunchEvents { hipEvent_t start, stop; bool used; };
 extern LaunchEvents* g_launch_events;
 extern int g_attn_pages_override;   // <= 0: pages per KV split chosen from the call's shape; else that many (test hook: batch and solo runs then cut their contexts alike)
+extern int g_attn_form;              // -1: attention kernel chosen from the call's shape; else that one (ATTN_*) on every call (test hook)
 extern int g_rows_wide;              // 1: gate/up and exit head beyond 256 rows run in blocks of 256 rows; 0: in passes of up to 512 rows (test hook)
 extern int g_block_tiles;            // > 0: every call of more than 16 rows runs blocked with that many weight tiles per workgroup (test hook)
 extern int g_rows_blocks_override;   // -1: built-in choice between K shares and row blocks; else 0, or row tiles per block (+100: eight weight tiles per workgroup)

@@ -1078,6 +1078,7 @@ int g_block_tiles = 0;             // test hook: > 0 runs every call of more tha
 LaunchEvents* g_launch_events = nullptr;
 int g_rows_blocks_override = -1;   // test and tuning hook: >= 0 replaces the choice below
 int g_attn_pages_override = 0;
+int g_attn_form = -1;              // test hook: >= 0 forces that attention kernel (ATTN_*) on every call
 static int rows_blocks_form(int ntiles, int ktiles, int M) {
   if (g_rows_blocks_override >= 0) return g_rows_blocks_override;
   // measured on the 8B shapes (N 4096 and 6144): the blocks win for K <= 4096 from about 200 rows when columns x
@@ -2010,6 +2011,8 @@ AttnPlan bf16_attention_plan(const int* kv_end, const int* seq_m, int B, int Hq,
   }
   AttnPlan ring{ATTN_RING, ring_pages_per_split(kv_end, seq_m, B, rep, Hkv, max_pages, max_splits), 1};
   ring.nsplit = ceil_div(max_pages, ring.per);
+  if (g_attn_form == ATTN_RING) return ring;
+  if (g_attn_form > ATTN_RING) return AttnPlan{g_attn_form, max_pages, 1};      // (both serve any call unsplit)
   if (g_attn_pages_override > 0) return ring;
   if (ring.nsplit == 1 && max_qt > EE_ATTN_COMPUTE) return AttnPlan{ATTN_BLOCK, max_pages, 1};
   const float floor_us = pages * Hkv * (EE_PAGE * 128 * 4.0f) / 6.5e6f, merge_us = 5.8f;

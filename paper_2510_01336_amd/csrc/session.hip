@@ -71,6 +71,7 @@ struct ee_session {
   std::vector<int> free_pages;
   bool debug_logits = false, time_kernels = false;
   int last_rows = 0, last_row0 = 0;   // rows of X behind the last exit head
+  int last_attn = -1;                 // attention kernel of the last pass (ATTN_*; fp32: -1)
   std::vector<KTimer> timers;
   int launches[KF_COUNT] = {0};
   // meta layout (offsets in ints)
@@ -452,6 +453,7 @@ static void run_layers(ee_session* s, int l0, int l1, const CallPlan& p, const C
   }
   AttnScratch scr;
   const AttnPlan attn = attention_plan(s, p, pos_add, scr);
+  s->last_attn = m->bf16 ? attn.kind : -1;
   for (int l = l0; l < l1; ++l) {
     const LayerLoc& L = m->L[l];
     const float* g1 = (const float*)(m->base + L.g1);
@@ -1450,6 +1452,13 @@ extern "C" int ee_debug_attention_split_pages(int pages) {
   g_attn_pages_override = pages;
   return EE_OK;
 }
+
+extern "C" int ee_debug_attention_form(int form) {
+  if (form < -1 || form > ATTN_TILE) { ee_set_error("form must be -1 (built-in choice), 0, 1 or 2"); return EE_ERR_ARG; }
+  g_attn_form = form;
+  return EE_OK;
+}
+extern "C" int ee_debug_last_attention(const ee_session* s) { return s ? s->last_attn : -1; }
 
 extern "C" int ee_debug_time_kernels(ee_session* s, int on) {
   if (!s) { ee_set_error("null session"); return EE_ERR_ARG; }

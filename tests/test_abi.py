@@ -118,6 +118,15 @@ def test_attention_split_selector_checks_its_argument(lib):
     assert lib.ee_debug_attention_split_pages(0) == 0
 
 
+def test_attention_form_selector_checks_its_argument(lib):
+    lib.ee_last_error.restype = ctypes.c_char_p
+    for ok in (0, 1, 2, -1):
+        assert lib.ee_debug_attention_form(ok) == 0, ok
+    for bad in (-2, 3):
+        assert lib.ee_debug_attention_form(bad) == -1 and b"form" in lib.ee_last_error(), bad
+    assert lib.ee_debug_last_attention(None) == -1
+
+
 def test_read_floor_checks_its_arguments(lib):
     """Bad arguments are refused before any device call."""
     lib.ee_last_error.restype = ctypes.c_char_p

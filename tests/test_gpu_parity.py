@@ -553,10 +553,10 @@ def test_read_floor_times_plain_reads():
 @pytest.mark.parametrize("rows", [257, 512, 513, 767, 1025])
 @pytest.mark.parametrize("name", ["bf16_wide", "bf16_d128"])
 def test_context_build_in_blocks_matches_the_512_row_passes(name, rows):
-    """Context builds of more than 256 / 512 rows run the blocked GEMMs (256-row blocks, 16 / 12 / 8 weight tiles) and the
-    block attention; the hooks force the forms used up to there (K shares, one row block, split attention).  The rows around
-    the block edges, a ragged last block and matrices whose tiles do not fill the last group: both ways within the bf16 bound
-    of each other and the same first token, on a prompt whose last row clears the margin."""
+    """Context builds of more than 256 / 512 rows as the library runs them (blocked GEMMs, attention by the shape of the call)
+    against the forms that the hooks force (K shares, 512-row passes, KV splits of four pages): rows around the block edges
+    and a ragged last block, both ways within the bf16 bound of each other and the same first token, on a prompt whose last
+    row clears the margin."""
     import paper_2510_01336_amd as hs
     # 2 * d_ffn / 16 weight tiles: 1546 (the wide form's floor is 1536, 1546 = 96 * 16 + 10) with few k-tiles, or narrow only
     cfg = bf16_small(d_ffn=12368, sigma=0.02) if name == "bf16_wide" else bf16_d128()
@@ -724,6 +724,85 @@ def test_fp32_heads_of_any_even_size_match_oracle(dim):
             gk, gv = sess.read_kv(b, l, 0, n)
             assert max_rel(gk, s.cache.K[l, :n]) <= tol and max_rel(gv, s.cache.V[l, :n]) <= tol, (b, l)
     sess.close(); model.close()
+
+
+_ATTN_CASES = {
+    # contexts that end at, before and behind page edges: one page, an odd and an even number of them
+    "edges": (lambda: bf16_small(), [1, 63, 64, 65, 127, 128, 129, 193, 256], 8),
+    # eleven and eight pages, 41 block rows of four query heads per KV head: more than one block of 128 query rows behind a context
+    "rep4": (lambda: bf16_small(), [700, 449], 40),
+    "rep8_d128": (lambda: bf16_d128(), [577, 130], 24),
+    "rep1": (lambda: bf16_small(n_q_heads=4, n_kv_heads=4), [321, 64], 60),
+}
+
+
+def _compare_kv(O, sess, tol):
+    for b, s in enumerate(O.seqs):
+        for g in range(3):
+            for l in O.cfg.group_layers(g):
+                n = s.len[g]
+                gk, gv = sess.read_kv(b, l, 0, n)
+                assert max_rel(gk, s.cache.K[l, :n]) <= tol and max_rel(gv, s.cache.V[l, :n]) <= tol, (b, l)
+
+
+@pytest.mark.parametrize("name", list(_ATTN_CASES))
+@pytest.mark.parametrize("form", [0, 1, 2], ids=["split", "block", "tile"])
+def test_forced_attention_matches_oracle(form, name):
+    """Each attention kernel on every call of a context build and two rounds, against the oracle: hidden rows and logits of the
+    last rows, decisions, and all cached K and V (which carry the attention of every row of the layers below)."""
+    import paper_2510_01336_amd as hs
+    make, ctx, k = _ATTN_CASES[name]
+    cfg, tol = make(), TOL["bf16"]
+    hs.ee_debug_attention_form(form)
+    try:
+        O, model, sess, first, gfirst = _setup(cfg, 31, ctx, 3 * (k + 1) + 2)
+        assert hs.ee_debug_last_attention(sess.handle) == form
+        assert gfirst.tolist() == first.tolist()
+        assert max_rel(sess.last_logits()[-1:], O.o.last_logits) <= tol and max_rel(sess.last_hidden()[-1:], O.o.last_hidden) <= tol
+        _compare_kv(O, sess, tol)
+        rng = np.random.default_rng(4)
+        for _ in range(2):
+            for b in range(len(ctx)):
+                sess.poison_dead_kv(b)
+            _round(O, sess, k, 0.8, rng, True, tol)
+            assert hs.ee_debug_last_attention(sess.handle) == form
+        _compare_kv(O, sess, tol)
+        sess.close(); model.close()
+    finally:
+        hs.ee_debug_attention_form(-1)
+
+
+@pytest.mark.parametrize("form", [-1, 1], ids=["chosen", "block"])
+@pytest.mark.parametrize("make", [bf16_small, bf16_d128], ids=["d64", "d128"])
+def test_context_build_over_several_passes_matches_oracle(make, form):
+    """A context build whose later passes start behind cached positions (512-row passes, which the smallest arena gives): a
+    prompt cut by two pass ends and a short one that shares the last pass, against the oracle."""
+    import re
+
+    import paper_2510_01336_amd as hs
+    cfg, tol, lens = make(), TOL["bf16"], [1100, 37]
+    O = OracleSide(cfg, 31)
+    prompts = []
+    for b, n in enumerate(lens):
+        for attempt in range(20):
+            prompts.append(synth.gen_prompt(cfg.vocab, n, 100 + 1000 * attempt + b))
+            if O.prefill_one(prompts[-1], n + 64)[1] > MARGIN:
+                break
+            O.drop_last(); prompts.pop()
+    assert len(prompts) == 2
+    model = hs.Model(cfg, 31)
+    with pytest.raises(hs.EEError) as e:
+        hs.Session(model, 2, 1200, 12, arena_bytes=1 << 12)
+    least = int(re.search(r"< (\d+)", str(e.value)).group(1))
+    hs.ee_debug_attention_form(form)
+    try:
+        sess = hs.Session(model, 2, 1200, 12, arena_bytes=least)
+        assert sess.prefill(prompts).tolist() == [s.C[-1] for s in O.seqs]
+        assert form < 0 or hs.ee_debug_last_attention(sess.handle) == form
+        _compare_kv(O, sess, tol)
+        sess.close(); model.close()
+    finally:
+        hs.ee_debug_attention_form(-1)
 
 
 @pytest.mark.parametrize("heads,dim,k,ctx", [
