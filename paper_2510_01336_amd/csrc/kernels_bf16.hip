@@ -1091,23 +1091,43 @@ static int rows_blocks_form(int ntiles, int ktiles, int M) {
   return 0;
 }
 
+// Whether a call of M rows runs as blocked launches over all its rows, else in parts of 512 rows and the rest.
+//   wide matrices of 1536 and more weight tiles: from 257 rows (the row-tiled kernel needs two row blocks there, and measured
+//     slower); not where a third row block of up to 128 rows would cost most of a second round of workgroups (8B gate/up at
+//     520 / 608 / 640 rows: 164 / 169 / 170 us blocked, 146 / 150 / 154 as 512 rows and the rest; the 70B one, whose blocks
+//     fill more than two rounds anyway, 488 blocked, 542 in parts)
+//   narrow ones: from 513 rows where their blocks of 8 weight tiles fill the chip.  A long K (more k-tiles than weight tiles)
+//     on a part of the chip is quicker in K shares up to 1024 rows: down at 520 / 1024 rows, 8B 141 / 180 us blocked, 109 / 153
+//     in parts; 1B widths 83 / 90 and 58 / 83; 70B at 520 and 900 rows 349 / 395 and 300 / 426, the latter on 256 blocks.  Nor
+//     do a few rows beyond 512 pay for a third row block on less than half of the chip (8B O at 520 rows 51 us, 42 in parts).
+// The hooks that force another form keep the parts.
+static bool runs_blocked(bool wide, int ntiles, int ktiles, int M) {
+  if (g_block_tiles > 0) return true;
+  if (wide) return g_rows_wide && M > 256 && ntiles >= 1536 && !(M > 512 && M <= 640 && 3 * ceil_div(ntiles, 16) <= 512);
+  if (M <= 512 || g_rows_blocks_override >= 0) return false;
+  const int blocks = ceil_div(ntiles, 8) * ceil_div(M, 256);
+  return ktiles <= ntiles ? M > 544 || blocks >= 128 : M > 1024 || blocks >= 256;
+}
+
+// up to 16 rows the skinny kernel serves every matrix, up to 32 those under 128 MB (the small projections are quicker without
+// the K-share reduction pass of the row-tiled kernel)
+int bf16_gemm_few_rows(int ntiles, int ktiles) { return (size_t)ntiles * ktiles * 1024 >= ((size_t)128 << 20) ? 16 : 32; }
+
 // more than 16 rows from row 0 of the operand; returns how many partial sums of squares per row an EPI_ADD call left
 int bf16_gemm_rows(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N,
                     const GemmOut& out0, float* scratch, float* inv_rms, int inv_cap) {
   const uint4* Wc = (const uint4*)W;
   const uint4* Ac = (const uint4*)A;
   const bool wide = epi == EPI_SWIGLU || epi == EPI_ARGMAX;
-  // Which calls run blocked: the wide matrices from 257 rows (as the one-launch forms below need two row blocks there, and
-  // measured slower), the narrow ones from 513 (below that their own forms and K shares are quicker for O and QKV: 32 and
-  // 43 us at 512 rows against 51 and 53).  The hooks that force another form keep the 512-row passes.
-  const bool blocked = g_block_tiles > 0 || (wide ? g_rows_wide && M > 256 && ntiles >= 1536 : M > 512 && g_rows_blocks_override < 0);
-  // else blocks of up to 512 rows, of equal size up to a row tile: calls beyond 512 rows stream the weights once per block
-  const int parts = blocked ? ceil_div(M, max(512, inv_cap)) : ceil_div(M, 512);
-  const int blk = ceil_div(ceil_div(M, parts), 16) * 16;
+  const bool whole = runs_blocked(wide, ntiles, ktiles, M);
+  // parts: blocked as many rows as inv_rms has factors for; else 512 rows and the rest, each streaming the weights once (three
+  // parts of 400 rows cost what three of 512 do: gate/up of 1376 weight tiles at 1200 rows 417 us, 368 as 512 + 512 + 176)
+  const int blk = whole ? ceil_div(ceil_div(M, ceil_div(M, max(512, inv_cap))), 16) * 16 : 512;
   if (M > blk) g_launch_events = nullptr;           // several launches: the caller's bracket times the call
-  int parts_left = ntiles;                          // (all row blocks of a call take the same form)
+  int parts_left = ntiles;                          // (EPI_ADD: all parts of a call take the same form)
   for (int m0 = 0; m0 < M; m0 += blk) {
     const int mc = min(blk, M - m0);
+    const bool blocked = whole || (wide && runs_blocked(wide, ntiles, ktiles, mc));
     GemmOut out = out0;
     // Deferred norm factors: up to 192 rows every consumer sums the few partials of its own rows (see gemm_rows_reduce_kernel);
     // beyond, too many workgroups would each read too many, and one launch reduces them to factors.  The blocked kernel reads
@@ -1130,7 +1150,11 @@ int bf16_gemm_rows(hipStream_t st, int epi, const bf16_t* W, int ntiles, int kti
 #undef BLOCK_LAUNCH
       continue;
     }
-    const int bt = rows_blocks_form(ntiles, ktiles, mc);
+    const int bt = rows_blocks_form(ntiles, ktiles, epi == EPI_ADD ? min(M, blk) : mc);
+    if (m0 > 0 && mc <= bf16_gemm_few_rows(ntiles, ktiles) && (epi != EPI_ADD || bt > 0 || rows_ksplit(ntiles, ktiles) == 1)) {
+      bf16_gemm(st, epi, W, ntiles, ktiles, A, mc, N, out, m0);        // (as such a call by itself; leaves a partial sum per weight tile)
+      continue;
+    }
     if (bt == 4 && launch_gemm_rows_blocks<4, 2>(st, epi, Wc, ntiles, ktiles, Ac, m0, mc, N, out)) continue;
     if (bt == 8 && launch_gemm_rows_blocks<8, 2>(st, epi, Wc, ntiles, ktiles, Ac, m0, mc, N, out)) continue;
     if (bt == 16 && launch_gemm_rows_blocks<16, 2>(st, epi, Wc, ntiles, ktiles, Ac, m0, mc, N, out)) continue;
@@ -1178,12 +1202,12 @@ static void launch_gemm_mt(hipStream_t st, int epi, const uint4* W, int ntiles, 
 
 // launch shape: nw waves per workgroup, ksplit of them per task, k-tiles per register set U (4 or 8; 4 at 17..32 rows)
 void bf16_gemm_cfg(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N,
-                   const GemmOut& out, int nw, int ksplit, int U) {
+                   const GemmOut& out, int nw, int ksplit, int U, int row0) {
   const uint4* Wc = (const uint4*)W;
   const uint4* Ac = (const uint4*)A;
   // (the session sends calls of more than 32 rows to the row-tiled kernel; should one arrive here it goes in passes of 32)
-  for (int m0 = 0; m0 < M; m0 += 32) {
-    const int mc = min(32, M - m0);
+  for (int m0 = row0; m0 < row0 + M; m0 += 32) {
+    const int mc = min(32, row0 + M - m0);
     if (mc <= 16) {
       if (U >= 8) launch_gemm_mt<1, 8>(st, epi, Wc, ntiles, ktiles, Ac, m0, mc, N, out, nw, ksplit);
       else launch_gemm_mt<1, 4>(st, epi, Wc, ntiles, ktiles, Ac, m0, mc, N, out, nw, ksplit);
@@ -1196,14 +1220,14 @@ void bf16_gemm_cfg(hipStream_t st, int epi, const bf16_t* W, int ntiles, int kti
 // Launch shape by task count (measured on MI355X at M <= 16): many tasks -> one wave streams a whole
 // strip (no reduction, deepest pipeline); few tasks -> split K over the waves of a workgroup so that
 // one to two thousand waves are in flight (the 70B projections with 320-512 tasks: two waves per task).  M may exceed 32: rows then go in passes of 32 (weights re-streamed).
-void bf16_gemm(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N, const GemmOut& out) {
+void bf16_gemm(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N, const GemmOut& out, int row0) {
   const int ntasks = (epi == EPI_SWIGLU || epi == EPI_ROPE) ? ntiles / 2 : ntiles;
   // launch shape by task count, from sweeps over the 8B and 70B matrix shapes at 9 rows
   int ksplit = ntasks >= 768 ? 1 : (ntasks >= 320 ? 2 : (ntasks >= 200 ? 8 : 4));
   while (ksplit > 1 && ktiles / ksplit < 4) ksplit >>= 1;
   const int U = (ntasks >= 768 || ntasks < 200 || ktiles / ksplit >= 32) ? 8 : 4;
   const int nw = ksplit > 4 ? ksplit : 4;
-  bf16_gemm_cfg(st, epi, W, ntiles, ktiles, A, M, N, out, nw, ksplit, U);
+  bf16_gemm_cfg(st, epi, W, ntiles, ktiles, A, M, N, out, nw, ksplit, U, row0);
 }
 
 // one workgroup of 1024 threads per row; the row's partials lie side by side ([row][tile]), so a wave's load is one

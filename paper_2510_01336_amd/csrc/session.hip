@@ -393,14 +393,12 @@ static void reset_accounting(ee_session* s) {
 // ---------------------------------------------------------------------------------------------
 // forward pass pieces
 // ---------------------------------------------------------------------------------------------
-// weights cross HBM once per call: up to 16 rows the skinny kernel, from 33 to 512 the row-tiled one, in
-// between the row-tiled one for matrices of 128 MB and more (measured: the small projections are quicker
-// without its K-share reduction pass); beyond 512 rows (wide matrices: 256) the blocked one
+// the skinny kernel for few rows, the row-tiled one up to 512 (wide matrices: 256), beyond the blocked one or the row-tiled one
+// in parts (see runs_blocked)
 // returns the number of partial sums of squares per row that an EPI_ADD call with a next operand leaves
 static int gemm(ee_session* s, int epi, const MatLoc& ml, const bf16_t* A, int M, const GemmOut& o) {
   const bf16_t* W = (const bf16_t*)(s->m->base + ml.off);
-  const bool big = (size_t)ml.ntiles() * ml.ktiles() * 1024 >= ((size_t)128 << 20);
-  if (M > (big ? 16 : 32)) return bf16_gemm_rows(s->st, epi, W, ml.ntiles(), ml.ktiles(), A, M, ml.N, o, s->gemm_part, s->inv_rms, s->inv_cap);
+  if (M > bf16_gemm_few_rows(ml.ntiles(), ml.ktiles())) return bf16_gemm_rows(s->st, epi, W, ml.ntiles(), ml.ktiles(), A, M, ml.N, o, s->gemm_part, s->inv_rms, s->inv_cap);
   bf16_gemm(s->st, epi, W, ml.ntiles(), ml.ktiles(), A, M, ml.N, o);
   return ml.ntiles();
 }

@@ -647,6 +647,40 @@ def test_blocked_gemm_in_every_form(name, rows):
     model.close()
 
 
+@pytest.mark.parametrize("batch", [16, 17, 18, 20, 21, 32, 33])
+@pytest.mark.parametrize("name", list(_BLOCK_CFGS))
+def test_calls_beyond_512_rows_in_every_route(name, batch):
+    """Batch-wide calls of 512 to 1056 rows as the library runs them -- one blocked launch, or 512 rows and the rest, whose last
+    part holds 32 rows (skinny kernel), up to 128, and up to 512 (row-tiled forms, K shares) -- against the blocked kernel
+    throughout: the same block of drafts behind the same contexts, through the adapters and heads as well."""
+    import paper_2510_01336_amd as hs
+    cfg = _BLOCK_CFGS[name]()
+    model = hs.Model(cfg, 31)
+    k = 31
+    sess = hs.Session(model, batch, 60, k + 5)
+    sess.enable_logits(True)
+    sess.prefill([synth.gen_prompt(cfg.vocab, 5 + b % 3, b) for b in range(batch)])
+    drafts = np.random.default_rng(batch).integers(0, cfg.vocab, (batch, k)).astype(np.int32)
+    got = []
+    hs.ee_debug_attention_form(0)
+    try:
+        for tiles in (0, 16):
+            hs.ee_debug_gemm_block_tiles(tiles)
+            sess.draft_inject(drafts)
+            sess.verify_intermediate()
+            got.append([sess.last_logits(), sess.last_hidden()])
+            assert len(got[-1][0]) == 32 * batch
+            for b in range(batch):
+                sess.rollback(b, 0b111, 5 + b % 3)
+    finally:
+        hs.ee_debug_gemm_block_tiles(0); hs.ee_debug_attention_form(-1)
+    for x, y in zip(*got):
+        assert np.isfinite(x).all()
+        for r0 in range(0, 32 * batch, 32):                     # (sequence by sequence: no part hides behind the others' scale)
+            assert max_rel(x[r0:r0 + 32], y[r0:r0 + 32].astype(np.float64)) <= TOL["bf16"], r0
+    sess.close(); model.close()
+
+
 # bytes of the session arenas of these shapes where a context-build pass never had more than 512 rows
 @pytest.mark.parametrize("batch,max_ctx,max_rows,nbytes", [(2, 3000, 20, 24127744), (64, 100, 12, 66178816)])
 def test_arena_of_512_row_passes_is_accepted(batch, max_ctx, max_rows, nbytes):
