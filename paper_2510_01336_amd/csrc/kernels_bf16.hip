@@ -2013,8 +2013,12 @@ static int ring_pages_per_split(const int* kv_end, const int* seq_m, int B, int 
   return min(per, max_pages);
 }
 
-// Kernel and split length of a call.  Long blocks that fill the chip unsplit take attn_block_kernel; else the cheaper of the
-// ring kernel and the tile kernel by what they measured (8B head shapes, microseconds; a merge launch adds 5.8):
+// Kernel and split length of a call.  Long blocks that fill the chip unsplit take attn_block_kernel: in a context build
+// always (it stops at a block's last page; one page is quicker in the ring, 8.0 us against 9.8), behind a longer context
+// if it needs fewer rounds of workgroups -- it takes eight q-tiles where the ring takes six, for a quarter more a page (8B
+// heads, 32 sequences behind 1000 positions: 7 / 9 / 13 q-tiles ring 56 / 57 / 83 us in 2 / 2 / 3 rounds, block 44 / 70 / 71 in
+// 1 / 2 / 2; 8 behind 4000: 16 / 25 q-tiles ring 82 / 154, block 103 / 101).  Else the cheaper of the ring kernel and the tile
+// kernel by what they measured (8B head shapes, head_dim 128, microseconds; a merge launch adds 5.8):
 //   ring: 3 + 1.5 per page of a split                       (one sequence, 9 rows, 2 pages a split: 11.1 with the merge)
 //   tile: 3.9 + 0.52 per page a workgroup reads -- one compute unit takes in no more than about 60 GB/s; more workgroups than
 //         compute units take their sum over the chip and 30 % (2 pages 4.6, 8 pages 7.7, 16 pages 12.3; 384 workgroups of 16
@@ -2038,7 +2042,16 @@ AttnPlan bf16_attention_plan(const int* kv_end, const int* seq_m, int B, int Hq,
   if (g_attn_form == ATTN_RING) return ring;
   if (g_attn_form > ATTN_RING) return AttnPlan{g_attn_form, max_pages, 1};      // (both serve any call unsplit)
   if (g_attn_pages_override > 0) return ring;
-  if (ring.nsplit == 1 && max_qt > EE_ATTN_COMPUTE) return AttnPlan{ATTN_BLOCK, max_pages, 1};
+  if (ring.nsplit == 1 && max_qt > EE_ATTN_COMPUTE && max_pages > 1) {
+    long rows = 0, cached = 0, wg_ring = 0, wg_block = 0;
+    for (int b = 0; b < B; ++b) {
+      if (kv_end[b] <= 0) continue;
+      const int q = ceil_div(seq_m[b] * rep, 16);
+      rows += seq_m[b]; cached += kv_end[b] - seq_m[b];
+      wg_ring += (long)Hkv * ceil_div(q, EE_ATTN_COMPUTE); wg_block += (long)Hkv * ceil_div(q, 8);
+    }
+    if (rows >= cached || 4 * ((wg_ring + 255) / 256) >= 5 * ((wg_block + 255) / 256)) return AttnPlan{ATTN_BLOCK, max_pages, 1};
+  }
   const float floor_us = pages * Hkv * (EE_PAGE * 128 * 4.0f) / 6.5e6f, merge_us = 5.8f;
   float least = max(3.0f + 1.5f * ring.per, floor_us) + (ring.nsplit > 1 ? merge_us : 0.f);
   AttnPlan best = ring;

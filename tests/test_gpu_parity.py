@@ -806,6 +806,37 @@ def test_forced_attention_matches_oracle(form, name):
         hs.ee_debug_attention_form(-1)
 
 
+@pytest.mark.parametrize("batch,ctx,k,build,block", [
+    (1, 60, 4, False, False), (1, 120, 4, True, False),          # one page: the ring; two: blocks
+    (100, 600, 24, True, True), (100, 600, 32, True, False),     # 7 q-tiles: 2 rounds of the ring, 1 of blocks; 9: 2 and 2
+    (60, 600, 32, True, False)])                                 # 9 q-tiles in one round either way
+def test_blocks_are_chosen_where_they_need_fewer_rounds(batch, ctx, k, build, block):
+    """The rule between the ring kernel and the block kernel for calls that fill the chip unsplit, in a context build and behind
+    it, and the chosen form's results against the other one's."""
+    import paper_2510_01336_amd as hs
+    cfg = bf16_small()
+    model = hs.Model(cfg, 31)
+    sess = hs.Session(model, batch, ctx + k + 8, k + 6)
+    sess.enable_logits(True)
+    sess.prefill([synth.gen_prompt(cfg.vocab, ctx, b) for b in range(batch)])
+    assert (hs.ee_debug_last_attention(sess.handle) == 1) == build
+    drafts = np.random.default_rng(k).integers(0, cfg.vocab, (batch, k)).astype(np.int32)
+    got = []
+    try:
+        for form in (-1, 0 if block else 1):
+            hs.ee_debug_attention_form(form)
+            sess.draft_inject(drafts)
+            sess.verify_intermediate()
+            got.append((hs.ee_debug_last_attention(sess.handle), sess.last_logits()))
+            for b in range(batch):
+                sess.rollback(b, 0b111, ctx)
+    finally:
+        hs.ee_debug_attention_form(-1)
+    assert (got[0][0] == 1) == block
+    assert max_rel(got[0][1], got[1][1].astype(np.float64)) <= TOL["bf16"]
+    sess.close(); model.close()
+
+
 @pytest.mark.parametrize("form", [-1, 1], ids=["chosen", "block"])
 @pytest.mark.parametrize("make", [bf16_small, bf16_d128], ids=["d64", "d128"])
 def test_context_build_over_several_passes_matches_oracle(make, form):
