@@ -283,7 +283,8 @@ int ee_debug_write_kv(ee_session* s, int seq, int layer, int pos0, int n, const 
  * with NaN: a test that pruned entries can never leak into a later result. */
 int ee_debug_poison_dead_kv(ee_session* s, int seq);
 /* Per-kernel launch accounting of the most recent draft/verify call: number of kernel launches
- * and, when enabled with ee_debug_time_kernels, HIP-event time (ms) per kernel family.        */
+ * and, when enabled with ee_debug_time_kernels, HIP-event time (ms) per kernel family.  Three families have no launch
+ * of their own and report 0: rope_append (in gemm_qkv), attn_combine (in attention) and copy_rows.       */
 int ee_debug_time_kernels(ee_session* s, int on);
 int ee_debug_kernel_times(ee_session* s, int32_t* n_families, const char** names /*[16]*/,
                           float* ms /*[16]*/, int32_t* launches /*[16]*/);

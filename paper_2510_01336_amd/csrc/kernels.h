@@ -3,8 +3,6 @@
 #include "common.h"
 
 // ---- dtype-independent ---------------------------------------------------------------------
-// dst[dst_idx[r]][:] = src[src_idx[r]][:]   (null index = identity)
-void k_copy_rows(hipStream_t st, float* dst, const int* dst_idx, int dst_add, const float* src, const int* src_idx, int M, int d);
 // per sequence: a = number of leading j < n_cand[b] with cand[b][j] == v[row0[b]+j];
 // next = v[row0+a] if a < m[b] else -1.  Sequences with m[b] == 0 report (-1, -1).
 void k_accept(hipStream_t st, const int* v, const CallMeta& meta, int cand_stride, int B, int* n_accept, int* next_tok);

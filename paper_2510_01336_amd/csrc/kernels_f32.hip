@@ -14,15 +14,6 @@ __device__ inline float wave_sum(float v) {
   return v;
 }
 
-__global__ void copy_rows_kernel(float* dst, const int* dst_idx, int dst_add, const float* src, const int* src_idx, int d) {
-  int r = blockIdx.x;
-  size_t so = (size_t)(src_idx ? src_idx[r] : r) * d, dof = (size_t)((dst_idx ? dst_idx[r] : r) + dst_add) * d;
-  for (int c = threadIdx.x; c < d; c += blockDim.x) dst[dof + c] = src[so + c];
-}
-void k_copy_rows(hipStream_t st, float* dst, const int* dst_idx, int dst_add, const float* src, const int* src_idx, int M, int d) {
-  hipLaunchKernelGGL(copy_rows_kernel, dim3(M), dim3(256), 0, st, dst, dst_idx, dst_add, src, src_idx, d);
-}
-
 // LeadingSubstringVerify (last function of Algorithms 1/2) given the verifier's arg-max tokens:
 // one wavefront per sequence, ballot over mismatches, count of leading matches.
 __global__ void accept_kernel(const int* v, const int* seq_row0, const int* seq_m, const int* cand, const int* n_cand,

@@ -294,7 +294,7 @@ static int check_capacity(ee_session* s, const std::vector<int>& want_positions)
 // per-call metadata
 // ---------------------------------------------------------------------------------------------
 struct CallPlan {
-  int M = 0, n_active = 0, max_m = 0, total_qt = 0, max_kv_end = 0;
+  int M = 0, max_m = 0, total_qt = 0;
   std::vector<int> m, p0;        // per sequence rows and first position (m = 0: not taking part)
 };
 
@@ -321,13 +321,13 @@ static int build_meta(ee_session* s, int si, CallPlan& p, RowFn row_fn, int unif
   if (row > s->maxM || qt > s->maxQT) { ee_set_error("internal: call exceeds work buffers (%d rows)", row); return EE_ERR_CAPACITY; }
   layout_meta(s, row, qt, uniforms);
   row = qt = 0;
-  p.M = 0; p.n_active = 0; p.max_m = 0; p.max_kv_end = 0;
+  p.max_m = 0;
   for (int b = 0; b < s->B; ++b) {
     int m = p.m[b];
     h[s->o_seq_row0 + b] = row; h[s->o_seq_m + b] = m; h[s->o_seq_p0 + b] = p.p0[b]; h[s->o_seq_qt0 + b] = qt;
     h[s->o_n_cand + b] = 0;
     if (m == 0) continue;
-    p.n_active++; p.max_m = std::max(p.max_m, m); p.max_kv_end = std::max(p.max_kv_end, p.p0[b] + m);
+    p.max_m = std::max(p.max_m, m);
     for (int r = 0; r < m; ++r, ++row) {
       h[s->o_row_seq + row] = b; h[s->o_row_pos + row] = p.p0[b] + r;
       int tok = 0, src = 0, dst = 0;
