@@ -95,7 +95,7 @@ extern int g_block_tiles;            // > 0: every call of more than 16 rows run
 extern int g_rows_blocks_override;   // -1: built-in choice between K shares and row blocks; else 0, or row tiles per block (+100: eight weight tiles per workgroup)
 size_t bf16_gemm_rows_scratch_floats(int ntiles, int ktiles);
 // Row-tiled variant for more than 16 rows (rows start at row 0 of the operand; the kernels read whole row tiles up to the
-// next of 64, 128, 192, 256, 384, 512 rows, beyond 512 up to the next row tile, which the operand buffer must hold).
+// next of 64, 128, 192, 256, 384, 512 rows, beyond 512 up to whole parts of 512, which the operand buffer must hold).
 // scratch: bf16_gemm_rows_scratch_floats() floats for this shape (may be null when that is 0); inv_rms: inv_cap (at least
 // 512) floats of scratch for the deferred RMSNorm factors; a call of more rows is cut into parts of that size.
 // Returns how many partial sums of squares per row an EPI_ADD call with nout left (n_part of the next NormIn).

@@ -741,12 +741,14 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
 // all blocks.  blockIdx.x enumerates them so that every XCD (workgroup id mod 8) works on consecutive ones, row blocks
 // fastest: the row blocks of a weight group run side by side and read its weights from one L2.
 // What bounds it: with sixteen weight tiles a k-tile is 1024 clocks of MFMAs per SIMD, 128 KiB of LDS traffic (1000 clocks)
-// and 32 KiB of requests, and the clock gives way under that load: 1365 TFLOP/s on the gate/up matrix at 4096 rows (705 us;
-// passes of 512 rows in the previous form 812 us), 1265 at 2048 rows.  Narrow matrices take 12 or 8 weight tiles so that the
-// blocks of a pass fill the chip without K shares: QKV at 2048 rows 95 us (four passes of 512 rows 174), O 67 (127), down
-// 188 (300).
-// K is never shared out: a row's sums run over K in one order in every form and for every row count, so its result does
-// not depend on the rows beside it (K shares of the down projection would gain 154 -> 127 us at 1096 rows, nothing from 2048).
+// and 32 KiB of requests, and the clock gives way under that load: 1361 TFLOP/s on the gate/up matrix at 4096 rows (707 us;
+// passes of 512 rows in the previous form 812 us), 1212-1245 at 2048 rows (386-397 us).  Narrow matrices take 12 or 8 weight tiles so that the
+// blocks of a pass fill the chip without K shares: QKV at 2048 rows 98 us (four passes of 512 rows 174), O 70 (127), down
+// 204 (300).
+// K is never shared out: among calls that run blocked a row's sums run over K in one order, whatever the form and the row
+// count.  (Between kernels they do not: skinny, row-tiled and K-share sums differ in order, and the row count decides which
+// kernel a call gets.)  K shares of the down projection measured 127 us against 154 at 1096 rows, nothing from 2048; shares
+// whose number follows the row count moved the full-depth comparison of a batch with its sequences alone past its bound.
 // ---------------------------------------------------------------------------------------------
 template <int EPI, int TN, bool FULL>
 __device__ __forceinline__ void gemm_block_body(u32x4* ring, const uint4* __restrict__ W, int ktiles, int ntiles, const uint4* __restrict__ A,
@@ -1584,9 +1586,9 @@ __global__ __launch_bounds__(64 * EE_ATTN_WAVES) void attn_kernel(const uint4* _
 // reads per product (32 KiB of fragments serve 68 MFMAs; the kernel above, one q-tile per wave, is bound by those reads), and
 // the two waves of a SIMD, one of each parity, run one's vector arithmetic under the other's MFMAs.  Pages reach LDS by direct
 // global->LDS loads into two slots of two pages each; a step is one pair of pages, with one barrier, and requests the next
-// pair while it works.  The two parities of a q-tile meet in LDS at the end.  Nothing is split over workgroups, so a row's
-// result depends on its own sequence alone.  8B width: 2048 rows without a context 61 us a layer (136 in four 512-row passes of
-// the kernel above), the 4096-row passes of an 8190-token prompt 383 us on average, 720 TFLOP/s (695).  A step of two pages
+// pair while it works.  The two parities of a q-tile meet in LDS at the end.  Nothing is split over workgroups, so where this
+// kernel runs a row's result depends on its own sequence alone (the batch decides whether it runs).  8B width: 2048 rows without a context 61-62 us a layer (136 in four 512-row passes of
+// the kernel above), the 4096-row passes of an 8190-token prompt 385 us on average, 714 TFLOP/s (695 us).  A step of two pages
 // takes about 6000 clocks against 2100-2400 each of MFMAs, vector arithmetic and LDS reads; the P.V product of the previous
 // page under this page's softmax inside each wave, as in the kernel above, only lengthened it (411 us).  blockIdx.x is the KV
 // head (with eight of them each XCD keeps one head's pages in its L2), the blocks with the most pages come first.
