@@ -293,10 +293,10 @@ int ee_debug_kernel_times(ee_session* s, int32_t* n_families, const char** names
  * projections (O, down, QKV, adapters) either with K shares and a reduction pass or with blocks of row_tiles*16
  * rows and no K shares; row_tiles = 4, 8 or 16 forces the second form for every such call (104 and 108: blocks of 4
  * and 8 row tiles with eight instead of four weight tiles per workgroup), 0 the first, -1 restores the built-in
- * choice.  Values >= 0 also keep the narrow projections of calls beyond 512 rows in passes of up to 512 rows of those
- * forms, which otherwise run in blocks of 256 rows over the whole call.  Two more values choose the form of the wide
- * projections (gate/up, exit head) beyond 256 rows: 1016 (the default) blocks of 256 rows, 1000 passes of up to 512
- * rows with eight weight tiles per workgroup.  Results of all forms agree to rounding order.
+ * choice.  Values >= 0 also keep the narrow projections of calls beyond 512 rows in parts of 512 rows and the rest in
+ * those forms; otherwise such calls run in blocks of 256 rows over the whole call where that is quicker.  Two more
+ * values choose the form of the wide projections (gate/up, exit head) beyond 256 rows: 1016 (the default) blocks of 256
+ * rows where they are quicker, 1000 parts of up to 512 rows with eight weight tiles per workgroup.  Results of all forms agree to rounding order.
  * EE_ERR_ARG for any other value. */
 int ee_debug_gemm_row_blocks(int row_tiles);
 
@@ -305,10 +305,11 @@ int ee_debug_gemm_row_blocks(int row_tiles);
  * its size; 0 restores the built-in choice.  The three give bit-identical results.  EE_ERR_ARG for any other value. */
 int ee_debug_gemm_block_tiles(int weight_tiles);
 
-/* Test support, process-wide: by default the attention kernel of a call (KV splits with a merge, a wave per page, or unsplit blocks
- * of 128 query rows) and the length of its KV splits follow the shape of the batch, and with them the order in which a
- * row's softmax partials are summed.  pages > 0 keeps every call in the splitting kernel and fixes the split length to that many 64-position pages for every call (raised where the split scratch would not
- * hold the count), so that a sequence is cut alike whether it runs alone or in a batch and the batched-inference
+/* Test support, process-wide: by default the attention kernel of a call (KV splits with a merge, a wave per page, or
+ * unsplit blocks of 128 query rows) and the length of its KV splits follow the shape of the batch, and with them the
+ * order in which a row's softmax partials are summed.  pages > 0 keeps every call in the splitting kernel and fixes the
+ * split length to that many 64-position pages for every call (raised where the split scratch would not hold the
+ * count), so that a sequence is cut alike whether it runs alone or in a batch and the batched-inference
  * claim (a sequence's results do not depend on its neighbours) can be checked bit for bit; 0 restores the built-in
  * choice.  EE_ERR_ARG for a negative value. */
 int ee_debug_attention_split_pages(int pages);
