@@ -98,7 +98,7 @@ struct MatLoc {          // one (possibly fused) weight matrix inside the model 
 
 struct LayerLoc {
   size_t g1 = 0, g2 = 0;     // fp32 gains [d]
-  MatLoc qkv, o, gu, down;   // gu: gate/up interleaved in 16-row tiles (gate tile j, up tile j, ...)
+  MatLoc qkv, o, gu, down;   // gu: gate and up interleaved (see phys_row)
 };
 
 #define EE_MAX_GROUPS 7        // L_d, L_i, up to four further verifier exits, L_f: at most seven layer groups
@@ -126,7 +126,7 @@ struct TensorMap {
   int rows, cols;
   size_t off;      // byte offset of matrix / vector / embedding
   int row_off;     // first physical row (fused QKV)
-  int interleave;  // 0 none, 1 gate (tiles 2j), 2 up (tiles 2j+1), 3 rotary halves of a head (see phys_row)
+  int interleave;  // 0 none, 1 / 2 gate / up in blocks of 16, 3 rotary halves of a head, 4 / 5 gate / up in blocks of 8 (see phys_row)
   int Kp;          // padded K of the matrix
   int hd;          // head_dim (interleave 3 only)
 };
@@ -134,17 +134,18 @@ int ee_tensor_map(const ee_model* m, int tensor_id, int layer, TensorMap* out);
 int ee_layout_model(ee_model* m);   // fills offsets, returns total bytes in m->bytes
 
 // physical row of logical row n.
-// interleave 1/2: gate and up tiles alternate, so one GEMM task (two adjacent 16-row tiles) holds gate and
-// up of the same 16 features.  interleave 3 (fused QKV of bf16 models): inside every head the 16-row tiles
-// of the two rotary halves alternate -- tile 2j holds features 16j..16j+15, tile 2j+1 their partners
-// D/2 + 16j.. -- so one GEMM task holds both elements of 16 rotary pairs.
+// interleave 1/2 (fp32): gate and up alternate in blocks of 16 rows.  interleave 4/5 (bf16 gate / up): every 16-row tile holds
+// eight gate rows and the up rows of the same eight features.  interleave 3 (fused QKV of bf16 models): inside every head a tile
+// holds eight features f..f+7 of the lower rotary half and their partners D/2 + f...  So the epilogue of a bf16 tile finds both
+// operands of its pairs inside the tile, and tiles can be dealt to workgroups one by one.
 __host__ __device__ inline int phys_row(int n, int row_off, int interleave, int hd) {
   if (interleave == 0) return row_off + n;
   if (interleave == 3) {
     const int r = row_off + n, h = r / hd, f = r % hd, half = hd >> 1;
-    const int hi = f >= half ? 1 : 0, fj = (f - hi * half) >> 4;
-    return h * hd + ((2 * fj + hi) << 4) + (f & 15);
+    const int hi = f >= half ? 1 : 0, fj = f - hi * half;
+    return h * hd + ((fj >> 3) << 4) + 8 * hi + (fj & 7);
   }
+  if (interleave >= 4) return ((n >> 3) << 4) + 8 * (interleave - 4) + (n & 7);
   return (((n >> 4) * 2 + (interleave - 1)) << 4) | (n & 15);
 }
 

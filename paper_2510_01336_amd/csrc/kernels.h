@@ -80,9 +80,10 @@ struct GemmOut {
 // Y^T tile = W tile (A operand) x X^T (B operand); W, A in fragment layout.  Rows go in passes of 32.
 // (rows row0 .. row0+M-1 of the operand, row0 a multiple of 16)
 void bf16_gemm(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N, const GemmOut& out, int row0 = 0);
+struct StripShape { int ns, nw, ksplit, U; };   // strips per wave, waves per workgroup, waves that share out K, k-tiles per register set
 void bf16_gemm_cfg(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N,
-                   const GemmOut& out, int nw, int ksplit, int U, int row0 = 0);
-int bf16_gemm_few_rows(int ntiles, int ktiles);   // most rows that go to the kernel above rather than to the row-tiled one
+                   const GemmOut& out, const StripShape& shape, int row0 = 0);
+#define EE_STRIP_ROWS 32           // most rows that go to the kernel above rather than to the row-tiled one
 // Launch timing: while this points to a pair of events, the next skinny-GEMM launch attaches them to the dispatch
 // itself (hipExtLaunchKernelGGL), so that they hold the kernel's own start and end rather than the times at which
 // two marker packets around it were processed; the launcher sets `used`.

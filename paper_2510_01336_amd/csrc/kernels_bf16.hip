@@ -160,13 +160,11 @@ void bf16_begin_pass(hipStream_t st, const bf16_t* emb, const int* tok, const fl
 
 // ---------------------------------------------------------------------------------------------
 // Skinny GEMM  Y[m][n] = sum_k X[m][k] W[n][k],  M <= 16*MT rows per launch, weights streamed once.
-// A task is one 16-row weight tile strip over the whole K, or two adjacent strips (NB = 2) when the
-// epilogue needs both at once: gate and up of the same features (SwiGLU), or the two rotary halves of
-// a head (RoPE).  A workgroup of nw waves runs nw/ksplit tasks; the ksplit waves of a task split K
-// into contiguous chunks, each wave streaming its chunk (1 KiB per MFMA step) through two register
-// sets of U k-tiles that take turns (one in flight while the other is multiplied); the partial 16x16
-// tiles are then summed through LDS in a fixed order (deterministic) and the task's first wave runs
-// the epilogue.
+// A strip is one 16-row weight tile over the whole K.  A wave takes NS strips and a share of K (ksplit waves of the workgroup share
+// it out in contiguous chunks) and streams them (1 KiB per MFMA step) through two register sets of U k-tiles that take turns (one in
+// flight while the other is multiplied); the partial 16x16 tiles are then summed through LDS in a fixed order (deterministic), the
+// strips dealt round the waves for that and for the epilogue.  Every strip is complete in itself (see phys_row), so strips can be
+// dealt to any number of waves and workgroups: strip_shape gives every compute unit the same number of them.
 // The MFMA computes Y^T = W X^T so that a lane ends up with 4 consecutive n of one row m.
 //
 // Epilogues (everything between two projections is fused here, so a layer is five launches, six when the attention is split over the KV axis and merged):
@@ -179,20 +177,39 @@ void bf16_begin_pass(hipStream_t st, const bf16_t* emb, const int* tok, const fl
 // ---------------------------------------------------------------------------------------------
 // ---- epilogue of one 16 x 16 output tile (or tile pair), shared by the skinny and the row-tiled GEMM ----
 // A lane of the epilogue wave holds, for row m = mt*16 + lane%16, the four consecutive outputs
-// n = 16*tile + 4*(lane/16) .. +3 (acc[0]); for the paired epilogues acc[1] is the same lane's slice of the
-// partner tile (up for gate, the rotary partner half for Q/K/V).
+// n = 16*tile + 4*(lane/16) .. +3.  Tiles of the paired epilogues hold eight features and their partners (up for gate, the other
+// rotary half for Q/K/V; see phys_row): the upper half of the wave holds the partners of the lower half's outputs.
 struct EpiPre {            // operands of the epilogue that do not depend on the product
   float4 res, gnext;       // EPI_ADD: residual row slice, gains of the next operand
-  float4 rc01, rc23;       // EPI_ROPE: (cos, sin) of the lane's four rotary pairs
+  float4 rc[2];            // EPI_ROPE: (cos, sin) of the lane's two or four rotary pairs
   int r_a, r_b;            // EPI_ROPE: Q heads: (global q-tile, row in tile); K/V heads: (page, position in page)
                            // EPI_ADD: r_a = row of the second destination
 };
 
-template <int EPI>
+// Deals the pairs of one tile (NF = 2), or of two neighbouring ones (NF = 4: wider stores), to all lanes: lo[i], hi[i] = output
+// pair_feature<NF> + i behind the first tile's first feature and its partner.
+template <int NF>
+__device__ inline void pair_up(const f32x4& a, const f32x4& b, float sc, float (&lo)[NF], float (&hi)[NF]) {
+  typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+#pragma unroll
+  for (int i = 0; i < NF; ++i) {
+    const u32x2_t r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a[i] * sc), __float_as_uint((NF == 2 ? a[2 + i] : b[i]) * sc), false, false);
+    lo[i] = __uint_as_float(r[0]); hi[i] = __uint_as_float(r[1]);
+  }
+}
+template <int NF>
+__device__ inline int pair_feature(int lane) { return NF == 2 ? ((lane >> 4) & 1) * 4 + (lane >> 5) * 2 : (lane >> 4) * 4; }
+template <int NF>
+__device__ inline void store_bf16(bf16_t* p, const float (&x)[NF]) {
+  if constexpr (NF == 2) *(uint32_t*)p = pack2(x[0], x[1]);
+  else *(uint2*)p = make_uint2(pack2(x[0], x[1]), pack2(x[2], x[3]));
+}
+
+template <int EPI, int NF = 2>
 __device__ inline void epi_prefetch(EpiPre& p, const GemmOut& out, int task, int row, bool ok, int lane) {
   const int g = lane >> 4;
   p.res = p.gnext = make_float4(0.f, 0.f, 0.f, 0.f);
-  p.rc01 = p.rc23 = make_float4(1.f, 0.f, 1.f, 0.f);
+  p.rc[0] = p.rc[1] = make_float4(1.f, 0.f, 1.f, 0.f);
   p.r_a = p.r_b = 0;
   if (EPI == EPI_ADD) {
     const int n = task * 16 + 4 * g;
@@ -202,12 +219,13 @@ __device__ inline void epi_prefetch(EpiPre& p, const GemmOut& out, int task, int
   }
   if (EPI == EPI_ROPE && ok) {
     const RopeOut& R = out.rope;
-    const int half = R.D >> 1, tph = R.D >> 5;
-    const int h = task / tph, f = (task % tph) * 16 + 4 * g;
+    const int half = R.D >> 1, tph = R.D >> 4;
+    const int h = task / tph, f = (task % tph) * 8 + pair_feature<NF>(lane);
     const int4 ri = R.rowinfo[row];              // (every operand here is indexed by the row alone: no dependent loads)
     if (h < R.Hq + R.Hkv) {
       const float4* c4 = (const float4*)(R.cs + (size_t)row * half + f);
-      p.rc01 = c4[0]; p.rc23 = c4[1];
+      p.rc[0] = c4[0];
+      if constexpr (NF == 4) p.rc[1] = c4[1];
     }
     if (h < R.Hq) {
       const int q = ri.y * (R.Hq / R.Hkv) + h % (R.Hq / R.Hkv);
@@ -218,48 +236,116 @@ __device__ inline void epi_prefetch(EpiPre& p, const GemmOut& out, int task, int
   }
 }
 
-// Deferred RMSNorm factors sc[i] of rows row0 + 16 * step * i + lane % 16 (row0 a multiple of 16; i < n of NT) from the
-// producer's partial sums of squares [partial][row], in a fixed order: a lane loads four rows (lane % 4) of every 16th partial
-// (lane / 4), a butterfly over the lanes adds them up.  The row tiles go side by side, so the chain is one tile's.
+// Deferred RMSNorm: row factors from the producer's partial sums of squares [partial][row], in a fixed order.  A lane loads four
+// rows (lane % 4) of every 16th partial (lane / 4); the sixteen lanes of a row quad then add up theirs.
+// sum over the lanes of equal lane % 4, delivered to all of them: the butterfly of norm_factor_kernel (neighbours first, so that
+// both add in one order)
+__device__ inline float quad_lane_sum(float x) {
+  typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+  x += __shfl_xor(x, 4, 64);
+  x += __shfl_xor(x, 8, 64);
+  u32x2_t r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
 template <int NT>
-__device__ inline void norm_factors(float (&sc)[NT], const NormIn& nin, int row0, int step, int n, int lane) {
+struct NormPartials { float4 t[NT][4]; };      // 64 partials of NT row tiles (row0 + 16 * step * i, i < n), requested ahead of their use
+template <int NT>
+__device__ inline void norm_request(NormPartials<NT>& q, const NormIn& nin, int row0, int step, int n, int c0, int lane) {
   const float* p = nin.ssq + row0 + 4 * (lane & 3);
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+      q.t[i][j] = *(const float4*)(p + (size_t)min(c0 + (lane >> 2) + 16 * j, nin.n_part - 1) * nin.stride + 16 * step * min(i, n - 1));
+}
+// Factors sc[i] of rows row0 + 16 * step * i + lane % 16 (row0 a multiple of 16; i < n of NT); q: partials 0..63.  The row tiles
+// go side by side, so the chain is one tile's.
+template <int NT>
+__device__ inline void norm_factors(float (&sc)[NT], NormPartials<NT>& q, const NormIn& nin, int row0, int step, int n, int lane) {
   float4 sv[NT];
 #pragma unroll
   for (int i = 0; i < NT; ++i) sv[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int c0 = lane >> 2; c0 < nin.n_part; c0 += 64) {
-    float4 t[NT][4];
+  for (int c0 = 0;;) {
 #pragma unroll
     for (int j = 0; j < 4; ++j)
+      if (c0 + (lane >> 2) + 16 * j < nin.n_part) {
 #pragma unroll
-      for (int i = 0; i < NT; ++i)
-        t[i][j] = *(const float4*)(p + (size_t)min(c0 + 16 * j, nin.n_part - 1) * nin.stride + 16 * step * min(i, n - 1));
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (c0 + 16 * j < nin.n_part) {
-#pragma unroll
-        for (int i = 0; i < NT; ++i) { sv[i].x += t[i][j].x; sv[i].y += t[i][j].y; sv[i].z += t[i][j].z; sv[i].w += t[i][j].w; }
+        for (int i = 0; i < NT; ++i) { sv[i].x += q.t[i][j].x; sv[i].y += q.t[i][j].y; sv[i].z += q.t[i][j].z; sv[i].w += q.t[i][j].w; }
       }
+    c0 += 64;
+    if (c0 >= nin.n_part) break;
+    norm_request<NT>(q, nin, row0, step, n, c0, lane);
   }
-#pragma unroll
-  for (int sh = 4; sh < 64; sh <<= 1)
-#pragma unroll
-    for (int i = 0; i < NT; ++i) {
-      sv[i].x += __shfl_xor(sv[i].x, sh, 64); sv[i].y += __shfl_xor(sv[i].y, sh, 64);
-      sv[i].z += __shfl_xor(sv[i].z, sh, 64); sv[i].w += __shfl_xor(sv[i].w, sh, 64);
-    }
-  const int mc = lane & 15;          // lanes with lane % 4 == q now hold rows 4q .. 4q+3
+  const int mc = lane & 15;
 #pragma unroll
   for (int i = 0; i < NT; ++i) {
+    sv[i].x = quad_lane_sum(sv[i].x); sv[i].y = quad_lane_sum(sv[i].y); sv[i].z = quad_lane_sum(sv[i].z); sv[i].w = quad_lane_sum(sv[i].w);
+    // lanes with lane % 4 == q now hold rows 4q .. 4q+3
     const float a = __shfl(sv[i].x, mc >> 2, 64), b = __shfl(sv[i].y, mc >> 2, 64), c = __shfl(sv[i].z, mc >> 2, 64), e = __shfl(sv[i].w, mc >> 2, 64);
     const float ss = (mc & 2) ? ((mc & 1) ? e : c) : ((mc & 1) ? b : a);
     sc[i] = 1.0f / sqrtf(ss * nin.inv_d + nin.eps);
   }
 }
 
+// The paired epilogues.  NF = 2: one tile; 4: tiles `tile` and `tile` + 1 (the next one's accumulators in acc1)
+template <int EPI, int NF>
+__device__ inline void epi_apply_pairs(const f32x4& acc0, const f32x4& acc1, float sc, const EpiPre& p, const GemmOut& out, int tile, int row, bool ok, int lane) {
+  float lo[NF], hi[NF];
+  pair_up<NF>(acc0, acc1, sc, lo, hi);
+  if (!ok) return;
+  if (EPI == EPI_SWIGLU) {
+    const int f = tile * 8 + pair_feature<NF>(lane);     // h[m][f ..] = silu(gate) * up
+    float h[NF];
+#pragma unroll
+    for (int v = 0; v < NF; ++v) h[v] = lo[v] / (1.0f + __expf(-lo[v])) * hi[v];
+    store_bf16<NF>(out.H + frag_offset(row, f, out.h_ktiles), h);
+  } else {
+    // head h, features f .. and their partners f + D/2 ..
+    const RopeOut& R = out.rope;
+    const int D = R.D, half = D >> 1, tph = D >> 4;
+    const int h = tile / tph, f = (tile % tph) * 8 + pair_feature<NF>(lane);
+    if (h < R.Hq + R.Hkv) {
+#pragma unroll
+      for (int v = 0; v < NF; ++v) {
+        const float4 t = p.rc[v >> 1];
+        const float c = v & 1 ? t.z : t.x, s = v & 1 ? t.w : t.y, a = lo[v], b = hi[v];
+        lo[v] = a * c - b * s;
+        hi[v] = b * c + a * s;
+      }
+    }
+    if (h < R.Hq) {
+      const int kvh = h / (R.Hq / R.Hkv), q15 = p.r_b;
+      const size_t qtile = ((size_t)kvh * R.total_qt + p.r_a) * (D >> 5);
+      const int d1 = f + half;
+      store_bf16<NF>(R.Q + ((qtile + (f >> 5)) * 64 + ((f & 31) >> 3) * 16 + q15) * 8 + (f & 7), lo);
+      store_bf16<NF>(R.Q + ((qtile + (d1 >> 5)) * 64 + ((d1 & 31) >> 3) * 16 + q15) * 8 + (d1 & 7), hi);
+    } else {
+      const int page = p.r_a, pp = p.r_b;
+      if (h < R.Hq + R.Hkv) {
+        bf16_t* slab = R.kv + kv_slab(R.layer, page, h - R.Hq, R.n_pages, R.Hkv, D);
+        store_bf16<NF>(slab + k_page_off(pp, f, D), lo);
+        store_bf16<NF>(slab + k_page_off(pp, f + half, D), hi);
+      } else {
+        bf16_t* slab = R.kv + kv_slab(R.layer, page, h - R.Hq - R.Hkv, R.n_pages, R.Hkv, D) + EE_PAGE * D;
+#pragma unroll
+        for (int v = 0; v < NF; v += 2) {
+          const uint32_t wl = pack2(lo[v], lo[v + 1]), wh = pack2(hi[v], hi[v + 1]);
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            slab[v_page_off(pp, f + v + j)] = (bf16_t)(wl >> (16 * j));
+            slab[v_page_off(pp, f + half + v + j)] = (bf16_t)(wh >> (16 * j));
+          }
+        }
+      }
+    }
+  }
+}
+
 // sc: the row's deferred RMSNorm factor (1 when the operand was already normalised)
 template <int EPI>
-__device__ inline void epi_apply(const f32x4& acc0, const f32x4& acc1, float sc, const EpiPre& p, const GemmOut& out, int task,
+__device__ inline void epi_apply(const f32x4& acc0, float sc, const EpiPre& p, const GemmOut& out, int task,
                                  int row, bool ok, int N, int lane, float* ss_out = nullptr) {
   const int g = lane >> 4;
   if (EPI == EPI_ADD) {
@@ -277,60 +363,8 @@ __device__ inline void epi_apply(const f32x4& acc0, const f32x4& acc1, float sc,
       if (ss_out) *ss_out = ss;                // (the caller adds up several tiles)
       else if (g == 0) out.nout.ssq[(size_t)task * out.nout.stride + row] = ss;
     }
-  } else if (EPI == EPI_SWIGLU) {
-    const int f = task * 16 + 4 * g;     // h[m][f..f+3] = silu(gate) * up
-    if (ok) {
-      float h[4];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const float gt = acc0[v] * sc, up = acc1[v] * sc;
-        h[v] = gt / (1.0f + __expf(-gt)) * up;
-      }
-      *(uint2*)(out.H + frag_offset(row, f, out.h_ktiles)) = make_uint2(pack2(h[0], h[1]), pack2(h[2], h[3]));
-    }
-  } else if (EPI == EPI_ROPE) {
-    // task = (head h, 16 rotary pairs f0..f0+15): acc0 holds features f, acc1 their partners f + D/2
-    const RopeOut& R = out.rope;
-    const int D = R.D, half = D >> 1, tph = D >> 5;
-    const int h = task / tph, f = (task % tph) * 16 + 4 * g;
-    if (ok) {
-      float lo[4], hi[4];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) { lo[v] = acc0[v] * sc; hi[v] = acc1[v] * sc; }
-      if (h < R.Hq + R.Hkv) {
-        const float cx[4] = {p.rc01.x, p.rc01.z, p.rc23.x, p.rc23.z}, sy[4] = {p.rc01.y, p.rc01.w, p.rc23.y, p.rc23.w};
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const float a = lo[v], b = hi[v];
-          lo[v] = a * cx[v] - b * sy[v];
-          hi[v] = b * cx[v] + a * sy[v];
-        }
-      }
-      const uint2 plo = make_uint2(pack2(lo[0], lo[1]), pack2(lo[2], lo[3]));
-      const uint2 phi = make_uint2(pack2(hi[0], hi[1]), pack2(hi[2], hi[3]));
-      if (h < R.Hq) {
-        const int kvh = h / (R.Hq / R.Hkv), q15 = p.r_b;
-        const size_t tile = ((size_t)kvh * R.total_qt + p.r_a) * tph;
-        const int d1 = f + half;
-        *(uint2*)(R.Q + ((tile + (f >> 5)) * 64 + ((f & 31) >> 3) * 16 + q15) * 8 + (f & 7)) = plo;
-        *(uint2*)(R.Q + ((tile + (d1 >> 5)) * 64 + ((d1 & 31) >> 3) * 16 + q15) * 8 + (d1 & 7)) = phi;
-      } else {
-        const int page = p.r_a, pp = p.r_b;
-        if (h < R.Hq + R.Hkv) {
-          bf16_t* slab = R.kv + kv_slab(R.layer, page, h - R.Hq, R.n_pages, R.Hkv, D);
-          *(uint2*)(slab + k_page_off(pp, f, D)) = plo;
-          *(uint2*)(slab + k_page_off(pp, f + half, D)) = phi;
-        } else {
-          bf16_t* slab = R.kv + kv_slab(R.layer, page, h - R.Hq - R.Hkv, R.n_pages, R.Hkv, D) + EE_PAGE * D;
-          const uint32_t wl[2] = {plo.x, plo.y}, wh[2] = {phi.x, phi.y};
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            slab[v_page_off(pp, f + v)] = (bf16_t)(wl[v >> 1] >> (16 * (v & 1)));
-            slab[v_page_off(pp, f + half + v)] = (bf16_t)(wh[v >> 1] >> (16 * (v & 1)));
-          }
-        }
-      }
-    }
+  } else if (EPI == EPI_SWIGLU || EPI == EPI_ROPE) {
+    epi_apply_pairs<EPI, 2>(acc0, acc0, sc, p, out, task, row, ok, lane);
   } else {   // EPI_ARGMAX: per-row (max, arg max) over this tile's 16 outputs; lowest index wins ties
     float best = -INFINITY; int bi = 0x7fffffff;
 #pragma unroll
@@ -354,130 +388,84 @@ __device__ inline void epi_apply(const f32x4& acc0, const f32x4& acc1, float sc,
   }
 }
 
-template <int MT, int NB, int U>
+template <int MT, int NS, int U>
 struct Frags {
-  u32x4 w[NB][U];
+  u32x4 w[NS][U];
   u32x4 x[MT][U];
 };
 
 // Requests the fragments of k-tiles kt .. kt+U-1 (indices past `last` repeat the last k-tile: valid memory; the
 // caller leaves those out of the product).  Nothing here touches a loaded value, so the wave does not wait.
-template <int MT, int NB, int U>
-__device__ inline void load_frags(Frags<MT, NB, U>& f, const u32x4* const (&wp)[NB], const u32x4* ap, int ktiles, int kt, int last) {
+template <int MT, int NS, int U>
+__device__ inline void load_frags(Frags<MT, NS, U>& f, const u32x4* const (&wp)[NS], const u32x4* const (&ap)[MT], int kt, int last) {
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int k = min(kt + u, last);
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) f.w[nb][u] = __builtin_nontemporal_load(&wp[nb][(size_t)k * 64]);
+    for (int s = 0; s < NS; ++s) f.w[s][u] = __builtin_nontemporal_load(&wp[s][(size_t)k * 64]);
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) f.x[mt][u] = ap[((size_t)mt * ktiles + k) * 64];
+    for (int mt = 0; mt < MT; ++mt) f.x[mt][u] = ap[mt][(size_t)k * 64];
   }
 }
 // acc += the product over the k-tiles kt .. kt+U-1 held in f; GUARD: only those below kt1 (kt and kt1 must be
 // uniform in a way the compiler can see, see the kernel)
-template <int MT, int NB, int U, bool GUARD>
-__device__ inline void mma_frags(f32x4 (&acc)[NB][MT], const Frags<MT, NB, U>& f, int kt, int kt1) {
+template <int MT, int NS, int U, bool GUARD>
+__device__ inline void mma_frags(f32x4 (&acc)[NS][MT], const Frags<MT, NS, U>& f, int kt, int kt1) {
 #pragma unroll
   for (int u = 0; u < U; ++u)
     if (!GUARD || kt + u < kt1) {         // (uniform)
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
+      for (int s = 0; s < NS; ++s)
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[nb][mt] = mfma16(f.w[nb][u], f.x[mt][u], acc[nb][mt]);
+        for (int mt = 0; mt < MT; ++mt) acc[s][mt] = mfma16(f.w[s][u], f.x[mt][u], acc[s][mt]);
     }
 }
 
-template <int MT, int EPI, int U>
-__global__ __launch_bounds__(64 * EE_MAX_WAVES) void gemm_skinny_kernel(const uint4* __restrict__ W, int ktiles, int ntasks,
+template <int MT, int EPI, int NS, int U>
+__global__ __launch_bounds__(64 * EE_MAX_WAVES) void gemm_skinny_kernel(const uint4* __restrict__ W, int ktiles, int ntiles,
                                                                         const uint4* __restrict__ A, int row0, int M, int N,
                                                                         GemmOut out, int ksplit) {
-  constexpr int NB = (EPI == EPI_SWIGLU || EPI == EPI_ROPE) ? 2 : 1;
-  __shared__ float4 red[EE_MAX_WAVES - 1][NB * MT][64];
-  __shared__ float ssq_red[EE_MAX_WAVES][MT * 16];
+  __shared__ f32x4 red[EE_MAX_WAVES][NS * MT][64];
+  __shared__ __align__(16) float ssq_red[EE_MAX_WAVES][MT * 16];
   // The wave's number is taken through a scalar register: the compiler then knows that everything derived from it (the
   // task, the K share and above all the conditions around the MFMAs of a short last group) is uniform and branches
   // on it.  A condition it takes for divergent it may turn into an EXEC mask without a branch -- and the matrix
   // instructions ignore EXEC, so a masked-off MFMA would still add its product.
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
-  const int task = blockIdx.x * (nw / ksplit) + wave / ksplit, kpart = wave % ksplit;
-  const bool active = task < ntasks;
+  const int tasks = nw / ksplit, task0 = blockIdx.x * tasks * NS, strip0 = task0 + wave / ksplit * NS, kpart = wave % ksplit;
   const int per = (ktiles + ksplit - 1) / ksplit;
   const int kt0 = kpart * per, kt1 = min(ktiles, kt0 + per);
 
-  f32x4 acc[NB][MT];
+  f32x4 acc[NS][MT];
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb)
+  for (int s = 0; s < NS; ++s)
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[nb][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int mt = 0; mt < MT; ++mt) acc[s][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  const bool stream = active && kt0 < kt1;
-  const u32x4* wp[NB];
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb) wp[nb] = (const u32x4*)W + (size_t)(task * NB + nb) * ktiles * 64 + lane;
-  const u32x4* ap = (const u32x4*)A + (size_t)(row0 >> 4) * ktiles * 64 + lane;
-  Frags<MT, NB, U> cur;
-
-  // Order of the requests: the partial sums of squares of the deferred RMSNorm (small, mostly L2), then the first
-  // weight fragments, then the epilogue's operands; the sums are formed once their loads are back, which frees their
-  // registers for the second set of fragments.  The load counter is in order, so nothing here waits for the weights.
-  constexpr int SB = 16 / MT;   // 16-byte loads per lane and m-tile in one batch (64 registers in all)
-  const bool normed = out.nin.ssq != nullptr && active;
+  const bool stream = strip0 < ntiles && kt0 < kt1;
   const int mc = lane & 15;
-  const bool epi_wave = active && kpart == 0;
+  const u32x4 *wp[NS], *ap[MT];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) wp[s] = (const u32x4*)W + (size_t)min(strip0 + s, ntiles - 1) * ktiles * 64 + lane;
+  // (rows past the last repeat it: no cache lines are fetched for them)
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) ap[mt] = (const u32x4*)A + (size_t)((row0 >> 4) + mt) * ktiles * 64 + (lane & 48) + max(0, min(mc, M - 1 - 16 * mt));
+  Frags<MT, NS, U> cur;
+
+  // Order of the requests: the partial sums of squares of the deferred RMSNorm (contiguous shares of the workgroup's waves, looked
+  // at behind the K loop), the first weight fragments, the epilogue's operands.
+  const bool normed = out.nin.ssq != nullptr;
+  const int np = normed ? out.nin.n_part : 0, cp = (np + nw - 1) / nw, cw = wave * cp, ce = min(np, cw + cp);
+  // strip whose epilogue this wave runs first
+  const int own = ksplit == 1 ? strip0 : task0 + wave;
+  const bool owner = own < ntiles && (ksplit == 1 || wave < tasks * NS);
   EpiPre pre[MT];
-  float ssl[MT];
+  NormPartials<MT> part;
+  if (normed) norm_request<MT>(part, out.nin, row0, 1, MT, cw, lane);
+  if (stream) load_frags<MT, NS, U>(cur, wp, ap, kt0, kt1 - 1);
+  if (owner) {
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt) ssl[mt] = 0.f;
-  {
-    // Deferred RMSNorm: sum of squares of row mt*16 + lane%16 from the producer's per-tile partials [partial][row], in
-    // a fixed order.  The ksplit waves of a task each sum a contiguous share of the partials; a lane loads four rows
-    // (lane % 4) of every 16th partial (lane / 4) at a time, the lanes' sums then meet in a butterfly.
-    const int np = normed ? out.nin.n_part : 0, cp = (np + ksplit - 1) / ksplit;
-    const int c0 = kpart * cp + (lane >> 2), c1 = min(np, (kpart + 1) * cp);
-    const float* p = out.nin.ssq + row0 + 4 * (lane & 3);
-    float4 t[MT][SB];
-    if (normed) {
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int j = 0; j < SB; ++j) t[mt][j] = *(const float4*)(p + (size_t)min(c0 + 16 * j, np - 1) * out.nin.stride + mt * 16);
-    }
-    if (stream) load_frags<MT, NB, U>(cur, wp, ap, ktiles, kt0, kt1 - 1);
-    if (epi_wave) {
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) epi_prefetch<EPI>(pre[mt], out, task, row0 + mt * 16 + mc, mt * 16 + mc < M, lane);
-    }
-    if (normed) {
-      float4 sv[MT];
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        sv[mt] = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-        for (int j = 0; j < SB; ++j)
-          if (c0 + 16 * j < c1) { sv[mt].x += t[mt][j].x; sv[mt].y += t[mt][j].y; sv[mt].z += t[mt][j].z; sv[mt].w += t[mt][j].w; }
-      }
-      for (int b0 = c0 + 16 * SB; b0 < c1; b0 += 16 * SB)      // (more partials than one batch: wide models, several row tiles)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-#pragma unroll
-          for (int j = 0; j < SB; ++j) t[mt][j] = *(const float4*)(p + (size_t)min(b0 + 16 * j, np - 1) * out.nin.stride + mt * 16);
-#pragma unroll
-          for (int j = 0; j < SB; ++j)
-            if (b0 + 16 * j < c1) { sv[mt].x += t[mt][j].x; sv[mt].y += t[mt][j].y; sv[mt].z += t[mt][j].z; sv[mt].w += t[mt][j].w; }
-        }
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-#pragma unroll
-        for (int sh = 4; sh < 64; sh <<= 1) {
-          sv[mt].x += __shfl_xor(sv[mt].x, sh, 64); sv[mt].y += __shfl_xor(sv[mt].y, sh, 64);
-          sv[mt].z += __shfl_xor(sv[mt].z, sh, 64); sv[mt].w += __shfl_xor(sv[mt].w, sh, 64);
-        }
-        // lanes with lane % 4 == q now hold rows 4q .. 4q+3; this lane wants row mc
-        const float a = __shfl(sv[mt].x, mc >> 2, 64), b = __shfl(sv[mt].y, mc >> 2, 64);
-        const float c = __shfl(sv[mt].z, mc >> 2, 64), e = __shfl(sv[mt].w, mc >> 2, 64);
-        ssl[mt] = (mc & 2) ? ((mc & 1) ? e : c) : ((mc & 1) ? b : a);
-      }
-    }
+    for (int mt = 0; mt < MT; ++mt) epi_prefetch<EPI>(pre[mt], out, own, row0 + mt * 16 + mc, mt * 16 + mc < M, lane);
   }
 
   // Two register sets of fragments take turns: while one is multiplied the other is in flight, and the next request
@@ -486,59 +474,86 @@ __global__ __launch_bounds__(64 * EE_MAX_WAVES) void gemm_skinny_kernel(const ui
     // Groups of U k-tiles; only the last one can be short.  In the loop every fragment requested is multiplied, with
     // no condition in between -- a request whose data might go unused would make the compiler drain the load counter
     // before the registers are requested again, and with it the set in flight.
-    Frags<MT, NB, U> oth;
+    Frags<MT, NS, U> oth;
     const int last = kt1 - 1;
     int kt = kt0;
     for (; kt + 2 * U < kt1; kt += 2 * U) {
-      load_frags<MT, NB, U>(oth, wp, ap, ktiles, kt + U, last);
-      mma_frags<MT, NB, U, false>(acc, cur, kt, kt1);
-      load_frags<MT, NB, U>(cur, wp, ap, ktiles, kt + 2 * U, last);
-      mma_frags<MT, NB, U, false>(acc, oth, kt + U, kt1);
+      load_frags<MT, NS, U>(oth, wp, ap, kt + U, last);
+      mma_frags<MT, NS, U, false>(acc, cur, kt, kt1);
+      load_frags<MT, NS, U>(cur, wp, ap, kt + 2 * U, last);
+      mma_frags<MT, NS, U, false>(acc, oth, kt + U, kt1);
     }
     if (kt + U < kt1) {                  // two groups left
-      load_frags<MT, NB, U>(oth, wp, ap, ktiles, kt + U, last);
-      mma_frags<MT, NB, U, false>(acc, cur, kt, kt1);
-      mma_frags<MT, NB, U, true>(acc, oth, kt + U, kt1);
+      load_frags<MT, NS, U>(oth, wp, ap, kt + U, last);
+      mma_frags<MT, NS, U, false>(acc, cur, kt, kt1);
+      mma_frags<MT, NS, U, true>(acc, oth, kt + U, kt1);
     } else {
-      mma_frags<MT, NB, U, true>(acc, cur, kt, kt1);
+      mma_frags<MT, NS, U, true>(acc, cur, kt, kt1);
     }
   }
 
-  // fixed-order reduction over the K parts of a task (every wave reaches the barrier)
-  if (ksplit > 1) {   // uniform branch
-    if (normed && lane < 16) {
+  if (normed) {
+    float4 sv[MT];
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) ssq_red[wave][mt * 16 + lane] = ssl[mt];
+    for (int mt = 0; mt < MT; ++mt) sv[mt] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int c0 = cw;;) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (c0 + (lane >> 2) + 16 * j < ce) {
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) { sv[mt].x += part.t[mt][j].x; sv[mt].y += part.t[mt][j].y; sv[mt].z += part.t[mt][j].z; sv[mt].w += part.t[mt][j].w; }
+        }
+      c0 += 64;
+      if (c0 >= ce) break;
+      norm_request<MT>(part, out.nin, row0, 1, MT, c0, lane);      // (more than 64 partials a wave: wide models)
     }
-    if (kpart > 0) {
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-          red[wave - 1][nb * MT + mt][lane] = make_float4(acc[nb][mt][0], acc[nb][mt][1], acc[nb][mt][2], acc[nb][mt][3]);
+    for (int mt = 0; mt < MT; ++mt) {
+      const float4 t = make_float4(quad_lane_sum(sv[mt].x), quad_lane_sum(sv[mt].y), quad_lane_sum(sv[mt].z), quad_lane_sum(sv[mt].w));
+      if (lane < 4) *(float4*)&ssq_red[wave][mt * 16 + 4 * lane] = t;
     }
-    __syncthreads();
   }
-  if (kpart != 0 || !active) return;
-  for (int w = 1; w < ksplit; ++w)
+  if (ksplit > 1) {
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
+    for (int s = 0; s < NS; ++s)
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        float4 t = red[wave + w - 1][nb * MT + mt][lane];
-        acc[nb][mt][0] += t.x; acc[nb][mt][1] += t.y; acc[nb][mt][2] += t.z; acc[nb][mt][3] += t.w;
-      }
-
+      for (int mt = 0; mt < MT; ++mt) red[wave][s * MT + mt][lane] = acc[s][mt];
+  }
+  if (ksplit > 1 || normed) __syncthreads();   // (uniform; every wave reaches it)
+  float sc[MT];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
-    const int m = mt * 16 + mc;
-    float sc = 1.0f;
+    sc[mt] = 1.0f;
     if (normed) {
-      float ss = ssl[mt];
-      for (int w = 1; w < ksplit; ++w) ss += ssq_red[wave + w][m];
-      sc = 1.0f / sqrtf(ss * out.nin.inv_d + out.nin.eps);
+      float ss = ssq_red[0][mt * 16 + mc];
+      for (int w = 1; w < nw; ++w) ss += ssq_red[w][mt * 16 + mc];
+      sc[mt] = 1.0f / sqrtf(ss * out.nin.inv_d + out.nin.eps);
     }
-    epi_apply<EPI>(acc[0][mt], acc[NB - 1][mt], sc, pre[mt], out, task, row0 + m, m < M, N, lane);
+  }
+  if (ksplit == 1) {
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      if (strip0 + s >= ntiles) continue;
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        const int m = mt * 16 + mc;
+        if (s > 0) epi_prefetch<EPI>(pre[mt], out, strip0 + s, row0 + m, m < M, lane);
+        epi_apply<EPI>(acc[s][mt], sc[mt], pre[mt], out, strip0 + s, row0 + m, m < M, N, lane);
+      }
+    }
+    return;
+  }
+  // the strips of the workgroup are dealt round its waves; the K parts of one are added in a fixed order
+  for (int i = wave; i < tasks * NS && task0 + i < ntiles; i += nw) {
+    const int w0 = i / NS * ksplit, s = i % NS;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      const int m = mt * 16 + mc;
+      if (i != wave) epi_prefetch<EPI>(pre[mt], out, task0 + i, row0 + m, m < M, lane);
+      f32x4 sum = red[w0][s * MT + mt][lane];
+      for (int w = 1; w < ksplit; ++w) sum += red[w0 + w][s * MT + mt][lane];
+      epi_apply<EPI>(sum, sc[mt], pre[mt], out, task0 + i, row0 + m, m < M, N, lane);
+    }
   }
 }
 
@@ -573,7 +588,6 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
   // rows row0 .. row0+M_all-1 of the operand (row0 a multiple of 16), of which this workgroup takes the block of
   // TMT*16 rows that blockIdx.z names; the deferred-norm factors and the K-share partials are indexed from row0,
   // everything the epilogue touches by the row itself
-  constexpr int NB = (EPI == EPI_SWIGLU || EPI == EPI_ROPE) ? 2 : 1;
   static_assert(TN == 2 || TN == 4, "weight tiles per wave");
   const int bx = blockIdx.x, rbase = blockIdx.z * (TMT * 16), M = min(M_all - rbase, TMT * 16);
   constexpr int TMW = TMT / 4;                      // row tiles per wave
@@ -718,19 +732,24 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
     if (out.nin.inv_rms && mt_first + mt * MT_STEP < mt_used) sc[mt] = out.nin.inv_rms[rbase + min((mt_first + mt * MT_STEP) * 16 + mc, M - 1)];
   }
   const int mt_own = (mt_used - mt_first + MT_STEP - 1) / MT_STEP;      // row tiles of this wave that hold rows
-  if (!out.nin.inv_rms && out.nin.ssq && mt_own > 0) norm_factors<TMW>(sc, out.nin, row0 + rbase + mt_first * 16, MT_STEP, min(mt_own, TMW), lane);
+  if (!out.nin.inv_rms && out.nin.ssq && mt_own > 0) {
+    NormPartials<TMW> part;
+    norm_request<TMW>(part, out.nin, row0 + rbase + mt_first * 16, MT_STEP, min(mt_own, TMW), 0, lane);
+    norm_factors<TMW>(sc, part, out.nin, row0 + rbase + mt_first * 16, MT_STEP, min(mt_own, TMW), lane);
+  }
+  constexpr int PT = EPI == EPI_SWIGLU || EPI == EPI_ROPE ? 2 : 1;      // tiles the epilogue takes at once
 #pragma unroll
-  for (int t = 0; t < TN / NB; ++t) {
-    const int nt = nt0 + t * NB;
-    if (nt >= ntiles) continue;
-    const int task = nt / NB;
+  for (int t = 0; t < TN; t += PT) {
+    const int task = nt0 + t;
+    if (task >= ntiles) continue;
 #pragma unroll
     for (int mt = 0; mt < TMW; ++mt) {
       const int m = (mt_first + mt * MT_STEP) * 16 + mc;
       if (mt_first + mt * MT_STEP >= mt_used) continue;
       EpiPre pre;
-      epi_prefetch<EPI>(pre, out, task, row0 + rbase + m, m < M, lane);
-      epi_apply<EPI>(acc[t * NB][mt], acc[t * NB + NB - 1][mt], sc[mt], pre, out, task, row0 + rbase + m, m < M, N, lane);
+      epi_prefetch<EPI, 2 * PT>(pre, out, task, row0 + rbase + m, m < M, lane);
+      if constexpr (PT == 2) epi_apply_pairs<EPI, 4>(acc[t][mt], acc[t + 1][mt], sc[mt], pre, out, task, row0 + rbase + m, m < M, lane);
+      else epi_apply<EPI>(acc[t][mt], sc[mt], pre, out, task, row0 + rbase + m, m < M, N, lane);
     }
   }
 }
@@ -753,8 +772,6 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
 template <int EPI, int TN, bool FULL>
 __device__ __forceinline__ void gemm_block_body(u32x4* ring, const uint4* __restrict__ W, int ktiles, int ntiles, const uint4* __restrict__ A,
                                                 int row0, int rbase, int M, int N, const GemmOut& out, int bx) {
-  constexpr int NB = (EPI == EPI_SWIGLU || EPI == EPI_ROPE) ? 2 : 1;
-  static_assert(TN % NB == 0, "a task's tiles stay in one wave");
   constexpr int TMT = 16, WT = 2 * TN, TMW = TMT / 4, TILES = WT + TMT, STAGE = TILES * 64;
   constexpr int S = (160 / TILES) & ~1;             // stages in the ring (even: fragments alternate between two register sets)
   constexpr int NJ = (TILES + 7) / 8;               // requests per wave and stage at most: tiles wave, wave + 8, ... (weights first)
@@ -848,19 +865,20 @@ __device__ __forceinline__ void gemm_block_body(u32x4* ring, const uint4* __rest
 #undef BLK_REQUEST
   __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
   const int mc = lane & 15;
+  constexpr int PT = EPI == EPI_SWIGLU || EPI == EPI_ROPE ? 2 : 1;      // tiles the epilogue takes at once
 #pragma unroll
-  for (int t = 0; t < TN / NB; ++t) {
-    const int nt = nt0 + t * NB;
-    if (nt >= ntiles) continue;
-    const int task = nt / NB;
+  for (int t = 0; t < TN; t += PT) {
+    const int task = nt0 + t;
+    if (task >= ntiles) continue;
 #pragma unroll
     for (int mt = 0; mt < TMW; ++mt) {
       const int m = (mt_first + mt * MT_STEP) * 16 + mc;
       if (mt_first + mt * MT_STEP >= mt_used) continue;
       const float sc = out.nin.inv_rms ? out.nin.inv_rms[rbase + min(m, M - 1)] : 1.0f;
       EpiPre pre;
-      epi_prefetch<EPI>(pre, out, task, row0 + rbase + m, m < M, lane);
-      epi_apply<EPI>(acc[t * NB][mt], acc[t * NB + NB - 1][mt], sc, pre, out, task, row0 + rbase + m, m < M, N, lane);
+      epi_prefetch<EPI, 2 * PT>(pre, out, task, row0 + rbase + m, m < M, lane);
+      if constexpr (PT == 2) epi_apply_pairs<EPI, 4>(acc[t][mt], acc[t + 1][mt], sc, pre, out, task, row0 + rbase + m, m < M, lane);
+      else epi_apply<EPI>(acc[t][mt], sc, pre, out, task, row0 + rbase + m, m < M, N, lane);
     }
   }
 }
@@ -885,34 +903,32 @@ __global__ __launch_bounds__(512) void gemm_block_kernel(const uint4* __restrict
 template <int EPI>
 __global__ __launch_bounds__(64 * EE_REDUCE_TASKS) void gemm_rows_reduce_kernel(const float* __restrict__ partial, int ksplit, int ntiles,
                                                                                 int TMT, int row0, int M, int N, GemmOut out) {
-  constexpr int NB = (EPI == EPI_SWIGLU || EPI == EPI_ROPE) ? 2 : 1;
   __shared__ float ssq[EE_REDUCE_TASKS][16];
   const int lane = threadIdx.x & 63, mc = lane & 15, wave = threadIdx.x >> 6;
   const int mtiles = (M + 15) >> 4;
   const int mt = blockIdx.x % mtiles, group = blockIdx.x / mtiles, task = group * EE_REDUCE_TASKS + wave;
-  const bool active = task * NB < ntiles;
+  const bool active = task < ntiles;
   const int m = mt * 16 + mc;
   float ss = 0.f;
   if (active) {
     EpiPre pre;
     epi_prefetch<EPI>(pre, out, task, row0 + m, m < M, lane);
     float sc[1] = {out.nin.inv_rms ? out.nin.inv_rms[min(m, M - 1)] : 1.0f};
-    f32x4 acc[NB];
+    const bool sums = !out.nin.inv_rms && out.nin.ssq;
+    NormPartials<1> part;
+    if (sums) norm_request<1>(part, out.nin, row0 + mt * 16, 1, 1, 0, lane);
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    const f32x4* pp = (const f32x4*)partial + ((size_t)task * TMT + mt) * 64 + lane;
+    for (int s0 = 0; s0 < ksplit; s0 += 8) {
+      f32x4 t[8];
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-      const f32x4* pp = (const f32x4*)partial + ((size_t)(task * NB + nb) * TMT + mt) * 64 + lane;
-      for (int s0 = 0; s0 < ksplit; s0 += 8) {
-        f32x4 t[8];
+      for (int i = 0; i < 8; ++i) t[i] = __builtin_nontemporal_load(pp + (size_t)min(s0 + i, ksplit - 1) * ntiles * TMT * 64);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) t[i] = __builtin_nontemporal_load(pp + (size_t)min(s0 + i, ksplit - 1) * ntiles * TMT * 64);
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-          if (s0 + i < ksplit) acc[nb] += t[i];
-      }
+      for (int i = 0; i < 8; ++i)
+        if (s0 + i < ksplit) acc += t[i];
     }
-    if (!out.nin.inv_rms && out.nin.ssq) norm_factors<1>(sc, out.nin, row0 + mt * 16, 1, 1, lane);
-    epi_apply<EPI>(acc[0], acc[NB - 1], sc[0], pre, out, task, row0 + m, m < M, N, lane, &ss);
+    if (sums) norm_factors<1>(sc, part, out.nin, row0 + mt * 16, 1, 1, lane);
+    epi_apply<EPI>(acc, sc[0], pre, out, task, row0 + m, m < M, N, lane, &ss);
   }
   if (EPI == EPI_ADD && out.nout.xn) {
     if (lane < 16) ssq[wave][lane] = ss;
@@ -990,8 +1006,7 @@ static bool launch_gemm_rows(hipStream_t st, int epi, const uint4* W, int ntiles
   }
 #undef ROWS_LAUNCH
   if (ksr > 1) {
-    const int nb = (epi == EPI_SWIGLU || epi == EPI_ROPE) ? 2 : 1;
-    dim3 rgrid(ceil_div(ntiles / nb, EE_REDUCE_TASKS) * ceil_div(M, 16));
+    dim3 rgrid(ceil_div(ntiles, EE_REDUCE_TASKS) * ceil_div(M, 16));
     switch (epi) {
       case EPI_ADD: hipLaunchKernelGGL((gemm_rows_reduce_kernel<EPI_ADD>), rgrid, rblk, 0, st, scratch, ksr, ntiles, TMT, row0, M, N, out); break;
       case EPI_SWIGLU: hipLaunchKernelGGL((gemm_rows_reduce_kernel<EPI_SWIGLU>), rgrid, rblk, 0, st, scratch, ksr, ntiles, TMT, row0, M, N, out); break;
@@ -1111,10 +1126,6 @@ static bool runs_blocked(bool wide, int ntiles, int ktiles, int M) {
   return ktiles <= ntiles ? M > 544 || blocks >= 128 : M > 1024 || blocks >= 256;
 }
 
-// up to 16 rows the skinny kernel serves every matrix, up to 32 those under 128 MB (the small projections are quicker without
-// the K-share reduction pass of the row-tiled kernel)
-int bf16_gemm_few_rows(int ntiles, int ktiles) { return (size_t)ntiles * ktiles * 1024 >= ((size_t)128 << 20) ? 16 : 32; }
-
 // more than 16 rows from row 0 of the operand; returns how many partial sums of squares per row an EPI_ADD call left
 int bf16_gemm_rows(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N,
                     const GemmOut& out0, float* scratch, float* inv_rms, int inv_cap) {
@@ -1153,7 +1164,7 @@ int bf16_gemm_rows(hipStream_t st, int epi, const bf16_t* W, int ntiles, int kti
       continue;
     }
     const int bt = rows_blocks_form(ntiles, ktiles, epi == EPI_ADD ? min(M, blk) : mc);
-    if (m0 > 0 && mc <= bf16_gemm_few_rows(ntiles, ktiles) && (epi != EPI_ADD || bt > 0 || rows_ksplit(ntiles, ktiles) == 1)) {
+    if (m0 > 0 && mc <= EE_STRIP_ROWS && (epi != EPI_ADD || bt > 0 || rows_ksplit(ntiles, ktiles) == 1)) {
       bf16_gemm(st, epi, W, ntiles, ktiles, A, mc, N, out, m0);        // (as such a call by itself; leaves a partial sum per weight tile)
       continue;
     }
@@ -1174,25 +1185,13 @@ int bf16_gemm_rows(hipStream_t st, int epi, const bf16_t* W, int ntiles, int kti
   return parts_left;
 }
 
-template <int MT, int U>
+template <int MT, int NS, int U>
 static void launch_gemm_mt(hipStream_t st, int epi, const uint4* W, int ntiles, int ktiles, const uint4* A, int row0, int M, int N,
                            const GemmOut& out, int nw, int ksplit) {
-  dim3 blk(64 * nw);
-  const int tpw = nw / ksplit;
-  const int ntasks = (epi == EPI_SWIGLU || epi == EPI_ROPE) ? ntiles / 2 : ntiles;
-  dim3 grid(ceil_div(ntasks, tpw));
+  dim3 blk(64 * nw), grid(ceil_div(ntiles, nw / ksplit * NS));
   LaunchEvents* ev = g_launch_events;
   g_launch_events = nullptr;                       // one launch per offer
-#define SKINNY_LAUNCH(E_)                                                                                                        \
-  do {                                                                                                                           \
-    if (ev) {                                                                                                                    \
-      hipExtLaunchKernelGGL((gemm_skinny_kernel<MT, E_, U>), grid, blk, 0, st, ev->start, ev->stop, 0, W, ktiles, ntasks, A, row0, M, N, \
-                            out, ksplit);                                                                                        \
-      ev->used = true;                                                                                                           \
-    } else {                                                                                                                     \
-      hipLaunchKernelGGL((gemm_skinny_kernel<MT, E_, U>), grid, blk, 0, st, W, ktiles, ntasks, A, row0, M, N, out, ksplit);      \
-    }                                                                                                                            \
-  } while (0)
+#define SKINNY_LAUNCH(E_) launch_timed(ev, gemm_skinny_kernel<MT, E_, NS, U>, grid, blk, st, W, ktiles, ntiles, A, row0, M, N, out, ksplit)
   switch (epi) {
     case EPI_ADD: SKINNY_LAUNCH(EPI_ADD); break;
     case EPI_SWIGLU: SKINNY_LAUNCH(EPI_SWIGLU); break;
@@ -1202,34 +1201,62 @@ static void launch_gemm_mt(hipStream_t st, int epi, const uint4* W, int ntiles, 
 #undef SKINNY_LAUNCH
 }
 
-// launch shape: nw waves per workgroup, ksplit of them per task, k-tiles per register set U (4 or 8; 4 at 17..32 rows)
-void bf16_gemm_cfg(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N,
-                   const GemmOut& out, int nw, int ksplit, int U, int row0) {
-  const uint4* Wc = (const uint4*)W;
-  const uint4* Ac = (const uint4*)A;
-  // (the session sends calls of more than 32 rows to the row-tiled kernel; should one arrive here it goes in passes of 32)
-  for (int m0 = row0; m0 < row0 + M; m0 += 32) {
-    const int mc = min(32, row0 + M - m0);
-    if (mc <= 16) {
-      if (U >= 8) launch_gemm_mt<1, 8>(st, epi, Wc, ntiles, ktiles, Ac, m0, mc, N, out, nw, ksplit);
-      else launch_gemm_mt<1, 4>(st, epi, Wc, ntiles, ktiles, Ac, m0, mc, N, out, nw, ksplit);
-    } else {
-      launch_gemm_mt<2, 4>(st, epi, Wc, ntiles, ktiles, Ac, m0, mc, N, out, nw, ksplit);
-    }
+// Launch shape for M <= 32 rows, from sweeps over the matrices of the 8B and 70B widths with cold weights (us; {strips, waves,
+// K parts, U}).  What bounds them is the memory path of a compute unit, which takes in weights and rows together at 35-50 GB/s,
+// so the shape has to give every compute unit the same share of the strips and, with several strips a wave, read the rows less
+// often.  `load`: strips on the busiest compute unit.
+//   wide (>= 768 strips): a strip per wave, as many waves a workgroup as deal the strips most evenly: gate/up at 9 rows 8B 40.0
+//     with four waves on 224 units, 38.9 with seven on 256; 70B 148 / 141.  At 17..32 rows seven strips a wave and K over eight
+//     waves where that deals them evenly too (the rows are then read once for seven strips): 8B 40.3, 70B 144 (row-tiled kernel
+//     44.2, 147); else one strip a wave: head of 32000 tokens 47.9 (50.3).
+//   narrow: K over four or eight waves.  Two or four strips a wave where that makes load * (1 + row tiles / strips) smaller: 70B
+//     QKV (640 strips) at 9 / 24 rows 32.8 / 37.9 with four, 35.1 / 41.6 with one; 70B down 70.2 / 74.4 with two, 77.4 / 92.6; 8B
+//     QKV (384) 13.3 / 15.5 with two, 13.8 / 16.6.  At one row tile, strips that fill the chip evenly and a K below 512 k-tiles stay
+//     at one a wave (70B O 25.9 / 27.0).
+static int strip_load(int ntiles, int per_wg) { return ceil_div(ceil_div(ntiles, per_wg), 256) * per_wg; }
+static StripShape strip_shape(int ntiles, int ktiles, int M) {
+  const int mt = M > 16 ? 2 : 1;
+  if (ntiles >= 768) {
+    if (mt == 2 && 256 * strip_load(ntiles, 7) <= ntiles * 23 / 20) return StripShape{7, 8, 8, 1};
+    int nw = 8;
+    for (int w = 7; w >= 4; --w)
+      if (strip_load(ntiles, w) < strip_load(ntiles, nw)) nw = w;
+    return StripShape{1, nw, 1, mt == 2 ? 4 : 8};
   }
+  int ns = 1;
+  if (ntiles >= 320 && (mt == 2 || ntiles % 256 != 0 || ktiles >= 512))
+    for (int n = 2; n <= 4; n *= 2)
+      if (strip_load(ntiles, n) * (n + mt) * ns < strip_load(ntiles, ns) * (ns + mt) * n) ns = n;
+  if (ns == 4) return StripShape{4, 8, 8, mt == 2 ? 2 : 4};
+  if (ns == 2) return StripShape{2, 4, 4, 4};
+  int ksplit = ntiles >= 200 && ntiles < 320 && ktiles >= 256 && mt == 1 ? 8 : 4;
+  while (ksplit > 1 && ktiles / ksplit < 4) ksplit >>= 1;
+  return StripShape{1, max(4, ksplit), ksplit, mt == 2 ? 4 : 8};
 }
 
-// Launch shape by task count (measured on MI355X at M <= 16): many tasks -> one wave streams a whole
-// strip (no reduction, deepest pipeline); few tasks -> split K over the waves of a workgroup so that
-// one to two thousand waves are in flight (the 70B projections with 320-512 tasks: two waves per task).  M may exceed 32: rows then go in passes of 32 (weights re-streamed).
+void bf16_gemm_cfg(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N,
+                   const GemmOut& out, const StripShape& sh, int row0) {
+  const uint4* Wc = (const uint4*)W;
+  const uint4* Ac = (const uint4*)A;
+#define STRIPS(MT_, NS_, U_) launch_gemm_mt<MT_, NS_, U_>(st, epi, Wc, ntiles, ktiles, Ac, row0, M, N, out, sh.nw, sh.ksplit)
+  if (M <= 16) {
+    if (sh.ns == 4) STRIPS(1, 4, 4);
+    else if (sh.ns == 2) STRIPS(1, 2, 4);
+    else STRIPS(1, 1, 8);
+  } else {
+    if (sh.ns == 7) STRIPS(2, 7, 1);
+    else if (sh.ns == 4) STRIPS(2, 4, 2);
+    else if (sh.ns == 2) STRIPS(2, 2, 4);
+    else STRIPS(2, 1, 4);
+  }
+#undef STRIPS
+}
+
 void bf16_gemm(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N, const GemmOut& out, int row0) {
-  const int ntasks = (epi == EPI_SWIGLU || epi == EPI_ROPE) ? ntiles / 2 : ntiles;
-  // launch shape by task count, from sweeps over the 8B and 70B matrix shapes at 9 rows
-  int ksplit = ntasks >= 768 ? 1 : (ntasks >= 320 ? 2 : (ntasks >= 200 ? 8 : 4));
-  while (ksplit > 1 && ktiles / ksplit < 4) ksplit >>= 1;
-  const int U = (ntasks >= 768 || ntasks < 200 || ktiles / ksplit >= 32) ? 8 : 4;
-  const int nw = ksplit > 4 ? ksplit : 4;
-  bf16_gemm_cfg(st, epi, W, ntiles, ktiles, A, M, N, out, nw, ksplit, U, row0);
+  for (int m0 = 0; m0 < M; m0 += 32) {      // (calls of more than 32 rows go to the row-tiled kernel; should one arrive here it goes in passes of 32)
+    const int mc = min(32, M - m0);
+    bf16_gemm_cfg(st, epi, W, ntiles, ktiles, A, mc, N, out, strip_shape(ntiles, ktiles, mc), row0 + m0);
+  }
 }
 
 // one workgroup of 1024 threads per row; the row's partials lie side by side ([row][tile]), so a wave's load is one

@@ -115,7 +115,7 @@ int ee_tensor_map(const ee_model* m, int tid, int layer, TensorMap* t) {
     default: break;
   }
   const LayerLoc& L = m->L[layer];
-  const int qi = m->bf16 ? 3 : 0;   // bf16 models keep the rotary halves of every head in adjacent tiles
+  const int qi = m->bf16 ? 3 : 0;   // bf16 models keep the rotary halves of every head in the same tiles
   switch (tid) {
     case EE_T_G1: *t = {1, d, 1, L.g1, 0, 0, 0, D}; break;
     case EE_T_G2: *t = {1, d, 1, L.g2, 0, 0, 0, D}; break;
@@ -123,8 +123,8 @@ int ee_tensor_map(const ee_model* m, int tid, int layer, TensorMap* t) {
     case EE_T_WK: *t = {0, c.n_kv_heads * D, d, L.qkv.off, c.n_q_heads * D, qi, L.qkv.Kp, D}; break;
     case EE_T_WV: *t = {0, c.n_kv_heads * D, d, L.qkv.off, (c.n_q_heads + c.n_kv_heads) * D, qi, L.qkv.Kp, D}; break;
     case EE_T_WO: *t = {0, d, c.n_q_heads * D, L.o.off, 0, 0, L.o.Kp, D}; break;
-    case EE_T_WGATE: *t = {0, c.d_ffn, d, L.gu.off, 0, 1, L.gu.Kp, D}; break;
-    case EE_T_WUP: *t = {0, c.d_ffn, d, L.gu.off, 0, 2, L.gu.Kp, D}; break;
+    case EE_T_WGATE: *t = {0, c.d_ffn, d, L.gu.off, 0, m->bf16 ? 4 : 1, L.gu.Kp, D}; break;
+    case EE_T_WUP: *t = {0, c.d_ffn, d, L.gu.off, 0, m->bf16 ? 5 : 2, L.gu.Kp, D}; break;
     case EE_T_WDOWN: *t = {0, d, c.d_ffn, L.down.off, 0, 0, L.down.Kp, D}; break;
     default: ee_set_error("unknown tensor id %d", tid); return EE_ERR_ARG;
   }

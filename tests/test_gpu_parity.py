@@ -104,6 +104,19 @@ def test_verify_rounds_match_oracle(name, cfg, ctx, k, bonus):
     sess.close(); model.close()
 
 
+@pytest.mark.parametrize("ctx,k", [([70], 7), ([70, 33], 8)], ids=["rows8", "rows18"])
+@pytest.mark.parametrize("d,ffn", [(256, 14336), (272, 14352), (272, 6160), (272, 5136), (256, 3088)])
+def test_strips_dealt_in_every_shape(d, ffn, ctx, k):
+    """Gate/up matrices of 1792 and 1794 strips (seven waves a workgroup, or seven strips a wave beyond 16 rows: even and
+    with a last workgroup of two), 770 (a ragged last workgroup), 642 (four strips a wave, the last of which holds two) and 386
+    (two strips a wave); K of 8 k-tiles and of 9, whose eight shares leave waves without any."""
+    tol = TOL["bf16"]
+    O, model, sess, first, gfirst = _setup(bf16_small(n_layers=3, exit_draft=1, exit_inter=2, d_model=d, d_ffn=ffn), 41, ctx, 3 * (k + 1) + 2)
+    assert gfirst.tolist() == first.tolist()
+    _round(O, sess, k, 0.8, np.random.default_rng(5), True, tol)
+    sess.close(); model.close()
+
+
 @pytest.mark.parametrize("row_tiles", [0, 4, 8, 16, 104, 108])
 def test_both_forms_of_the_narrow_projection_gemm_match_oracle(row_tiles):
     """The narrow projections (O, down, QKV, adapters) of a call with more than 16 rows run either with K shares and
