@@ -7,6 +7,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import weakref
 from typing import Optional, Sequence, Tuple
 
 import numpy as np
@@ -389,14 +390,14 @@ def ee_debug_enable_logits(session: int, on: bool) -> None:
     _chk(lib.ee_debug_enable_logits(session, int(on)))
 
 
-def ee_debug_last_logits(session: int, max_rows: int, vocab: int) -> np.ndarray:
-    out, n = np.empty((max_rows, vocab), np.float32), C.c_int32()
+def ee_debug_last_logits(session: int, max_rows: int, vocab: int, out: Optional[np.ndarray] = None) -> np.ndarray:
+    out, n = np.empty((max_rows, vocab), np.float32) if out is None else out, C.c_int32()
     _chk(lib.ee_debug_last_logits(session, _p_f32(out), max_rows, C.byref(n)))
     return out[:n.value]
 
 
-def ee_debug_last_hidden(session: int, max_rows: int, d: int) -> np.ndarray:
-    out, n = np.empty((max_rows, d), np.float32), C.c_int32()
+def ee_debug_last_hidden(session: int, max_rows: int, d: int, out: Optional[np.ndarray] = None) -> np.ndarray:
+    out, n = np.empty((max_rows, d), np.float32) if out is None else out, C.c_int32()
     _chk(lib.ee_debug_last_hidden(session, _p_f32(out), max_rows, C.byref(n)))
     return out[:n.value]
 
@@ -493,6 +494,42 @@ class Model:
             pass
 
 
+class _ResultBlocks:
+    """Page-locked host memory for the rows a session returns.  The GPU writes such an array directly (2.4 MB of hidden rows 55 us);
+    into ordinary fresh memory the runtime copies through its own staging buffer, 1 MiB at a time, and every page is faulted in
+    (225 us).  A block is lent to one array at a time and free again once that array and its views are gone; up to BLOCKS blocks of
+    at most LARGEST bytes per session, other requests get ordinary memory.  The memory goes with the session (a lent block with
+    its array)."""
+    BLOCKS, LARGEST, SMALLEST = 6, 16 << 20, 1 << 16
+
+    def __init__(self, rows: int, cols: int):
+        self.nbytes = min(rows * cols * 4, self.LARGEST)
+        self.blocks = []                       # [tensor, weak reference to the array it is lent to]
+        for _ in range(2 if self.nbytes >= self.SMALLEST else 0):
+            self._add()
+
+    def _add(self):
+        import torch
+        try:
+            self.blocks.append([torch.empty(self.nbytes, dtype=torch.uint8, pin_memory=True), None])
+        except RuntimeError:                   # no more page-locked memory: ordinary memory does
+            return None
+        return self.blocks[-1]
+
+    def take(self, rows: int, cols: int) -> Optional[np.ndarray]:
+        need = rows * cols * 4
+        if need > self.nbytes or need < self.SMALLEST:
+            return None
+        block = next((b for b in self.blocks if b[1] is None or b[1]() is None), None)
+        if block is None and len(self.blocks) < self.BLOCKS:
+            block = self._add()
+        if block is None:
+            return None
+        whole = block[0].numpy()               # (views keep it alive: its own base is the tensor, not another array)
+        block[1] = weakref.ref(whole)
+        return whole[:need].view(np.float32).reshape(rows, cols)
+
+
 class Session:
     """Owns the device arena of one session; methods forward to the C entry points."""
 
@@ -503,6 +540,7 @@ class Session:
         self.nbytes = arena_bytes or ee_session_bytes(model.handle, batch, max_ctx, max_rows, total_pages)
         self._buf, ptr = _arena(self.nbytes)
         self.handle = ee_session_create(model.handle, batch, max_ctx, max_rows, total_pages, ptr, self.nbytes, model.stream)
+        self._hidden, self._logits = _ResultBlocks(batch * max_rows, model.cfg.d_model), None
 
     def prefill(self, prompts: Sequence[np.ndarray]) -> np.ndarray:
         lens = np.array([len(p) for p in prompts], np.int32)
@@ -576,12 +614,16 @@ class Session:
 
     def enable_logits(self, on: bool = True) -> None:
         ee_debug_enable_logits(self.handle, on)
+        if on and self._logits is None:
+            self._logits = _ResultBlocks(self.batch * self.max_rows, self.model.cfg.vocab)
 
     def last_logits(self, max_rows: Optional[int] = None) -> np.ndarray:
-        return ee_debug_last_logits(self.handle, max_rows or max(512, self.batch * self.max_rows), self.model.cfg.vocab)
+        rows, vocab = max_rows or max(512, self.batch * self.max_rows), self.model.cfg.vocab
+        return ee_debug_last_logits(self.handle, rows, vocab, self._logits and self._logits.take(rows, vocab))
 
     def last_hidden(self, max_rows: Optional[int] = None) -> np.ndarray:
-        return ee_debug_last_hidden(self.handle, max_rows or max(512, self.batch * self.max_rows), self.model.cfg.d_model)
+        rows, d = max_rows or max(512, self.batch * self.max_rows), self.model.cfg.d_model
+        return ee_debug_last_hidden(self.handle, rows, d, self._hidden.take(rows, d))
 
     def read_kv(self, seq: int, layer: int, pos0: int, n: int):
         return ee_debug_read_kv(self.handle, seq, layer, pos0, n, self.model.cfg.n_kv_heads, self.model.cfg.head_dim)
@@ -601,7 +643,7 @@ class Session:
     def close(self) -> None:
         if self.handle:
             ee_session_free(self.handle)
-            self.handle, self._buf = None, None
+            self.handle, self._buf, self._hidden, self._logits = None, None, None, None
 
     def __del__(self):
         try:

@@ -360,6 +360,32 @@ def test_batched_equals_solo(pinned):
         hs.ee_debug_gemm_row_blocks(-1)
 
 
+def test_returned_rows_outlive_later_calls_and_the_session():
+    """Rows come back in page-locked blocks that are lent to one array at a time: eight arrays held at once (more than there
+    are blocks), a view of the first kept alone, then the session closed -- every one still holds what its call returned."""
+    cfg = bf16_small()
+    k = 8
+    O, model, sess, _, _ = _setup(cfg, 58, [60, 40], 3 * (k + 1) + 2)
+    held, want = [], []
+    for i in range(8):
+        sess.draft_inject(np.random.default_rng(i).integers(0, cfg.vocab, (2, k)).astype(np.int32))
+        sess.verify_intermediate()
+        rows = sess.last_logits(18)
+        assert rows.shape == (18, cfg.vocab) and all(not np.shares_memory(rows, h) for h in held)
+        held.append(rows); want.append(rows.copy())
+        for b in range(2):
+            sess.rollback(b, 0b111, O.seqs[b].len[0])
+    assert any(not np.array_equal(want[0], w) for w in want[1:])
+    view = held[0][3:5]
+    del held[0], rows
+    again = sess.last_logits(18)
+    assert not np.shares_memory(again, view) and np.array_equal(again, want[7])
+    sess.close(); model.close()
+    assert np.array_equal(view, want[0][3:5])
+    for h, w in zip(held, want[1:]):
+        assert np.array_equal(h, w)
+
+
 def test_rerun_is_bit_identical():
     cfg = bf16_d128()
     k = 8
