@@ -578,22 +578,27 @@ __global__ __launch_bounds__(64 * EE_MAX_WAVES) void gemm_skinny_kernel(const ui
 // gemm_rows_reduce_kernel sums the K shares in a fixed order and runs the same epilogue.
 // ---------------------------------------------------------------------------------------------
 #define EE_ROWS_TN 4
+// Whether the partial tiles of K shares stay in the L2 for the reduce kernel, else they stream to memory.  Measured with the
+// reduction, 8B widths, us, streamed / kept: QKV at 36 / 144 / 192 rows 20.0 / 18.6, 28.4 / 26.0, 32.5 / 31.5 (70B at 144: 49.5 / 46.1);
+// O at 36 / 64 rows 14.5 / 13.4, 15.4 / 14.0; down at 64 / 81 / 112 rows 29.4 / 28.6, 32.5 / 33.8, 34.3 / 35.6: its seven shares of more
+// than 64 rows are written all at once at the end of the launch and are better out of the way.
+__device__ inline bool keep_partials(int epi, int M) { return epi == EPI_ROPE || M <= 64; }
 // s_waitcnt immediate: at most n vector-memory loads outstanding, all LDS reads done, export counter untouched
 __host__ __device__ constexpr int waitcnt_vm_lgkm0(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4); }
 
-template <int TMT, int EPI, bool FULL, int TN>
+template <int TMT, int EPI, bool FULL, int TN, int WT = 2 * TN>
 __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict__ W, int ktiles, int ntiles,
                                                         const uint4* __restrict__ A, int row0, int M_all, int N, GemmOut out,
                                                         int per, float* __restrict__ partial) {
   // rows row0 .. row0+M_all-1 of the operand (row0 a multiple of 16), of which this workgroup takes the block of
   // TMT*16 rows that blockIdx.z names; the deferred-norm factors and the K-share partials are indexed from row0,
   // everything the epilogue touches by the row itself
-  static_assert(TN == 2 || TN == 4, "weight tiles per wave");
+  static_assert((TN == 2 || TN == 4) && (WT == 2 * TN || WT == 2 * TN - 1), "weight tiles per wave");
   const int bx = blockIdx.x, rbase = blockIdx.z * (TMT * 16), M = min(M_all - rbase, TMT * 16);
   constexpr int TMW = TMT / 4;                      // row tiles per wave
   static_assert(TMT % 4 == 0 && TMT >= 4 && TMT <= 32, "row tiles split four ways");
-  constexpr int STAGE = (2 * TN + TMT) * 64;        // 16-byte units: weight tiles first, then row tiles
-  constexpr int S = (160 / (2 * TN + TMT)) & ~1;    // stages in the ring: what 160 KiB of LDS holds (even: fragments alternate between two register sets)
+  constexpr int STAGE = (WT + TMT) * 64;        // 16-byte units: weight tiles first, then row tiles
+  constexpr int S = (160 / (WT + TMT)) & ~1;    // stages in the ring: what 160 KiB of LDS holds (even: fragments alternate between two register sets)
   constexpr int XHI = (TMT + 7) / 8;                // row tiles a wave requests per stage at most: wave, wave+8, ...
   constexpr int LHI = 1 + XHI;                      // requests per stage at most (one weight tile, XHI row tiles)
   static_assert((S - 1) * LHI < 64, "the load counter has six bits");
@@ -603,7 +608,7 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
   const int rq = wave_s >> 1, nh = wave_s & 1;
   const int rqv = wave >> 1, nhv = wave & 1;                    // the same again from the vector register: one address register
                                                                 // serves all LDS reads, the slots being constant offsets from it
-  const int nt0 = bx * (2 * TN) + nh * TN;                      // first weight tile of this wave
+  const int nt0 = bx * WT + nh * TN;                      // first weight tile of this wave
   // Row tiles of this wave: TMW in a row when all of them hold rows (FULL: the guards below fold away), else
   // rq, rq+4, ..., so that the tiles past the last row, which are neither requested nor multiplied, are spread
   // over the four wave pairs.  The launcher picks the smallest TMT that holds the rows, so the unused tiles are
@@ -629,12 +634,12 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
   // this wave's last row tile holds rows: XHI requests per stage, else one less; with four weight tiles per
   // workgroup (TN = 2) only the first four waves request one
   const bool hi = (FULL && TMT % 8 == 0) || wave_s + 8 * (XHI - 1) < mt_used;
-  const bool wreq = TN >= 4 || wave_s < 2 * TN;
+  const bool wreq = WT >= 8 || wave_s < WT;
   // LDS byte address of this wave's weight tile in stage 0 as a scalar: every request's LDS address is this plus a
   // constant, so none of them occupies a vector register (measured: 3-4 % at 24 and 32 row tiles)
   const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(lptr_t)&ring[0][0]) + 1024u * wave_s;
 #define ROWS_LDS(slot_, tile_) ((lptr_t)(size_t)(lds0 + 16u * ((slot_) * STAGE + (tile_) * 64)))
-  const u32x4* wsrc = (const u32x4*)W + (size_t)min(bx * (2 * TN) + wave, ntiles - 1) * ktiles * 64 + lane;
+  const u32x4* wsrc = (const u32x4*)W + (size_t)min(bx * WT + wave, ntiles - 1) * ktiles * 64 + lane;
   const u32x4* xsrc = (const u32x4*)A + (size_t)(((row0 + rbase) >> 4) + wave) * ktiles * 64 + lane;
   // (weights: streaming hint)
 #define ROWS_REQUEST(slot_, kt_)                                                                              \
@@ -643,10 +648,10 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
     if (wreq) __builtin_amdgcn_global_load_lds((gptr_t)(wsrc + k_), ROWS_LDS(slot_, 0), 16, 0, 2);                \
     _Pragma("unroll") for (int j = 0; j < XHI - 1; ++j)                                                       \
       __builtin_amdgcn_global_load_lds((gptr_t)(xsrc + (size_t)(8 * j) * ktiles * 64 + k_),                   \
-                                       ROWS_LDS(slot_, 2 * TN + 8 * j), 16, 0, 0);                            \
+                                       ROWS_LDS(slot_, WT + 8 * j), 16, 0, 0);                            \
     if (hi)                                                                                                   \
       __builtin_amdgcn_global_load_lds((gptr_t)(xsrc + (size_t)(8 * (XHI - 1)) * ktiles * 64 + k_),           \
-                                       ROWS_LDS(slot_, 2 * TN + 8 * (XHI - 1)), 16, 0, 0);                    \
+                                       ROWS_LDS(slot_, WT + 8 * (XHI - 1)), 16, 0, 0);                    \
   } while (0)
 #define ROWS_WAIT(stages_)                                                                                    \
   do {                                                                                                        \
@@ -658,7 +663,7 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
 #define ROWS_READ(buf_, slot_)                                                                               \
   do {                                                                                                        \
     const u32x4* wl_ = &ring[slot_][(nhv * TN) * 64 + lane];                                                  \
-    const u32x4* xl_ = &ring[slot_][(2 * TN + (FULL ? rqv * TMW : rqv)) * 64 + lane];                         \
+    const u32x4* xl_ = &ring[slot_][(WT + (FULL ? rqv * TMW : rqv)) * 64 + lane];                         \
     _Pragma("unroll") for (int tn = 0; tn < TN; ++tn) wf[buf_][tn] = wl_[tn * 64];                            \
     _Pragma("unroll") for (int mt = 0; mt < TMW; ++mt) xf[buf_][mt] = xl_[mt * MT_STEP * 64];                 \
   } while (0)
@@ -680,7 +685,7 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
     const int cb_ = (u_) & 1, nb_ = cb_ ^ 1, ns_ = ((u_) + 1) % S;                                            \
     ROWS_REQUEST(((u_) + S - 1) % S, kt + (u_) + S - 1);                                                      \
     const u32x4* wl_ = &ring[ns_][(nhv * TN) * 64 + lane];                                                    \
-    const u32x4* xl_ = &ring[ns_][(2 * TN + (FULL ? rqv * TMW : rqv)) * 64 + lane];                           \
+    const u32x4* xl_ = &ring[ns_][(WT + (FULL ? rqv * TMW : rqv)) * 64 + lane];                           \
     const bool on_ = !(guard_) || kt + (u_) < kt1;                                                            \
     __builtin_amdgcn_sched_barrier(0);                                                                        \
     _Pragma("unroll") for (int mt = 0; mt < TMW; ++mt) {                                                      \
@@ -721,7 +726,8 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
 #pragma unroll
       for (int mt = 0; mt < TMW; ++mt)
         if (mt_first + mt * MT_STEP < mt_used)
-          __builtin_nontemporal_store(acc[tn][mt], pp + ((size_t)(nt0 + tn) * TMT + mt_first + mt * MT_STEP) * 64);
+          if (keep_partials(EPI, M_all)) pp[((size_t)(nt0 + tn) * TMT + mt_first + mt * MT_STEP) * 64] = acc[tn][mt];
+          else __builtin_nontemporal_store(acc[tn][mt], pp + ((size_t)(nt0 + tn) * TMT + mt_first + mt * MT_STEP) * 64);
     }
     return;
   }
@@ -741,14 +747,16 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
 #pragma unroll
   for (int t = 0; t < TN; t += PT) {
     const int task = nt0 + t;
-    if (task >= ntiles) continue;
+    if (task >= ntiles || (WT < 2 * TN && nh && t == TN - 1)) continue;
+    const bool lone = PT == 2 && WT < 2 * TN && nh && t == TN - 2;      // (the wave's last tile is not there)
 #pragma unroll
     for (int mt = 0; mt < TMW; ++mt) {
       const int m = (mt_first + mt * MT_STEP) * 16 + mc;
       if (mt_first + mt * MT_STEP >= mt_used) continue;
       EpiPre pre;
       epi_prefetch<EPI, 2 * PT>(pre, out, task, row0 + rbase + m, m < M, lane);
-      if constexpr (PT == 2) epi_apply_pairs<EPI, 4>(acc[t][mt], acc[t + 1][mt], sc[mt], pre, out, task, row0 + rbase + m, m < M, lane);
+      if (lone) epi_apply_pairs<EPI, 2>(acc[t][mt], acc[t][mt], sc[mt], pre, out, task, row0 + rbase + m, m < M, lane);
+      else if constexpr (PT == 2) epi_apply_pairs<EPI, 4>(acc[t][mt], acc[t + 1][mt], sc[mt], pre, out, task, row0 + rbase + m, m < M, lane);
       else epi_apply<EPI>(acc[t][mt], sc[mt], pre, out, task, row0 + rbase + m, m < M, N, lane);
     }
   }
@@ -896,7 +904,9 @@ __global__ __launch_bounds__(512) void gemm_block_kernel(const uint4* __restrict
   else gemm_block_body<EPI, TN, false>(ring, W, ktiles, ntiles, A, row0, rbase, M, N, out, bx);
 }
 
-// Sums the K shares of a row tile and runs the epilogue, one wave per task; the four waves of a workgroup take four tasks of
+// Sums the K shares of a row tile and runs the epilogue, one wave per task.  Where the partial tiles are kept in the L2
+// (keep_partials) the workgroups of a column group (eight weight tiles) run on the XCD that its K shares ran on: workgroup id mod 8,
+// where the number of columns is a multiple of 8.  The four waves of a workgroup take four tasks of
 // the same row tile and leave one partial sum of squares per row for the four of them, so that the next projection finds a
 // quarter of the partials and reads its factors itself (a launch of its own for that took 4.5 us).
 #define EE_REDUCE_TASKS 4
@@ -906,7 +916,16 @@ __global__ __launch_bounds__(64 * EE_REDUCE_TASKS) void gemm_rows_reduce_kernel(
   __shared__ float ssq[EE_REDUCE_TASKS][16];
   const int lane = threadIdx.x & 63, mc = lane & 15, wave = threadIdx.x >> 6;
   const int mtiles = (M + 15) >> 4;
-  const int mt = blockIdx.x % mtiles, group = blockIdx.x / mtiles, task = group * EE_REDUCE_TASKS + wave;
+  constexpr int QUADS = 2 * EE_ROWS_TN / EE_REDUCE_TASKS;
+  int mt, group;
+  if (keep_partials(EPI, M)) {
+    const int i = blockIdx.x >> 3, column = i / (mtiles * QUADS) * 8 + (blockIdx.x & 7);
+    mt = i % mtiles; group = column * QUADS + i / mtiles % QUADS;
+  } else {
+    mt = blockIdx.x % mtiles; group = blockIdx.x / mtiles;
+  }
+  const int task = group * EE_REDUCE_TASKS + wave;
+  if (group * EE_REDUCE_TASKS >= ntiles) return;      // whole workgroup
   const bool active = task < ntiles;
   const int m = mt * 16 + mc;
   float ss = 0.f;
@@ -958,6 +977,9 @@ __global__ __launch_bounds__(256) void norm_factor_kernel(const float* __restric
   if (t == 0) inv_rms[row] = 1.0f / sqrtf(ss * inv_d + eps);
 }
 
+// strips (weight tiles) on the busiest compute unit when workgroups take per_wg each
+static int strip_load(int ntiles, int per_wg) { return ceil_div(ceil_div(ntiles, per_wg), 256) * per_wg; }
+
 // number of K shares the row-tiled GEMM runs with: enough workgroups for the chip, at least 16 k-tiles each
 static int rows_ksplit(int ntiles, int ktiles) {
   const int groups = ceil_div(ntiles, 2 * EE_ROWS_TN);
@@ -998,6 +1020,17 @@ static bool launch_gemm_rows(hipStream_t st, int epi, const uint4* W, int ntiles
     if (full) launch_timed(ev, gemm_rows_kernel<TMT, E_, true, EE_ROWS_TN>, grid, blk, st, W, ktiles, ntiles, A, row0, M, N, out, per, scratch); \
     else launch_timed(ev, gemm_rows_kernel<TMT, E_, TMT == 32, EE_ROWS_TN>, grid, blk, st, W, ktiles, ntiles, A, row0, M, N, out, per, scratch); \
   } while (0)
+  // Seven weight tiles a workgroup where that deals a wide matrix more evenly over several rounds of workgroups: 70B gate/up at
+  // 36 / 64 / 96 rows 153 / 159 / 176 us with eight, 148 / 152 / 169 with seven.  Not in one round (8B 43.5 either way at 36 rows,
+  // 48.0 / 49.6 at 128) and not beyond 96 rows (70B at 144 rows 193 / 200), where the k-tile step, not the bytes, sets the time.
+  if constexpr (TMT <= 8) {
+    if (epi == EPI_SWIGLU && M <= 96 && grid.x > 256 && strip_load(ntiles, 7) < strip_load(ntiles, 8)) {
+      grid.x = ceil_div(ntiles, 7);
+      if (full) launch_timed(ev, gemm_rows_kernel<TMT, EPI_SWIGLU, true, EE_ROWS_TN, 7>, grid, blk, st, W, ktiles, ntiles, A, row0, M, N, out, per, scratch);
+      else launch_timed(ev, gemm_rows_kernel<TMT, EPI_SWIGLU, false, EE_ROWS_TN, 7>, grid, blk, st, W, ktiles, ntiles, A, row0, M, N, out, per, scratch);
+      return false;
+    }
+  }
   switch (epi) {
     case EPI_ADD: ROWS_LAUNCH(EPI_ADD); break;
     case EPI_SWIGLU: ROWS_LAUNCH(EPI_SWIGLU); break;
@@ -1006,7 +1039,7 @@ static bool launch_gemm_rows(hipStream_t st, int epi, const uint4* W, int ntiles
   }
 #undef ROWS_LAUNCH
   if (ksr > 1) {
-    dim3 rgrid(ceil_div(ntiles, EE_REDUCE_TASKS) * ceil_div(M, 16));
+    dim3 rgrid(ceil_div(grid.x, 8) * 8 * (2 * EE_ROWS_TN / EE_REDUCE_TASKS) * ceil_div(M, 16));
     switch (epi) {
       case EPI_ADD: hipLaunchKernelGGL((gemm_rows_reduce_kernel<EPI_ADD>), rgrid, rblk, 0, st, scratch, ksr, ntiles, TMT, row0, M, N, out); break;
       case EPI_SWIGLU: hipLaunchKernelGGL((gemm_rows_reduce_kernel<EPI_SWIGLU>), rgrid, rblk, 0, st, scratch, ksr, ntiles, TMT, row0, M, N, out); break;
@@ -1213,7 +1246,6 @@ static void launch_gemm_mt(hipStream_t st, int epi, const uint4* W, int ntiles, 
 //     QKV (640 strips) at 9 / 24 rows 32.8 / 37.9 with four, 35.1 / 41.6 with one; 70B down 70.2 / 74.4 with two, 77.4 / 92.6; 8B
 //     QKV (384) 13.3 / 15.5 with two, 13.8 / 16.6.  At one row tile, strips that fill the chip evenly and a K below 512 k-tiles stay
 //     at one a wave (70B O 25.9 / 27.0).
-static int strip_load(int ntiles, int per_wg) { return ceil_div(ceil_div(ntiles, per_wg), 256) * per_wg; }
 static StripShape strip_shape(int ntiles, int ktiles, int M) {
   const int mt = M > 16 ? 2 : 1;
   if (ntiles >= 768) {

@@ -117,6 +117,17 @@ def test_strips_dealt_in_every_shape(d, ffn, ctx, k):
     sess.close(); model.close()
 
 
+@pytest.mark.parametrize("batch", [4, 10])
+def test_seven_weight_tiles_a_workgroup_match_oracle(batch):
+    """Gate/up of 3580 weight tiles at 36 and 90 rows: 512 workgroups of seven, the last of three."""
+    k, tol = 8, TOL["bf16"]
+    O, model, sess, first, gfirst = _setup(bf16_small(n_layers=3, exit_draft=1, exit_inter=2, d_model=272, d_ffn=28640), 41,
+                                           [20 + 9 * b for b in range(batch)], 3 * (k + 1) + 2)
+    assert gfirst.tolist() == first.tolist()
+    _round(O, sess, k, 0.8, np.random.default_rng(5), True, tol)
+    sess.close(); model.close()
+
+
 @pytest.mark.parametrize("row_tiles", [0, 4, 8, 16, 104, 108])
 def test_both_forms_of_the_narrow_projection_gemm_match_oracle(row_tiles):
     """The narrow projections (O, down, QKV, adapters) of a call with more than 16 rows run either with K shares and
