@@ -748,7 +748,7 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
   for (int t = 0; t < TN; t += PT) {
     const int task = nt0 + t;
     if (task >= ntiles || (WT < 2 * TN && nh && t == TN - 1)) continue;
-    const bool lone = PT == 2 && WT < 2 * TN && nh && t == TN - 2;      // (the wave's last tile is not there)
+    const bool lone = PT == 2 && WT < 2 * TN && ((nh && t == TN - 2) || task + 1 >= ntiles);      // (the next tile is another workgroup's or none)
 #pragma unroll
     for (int mt = 0; mt < TMW; ++mt) {
       const int m = (mt_first + mt * MT_STEP) * 16 + mc;
