@@ -14,6 +14,8 @@ __device__ inline void take_token(const TakeToken& t, int r, int tok) {
   t.tok_next[r] = tok;
   t.draft_out[t.row_seq[r] * t.stride + t.j] = tok;
 }
+// dst[0..n) <- src (host memory, read before the call returns; n and dst whole int4s); false: too many, nothing done
+bool k_store_meta(hipStream_t st, const int* src, int* dst, int n);
 void k_fill_nan_dead_kv(hipStream_t st, bool bf16, void* kv, const int* pages, int n_owned_pages, int len,
                         int layer0, int layer1, int n_pages, int n_kv, int D);
 void k_read_kv(hipStream_t st, bool bf16, const void* kv, const int* pages, int layer, int pos0, int n,
@@ -69,7 +71,8 @@ struct RopeOut {
   bf16_t *Q = nullptr, *kv = nullptr;
 };
 struct GemmOut {
-  float* Y = nullptr; int ldy = 0;        // EPI_ADD: residual stream, Y += product (row-major fp32); EPI_ARGMAX: optional logits
+  float* Y = nullptr; int ldy = 0;        // EPI_ADD: residual stream, Y = R + product (row-major fp32); EPI_ARGMAX: optional logits
+  const float* R = nullptr;               // EPI_ADD: the rows added to (usually Y itself; null: none)
   float* Y2 = nullptr; const int* y2_idx = nullptr; int y2_add = 0;   // EPI_ADD: the new rows also go to Y2[y2_idx[row] + y2_add] (kept hidden rows of an exit)
   bf16_t* H = nullptr; int h_ktiles = 0;  // EPI_SWIGLU target (fragment layout)
   float* pmax = nullptr; int* pidx = nullptr; int pstride = 0;   // EPI_ARGMAX partials [row][pstride >= ntiles]

@@ -213,7 +213,7 @@ __device__ inline void epi_prefetch(EpiPre& p, const GemmOut& out, int task, int
   p.r_a = p.r_b = 0;
   if (EPI == EPI_ADD) {
     const int n = task * 16 + 4 * g;
-    if (ok) p.res = *(const float4*)(out.Y + (size_t)row * out.ldy + n);
+    if (ok && out.R) p.res = *(const float4*)(out.R + (size_t)row * out.ldy + n);
     if (out.nout.xn) p.gnext = *(const float4*)(out.nout.g + n);
     if (out.Y2 && ok) p.r_a = out.y2_idx[row] + out.y2_add;
   }

@@ -5,6 +5,7 @@
 #include <hip/hip_ext.h>
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 
 // ---------------------------------------------------------------------------------------------
 // helpers
@@ -37,6 +38,28 @@ __global__ void accept_kernel(const int* v, const int* seq_row0, const int* seq_
 void k_accept(hipStream_t st, const int* v, const CallMeta& meta, int cand_stride, int B, int* n_accept, int* next_tok) {
   hipLaunchKernelGGL(accept_kernel, dim3(B), dim3(64), 0, st, v, meta.seq_row0, meta.seq_m, meta.cand, meta.n_cand,
                      cand_stride, n_accept, next_tok);
+}
+
+// The metadata of a small call travels as the argument of a kernel that stores it: no copy command, no event, and the host's block
+// is free again when the launch returns (a copy of 1 KB from pinned memory with its event took 8-10 us of host time a call).
+template <int N>
+struct MetaInts { int4 v[N / 4]; };
+template <int N>
+__global__ __launch_bounds__(N / 4) void store_meta_kernel(MetaInts<N> meta, int4* dst, int n4) {
+  if ((int)threadIdx.x < n4) dst[threadIdx.x] = meta.v[threadIdx.x];
+}
+template <int N>
+static void store_meta(hipStream_t st, const int* src, int* dst, int n) {
+  MetaInts<N> meta;
+  memcpy(&meta, src, n * sizeof(int));
+  hipLaunchKernelGGL((store_meta_kernel<N>), dim3(1), dim3(N / 4), 0, st, meta, (int4*)dst, n / 4);
+}
+// n: a multiple of 4
+bool k_store_meta(hipStream_t st, const int* src, int* dst, int n) {
+  if (n <= 256) store_meta<256>(st, src, dst, n);
+  else if (n <= 768) store_meta<768>(st, src, dst, n);
+  else return false;
+  return true;
 }
 
 __global__ void fill_nan_dead_kv_kernel(void* kv, int bf16, const int* pages, int n_owned, int len, int layer0, int layer1,

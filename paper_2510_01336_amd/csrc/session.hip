@@ -346,6 +346,7 @@ static int build_meta(ee_session* s, int si, CallPlan& p, RowFn row_fn, int unif
 }
 static int upload_meta(ee_session* s, int si) {
   MetaSlot& sl = s->slot[si];
+  if (k_store_meta(s->st, sl.h, sl.d, (int)s->meta_ints)) return EE_OK;
   HIP_TRY(hipMemcpyAsync(sl.d, sl.h, s->meta_ints * sizeof(int), hipMemcpyHostToDevice, s->st));
   HIP_TRY(hipEventRecord(sl.copied, s->st));
   sl.in_flight = true;
@@ -471,13 +472,13 @@ static void run_layers(ee_session* s, int l0, int l1, const CallPlan& p, const C
       KF(KF_GEMM_QKV, gemm(s, EPI_ROPE, L.qkv, (const bf16_t*)s->XN, M, o));
       KF(KF_ATTN, bf16_attention(st, attn, (const bf16_t*)s->Qb, (const bf16_t*)s->kv, mt, pos_add, s->B, p.max_m, p.total_qt,
                                  Hq, Hkv, D, l, s->n_pages, s->pps, scr, (bf16_t*)s->AO, L.o.ktiles()));
-      o = GemmOut(); o.Y = s->X; o.ldy = d; o.nout = nout; o.nout.g = g2;
+      o = GemmOut(); o.Y = s->X; o.R = s->X; o.ldy = d; o.nout = nout; o.nout.g = g2;
       KF(KF_GEMM_O, nin.n_part = gemm(s, EPI_ADD, L.o, (const bf16_t*)s->AO, M, o));
       o = GemmOut(); o.H = (bf16_t*)s->H; o.h_ktiles = L.down.ktiles(); o.nin = nin;
       KF(KF_GEMM_GU, gemm(s, EPI_SWIGLU, L.gu, (const bf16_t*)s->XN, M, o));
       // the down projection leaves the operand of whatever reads the stream next: the next layer's QKV
       // projection, or the shared exit head behind the last layer of the pass
-      o = GemmOut(); o.Y = s->X; o.ldy = d; o.nout = nout;
+      o = GemmOut(); o.Y = s->X; o.R = s->X; o.ldy = d; o.nout = nout;
       o.nout.g = l + 1 < l1 ? (const float*)(m->base + m->L[l + 1].g1) : (const float*)(m->base + closing_gain(m, l1));
       if (l + 1 == l1) { o.Y2 = sink.rows; o.y2_idx = sink.row_idx; o.y2_add = sink.add; }
       KF(KF_GEMM_DOWN, s->ssq_parts = gemm(s, EPI_ADD, L.down, (const bf16_t*)s->H, M, o));
@@ -522,15 +523,13 @@ static void exit_head(ee_session* s, int M, int which, int row0 = 0, const int* 
     NormIn nin;
     nin.ssq = s->ssq + row0; nin.n_part = s->ssq_parts; nin.stride = Mp; nin.inv_d = 1.0f / (float)d; nin.eps = c.rms_eps;
     if (aux) {
-      // t = A n(x): rows into T (cleared: the epilogue adds to what it finds) and as the next operand TF;
-      // z = x + B t: into a copy of the rows, leaving the shared head's operand XN = bf16(z * gfinal)
-      (void)hipMemsetAsync(s->T, 0, (size_t)M * r * sizeof(float), st);
-      (void)hipMemcpyAsync(s->Z, s->X, (size_t)M * d * sizeof(float), hipMemcpyDeviceToDevice, st);
+      // t = A n(x): rows into T and as the next operand TF; z = x + B t: into rows of its own (the stream itself stays as it is),
+      // leaving the shared head's operand XN = bf16(z * gfinal)
       GemmOut o;
       o.nin = nin; o.Y = s->T; o.ldy = r;
       o.nout.xn = (bf16_t*)s->TF; o.nout.ktiles = r / 32; o.nout.ssq = s->ssq_t; o.nout.stride = s->headMp; o.nout.g = s->ones;
       KF(KF_GEMM_HEAD, gemm(s, EPI_ADD, m->auxA[which], (const bf16_t*)s->XN, M, o));
-      o = GemmOut(); o.Y = s->Z; o.ldy = d;
+      o = GemmOut(); o.Y = s->Z; o.R = s->X; o.ldy = d;
       o.nout.xn = (bf16_t*)s->XN; o.nout.ktiles = ceil_div(d, 32); o.nout.ssq = s->ssq; o.nout.stride = Mp; o.nout.g = gf;
       KF(KF_GEMM_HEAD, nin.n_part = gemm(s, EPI_ADD, m->auxB[which], (const bf16_t*)s->TF, M, o));
     }

@@ -397,6 +397,30 @@ def test_returned_rows_outlive_later_calls_and_the_session():
         assert np.array_equal(h, w)
 
 
+@pytest.mark.parametrize("pages", [136, 137, 648, 649])
+def test_metadata_of_every_size_reaches_the_kernels(pages):
+    """A call of nine rows whose metadata holds 256, 260, 768 and 772 integers (the block table makes up the size): stored by
+    a kernel of 256 or 768 integers, or copied.  The rounds equal those of a session with a short table bit for bit."""
+    import paper_2510_01336_amd as hs
+    cfg, k, rows = bf16_small(), 8, 29
+    model = hs.Model(cfg, 58)
+    prompt, drafts = synth.gen_prompt(cfg.vocab, 60, 3), np.random.default_rng(2).integers(0, cfg.vocab, (1, k)).astype(np.int32)
+    got = []
+    for n in (4, pages):
+        sess = hs.Session(model, 1, n * 64, rows, 4)
+        sess.enable_logits(True)
+        first = sess.prefill([prompt])
+        sess.draft_inject(drafts)
+        vi = sess.verify_intermediate()
+        li = sess.last_logits(k + 1)
+        vf = sess.verify_full()
+        got.append((first, vi, li, vf[0], vf[1], vf[2][0], sess.last_logits(2 * k)))
+        sess.close()
+    model.close()
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+
+
 def test_rerun_is_bit_identical():
     cfg = bf16_d128()
     k = 8
