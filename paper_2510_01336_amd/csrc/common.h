@@ -52,10 +52,16 @@ __host__ __device__ inline size_t align_up(size_t x, size_t a) { return (x + a -
 // Fragment-tiled bf16 matrix: rows r (padded to 16) x cols k (padded to 32), stored as
 // [r/16][k/32][64 lanes][8 elements] so that one wavefront reads one 16x32 MFMA operand
 // (v_mfma_f32_16x16x32_bf16: lane l holds row l%16, k = 8*(l/16)..+7) as 1 KiB of contiguous
-// memory, 16 B per lane.  Used for weights (row = output feature) and activations (row = token).
+// memory, 16 B per lane.  Used for weights (row = output feature).
 // ---------------------------------------------------------------------------------------------
 __host__ __device__ inline size_t frag_offset(int r, int k, int ktiles) {
   return ((size_t)(r >> 4) * ktiles + (k >> 5)) * 512 + (size_t)((((k & 31) >> 3) << 4) + (r & 15)) * 8 + (k & 7);
+}
+// Activations (row = token) have the same tiles and 16-byte units, ordered [row/4][k/8][row%4] inside a tile: a call of few rows
+// then reads only the 256-byte quads that hold rows, and a wave's load still consists of whole 64-byte runs.
+__host__ __device__ inline int act_unit(int m, int g) { return (m >> 2) * 16 + g * 4 + (m & 3); }      // row m of 16, k group g of 4
+__host__ __device__ inline size_t act_offset(int r, int k, int ktiles) {
+  return ((size_t)(r >> 4) * ktiles + (k >> 5)) * 512 + (size_t)act_unit(r & 15, (k & 31) >> 3) * 8 + (k & 7);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -61,7 +61,7 @@ __global__ __launch_bounds__(256) void bf16_rmsnorm_kernel(const float* __restri
     if (c < nch) {
       uint2 pk = make_uint2(pack2(xv[i].x * inv * gv[i].x, xv[i].y * inv * gv[i].y),
                             pack2(xv[i].z * inv * gv[i].z, xv[i].w * inv * gv[i].w));
-      *(uint2*)(out + frag_offset(r, c * 4, ktiles)) = pk;
+      *(uint2*)(out + act_offset(r, c * 4, ktiles)) = pk;
     }
   }
 }
@@ -142,7 +142,7 @@ __global__ __launch_bounds__(256) void bf16_begin_pass_kernel(const bf16_t* __re
     if (c < nch) {
       uint2 pk = make_uint2(pack2(xv[i].x * inv * gv[i].x, xv[i].y * inv * gv[i].y),
                             pack2(xv[i].z * inv * gv[i].z, xv[i].w * inv * gv[i].w));
-      *(uint2*)(out + frag_offset(r, c * 4, ktiles)) = pk;
+      *(uint2*)(out + act_offset(r, c * 4, ktiles)) = pk;
     }
   }
 }
@@ -300,7 +300,7 @@ __device__ inline void epi_apply_pairs(const f32x4& acc0, const f32x4& acc1, flo
     float h[NF];
 #pragma unroll
     for (int v = 0; v < NF; ++v) h[v] = lo[v] / (1.0f + __expf(-lo[v])) * hi[v];
-    store_bf16<NF>(out.H + frag_offset(row, f, out.h_ktiles), h);
+    store_bf16<NF>(out.H + act_offset(row, f, out.h_ktiles), h);
   } else {
     // head h, features f .. and their partners f + D/2 ..
     const RopeOut& R = out.rope;
@@ -356,7 +356,7 @@ __device__ inline void epi_apply(const f32x4& acc0, float sc, const EpiPre& p, c
     if (out.Y2 && ok) *(float4*)(out.Y2 + (size_t)p.r_a * out.ldy + n) = r;
     if (out.nout.xn) {
       const float4 gn = p.gnext;
-      if (ok) *(uint2*)(out.nout.xn + frag_offset(row, n, out.nout.ktiles)) = make_uint2(pack2(r.x * gn.x, r.y * gn.y), pack2(r.z * gn.z, r.w * gn.w));
+      if (ok) *(uint2*)(out.nout.xn + act_offset(row, n, out.nout.ktiles)) = make_uint2(pack2(r.x * gn.x, r.y * gn.y), pack2(r.z * gn.z, r.w * gn.w));
       float ss = ok ? (r.x * r.x + r.y * r.y) + (r.z * r.z + r.w * r.w) : 0.f;
       ss += __shfl_xor(ss, 16, 64);
       ss += __shfl_xor(ss, 32, 64);
@@ -447,9 +447,9 @@ __global__ __launch_bounds__(64 * EE_MAX_WAVES) void gemm_skinny_kernel(const ui
   const u32x4 *wp[NS], *ap[MT];
 #pragma unroll
   for (int s = 0; s < NS; ++s) wp[s] = (const u32x4*)W + (size_t)min(strip0 + s, ntiles - 1) * ktiles * 64 + lane;
-  // (rows past the last repeat it: no cache lines are fetched for them)
+  // (rows past the last repeat it: the quads behind the last row's are not fetched)
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt) ap[mt] = (const u32x4*)A + (size_t)((row0 >> 4) + mt) * ktiles * 64 + (lane & 48) + max(0, min(mc, M - 1 - 16 * mt));
+  for (int mt = 0; mt < MT; ++mt) ap[mt] = (const u32x4*)A + (size_t)((row0 >> 4) + mt) * ktiles * 64 + act_unit(max(0, min(mc, M - 1 - 16 * mt)), lane >> 4);
   Frags<MT, NS, U> cur;
 
   // Order of the requests: the partial sums of squares of the deferred RMSNorm (contiguous shares of the workgroup's waves, looked
@@ -640,7 +640,7 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
   const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(lptr_t)&ring[0][0]) + 1024u * wave_s;
 #define ROWS_LDS(slot_, tile_) ((lptr_t)(size_t)(lds0 + 16u * ((slot_) * STAGE + (tile_) * 64)))
   const u32x4* wsrc = (const u32x4*)W + (size_t)min(bx * WT + wave, ntiles - 1) * ktiles * 64 + lane;
-  const u32x4* xsrc = (const u32x4*)A + (size_t)(((row0 + rbase) >> 4) + wave) * ktiles * 64 + lane;
+  const u32x4* xsrc = (const u32x4*)A + (size_t)(((row0 + rbase) >> 4) + wave) * ktiles * 64 + act_unit(lane & 15, lane >> 4);
   // (weights: streaming hint)
 #define ROWS_REQUEST(slot_, kt_)                                                                              \
   do {                                                                                                        \
@@ -806,7 +806,7 @@ __device__ __forceinline__ void gemm_block_body(u32x4* ring, const uint4* __rest
   for (int j = 0; j < NJ; ++j) {
     const int t = wave_s + 8 * j;
     const size_t tile = t < WT ? (size_t)min(bx * WT + t, ntiles - 1) : (size_t)(((row0 + rbase) >> 4) + t - WT);
-    src[j] = (t < WT ? (const u32x4*)W : (const u32x4*)A) + tile * ktiles * 64 + lane;
+    src[j] = (t < WT ? (const u32x4*)W + lane : (const u32x4*)A + act_unit(lane & 15, lane >> 4)) + tile * ktiles * 64;
   }
   // requests of this wave per stage: its tiles that exist and, among the row tiles, hold rows (a prefix of its list)
   const int have = WT + mt_used;
@@ -1625,7 +1625,7 @@ __global__ __launch_bounds__(64 * EE_ATTN_WAVES) void attn_kernel(const uint4* _
         const int row = seq_row0[b] + qrow / rep, col0 = (kvh * rep + qrow % rep) * D + 4 * g;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
-          *(uint2*)(out + frag_offset(row, col0 + dt * 16, out_ktiles)) =
+          *(uint2*)(out + act_offset(row, col0 + dt * 16, out_ktiles)) =
               make_uint2(pack2(o[i][dt][0] * inv, o[i][dt][1] * inv), pack2(o[i][dt][2] * inv, o[i][dt][3] * inv));
       }
     } else {
@@ -1827,7 +1827,7 @@ __global__ __launch_bounds__(512) void attn_block_kernel(const uint4* __restrict
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) {
       const f32x4 x = po[(i * DT + dt) * 64];
-      *(uint2*)(out + frag_offset(row, col0 + dt * 16, out_ktiles)) =
+      *(uint2*)(out + act_offset(row, col0 + dt * 16, out_ktiles)) =
           make_uint2(pack2(o[i][dt][0] * a0 + x[0] * a1, o[i][dt][1] * a0 + x[1] * a1), pack2(o[i][dt][2] * a0 + x[2] * a1, o[i][dt][3] * a0 + x[3] * a1));
     }
   }
@@ -1963,7 +1963,7 @@ __global__ __launch_bounds__(512) void attn_tile_kernel(const uint4* __restrict_
     if (qrow < nq) {
       const float inv = 1.0f / l;
       const int row = row0 + qrow / rep, col = (kvh * rep + qrow % rep) * D + wave * 16 + 4 * g;
-      *(uint2*)(out + frag_offset(row, col, out_ktiles)) = make_uint2(pack2(acc[0] * inv, acc[1] * inv), pack2(acc[2] * inv, acc[3] * inv));
+      *(uint2*)(out + act_offset(row, col, out_ktiles)) = make_uint2(pack2(acc[0] * inv, acc[1] * inv), pack2(acc[2] * inv, acc[3] * inv));
     }
   } else {
     const size_t slot = ((size_t)gqt * Hkv + kvh) * nsplit + sp;
@@ -2052,7 +2052,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
     const int row = seq_row0[b] + qrow / rep, col0 = (kvh * rep + qrow % rep) * D + dq * DW * 16 + 4 * g;
 #pragma unroll
     for (int j = 0; j < DW; ++j)
-      *(uint2*)(out + frag_offset(row, col0 + j * 16, out_ktiles)) =
+      *(uint2*)(out + act_offset(row, col0 + j * 16, out_ktiles)) =
           make_uint2(pack2(acc[j][0] * inv, acc[j][1] * inv), pack2(acc[j][2] * inv, acc[j][3] * inv));
   }
 }

@@ -397,6 +397,31 @@ def test_returned_rows_outlive_later_calls_and_the_session():
         assert np.array_equal(h, w)
 
 
+@pytest.mark.parametrize("batch", [3, 4, 5, 8, 9, 13, 16])
+def test_rows_of_every_quad_equal_a_lone_row(batch):
+    """A few rows are read in quads of four, the rows past the last one standing in for those that are not there: one prompt in
+    every slot of a batch, decoded by one row each, gives every slot the logits and hidden row of the prompt alone."""
+    import paper_2510_01336_amd as hs
+    cfg = bf16_small()
+    model = hs.Model(cfg, 58)
+    prompt = synth.gen_prompt(cfg.vocab, 2, 3)
+    got = []
+    hs.ee_debug_attention_form(2)
+    try:
+        for n in (1, batch):
+            sess = hs.Session(model, n, 64, 12)
+            sess.enable_logits(True)
+            sess.prefill([prompt] * n)
+            tokens = sess.decode_ar(1)
+            got.append((tokens, sess.last_logits(n), sess.last_hidden(n)))
+            sess.close()
+    finally:
+        hs.ee_debug_attention_form(-1)
+    model.close()
+    for alone, rows in zip(*got):
+        assert np.array_equal(np.repeat(alone, batch, axis=0), rows)
+
+
 @pytest.mark.parametrize("pages", [136, 137, 648, 649])
 def test_metadata_of_every_size_reaches_the_kernels(pages):
     """A call of nine rows whose metadata holds 256, 260, 768 and 772 integers (the block table makes up the size): stored by
