@@ -492,7 +492,7 @@ def main():
     gu_bytes += rows * cfg.d_model * es + rows * cfg.d_ffn * es   # normed input rows in, SwiGLU rows out
     gu_avg_s = gu_ms / gu_n * 1e-3
     achieved = gu_bytes / gu_avg_s / 1e9
-    gu_kernel = "gemm_skinny_kernel<1,SWIGLU>" if rows <= 16 else "gemm_rows_kernel<.,SWIGLU> / gemm_skinny_kernel<1,SWIGLU>, mean over the step's launches;"
+    gu_kernel = "gemm_skinny_kernel<.,SWIGLU>" if rows <= 32 else "gemm_rows_kernel<.,SWIGLU> / gemm_skinny_kernel<1,SWIGLU>, mean over the step's launches;"
     roofline = {"bound": "hbm", "kernel": gu_kernel + " (gate/up projection + SiLU*mul)",
                 "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                 "traffic": MEASURED_TRAFFIC.get(args.workload, (None, None))[0],

@@ -498,9 +498,9 @@ class _ResultBlocks:
     """Page-locked host memory for the rows a session returns.  The GPU writes such an array directly (2.4 MB of hidden rows 55 us);
     into ordinary fresh memory the runtime copies through its own staging buffer, 1 MiB at a time, and every page is faulted in
     (225 us).  A block is lent to one array at a time and free again once that array and its views are gone; up to BLOCKS blocks of
-    at most LARGEST bytes per session, other requests get ordinary memory.  The memory goes with the session (a lent block with
+    at most LARGEST bytes per session, other requests (and those below SMALLEST, where it makes no difference) get ordinary memory.  The memory goes with the session (a lent block with
     its array)."""
-    BLOCKS, LARGEST, SMALLEST = 6, 16 << 20, 1 << 16
+    BLOCKS, LARGEST, SMALLEST = 6, 16 << 20, 1 << 18
 
     def __init__(self, rows: int, cols: int):
         self.nbytes = min(rows * cols * 4, self.LARGEST)

@@ -374,7 +374,7 @@ def test_batched_equals_solo(pinned):
 def test_returned_rows_outlive_later_calls_and_the_session():
     """Rows come back in page-locked blocks that are lent to one array at a time: eight arrays held at once (more than there
     are blocks), a view of the first kept alone, then the session closed -- every one still holds what its call returned."""
-    cfg = bf16_small()
+    cfg = bf16_small(vocab=4096)               # (18 rows of logits: 295 KB, above the least size that gets a block)
     k = 8
     O, model, sess, _, _ = _setup(cfg, 58, [60, 40], 3 * (k + 1) + 2)
     held, want = [], []
