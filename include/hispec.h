@@ -311,7 +311,9 @@ int ee_debug_gemm_block_tiles(int weight_tiles);
  * split length to that many 64-position pages for every call (raised where the split scratch would not hold the
  * count), so that a sequence is cut alike whether it runs alone or in a batch and the batched-inference
  * claim (a sequence's results do not depend on its neighbours) can be checked bit for bit; 0 restores the built-in
- * choice.  EE_ERR_ARG for a negative value. */
+ * choice.  That also needs one GEMM kernel alone and in the batch, since kernels sum over K in different orders: calls of up
+ * to 32 rows where every matrix of the model is under 128 MB, of up to 16 rows otherwise, or of 33 to 512 rows with the
+ * narrow projections held to one form (ee_debug_gemm_row_blocks).  EE_ERR_ARG for a negative value. */
 int ee_debug_attention_split_pages(int pages);
 
 /* Test support, process-wide: the attention kernel of every bf16 call -- 0 KV splits with a merge, 1 blocks of 128 query rows,

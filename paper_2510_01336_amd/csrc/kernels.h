@@ -1,6 +1,7 @@
 // Launchers of the HIP kernels (internal).  All work is enqueued on `st`; nothing synchronises.
 #pragma once
 #include "common.h"
+#include "strips.h"
 
 // ---- dtype-independent ---------------------------------------------------------------------
 // per sequence: a = number of leading j < n_cand[b] with cand[b][j] == v[row0[b]+j];
@@ -83,7 +84,6 @@ struct GemmOut {
 // Y^T tile = W tile (A operand) x X^T (B operand); W, A in fragment layout.  Rows go in passes of 32.
 // (rows row0 .. row0+M-1 of the operand, row0 a multiple of 16)
 void bf16_gemm(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N, const GemmOut& out, int row0 = 0);
-struct StripShape { int ns, nw, ksplit, U; };   // strips per wave, waves per workgroup, waves that share out K, k-tiles per register set
 void bf16_gemm_cfg(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N,
                    const GemmOut& out, const StripShape& shape, int row0 = 0);
 #define EE_STRIP_ROWS 32           // most rows that go to the kernel above rather than to the row-tiled one

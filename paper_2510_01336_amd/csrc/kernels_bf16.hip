@@ -774,7 +774,7 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
 // 204 (300).
 // K is never shared out: among calls that run blocked a row's sums run over K in one order, whatever the form and the row
 // count.  (Between kernels they do not: skinny, row-tiled and K-share sums differ in order, and the row count decides which
-// kernel a call gets.)  K shares of the down projection measured 127 us against 154 at 1096 rows, nothing from 2048; shares
+// kernel a call gets.  Within the skinny kernel the order is the matrix's own below 128 MB, see strip_parts.)  K shares of the down projection measured 127 us against 154 at 1096 rows, nothing from 2048; shares
 // whose number follows the row count moved the full-depth comparison of a batch with its sequences alone past its bound.
 // ---------------------------------------------------------------------------------------------
 template <int EPI, int TN, bool FULL>
@@ -976,9 +976,6 @@ __global__ __launch_bounds__(256) void norm_factor_kernel(const float* __restric
   for (int sh = 1; sh < 64; sh <<= 1) ss += __shfl_xor(ss, sh, 64);
   if (t == 0) inv_rms[row] = 1.0f / sqrtf(ss * inv_d + eps);
 }
-
-// strips (weight tiles) on the busiest compute unit when workgroups take per_wg each
-static int strip_load(int ntiles, int per_wg) { return ceil_div(ceil_div(ntiles, per_wg), 256) * per_wg; }
 
 // number of K shares the row-tiled GEMM runs with: enough workgroups for the chip, at least 16 k-tiles each
 static int rows_ksplit(int ntiles, int ktiles) {
@@ -1232,38 +1229,6 @@ static void launch_gemm_mt(hipStream_t st, int epi, const uint4* W, int ntiles, 
     default: SKINNY_LAUNCH(EPI_ARGMAX); break;
   }
 #undef SKINNY_LAUNCH
-}
-
-// Launch shape for M <= 32 rows, from sweeps over the matrices of the 8B and 70B widths with cold weights (us; {strips, waves,
-// K parts, U}).  What bounds them is the memory path of a compute unit, which takes in weights and rows together at 35-50 GB/s,
-// so the shape has to give every compute unit the same share of the strips and, with several strips a wave, read the rows less
-// often.  `load`: strips on the busiest compute unit.
-//   wide (>= 768 strips): a strip per wave, as many waves a workgroup as deal the strips most evenly: gate/up at 9 rows 8B 40.0
-//     with four waves on 224 units, 38.9 with seven on 256; 70B 148 / 141.  At 17..32 rows seven strips a wave and K over eight
-//     waves where that deals them evenly too (the rows are then read once for seven strips): 8B 40.3, 70B 144 (row-tiled kernel
-//     44.2, 147); else one strip a wave: head of 32000 tokens 47.9 (50.3).
-//   narrow: K over four or eight waves.  Two or four strips a wave where that makes load * (1 + row tiles / strips) smaller: 70B
-//     QKV (640 strips) at 9 / 24 rows 32.8 / 37.9 with four, 35.1 / 41.6 with one; 70B down 70.2 / 74.4 with two, 77.4 / 92.6; 8B
-//     QKV (384) 13.3 / 15.5 with two, 13.8 / 16.6.  At one row tile, strips that fill the chip evenly and a K below 512 k-tiles stay
-//     at one a wave (70B O 25.9 / 27.0).
-static StripShape strip_shape(int ntiles, int ktiles, int M) {
-  const int mt = M > 16 ? 2 : 1;
-  if (ntiles >= 768) {
-    if (mt == 2 && 256 * strip_load(ntiles, 7) <= ntiles * 23 / 20) return StripShape{7, 8, 8, 1};
-    int nw = 8;
-    for (int w = 7; w >= 4; --w)
-      if (strip_load(ntiles, w) < strip_load(ntiles, nw)) nw = w;
-    return StripShape{1, nw, 1, mt == 2 ? 4 : 8};
-  }
-  int ns = 1;
-  if (ntiles >= 320 && (mt == 2 || ntiles % 256 != 0 || ktiles >= 512))
-    for (int n = 2; n <= 4; n *= 2)
-      if (strip_load(ntiles, n) * (n + mt) * ns < strip_load(ntiles, ns) * (ns + mt) * n) ns = n;
-  if (ns == 4) return StripShape{4, 8, 8, mt == 2 ? 2 : 4};
-  if (ns == 2) return StripShape{2, 4, 4, 4};
-  int ksplit = ntiles >= 200 && ntiles < 320 && ktiles >= 256 && mt == 1 ? 8 : 4;
-  while (ksplit > 1 && ktiles / ksplit < 4) ksplit >>= 1;
-  return StripShape{1, max(4, ksplit), ksplit, mt == 2 ? 4 : 8};
 }
 
 void bf16_gemm_cfg(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N,

@@ -1,0 +1,26 @@
+// Host program behind test_strips_host.py: the launch shapes of the few-row GEMM (csrc/strips.h).
+//   strips_host                          every matrix of up to 4200 strips: prints the sizes whose shape breaks a rule
+//   strips_host NTILES KTILES M          prints "strips-per-wave waves K-parts" of that call
+#include "../paper_2510_01336_amd/csrc/strips.h"
+#include <cstdio>
+#include <cstdlib>
+
+int main(int argc, char** argv) {
+  if (argc == 4) {
+    const StripShape s = strip_shape(atoi(argv[1]), atoi(argv[2]), atoi(argv[3]));
+    printf("%d %d %d\n", s.ns, s.nw, s.ksplit);
+    return 0;
+  }
+  int bad = 0;
+  auto wrong = [&](int nt, int kt, int M, const char* what) { if (++bad <= 20) printf("%d strips, %d k-tiles, %d rows: %s\n", nt, kt, M, what); };
+  for (int nt = 1; nt <= 4200; ++nt)
+    for (int kt : {1, 2, 3, 5, 8, 9, 15, 16, 17, 31, 32, 64, 96, 112, 128, 255, 256, 344, 448, 512, 896})
+      for (int M : {1, 9, 16, 17, 24, 32}) {
+        const StripShape s = strip_shape(nt, kt, M), one = strip_shape(nt, kt, 1);
+        if (s.nw < 1 || s.nw > EE_MAX_WAVES || s.ksplit < 1 || s.nw % s.ksplit) wrong(nt, kt, M, "waves do not share out the strips");
+        if (s.ns != 1 && s.ns != 2 && s.ns != 4 && !(s.ns == 7 && M > 16)) wrong(nt, kt, M, "no kernel for so many strips a wave");
+        // the K shares, and the shares of the norm's partial sums (one a wave), set the order of a row's sums
+        if (!strips_large(nt, kt) && (s.ksplit != one.ksplit || s.nw != one.nw)) wrong(nt, kt, M, "sums in another order than one row alone");
+      }
+  return bad != 0;
+}

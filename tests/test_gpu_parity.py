@@ -422,6 +422,33 @@ def test_rows_of_every_quad_equal_a_lone_row(batch):
         assert np.array_equal(np.repeat(alone, batch, axis=0), rows)
 
 
+@pytest.mark.parametrize("batch", [17, 27, 32])
+@pytest.mark.parametrize("shape", [dict(d_model=256, d_ffn=14336, vocab=28672), dict(n_q_heads=96, n_kv_heads=16),
+                                   dict(d_model=3584, d_ffn=8192)], ids=["1792_strips", "512_strips", "224_strips_256_ktiles"])
+def test_a_row_has_the_same_bits_beside_any_number_of_others(batch, shape):
+    """Matrices below 128 MB, whose rows are summed in one order from 1 to 32 rows: gate/up and head of 1792 strips, QKV of 512 strips
+    and 8 k-tiles, down of 224 strips and 256 k-tiles.  One prompt of one token in every slot of a batch, built and decoded by one row each."""
+    import paper_2510_01336_amd as hs
+    cfg = bf16_small(n_layers=3, exit_draft=1, exit_inter=2, **shape)
+    model = hs.Model(cfg, 58)
+    prompt = synth.gen_prompt(cfg.vocab, 1, 3)
+    got = []
+    hs.ee_debug_attention_form(2)
+    try:
+        for n in (1, batch):
+            sess = hs.Session(model, n, 64, 12)
+            sess.enable_logits(True)
+            sess.prefill([prompt] * n)
+            tokens = sess.decode_ar(1)
+            got.append((tokens, sess.last_logits(n), sess.last_hidden(n)))
+            sess.close()
+    finally:
+        hs.ee_debug_attention_form(-1)
+    model.close()
+    for alone, rows in zip(*got):
+        assert np.array_equal(np.repeat(alone, batch, axis=0), rows)
+
+
 @pytest.mark.parametrize("pages", [136, 137, 648, 649])
 def test_metadata_of_every_size_reaches_the_kernels(pages):
     """A call of nine rows whose metadata holds 256, 260, 768 and 772 integers (the block table makes up the size): stored by
