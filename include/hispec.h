@@ -289,8 +289,9 @@ int ee_debug_time_kernels(ee_session* s, int on);
 int ee_debug_kernel_times(ee_session* s, int32_t* n_families, const char** names /*[16]*/,
                           float* ms /*[16]*/, int32_t* launches /*[16]*/);
 
-/* Test and tuning support, process-wide: the row-tiled GEMM (calls of more than 16 rows) serves the narrow
- * projections (O, down, QKV, adapters) either with K shares and a reduction pass or with blocks of row_tiles*16
+/* Test and tuning support, process-wide: the row-tiled GEMM (calls of more than 32 rows; of matrices of 128 MB and more also
+ * those of 17 to 32 rows, where that is quicker or a form is forced here or below) serves the narrow projections
+ * (O, down, QKV, adapters) either with K shares and a reduction pass or with blocks of row_tiles*16
  * rows and no K shares; row_tiles = 4, 8 or 16 forces the second form for every such call (104 and 108: blocks of 4
  * and 8 row tiles with eight instead of four weight tiles per workgroup), 0 the first, -1 restores the built-in
  * choice.  Values >= 0 also keep the narrow projections of calls beyond 512 rows in parts of 512 rows and the rest in

@@ -86,7 +86,6 @@ struct GemmOut {
 void bf16_gemm(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N, const GemmOut& out, int row0 = 0);
 void bf16_gemm_cfg(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N,
                    const GemmOut& out, const StripShape& shape, int row0 = 0);
-#define EE_STRIP_ROWS 32           // most rows that go to the kernel above rather than to the row-tiled one
 // Launch timing: while this points to a pair of events, the next skinny-GEMM launch attaches them to the dispatch
 // itself (hipExtLaunchKernelGGL), so that they hold the kernel's own start and end rather than the times at which
 // two marker packets around it were processed; the launcher sets `used`.
@@ -95,9 +94,12 @@ extern LaunchEvents* g_launch_events;
 extern int g_attn_pages_override;   // <= 0: pages per KV split chosen from the call's shape; else that many (test hook: batch and solo runs then cut their contexts alike)
 extern int g_attn_form;              // -1: attention kernel chosen from the call's shape; else that one (ATTN_*) on every call (test hook)
 extern int g_rows_wide;              // 1: gate/up and exit head beyond 256 rows run in blocks of 256 rows; 0: in passes of up to 512 rows (test hook)
-extern int g_block_tiles;            // > 0: every call of more than 16 rows runs blocked with that many weight tiles per workgroup (test hook)
+extern int g_block_tiles;            // > 0: every call that the skinny kernel does not have to serve runs blocked with that many weight tiles per workgroup (test hook)
 extern int g_rows_blocks_override;   // -1: built-in choice between K shares and row blocks; else 0, or row tiles per block (+100: eight weight tiles per workgroup)
 size_t bf16_gemm_rows_scratch_floats(int ntiles, int ktiles);
+// Whether bf16_gemm serves a call of M rows, else bf16_gemm_rows.  While a test hook forces a form of the latter, it gets every call of
+// more than 16 rows of a matrix of 128 MB and more.
+bool bf16_takes_strips(int ntiles, int ktiles, int M);
 // Row-tiled variant for more than 16 rows (rows start at row 0 of the operand; the kernels read whole row tiles up to the
 // next of 64, 128, 192, 256, 384, 512 rows, beyond 512 up to whole parts of 512, which the operand buffer must hold).
 // scratch: bf16_gemm_rows_scratch_floats() floats for this shape (may be null when that is 0); inv_rms: inv_cap (at least

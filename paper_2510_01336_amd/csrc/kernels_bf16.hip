@@ -558,7 +558,7 @@ __global__ __launch_bounds__(64 * EE_MAX_WAVES) void gemm_skinny_kernel(const ui
 }
 
 // ---------------------------------------------------------------------------------------------
-// Row-tiled GEMM for a block of 32 < M <= 512 rows: weights cross HBM once per block, but every weight fragment now
+// Row-tiled GEMM for a block of 16 < M <= 512 rows (up to 32 only where that is quicker than the skinny kernel, see strips_serve): weights cross HBM once per block, but every weight fragment now
 // meets up to 32 row tiles, so the kernel sits near the machine's ridge (M flop per weight byte).
 // Workgroup = 8 waves (two per SIMD: one wave alone does not keep a matrix pipe busy) on a group of
 // WT = 8 weight tiles (128 output features; 7 where that deals a wide matrix more evenly, see the launcher) and a share of K (grid.y); wave (rq, nh) owns 4 of the tiles and a
@@ -577,7 +577,6 @@ __global__ __launch_bounds__(64 * EE_MAX_WAVES) void gemm_skinny_kernel(const ui
 // With grid.y == 1 the epilogue is fused; otherwise fp32 partial tiles go to scratch and
 // gemm_rows_reduce_kernel sums the K shares in a fixed order and runs the same epilogue.
 // ---------------------------------------------------------------------------------------------
-#define EE_ROWS_TN 4
 // Whether the partial tiles of K shares stay in the L2 for the reduce kernel, else they stream to memory.  Measured with the
 // reduction, 8B widths, us, streamed / kept: QKV at 36 / 144 / 192 rows 20.0 / 18.6, 28.4 / 26.0, 32.5 / 31.5 (70B at 144: 49.5 / 46.1);
 // O at 36 / 64 rows 14.5 / 13.4, 15.4 / 14.0; down at 64 / 81 / 112 rows 29.4 / 28.6, 32.5 / 33.8, 34.3 / 35.6: its seven shares of more
@@ -977,13 +976,6 @@ __global__ __launch_bounds__(256) void norm_factor_kernel(const float* __restric
   if (t == 0) inv_rms[row] = 1.0f / sqrtf(ss * inv_d + eps);
 }
 
-// number of K shares the row-tiled GEMM runs with: enough workgroups for the chip, at least 16 k-tiles each
-static int rows_ksplit(int ntiles, int ktiles) {
-  const int groups = ceil_div(ntiles, 2 * EE_ROWS_TN);
-  int ks = groups >= 192 ? 1 : min(8, ceil_div(224, groups));
-  while (ks > 1 && ktiles / ks < 16) --ks;
-  return ks;
-}
 size_t bf16_gemm_rows_scratch_floats(int ntiles, int ktiles) {
   const int ks = rows_ksplit(ntiles, ktiles);
   return ks > 1 ? (size_t)ks * ntiles * 32 * 256 : 0;       // [k share][weight tile][up to 32 row tiles][64 lanes x 4]
@@ -1118,7 +1110,7 @@ static void launch_block(hipStream_t st, const uint4* W, int ntiles, int ktiles,
   launch_timed(ev, gemm_block_kernel<EPI, TN>, grid, blk, st, W, ktiles, ntiles, A, row0, M, N, out);
 }
 int g_rows_wide = 1;               // test and tuning hook: 0 keeps wide matrices in passes of up to 512 rows
-int g_block_tiles = 0;             // test hook: > 0 runs every call of more than 16 rows blocked, with so many weight tiles per workgroup
+int g_block_tiles = 0;             // test hook: > 0 runs every call that reaches bf16_gemm_rows blocked, with so many weight tiles per workgroup
 
 // Form of the launch above for a call of M rows: row tiles per block, plus 100 with eight weight tiles per workgroup
 // (TN = 4) instead of four; 0: use the K-share kernel (wide matrices, and shapes where it measured faster).
@@ -1154,6 +1146,11 @@ static bool runs_blocked(bool wide, int ntiles, int ktiles, int M) {
   if (M <= 512 || g_rows_blocks_override >= 0) return false;
   const int blocks = ceil_div(ntiles, 8) * ceil_div(M, 256);
   return ktiles <= ntiles ? M > 544 || blocks >= 128 : M > 1024 || blocks >= 256;
+}
+
+bool bf16_takes_strips(int ntiles, int ktiles, int M) {
+  const bool forced = (g_block_tiles > 0 || g_rows_blocks_override >= 0) && M > 16 && strips_large(ntiles, ktiles);
+  return strips_serve(ntiles, ktiles, M) && !forced;
 }
 
 // more than 16 rows from row 0 of the operand; returns how many partial sums of squares per row an EPI_ADD call left
@@ -1194,7 +1191,7 @@ int bf16_gemm_rows(hipStream_t st, int epi, const bf16_t* W, int ntiles, int kti
       continue;
     }
     const int bt = rows_blocks_form(ntiles, ktiles, epi == EPI_ADD ? min(M, blk) : mc);
-    if (m0 > 0 && mc <= EE_STRIP_ROWS && (epi != EPI_ADD || bt > 0 || rows_ksplit(ntiles, ktiles) == 1)) {
+    if (m0 > 0 && bf16_takes_strips(ntiles, ktiles, mc) && (epi != EPI_ADD || bt > 0 || rows_ksplit(ntiles, ktiles) == 1)) {
       bf16_gemm(st, epi, W, ntiles, ktiles, A, mc, N, out, m0);        // (as such a call by itself; leaves a partial sum per weight tile)
       continue;
     }

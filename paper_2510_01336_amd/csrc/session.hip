@@ -394,12 +394,12 @@ static void reset_accounting(ee_session* s) {
 // ---------------------------------------------------------------------------------------------
 // forward pass pieces
 // ---------------------------------------------------------------------------------------------
-// the skinny kernel for few rows, the row-tiled one up to 512 (wide matrices: 256), beyond the blocked one or the row-tiled one
+// the skinny kernel for few rows (see strips_serve), the row-tiled one up to 512 (wide matrices: 256), beyond the blocked one or the row-tiled one
 // in parts (see runs_blocked)
 // returns the number of partial sums of squares per row that an EPI_ADD call with a next operand leaves
 static int gemm(ee_session* s, int epi, const MatLoc& ml, const bf16_t* A, int M, const GemmOut& o) {
   const bf16_t* W = (const bf16_t*)(s->m->base + ml.off);
-  if (M > EE_STRIP_ROWS) return bf16_gemm_rows(s->st, epi, W, ml.ntiles(), ml.ktiles(), A, M, ml.N, o, s->gemm_part, s->inv_rms, s->inv_cap);
+  if (!bf16_takes_strips(ml.ntiles(), ml.ktiles(), M)) return bf16_gemm_rows(s->st, epi, W, ml.ntiles(), ml.ktiles(), A, M, ml.N, o, s->gemm_part, s->inv_rms, s->inv_cap);
   bf16_gemm(s->st, epi, W, ml.ntiles(), ml.ktiles(), A, M, ml.N, o);
   return ml.ntiles();
 }

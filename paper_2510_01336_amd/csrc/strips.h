@@ -4,12 +4,50 @@
 #include "common.h"
 #include <algorithm>
 
+#define EE_STRIP_ROWS 32   // most rows of a call of the few-row GEMM
+#define EE_ROWS_TN 4       // weight tiles a wave of the row-tiled GEMM takes (a workgroup: twice as many)
 struct StripShape { int ns, nw, ksplit, U; };   // strips per wave, waves per workgroup, waves that share out K, k-tiles per register set
 
 // strips (weight tiles) on the busiest compute unit when workgroups take per_wg each
 inline int strip_load(int ntiles, int per_wg) { return ceil_div(ceil_div(ntiles, per_wg), 256) * per_wg; }
 // 128 MB and more of weights
 inline bool strips_large(int ntiles, int ktiles) { return (size_t)ntiles * ktiles * 1024 >= ((size_t)128 << 20); }
+
+// number of K shares the row-tiled GEMM runs with: enough workgroups for the chip, at least 16 k-tiles each
+inline int rows_ksplit(int ntiles, int ktiles) {
+  const int groups = ceil_div(ntiles, 2 * EE_ROWS_TN);
+  int ks = groups >= 192 ? 1 : std::min(8, ceil_div(224, groups));
+  while (ks > 1 && ktiles / ks < 16) --ks;
+  return ks;
+}
+// A call of 17..32 rows of a large matrix goes to the few-row GEMM or to the row-tiled one, whichever measured faster (one launch behind
+// another, cold weights, us at 17 / 24 / 32 rows, strips against row-tiled with its reduction; n x k: weight tiles x k-tiles):
+//   wide, seven strips a wave (the rows are read once for seven strips, which is worth a third more than an even share on the busiest
+//     compute unit): gate/up 8B 39.9 / 39.9 / 40.0 (44.3), 70B 145 / 146 / 147 (149), 1376 x 128 32.4 / 32.6 / 32.9 (49.3), 2752 x 256
+//     121 / 122 / 125 (131); head of 128256 tokens 8B 175 / 179 / 183 (185 / 187 / 189), 70B 328 / 333 / 340 (333 / 336 / 340).  The row-tiled
+//     kernel suffers where K is a multiple of 2048, so that all its strips start at one place of the memory channels; where it is
+//     not, a head of many rounds is quicker there: 8016 x 96 143 / 146 / 149 (133 / 134 / 136), 9496 x 80 149 / 152 / 156 (144 / 146 / 148)
+//   wide, one strip a wave, where the row-tiled kernel would need K shares (960 x 160 32.7 / 32.9 / 35.0, 34.0) or K is short and
+//     either a multiple of 2048 (2000 x 128 46.0 / 48.0 / 51.4, 50.6; 3000 x 64 37.5 / 38.1 / 39.8, 50.4) or the row-tiled kernel's last
+//     round half empty (2368 x 112 56.4 / 57.4 / 60.6, 61.1); not 2000 x 96 36.4 / 37.7 / 40.0 (35.7), 2000 x 160 57.4 / 60.4 / 65.0 (56.0),
+//     2000 x 256 89 / 96 / 103 (87)
+//   narrow, where pairs of strips are an even deal: 70B O 28.4 / 28.9 / 29.3 (32.0); of a long K, where the rows outgrow the weights, up
+//     to 20 rows: 70B down 73.0 / 76.4 / 81.0 (75.1), 512 x 688 60.7 / 62.4 / 65.5 (61.5).  Never uneven ones: 70B QKV 37.9 / 38.7 / 39.9
+//     (37.2), 13B down 31.9 / 34.0 / 36.4 (26.9)
+inline bool strips_by_seven(int ntiles, int ktiles) {
+  const int load = strip_load(ntiles, 7);
+  return strips_large(ntiles, ktiles) && ntiles >= 768 && 3 * 256 * load <= 4 * ntiles && (ktiles % 64 == 0 || load <= 28);
+}
+// whether the few-row GEMM serves a call of M rows: up to 16 of any matrix, up to 32 of those below 128 MB, else as above
+inline bool strips_serve(int ntiles, int ktiles, int M) {
+  if (M <= 16 || !strips_large(ntiles, ktiles)) return M <= EE_STRIP_ROWS;
+  if (M > EE_STRIP_ROWS) return false;
+  if (ntiles < 768) return 256 * strip_load(ntiles, 2) <= ntiles * 23 / 20 && (ktiles < 512 || M <= 20);
+  if (strips_by_seven(ntiles, ktiles) || rows_ksplit(ntiles, ktiles) > 1) return true;
+  const int groups = ceil_div(ntiles, 2 * EE_ROWS_TN);
+  const bool rows_even = ceil_div(groups, 256) * 256 <= groups * 23 / 20;
+  return ktiles <= 128 && (ktiles % 64 == 0 || !rows_even);
+}
 
 // K shares of a strip.  Below 128 MB they are a matter of the matrix alone: a row's sums then run over K in one order and are the same
 // bits however many rows are beside it (up to EE_STRIP_ROWS).  A large wide matrix is summed over the whole K by one wave up to 16 rows,
@@ -30,8 +68,7 @@ inline int strip_parts(int ntiles, int ktiles) {
 // often.  `load`: strips on the busiest compute unit.
 //   wide (>= 768 strips): a strip per wave, as many waves a workgroup as deal the strips most evenly: gate/up at 9 rows 8B 40.0
 //     with four waves on 224 units, 38.9 with seven on 256; 70B 148 / 141.  At 17..32 rows of a large matrix seven strips a wave and
-//     K over eight waves where that deals them evenly too (the rows are then read once for seven strips): 8B 40.3, 70B 144 (row-tiled
-//     kernel 44.2, 147); else one strip a wave: head of 32000 tokens 47.9 (50.3).
+//     K over eight waves, see above.
 //   narrow: K over four or eight waves.  Two or four strips a wave where that makes load * (1 + row tiles / strips) smaller: 70B
 //     QKV (640 strips) at 9 / 24 rows 32.8 / 37.9 with four, 35.1 / 41.6 with one; 70B down 70.2 / 74.4 with two, 77.4 / 92.6; 8B
 //     QKV (384) 13.3 / 15.5 with two, 13.8 / 16.6.  At one row tile, strips that fill the chip evenly and a K below 512 k-tiles stay
@@ -39,7 +76,7 @@ inline int strip_parts(int ntiles, int ktiles) {
 inline StripShape strip_shape(int ntiles, int ktiles, int M) {
   const int mt = M > 16 ? 2 : 1, parts = strip_parts(ntiles, ktiles);
   if (ntiles >= 768) {
-    if (mt == 2 && strips_large(ntiles, ktiles) && 256 * strip_load(ntiles, 7) <= ntiles * 23 / 20) return StripShape{7, 8, 8, 1};
+    if (mt == 2 && strips_by_seven(ntiles, ktiles)) return StripShape{7, 8, 8, 1};
     int nw = 8;
     for (int w = 7; w >= 4; --w)
       if (strip_load(ntiles, w) < strip_load(ntiles, nw)) nw = w;

@@ -1,6 +1,6 @@
 // Host program behind test_strips_host.py: the launch shapes of the few-row GEMM (csrc/strips.h).
 //   strips_host                          every matrix of up to 4200 strips: prints the sizes whose shape breaks a rule
-//   strips_host NTILES KTILES M          prints "strips-per-wave waves K-parts" of that call
+//   strips_host NTILES KTILES M          prints "strips-per-wave waves K-parts" of that call, or "rows": not a call of this kernel
 #include "../paper_2510_01336_amd/csrc/strips.h"
 #include <cstdio>
 #include <cstdlib>
@@ -8,7 +8,8 @@
 int main(int argc, char** argv) {
   if (argc == 4) {
     const StripShape s = strip_shape(atoi(argv[1]), atoi(argv[2]), atoi(argv[3]));
-    printf("%d %d %d\n", s.ns, s.nw, s.ksplit);
+    if (!strips_serve(atoi(argv[1]), atoi(argv[2]), atoi(argv[3]))) printf("rows\n");
+    else printf("%d %d %d\n", s.ns, s.nw, s.ksplit);
     return 0;
   }
   int bad = 0;
@@ -16,6 +17,8 @@ int main(int argc, char** argv) {
   for (int nt = 1; nt <= 4200; ++nt)
     for (int kt : {1, 2, 3, 5, 8, 9, 15, 16, 17, 31, 32, 64, 96, 112, 128, 255, 256, 344, 448, 512, 896})
       for (int M : {1, 9, 16, 17, 24, 32}) {
+        if (strips_serve(nt, kt, 33) || !strips_serve(nt, kt, 16) || (!strips_large(nt, kt) && !strips_serve(nt, kt, 32))) wrong(nt, kt, M, "wrong kernel");
+        if (!strips_serve(nt, kt, M)) continue;
         const StripShape s = strip_shape(nt, kt, M), one = strip_shape(nt, kt, 1);
         if (s.nw < 1 || s.nw > EE_MAX_WAVES || s.ksplit < 1 || s.nw % s.ksplit) wrong(nt, kt, M, "waves do not share out the strips");
         if (s.ns != 1 && s.ns != 2 && s.ns != 4 && !(s.ns == 7 && M > 16)) wrong(nt, kt, M, "no kernel for so many strips a wave");

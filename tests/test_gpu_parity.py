@@ -449,6 +449,27 @@ def test_a_row_has_the_same_bits_beside_any_number_of_others(batch, shape):
         assert np.array_equal(np.repeat(alone, batch, axis=0), rows)
 
 
+@pytest.mark.parametrize("batch", [18, 27])
+def test_17_to_32_rows_at_the_70b_width_agree_with_a_row_alone(batch):
+    """Matrices of 128 MB and more, which get strips or the row-tiled kernel: at the 70B width QKV and head of the row-tiled one (QKV in K
+    shares), down of either, gate/up as seven strips a wave (32 k-tiles a K share).  Another order of the sums over K: bf16 accuracy."""
+    import paper_2510_01336_amd as hs
+    cfg = bf16_small(n_layers=3, exit_draft=1, exit_inter=2, d_model=8192, n_q_heads=64, n_kv_heads=8, head_dim=128, d_ffn=28672, vocab=32000, sigma=0.02)
+    model = hs.Model(cfg, 58)
+    prompt = synth.gen_prompt(cfg.vocab, 1, 3)
+    got = []
+    for n in (1, batch):
+        sess = hs.Session(model, n, 64, 12)
+        sess.enable_logits(True)
+        sess.prefill([prompt] * n)
+        got.append((sess.last_logits(n), sess.last_hidden(n)))
+        sess.close()
+    model.close()
+    for alone, rows in zip(*got):
+        assert max_rel(rows[0], alone[0].astype(np.float64)) <= TOL["bf16"]
+        assert all(np.array_equal(rows[0], r) for r in rows[1:])       # (the same row in every slot)
+
+
 @pytest.mark.parametrize("pages", [136, 137, 648, 649])
 def test_metadata_of_every_size_reaches_the_kernels(pages):
     """A call of nine rows whose metadata holds 256, 260, 768 and 772 integers (the block table makes up the size): stored by

@@ -23,3 +23,21 @@ def test_shapes_of_every_size_keep_their_rules(strips_host):
     """Whole K shares to whole waves, and below 128 MB one order of a row's sums from 1 to 32 rows."""
     run = subprocess.run([strips_host], stdout=subprocess.PIPE, text=True)
     assert run.returncode == 0, run.stdout
+
+
+# weight tiles, k-tiles: kernel at 17, 24 and 32 rows
+@pytest.mark.parametrize("ntiles,ktiles,want", [
+    (640, 256, ["rows"] * 3),                           # 70B QKV: 160 workgroups of strips
+    (320, 432, ["rows"] * 3),                           # 13B down
+    (512, 256, ["2 4 4"] * 3),                          # 70B O
+    (512, 896, ["2 4 4", "rows", "rows"]),              # 70B down
+    (1792, 128, ["7 8 8"] * 3), (3584, 256, ["7 8 8"] * 3), (8016, 128, ["7 8 8"] * 3),      # 8B, 70B gate/up, 8B head
+    (1376, 128, ["7 8 8"] * 3), (2752, 256, ["7 8 8"] * 3),                                  # a third more than an even deal
+    (8016, 96, ["rows"] * 3), (2000, 256, ["rows"] * 3),
+    (2000, 128, ["1 8 1"] * 3),
+    (256, 448, ["1 8 8"] * 3), (384, 128, ["2 4 4"] * 3),                                    # below 128 MB
+])
+def test_calls_of_17_to_32_rows_get_the_quicker_kernel(strips_host, ntiles, ktiles, want):
+    got = [subprocess.run([strips_host, str(ntiles), str(ktiles), str(m)], stdout=subprocess.PIPE, text=True, check=True).stdout.strip()
+           for m in (17, 24, 32)]
+    assert got == want
