@@ -67,7 +67,9 @@ inline int strip_parts(int ntiles, int ktiles) {
 // so the shape has to give every compute unit the same share of the strips and, with several strips a wave, read the rows less
 // often.  `load`: strips on the busiest compute unit.
 //   wide (>= 768 strips): a strip per wave, as many waves a workgroup as deal the strips most evenly: gate/up at 9 rows 8B 40.0
-//     with four waves on 224 units, 38.9 with seven on 256; 70B 148 / 141.  At 17..32 rows of a large matrix seven strips a wave and
+//     with four waves on 224 units, 38.9 with seven on 256; 70B 148 / 141.  Of equal deals four waves, whose workgroups start and end
+//     sooner, where K is short (8016 x 64 at 9 rows 83.7, eight waves 92.0; 9496 x 80 120, 125; 5000 x 96 75.3, five 85.0), eight where
+//     it is long (8016 x 128 at 9 / 16 rows 163.7 / 166.1, four 164.7 / 167.9; 8016 x 256 309 / 311, four 321 / 329).  At 17..32 rows of a large matrix seven strips a wave and
 //     K over eight waves, see above.
 //   narrow: K over four or eight waves.  Two or four strips a wave where that makes load * (1 + row tiles / strips) smaller: 70B
 //     QKV (640 strips) at 9 / 24 rows 32.8 / 37.9 with four, 35.1 / 41.6 with one; 70B down 70.2 / 74.4 with two, 77.4 / 92.6; 8B
@@ -77,8 +79,8 @@ inline StripShape strip_shape(int ntiles, int ktiles, int M) {
   const int mt = M > 16 ? 2 : 1, parts = strip_parts(ntiles, ktiles);
   if (ntiles >= 768) {
     if (mt == 2 && strips_by_seven(ntiles, ktiles)) return StripShape{7, 8, 8, 1};
-    int nw = 8;
-    for (int w = 7; w >= 4; --w)
+    int nw = ktiles >= 128 && strip_load(ntiles, 8) <= strip_load(ntiles, 4) ? 8 : 4;
+    for (int w = 5; w <= 8; ++w)
       if (strip_load(ntiles, w) < strip_load(ntiles, nw)) nw = w;
     return StripShape{1, nw, 1, mt == 2 ? 4 : 8};
   }

@@ -25,6 +25,12 @@ def test_shapes_of_every_size_keep_their_rules(strips_host):
     assert run.returncode == 0, run.stdout
 
 
+@pytest.mark.parametrize("ntiles,ktiles,want", [(8016, 64, "1 4 1"), (5000, 96, "1 4 1"), (5000, 128, "1 4 1"), (8016, 128, "1 8 1"), (2000, 256, "1 8 1"),
+                                                (1792, 64, "1 7 1"), (1792, 128, "1 7 1"), (3584, 256, "1 7 1"), (1376, 128, "1 6 1"), (1024, 64, "1 4 1")])
+def test_of_equal_deals_four_waves_for_a_short_k(strips_host, ntiles, ktiles, want):
+    assert subprocess.run([strips_host, str(ntiles), str(ktiles), "9"], stdout=subprocess.PIPE, text=True, check=True).stdout.strip() == want
+
+
 # weight tiles, k-tiles: kernel at 17, 24 and 32 rows
 @pytest.mark.parametrize("ntiles,ktiles,want", [
     (640, 256, ["rows"] * 3),                           # 70B QKV: 160 workgroups of strips
