@@ -6,7 +6,9 @@ Module-level functions carry the names of the C entry points (include/hispec.h).
 from __future__ import annotations
 
 import ctypes as C
+import mmap
 import os
+import threading
 import weakref
 from typing import Optional, Sequence, Tuple
 
@@ -390,14 +392,14 @@ def ee_debug_enable_logits(session: int, on: bool) -> None:
     _chk(lib.ee_debug_enable_logits(session, int(on)))
 
 
-def ee_debug_last_logits(session: int, max_rows: int, vocab: int, out: Optional[np.ndarray] = None) -> np.ndarray:
-    out, n = np.empty((max_rows, vocab), np.float32) if out is None else out, C.c_int32()
+def ee_debug_last_logits(session: int, max_rows: int, vocab: int) -> np.ndarray:
+    out, n = np.empty((max_rows, vocab), np.float32), C.c_int32()
     _chk(lib.ee_debug_last_logits(session, _p_f32(out), max_rows, C.byref(n)))
     return out[:n.value]
 
 
-def ee_debug_last_hidden(session: int, max_rows: int, d: int, out: Optional[np.ndarray] = None) -> np.ndarray:
-    out, n = np.empty((max_rows, d), np.float32) if out is None else out, C.c_int32()
+def ee_debug_last_hidden(session: int, max_rows: int, d: int) -> np.ndarray:
+    out, n = np.empty((max_rows, d), np.float32), C.c_int32()
     _chk(lib.ee_debug_last_hidden(session, _p_f32(out), max_rows, C.byref(n)))
     return out[:n.value]
 
@@ -494,40 +496,88 @@ class Model:
             pass
 
 
+class _LentAtFork:
+    """Keeps the arrays that lie in page-locked blocks readable in a forked process (os.fork, multiprocessing), which does not get
+    the mappings of such memory: their contents are copied ahead of the fork, and the child puts them at the same addresses."""
+    lock, contents, lent = threading.Lock(), [], {}
+
+    @classmethod
+    def add(cls, whole: np.ndarray) -> "weakref.ref[np.ndarray]":
+        addr = whole.__array_interface__["data"][0]
+        ref = cls.lent[addr] = weakref.ref(whole, lambda r: cls.lent.pop(addr, None) if cls.lent.get(addr) is r else None)
+        return ref
+
+    @classmethod
+    def before(cls) -> None:
+        cls.lock.acquire()
+        for addr, ref in list(cls.lent.items()):
+            whole = ref()
+            if whole is not None:
+                cls.contents.append((addr, whole.tobytes()))
+
+    @classmethod
+    def after_in_parent(cls) -> None:
+        cls.contents.clear()
+        cls.lock.release()
+
+    @classmethod
+    def after_in_child(cls) -> None:
+        libc = C.CDLL(None)
+        libc.mmap.restype, libc.mmap.argtypes = C.c_void_p, [C.c_void_p, C.c_size_t, C.c_int, C.c_int, C.c_int, C.c_long]
+        fixed_noreplace = 0x100000             # (a place that is taken is left alone)
+        for addr, data in cls.contents:
+            start = addr & -mmap.PAGESIZE
+            if libc.mmap(start, addr + len(data) - start, mmap.PROT_READ | mmap.PROT_WRITE, mmap.MAP_PRIVATE | mmap.MAP_ANONYMOUS | fixed_noreplace, -1, 0) == start:
+                C.memmove(addr, data, len(data))
+        cls.after_in_parent()
+
+
+os.register_at_fork(before=_LentAtFork.before, after_in_parent=_LentAtFork.after_in_parent, after_in_child=_LentAtFork.after_in_child)
+
+
 class _ResultBlocks:
     """Page-locked host memory for the rows a session returns.  The GPU writes such an array directly (2.4 MB of hidden rows 55 us);
     into ordinary fresh memory the runtime copies through its own staging buffer, 1 MiB at a time, and every page is faulted in
-    (225 us).  A block is lent to one array at a time and free again once that array and its views are gone; up to BLOCKS blocks of
-    at most LARGEST bytes per session, other requests (and those below SMALLEST, where it makes no difference) get ordinary memory.  The memory goes with the session (a lent block with
-    its array)."""
+    (225 us; a page-locked staging buffer and a copy on several threads are no quicker in a decoding program).  A block is made when
+    a call first needs it, lent to one array at a time and free again once that array and its views are gone; up to BLOCKS blocks of
+    at most LARGEST bytes, other requests (and results below SMALLEST, where it makes no difference) get ordinary memory.  With the
+    session (a lent block with its array) the memory goes back to torch's pool of page-locked memory.
+    A forked process does not inherit page-locked memory: see _LentAtFork."""
     BLOCKS, LARGEST, SMALLEST = 6, 16 << 20, 1 << 18
 
-    def __init__(self, rows: int, cols: int):
-        self.nbytes = min(rows * cols * 4, self.LARGEST)
+    def __init__(self):
         self.blocks = []                       # [tensor, weak reference to the array it is lent to]
-        for _ in range(2 if self.nbytes >= self.SMALLEST else 0):
-            self._add()
+        self.lock = threading.Lock()
 
-    def _add(self):
+    def _take(self, nbytes: int) -> Optional[np.ndarray]:
         import torch
-        try:
-            self.blocks.append([torch.empty(self.nbytes, dtype=torch.uint8, pin_memory=True), None])
-        except RuntimeError:                   # no more page-locked memory: ordinary memory does
-            return None
-        return self.blocks[-1]
+        with self.lock:
+            free = [b for b in self.blocks if b[1] is None or b[1]() is None]
+            block = next((b for b in free if b[0].numel() >= nbytes), None)
+            if block is None:
+                if free:                       # (a larger request than before: the block makes room)
+                    self.blocks = [b for b in self.blocks if b is not free[0]]
+                if len(self.blocks) == self.BLOCKS:
+                    return None
+                try:
+                    block = [torch.empty(nbytes, dtype=torch.uint8, pin_memory=True), None]
+                except RuntimeError:           # no more page-locked memory: ordinary memory does
+                    return None
+                self.blocks.append(block)
+            whole = block[0].numpy()           # (views keep it alive: its own base is the tensor, not another array)
+            block[1] = _LentAtFork.add(whole)
+            return whole
 
-    def take(self, rows: int, cols: int) -> Optional[np.ndarray]:
+    def read(self, entry, session: int, rows: int, cols: int) -> Optional[np.ndarray]:
+        """What `entry` (ee_debug_last_hidden / ee_debug_last_logits of the library) copies out; None: no block for that."""
         need = rows * cols * 4
-        if need > self.nbytes or need < self.SMALLEST:
+        whole = self._take(need) if self.SMALLEST <= need <= self.LARGEST else None
+        if whole is None:
             return None
-        block = next((b for b in self.blocks if b[1] is None or b[1]() is None), None)
-        if block is None and len(self.blocks) < self.BLOCKS:
-            block = self._add()
-        if block is None:
-            return None
-        whole = block[0].numpy()               # (views keep it alive: its own base is the tensor, not another array)
-        block[1] = weakref.ref(whole)
-        return whole[:need].view(np.float32).reshape(rows, cols)
+        out, n = whole[:need].view(np.float32).reshape(rows, cols), C.c_int32()
+        _chk(entry(session, _p_f32(out), rows, C.byref(n)))
+        out = out[:n.value]
+        return out.copy() if out.nbytes < self.SMALLEST else out
 
 
 class Session:
@@ -539,8 +589,8 @@ class Session:
         self.handle = None
         self.nbytes = arena_bytes or ee_session_bytes(model.handle, batch, max_ctx, max_rows, total_pages)
         self._buf, ptr = _arena(self.nbytes)
+        self._hidden, self._logits = _ResultBlocks(), _ResultBlocks()
         self.handle = ee_session_create(model.handle, batch, max_ctx, max_rows, total_pages, ptr, self.nbytes, model.stream)
-        self._hidden, self._logits = _ResultBlocks(batch * max_rows, model.cfg.d_model), None
 
     def prefill(self, prompts: Sequence[np.ndarray]) -> np.ndarray:
         lens = np.array([len(p) for p in prompts], np.int32)
@@ -614,16 +664,17 @@ class Session:
 
     def enable_logits(self, on: bool = True) -> None:
         ee_debug_enable_logits(self.handle, on)
-        if on and self._logits is None:
-            self._logits = _ResultBlocks(self.batch * self.max_rows, self.model.cfg.vocab)
+
+    def _last(self, blocks: _ResultBlocks, entry, ordinary, max_rows: Optional[int], cols: int) -> np.ndarray:
+        rows = max_rows or max(512, self.batch * self.max_rows)
+        out = blocks.read(entry, self.handle, rows, cols) if self.handle else None
+        return ordinary(self.handle, rows, cols) if out is None else out
 
     def last_logits(self, max_rows: Optional[int] = None) -> np.ndarray:
-        rows, vocab = max_rows or max(512, self.batch * self.max_rows), self.model.cfg.vocab
-        return ee_debug_last_logits(self.handle, rows, vocab, self._logits and self._logits.take(rows, vocab))
+        return self._last(self._logits, lib.ee_debug_last_logits, ee_debug_last_logits, max_rows, self.model.cfg.vocab)
 
     def last_hidden(self, max_rows: Optional[int] = None) -> np.ndarray:
-        rows, d = max_rows or max(512, self.batch * self.max_rows), self.model.cfg.d_model
-        return ee_debug_last_hidden(self.handle, rows, d, self._hidden.take(rows, d))
+        return self._last(self._hidden, lib.ee_debug_last_hidden, ee_debug_last_hidden, max_rows, self.model.cfg.d_model)
 
     def read_kv(self, seq: int, layer: int, pos0: int, n: int):
         return ee_debug_read_kv(self.handle, seq, layer, pos0, n, self.model.cfg.n_kv_heads, self.model.cfg.head_dim)
@@ -643,7 +694,7 @@ class Session:
     def close(self) -> None:
         if self.handle:
             ee_session_free(self.handle)
-            self.handle, self._buf, self._hidden, self._logits = None, None, None, None
+            self.handle, self._buf, self._hidden, self._logits = None, None, _ResultBlocks(), _ResultBlocks()
 
     def __del__(self):
         try:

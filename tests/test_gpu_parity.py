@@ -371,12 +371,29 @@ def test_batched_equals_solo(pinned):
         hs.ee_debug_gemm_row_blocks(-1)
 
 
+def _equal_in_a_forked_process(arrays, want):
+    """A forked process compares the arrays and reports by its exit code."""
+    import os
+    pid = os.fork()
+    if pid == 0:
+        code = 1
+        try:
+            code = 0 if all(np.array_equal(a, w) for a, w in zip(arrays, want)) else 2
+        finally:
+            os._exit(code)
+    return os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]) == 0
+
+
 def test_returned_rows_outlive_later_calls_and_the_session():
     """Rows come back in page-locked blocks that are lent to one array at a time: eight arrays held at once (more than there
-    are blocks), a view of the first kept alone, then the session closed -- every one still holds what its call returned."""
+    are blocks), a view of the first kept alone, then the session closed -- every one still holds what its call returned, here
+    and in a forked process.  A call without a number of rows gets a block too; a closed session raises the library's error."""
+    import threading
+    import paper_2510_01336_amd as hs
     cfg = bf16_small(vocab=4096)               # (18 rows of logits: 295 KB, above the least size that gets a block)
     k = 8
     O, model, sess, _, _ = _setup(cfg, 58, [60, 40], 3 * (k + 1) + 2)
+    assert not sess._logits.blocks and not sess._hidden.blocks       # (made by the calls that need them)
     held, want = [], []
     for i in range(8):
         sess.draft_inject(np.random.default_rng(i).integers(0, cfg.vocab, (2, k)).astype(np.int32))
@@ -384,6 +401,7 @@ def test_returned_rows_outlive_later_calls_and_the_session():
         rows = sess.last_logits(18)
         assert rows.shape == (18, cfg.vocab) and all(not np.shares_memory(rows, h) for h in held)
         held.append(rows); want.append(rows.copy())
+        assert np.array_equal(sess.last_logits(7), rows[:7])
         for b in range(2):
             sess.rollback(b, 0b111, O.seqs[b].len[0])
     assert any(not np.array_equal(want[0], w) for w in want[1:])
@@ -391,7 +409,28 @@ def test_returned_rows_outlive_later_calls_and_the_session():
     del held[0], rows
     again = sess.last_logits(18)
     assert not np.shares_memory(again, view) and np.array_equal(again, want[7])
-    sess.close(); model.close()
+    assert len(sess._logits.blocks) == sess._logits.BLOCKS
+    assert _equal_in_a_forked_process([view] + held, [want[0][3:5]] + want[1:])
+    got = [None] * 4                           # several threads read one session
+    def read(i):
+        got[i] = [sess.last_logits(18) for _ in range(5)]
+    threads = [threading.Thread(target=read, args=(i,)) for i in range(4)]
+    for t in threads: t.start()
+    for t in threads: t.join()
+    assert all(np.array_equal(x, want[7]) for g in got for x in g)
+    del got
+    held = held[3:]; want[1:] = want[4:]
+    default = sess.last_logits()               # (a larger request: up to 512 rows)
+    assert default.shape == (18, cfg.vocab) and np.array_equal(default, want[-1]) and default.base is not None
+    assert any(b[0].numel() == 512 * cfg.vocab * 4 for b in sess._logits.blocks)
+    sess.close()
+    for call in (sess.last_logits, sess.last_hidden):
+        with pytest.raises(hs.EEError):
+            call(18)
+        with pytest.raises(hs.EEError):
+            call()
+    model.close()
+    assert _equal_in_a_forked_process([view, default] + held, [want[0][3:5], want[-1]] + want[1:])
     assert np.array_equal(view, want[0][3:5])
     for h, w in zip(held, want[1:]):
         assert np.array_equal(h, w)
