@@ -183,7 +183,7 @@ int ee_verify_intermediate(ee_session* s, int32_t* n_accept, int32_t* next_token
  * and factors, the K-share partials of the row-tiled GEMM) taken from a static device array inside the library
  * instead of the session arena.  Arguments, results, state transition and errors as ee_verify_intermediate, and
  * bit-identical results (same kernels, same split plan).  The array holds 32 MiB per GPU from the first such call on
- * that GPU until the process ends; a call that needs more (about: more than 16 block rows in total on an 8B-sized
+ * that GPU until the process ends; a call that needs more (about: more than 32 block rows in total on an 8B-sized
  * model, or a very long context) returns EE_ERR_CAPACITY before any device work and leaves the session unchanged.
  * The call allocates nothing (no hipMalloc / hipFree / event or stream creation; EE_ERR_STATE while kernel timing
  * is enabled, which creates events).  Every such call on a GPU uses that GPU's one array, which keeps the previous

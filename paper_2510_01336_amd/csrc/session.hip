@@ -959,13 +959,10 @@ static int place_scratch_static(ee_session* s, const CallPlan& p) {
   const int stride = p.M <= 64 ? 64 : ceil_div(p.M, 512) * 512;      // whole GEMM passes of this call's rows
   float* ssq = cv.take<float>((size_t)ceil_div(c.d_model, 16) * stride);
   float* inv_rms = cv.take<float>(512);
-  float* gemm_part = nullptr;
-  if (p.M > 16) {                                   // the row-tiled GEMM may run: room for its K shares
-    size_t gp = 0;
-    for (const MatLoc* ml : {&m->L[0].qkv, &m->L[0].o, &m->L[0].gu, &m->L[0].down, &m->head, &m->auxA[0], &m->auxB[0]})
-      if (ml->Np > 0) gp = std::max(gp, bf16_gemm_rows_scratch_floats(ml->ntiles(), ml->ktiles()));
-    gemm_part = cv.take<float>(gp);
-  }
+  size_t gp = 0;                                    // room for the K shares of the projections that the row-tiled GEMM serves
+  for (const MatLoc* ml : {&m->L[0].qkv, &m->L[0].o, &m->L[0].gu, &m->L[0].down, &m->head, &m->auxA[0], &m->auxB[0]})
+    if (ml->Np > 0 && !bf16_takes_strips(ml->ntiles(), ml->ktiles(), p.M)) gp = std::max(gp, bf16_gemm_rows_scratch_floats(ml->ntiles(), ml->ktiles()));
+  float* gemm_part = cv.take<float>(gp);
   if (cv.cur > EE_STATIC_SCRATCH_BYTES) {
     ee_set_error("this call needs %zu bytes of scratch, the static array holds %zu: use ee_verify_intermediate", cv.cur,
                  (size_t)EE_STATIC_SCRATCH_BYTES);

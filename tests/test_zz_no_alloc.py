@@ -46,22 +46,23 @@ def test_static_scratch_call_equals_the_arena_call():
 
 
 def test_static_scratch_at_the_8b_width_and_its_limit():
-    """9 block rows at the 8B width (the benchmark's call shape) fit the 32 MiB array and give the arena call's
-    results bit for bit; 16 x 9 rows need the row-tiled GEMM's K-share partials, which do not fit: refused, session
+    """9 block rows at the 8B width (the benchmark's call shape) and 27, which the few-row kernel serves too, fit the 32 MiB array and
+    give the arena call's results bit for bit; 16 x 9 rows need the row-tiled GEMM's K-share partials, which do not fit: refused, session
     unchanged, and the ordinary call then serves the same block."""
     import paper_2510_01336_amd as hs
     cfg = synth.llama8b_config(n_layers=3, exit_draft=1, exit_inter=2, gamma=(1.0, 0.3, 0.3))
     k = 8
     model = hs.Model(cfg, 20251001)
-    sess = hs.Session(model, 1, 400, 2 * (k + 1) + 2)
-    sess.enable_logits(True)
-    sess.prefill([synth.gen_prompt(cfg.vocab, 300, 1)])
     rng = np.random.default_rng(1)
-    drafts = rng.integers(0, cfg.vocab, (1, k)).astype(np.int32)
-    ref, got = _both_ways(sess, drafts, [300])
-    for r, g in zip(ref, got):
-        assert np.array_equal(r, g)
-    sess.close()
+    for ctx in ([300], [300, 120, 77]):
+        sess = hs.Session(model, len(ctx), 400, 2 * (k + 1) + 2)
+        sess.enable_logits(True)
+        sess.prefill([synth.gen_prompt(cfg.vocab, n, 1 + b) for b, n in enumerate(ctx)])
+        drafts = rng.integers(0, cfg.vocab, (len(ctx), k)).astype(np.int32)
+        ref, got = _both_ways(sess, drafts, ctx)
+        for r, g in zip(ref, got):
+            assert np.array_equal(r, g)
+        sess.close()
     B = 16
     sess = hs.Session(model, B, 128, 2 * (k + 1) + 2)
     sess.prefill([synth.gen_prompt(cfg.vocab, 20 + b, 50 + b) for b in range(B)])
