@@ -72,7 +72,7 @@ struct RopeOut {
   bf16_t *Q = nullptr, *kv = nullptr;
 };
 struct GemmOut {
-  float* Y = nullptr; int ldy = 0;        // EPI_ADD: residual stream, Y = R + product (row-major fp32); EPI_ARGMAX: optional logits
+  float* Y = nullptr; int ldy = 0;        // EPI_ADD: residual stream, Y = R + product (row-major fp32; null: only the next operand); EPI_ARGMAX: optional logits
   const float* R = nullptr;               // EPI_ADD: the rows added to (usually Y itself; null: none)
   float* Y2 = nullptr; const int* y2_idx = nullptr; int y2_add = 0;   // EPI_ADD: the new rows also go to Y2[y2_idx[row] + y2_add] (kept hidden rows of an exit)
   bf16_t* H = nullptr; int h_ktiles = 0;  // EPI_SWIGLU target (fragment layout)
@@ -81,11 +81,9 @@ struct GemmOut {
   NormOut nout;
   RopeOut rope;
 };
-// Y^T tile = W tile (A operand) x X^T (B operand); W, A in fragment layout.  Rows go in passes of 32.
-// (rows row0 .. row0+M-1 of the operand, row0 a multiple of 16)
+// Y^T tile = W tile (A operand) x X^T (B operand); W in fragment layout, A in that of the activations.  Up to 32 rows, row0 .. row0+M-1
+// of the operand (row0 a multiple of 16), in the launch shape of strip_shape.
 void bf16_gemm(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N, const GemmOut& out, int row0 = 0);
-void bf16_gemm_cfg(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N,
-                   const GemmOut& out, const StripShape& shape, int row0 = 0);
 // Launch timing: while this points to a pair of events, the next skinny-GEMM launch attaches them to the dispatch
 // itself (hipExtLaunchKernelGGL), so that they hold the kernel's own start and end rather than the times at which
 // two marker packets around it were processed; the launcher sets `used`.

@@ -352,7 +352,7 @@ __device__ inline void epi_apply(const f32x4& acc0, float sc, const EpiPre& p, c
     const int n = task * 16 + 4 * g;
     float4 r = make_float4(acc0[0] * sc, acc0[1] * sc, acc0[2] * sc, acc0[3] * sc);
     r.x += p.res.x; r.y += p.res.y; r.z += p.res.z; r.w += p.res.w;
-    if (ok) *(float4*)(out.Y + (size_t)row * out.ldy + n) = r;
+    if (out.Y && ok) *(float4*)(out.Y + (size_t)row * out.ldy + n) = r;
     if (out.Y2 && ok) *(float4*)(out.Y2 + (size_t)p.r_a * out.ldy + n) = r;
     if (out.nout.xn) {
       const float4 gn = p.gnext;
@@ -724,9 +724,10 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
       if (nt0 + tn >= ntiles) continue;
 #pragma unroll
       for (int mt = 0; mt < TMW; ++mt)
-        if (mt_first + mt * MT_STEP < mt_used)
+        if (mt_first + mt * MT_STEP < mt_used) {
           if (keep_partials(EPI, M_all)) pp[((size_t)(nt0 + tn) * TMT + mt_first + mt * MT_STEP) * 64] = acc[tn][mt];
           else __builtin_nontemporal_store(acc[tn][mt], pp + ((size_t)(nt0 + tn) * TMT + mt_first + mt * MT_STEP) * 64);
+        }
     }
     return;
   }
@@ -1015,7 +1016,8 @@ static bool launch_gemm_rows(hipStream_t st, int epi, const uint4* W, int ntiles
   if constexpr (TMT <= 8) {
     if (epi == EPI_SWIGLU && M <= 96 && grid.x > 256 && strip_load(ntiles, 7) < strip_load(ntiles, 8)) {
       grid.x = ceil_div(ntiles, 7);
-      if (full) launch_timed(ev, gemm_rows_kernel<TMT, EPI_SWIGLU, true, EE_ROWS_TN, 7>, grid, blk, st, W, ktiles, ntiles, A, row0, M, N, out, per, scratch);
+      constexpr bool kFull = TMT == 4;      // (96 rows never fill eight row tiles)
+      if (full && kFull) launch_timed(ev, gemm_rows_kernel<TMT, EPI_SWIGLU, kFull, EE_ROWS_TN, 7>, grid, blk, st, W, ktiles, ntiles, A, row0, M, N, out, per, scratch);
       else launch_timed(ev, gemm_rows_kernel<TMT, EPI_SWIGLU, false, EE_ROWS_TN, 7>, grid, blk, st, W, ktiles, ntiles, A, row0, M, N, out, per, scratch);
       return false;
     }
@@ -1228,10 +1230,10 @@ static void launch_gemm_mt(hipStream_t st, int epi, const uint4* W, int ntiles, 
 #undef SKINNY_LAUNCH
 }
 
-void bf16_gemm_cfg(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N,
-                   const GemmOut& out, const StripShape& sh, int row0) {
+void bf16_gemm(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N, const GemmOut& out, int row0) {
   const uint4* Wc = (const uint4*)W;
   const uint4* Ac = (const uint4*)A;
+  const StripShape sh = strip_shape(ntiles, ktiles, M);
 #define STRIPS(MT_, NS_, U_) launch_gemm_mt<MT_, NS_, U_>(st, epi, Wc, ntiles, ktiles, Ac, row0, M, N, out, sh.nw, sh.ksplit)
   if (M <= 16) {
     if (sh.ns == 4) STRIPS(1, 4, 4);
@@ -1244,13 +1246,6 @@ void bf16_gemm_cfg(hipStream_t st, int epi, const bf16_t* W, int ntiles, int kti
     else STRIPS(2, 1, 4);
   }
 #undef STRIPS
-}
-
-void bf16_gemm(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles, const bf16_t* A, int M, int N, const GemmOut& out, int row0) {
-  for (int m0 = 0; m0 < M; m0 += 32) {      // (calls of more than 32 rows go to the row-tiled kernel; should one arrive here it goes in passes of 32)
-    const int mc = min(32, M - m0);
-    bf16_gemm_cfg(st, epi, W, ntiles, ktiles, A, mc, N, out, strip_shape(ntiles, ktiles, mc), row0 + m0);
-  }
 }
 
 // one workgroup of 1024 threads per row; the row's partials lie side by side ([row][tile]), so a wave's load is one

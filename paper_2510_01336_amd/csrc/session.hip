@@ -56,8 +56,8 @@ struct ee_session {
   float* Pup[4] = {nullptr, nullptr, nullptr, nullptr};   // the same for the buffers of levels 2..n-1
   bool need_logits = false;
   float *part_o = nullptr, *part_ml = nullptr, *pmax = nullptr, *ssq = nullptr, *gemm_part = nullptr, *inv_rms = nullptr;
-  // auxiliary exit heads: adapter output rows z [maxM][d], its rank-r intermediate (fp32 rows and, for bf16
-  // models, the bf16 operand of the up projection), that operand's unused sum-of-squares partials, unit gains
+  // auxiliary exit heads: adapter output rows z [maxM][d], its rank-r intermediate (T: fp32 models, the rows; TF: bf16
+  // models, the operand of the up projection), that operand's unused sum-of-squares partials, unit gains
   float *Z = nullptr, *T = nullptr, *ssq_t = nullptr, *ones = nullptr;
   void* TF = nullptr;
   size_t part_units = 0;        // capacity of the attention split scratch in (q-tile, split) units per KV head
@@ -129,7 +129,7 @@ static size_t carve(ee_session* s, char* base) {
   s->LOGITS = cv.take<float>((size_t)s->headM * c.vocab);
   if (c.head_rank > 0) {
     s->Z = cv.take<float>((size_t)s->headM * d);
-    s->T = cv.take<float>((size_t)s->headM * c.head_rank);
+    s->T = bf ? nullptr : cv.take<float>((size_t)s->headM * c.head_rank);
     if (bf) {
       s->TF = cv.take<bf16_t>((size_t)s->headMp * c.head_rank);
       s->ssq_t = cv.take<float>((size_t)ceil_div(c.head_rank, 16) * s->headMp);
@@ -523,10 +523,10 @@ static void exit_head(ee_session* s, int M, int which, int row0 = 0, const int* 
     NormIn nin;
     nin.ssq = s->ssq + row0; nin.n_part = s->ssq_parts; nin.stride = Mp; nin.inv_d = 1.0f / (float)d; nin.eps = c.rms_eps;
     if (aux) {
-      // t = A n(x): rows into T and as the next operand TF; z = x + B t: into rows of its own (the stream itself stays as it is),
+      // t = A n(x): only as the next operand TF; z = x + B t: into rows of its own (the stream itself stays as it is),
       // leaving the shared head's operand XN = bf16(z * gfinal)
       GemmOut o;
-      o.nin = nin; o.Y = s->T; o.ldy = r;
+      o.nin = nin;
       o.nout.xn = (bf16_t*)s->TF; o.nout.ktiles = r / 32; o.nout.ssq = s->ssq_t; o.nout.stride = s->headMp; o.nout.g = s->ones;
       KF(KF_GEMM_HEAD, gemm(s, EPI_ADD, m->auxA[which], (const bf16_t*)s->XN, M, o));
       o = GemmOut(); o.Y = s->Z; o.R = s->X; o.ldy = d;

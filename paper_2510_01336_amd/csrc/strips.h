@@ -6,7 +6,7 @@
 
 #define EE_STRIP_ROWS 32   // most rows of a call of the few-row GEMM
 #define EE_ROWS_TN 4       // weight tiles a wave of the row-tiled GEMM takes (a workgroup: twice as many)
-struct StripShape { int ns, nw, ksplit, U; };   // strips per wave, waves per workgroup, waves that share out K, k-tiles per register set
+struct StripShape { int ns, nw, ksplit; };   // strips per wave, waves per workgroup, waves that share out K
 
 // strips (weight tiles) on the busiest compute unit when workgroups take per_wg each
 inline int strip_load(int ntiles, int per_wg) { return ceil_div(ceil_div(ntiles, per_wg), 256) * per_wg; }
@@ -62,8 +62,7 @@ inline int strip_parts(int ntiles, int ktiles) {
   return parts;
 }
 
-// Launch shape for M <= 32 rows, from sweeps over the matrices of the 8B and 70B widths with cold weights (us; {strips, waves,
-// K parts, U}).  What bounds them is the memory path of a compute unit, which takes in weights and rows together at 35-50 GB/s,
+// Launch shape for M <= 32 rows, from sweeps over the matrices of the 8B and 70B widths with cold weights (us).  What bounds them is the memory path of a compute unit, which takes in weights and rows together at 35-50 GB/s,
 // so the shape has to give every compute unit the same share of the strips and, with several strips a wave, read the rows less
 // often.  `load`: strips on the busiest compute unit.
 //   wide (>= 768 strips): a strip per wave, as many waves a workgroup as deal the strips most evenly: gate/up at 9 rows 8B 40.0
@@ -78,17 +77,17 @@ inline int strip_parts(int ntiles, int ktiles) {
 inline StripShape strip_shape(int ntiles, int ktiles, int M) {
   const int mt = M > 16 ? 2 : 1, parts = strip_parts(ntiles, ktiles);
   if (ntiles >= 768) {
-    if (mt == 2 && strips_by_seven(ntiles, ktiles)) return StripShape{7, 8, 8, 1};
+    if (mt == 2 && strips_by_seven(ntiles, ktiles)) return StripShape{7, 8, 8};
     int nw = ktiles >= 128 && strip_load(ntiles, 8) <= strip_load(ntiles, 4) ? 8 : 4;
     for (int w = 5; w <= 8; ++w)
       if (strip_load(ntiles, w) < strip_load(ntiles, nw)) nw = w;
-    return StripShape{1, nw, 1, mt == 2 ? 4 : 8};
+    return StripShape{1, nw, 1};
   }
   int ns = 1;
   if (ntiles >= 320 && (mt == 2 || ntiles % 256 != 0 || ktiles >= 512))
     for (int n = 2; n <= 4; n *= 2)
       if (strip_load(ntiles, n) * (n + mt) * ns < strip_load(ntiles, ns) * (ns + mt) * n) ns = n;
-  if (ns == 4) return StripShape{4, 8, parts, mt == 2 ? 2 : 4};
-  if (ns == 2) return StripShape{2, 4, parts, 4};
-  return StripShape{1, std::max(4, parts), parts, mt == 2 ? 4 : 8};
+  if (ns == 4) return StripShape{4, 8, parts};
+  if (ns == 2) return StripShape{2, 4, parts};
+  return StripShape{1, std::max(4, parts), parts};
 }
