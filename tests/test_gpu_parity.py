@@ -105,11 +105,12 @@ def test_verify_rounds_match_oracle(name, cfg, ctx, k, bonus):
 
 
 @pytest.mark.parametrize("ctx,k", [([70], 7), ([70, 33], 8)], ids=["rows8", "rows18"])
-@pytest.mark.parametrize("d,ffn", [(256, 14336), (272, 14352), (272, 6160), (272, 5136), (256, 3088)])
+@pytest.mark.parametrize("d,ffn", [(256, 14336), (272, 14304), (272, 14352), (272, 6160), (272, 5136), (256, 3088)])
 def test_strips_dealt_in_every_shape(d, ffn, ctx, k):
-    """Gate/up matrices of 1792 and 1794 strips (seven waves a workgroup, or seven strips a wave beyond 16 rows: even and
-    with a last workgroup of two), 770 (a ragged last workgroup), 642 (four strips a wave, the last of which holds two) and 386
-    (two strips a wave); K of 8 k-tiles and of 9, whose eight shares leave waves without any."""
+    """Gate/up matrices of 1792 and 1788 strips (one strip a wave, seven waves a workgroup: even, and a last workgroup of three), of
+    1794 and 770 (four waves a workgroup, a last one of two), 642 (four strips a wave, K over eight waves, the last strips a pair) and
+    386 (two strips a wave, K over four); K of 8 k-tiles and of 9, whose shares leave waves without any.  The shapes are checked
+    in test_strips_host.py."""
     tol = TOL["bf16"]
     O, model, sess, first, gfirst = _setup(bf16_small(n_layers=3, exit_draft=1, exit_inter=2, d_model=d, d_ffn=ffn), 41, ctx, 3 * (k + 1) + 2)
     assert gfirst.tolist() == first.tolist()
@@ -488,12 +489,17 @@ def test_a_row_has_the_same_bits_beside_any_number_of_others(batch, shape):
         assert np.array_equal(np.repeat(alone, batch, axis=0), rows)
 
 
-@pytest.mark.parametrize("batch", [18, 27])
-def test_17_to_32_rows_at_the_70b_width_agree_with_a_row_alone(batch):
-    """Matrices of 128 MB and more, which get strips or the row-tiled kernel: at the 70B width QKV and head of the row-tiled one (QKV in K
-    shares), down of either, gate/up as seven strips a wave (32 k-tiles a K share).  Another order of the sums over K: bf16 accuracy."""
+@pytest.mark.parametrize("batch", [18, 27, 32])
+@pytest.mark.parametrize("shape", [dict(d_model=8192, n_q_heads=64, head_dim=128, n_kv_heads=8, d_ffn=28672, vocab=32000),
+                                   dict(d_model=2400, d_ffn=14320, vocab=28632), dict(d_model=2720, d_ffn=14320, vocab=28632),
+                                   dict(d_model=3104, d_ffn=11008, vocab=28632)], ids=["70b", "75_ktiles", "85_ktiles", "97_ktiles"])
+def test_17_to_32_rows_of_large_matrices_agree_with_a_row_alone(batch, shape):
+    """Matrices of 128 MB and more, which get strips or the row-tiled kernel.  70B width: QKV and head of the row-tiled one (QKV in K
+    shares), down of either, gate/up as seven strips a wave (32 k-tiles a K share).  Then gate/up and head of 1790 strips, seven a wave with a
+    last workgroup of five, in K shares of 10 k-tiles and a last one of 5, of 11 and 8, of 13 and 6; 1376 strips a wave short of an even deal.
+    Another order of the sums over K than one row alone: bf16 accuracy.  The shapes are checked in test_strips_host.py."""
     import paper_2510_01336_amd as hs
-    cfg = bf16_small(n_layers=3, exit_draft=1, exit_inter=2, d_model=8192, n_q_heads=64, n_kv_heads=8, head_dim=128, d_ffn=28672, vocab=32000, sigma=0.02)
+    cfg = bf16_small(n_layers=3, exit_draft=1, exit_inter=2, sigma=0.02, **shape)
     model = hs.Model(cfg, 58)
     prompt = synth.gen_prompt(cfg.vocab, 1, 3)
     got = []
