@@ -577,11 +577,12 @@ __global__ __launch_bounds__(64 * EE_MAX_WAVES) void gemm_skinny_kernel(const ui
 // With grid.y == 1 the epilogue is fused; otherwise fp32 partial tiles go to scratch and
 // gemm_rows_reduce_kernel sums the K shares in a fixed order and runs the same epilogue.
 // ---------------------------------------------------------------------------------------------
-// Whether the partial tiles of K shares stay in the L2 for the reduce kernel, else they stream to memory.  Measured with the
-// reduction, 8B widths, us, streamed / kept: QKV at 36 / 144 / 192 rows 20.0 / 18.6, 28.4 / 26.0, 32.5 / 31.5 (70B at 144: 49.5 / 46.1);
-// O at 36 / 64 rows 14.5 / 13.4, 15.4 / 14.0; down at 64 / 81 / 112 rows 29.4 / 28.6, 32.5 / 33.8, 34.3 / 35.6: its seven shares of more
-// than 64 rows are written all at once at the end of the launch and are better out of the way.
-__device__ inline bool keep_partials(int epi, int M) { return epi == EPI_ROPE || M <= 64; }
+// Whether the partial tiles of K shares stay in the L2 for the reduce kernel, else they stream to memory.  Kernel and reduction inside
+// decoding steps of so many rows (kernel trace), us, streamed / kept: 8B QKV at 36 / 64 / 144 / 192 rows 19.6 / 19.0, 20.7 / 20.3, 30.7 / 28.2,
+// 34.0 / 33.6; 70B QKV at 144 / 192 / 256 / 512 rows 56.0 / 53.6, 63.2 / 63.4, 71.9 / 73.6, 111.6 / 112.7; 8B O at 36 / 144 15.6 / 14.8, 21.9 / 20.8; 8B
+// down at 36 / 96 / 144 / 256 / 512 29.5 / 29.2, 34.6 / 34.9, 38.8 / 37.3, 52.1 / 50.8, 74.8 / 73.5; 70B down at 144 / 256 97.5 / 96.2, 133 / 131.
+// So only the widest partial sums, those of QKV beyond 192 rows, are better out of the way.
+__device__ inline bool keep_partials(int epi, int M) { return epi != EPI_ROPE || M <= 192; }
 // s_waitcnt immediate: at most n vector-memory loads outstanding, all LDS reads done, export counter untouched
 __host__ __device__ constexpr int waitcnt_vm_lgkm0(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4); }
 
