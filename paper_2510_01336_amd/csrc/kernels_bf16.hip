@@ -186,17 +186,21 @@ struct EpiPre {            // operands of the epilogue that do not depend on the
                            // EPI_ADD: r_a = row of the second destination
 };
 
-// Deals the pairs of one tile (NF = 2), or of two neighbouring ones (NF = 4: wider stores), to all lanes: lo[i], hi[i] = output
-// pair_feature<NF> + i behind the first tile's first feature and its partner.
-template <int NF>
-__device__ inline void pair_up(const f32x4& a, const f32x4& b, float sc, float (&lo)[NF], float (&hi)[NF]) {
+// Deals the pairs of one tile to all lanes: lo[i], hi[i] = output pair_feature<2> + i behind the tile's first feature and its partner.
+__device__ inline void pair_up(const f32x4& a, float sc, float (&lo)[2], float (&hi)[2]) {
   typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 #pragma unroll
-  for (int i = 0; i < NF; ++i) {
-    const u32x2_t r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a[i] * sc), __float_as_uint((NF == 2 ? a[2 + i] : b[i]) * sc), false, false);
+  for (int i = 0; i < 2; ++i) {
+    const u32x2_t r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a[i] * sc), __float_as_uint(a[2 + i] * sc), false, false);
     lo[i] = __uint_as_float(r[0]); hi[i] = __uint_as_float(r[1]);
   }
 }
+// The kernels that stage weight tiles in LDS need no such exchange: of a pair of tiles t and t + 1 they fetch the sixteen features into
+// one slot and their partners into the next, so that a lane finds both in its two accumulators (QKV of 96 x 16 tiles at 512
+// rows 30.6 -> 28.4 us, 8B gate/up at 2048 with the stores below 374.8 -> 368.6).  Lane `lane` of slot `slot` fetches unit paired_unit of tile
+// (slot & ~1) + paired_tile:
+__device__ inline int paired_tile(int lane) { return (lane >> 3) & 1; }
+__device__ inline int paired_unit(int lane, int slot) { return (lane >> 4) * 16 + (lane & 7) + 8 * (slot & 1); }
 template <int NF>
 __device__ inline int pair_feature(int lane) { return NF == 2 ? ((lane >> 4) & 1) * 4 + (lane >> 5) * 2 : (lane >> 4) * 4; }
 template <int NF>
@@ -289,12 +293,9 @@ __device__ inline void norm_factors(float (&sc)[NT], NormPartials<NT>& q, const 
   }
 }
 
-// The paired epilogues.  NF = 2: one tile; 4: tiles `tile` and `tile` + 1 (the next one's accumulators in acc1)
+// The paired epilogues on a lane's features lo and their partners hi.  NF = 2: of one tile; 4: of tiles `tile` and `tile` + 1
 template <int EPI, int NF>
-__device__ inline void epi_apply_pairs(const f32x4& acc0, const f32x4& acc1, float sc, const EpiPre& p, const GemmOut& out, int tile, int row, bool ok, int lane) {
-  float lo[NF], hi[NF];
-  pair_up<NF>(acc0, acc1, sc, lo, hi);
-  if (!ok) return;
+__device__ inline void epi_store_pairs(float (&lo)[NF], float (&hi)[NF], const EpiPre& p, const GemmOut& out, int tile, int row, int lane) {
   if (EPI == EPI_SWIGLU) {
     const int f = tile * 8 + pair_feature<NF>(lane);     // h[m][f ..] = silu(gate) * up
     float h[NF];
@@ -311,8 +312,8 @@ __device__ inline void epi_apply_pairs(const f32x4& acc0, const f32x4& acc1, flo
       for (int v = 0; v < NF; ++v) {
         const float4 t = p.rc[v >> 1];
         const float c = v & 1 ? t.z : t.x, s = v & 1 ? t.w : t.y, a = lo[v], b = hi[v];
-        lo[v] = a * c - b * s;
-        hi[v] = b * c + a * s;
+        lo[v] = fmaf(a, c, -(b * s));      // (spelled out: the same rounding in every kernel)
+        hi[v] = fmaf(b, c, a * s);
       }
     }
     if (h < R.Hq) {
@@ -343,6 +344,42 @@ __device__ inline void epi_apply_pairs(const f32x4& acc0, const f32x4& acc1, flo
   }
 }
 
+// one tile as it lies in memory (eight features and their partners)
+template <int EPI>
+__device__ inline void epi_apply_tile(const f32x4& acc, float sc, const EpiPre& p, const GemmOut& out, int tile, int row, bool ok, int lane) {
+  float lo[2], hi[2];
+  pair_up(acc, sc, lo, hi);
+  if (ok) epi_store_pairs<EPI, 2>(lo, hi, p, out, tile, row, lane);
+}
+// tiles `tile` and `tile` + 1, fetched as paired_unit says
+template <int EPI>
+__device__ inline void epi_apply_pair(const f32x4& acc0, const f32x4& acc1, float sc, const EpiPre& p, const GemmOut& out, int tile, int row, bool ok, int lane) {
+  float lo[4], hi[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) { lo[v] = acc0[v] * sc; hi[v] = acc1[v] * sc; }
+  if (ok) epi_store_pairs<EPI, 4>(lo, hi, p, out, tile, row, lane);
+}
+
+// SwiGLU of the pair for two row tiles at once: lanes 16..31 and 48..63 give their features to the lanes below them and take over the
+// second row tile, so that every lane stores a whole 16-byte unit.  Halves of units, in runs of 64 bytes, made gate/up launches with
+// little K slower than with an operand in fragment order: 86 x 8 tiles at 512 / 2048 rows 17.9 / 69.9 us, 17.4 / 67.4 in fragment order, 16.2 /
+// 62.6 as it is now.
+__device__ inline void epi_swiglu_two_rows(const f32x4& gate0, const f32x4& up0, float sc0, const f32x4& gate1, const f32x4& up1, float sc1, const GemmOut& out,
+                                           int tile, int row0, bool ok0, int row1, bool ok1, int lane) {
+  typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+  float h0[4], h1[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const float a = gate0[v] * sc0, b = gate1[v] * sc1;
+    h0[v] = a / (1.0f + __expf(-a)) * (up0[v] * sc0);
+    h1[v] = b / (1.0f + __expf(-b)) * (up1[v] * sc1);
+  }
+  const u32x2_t x = __builtin_amdgcn_permlane16_swap(pack2(h0[0], h0[1]), pack2(h1[0], h1[1]), false, false);
+  const u32x2_t y = __builtin_amdgcn_permlane16_swap(pack2(h0[2], h0[3]), pack2(h1[2], h1[3]), false, false);
+  const bool second = lane & 16;
+  if (second ? ok1 : ok0) *(uint4*)(out.H + act_offset(second ? row1 : row0, tile * 8 + (lane >> 5) * 8, out.h_ktiles)) = make_uint4(x[0], y[0], x[1], y[1]);
+}
+
 // sc: the row's deferred RMSNorm factor (1 when the operand was already normalised)
 template <int EPI>
 __device__ inline void epi_apply(const f32x4& acc0, float sc, const EpiPre& p, const GemmOut& out, int task,
@@ -364,7 +401,7 @@ __device__ inline void epi_apply(const f32x4& acc0, float sc, const EpiPre& p, c
       else if (g == 0) out.nout.ssq[(size_t)task * out.nout.stride + row] = ss;
     }
   } else if (EPI == EPI_SWIGLU || EPI == EPI_ROPE) {
-    epi_apply_pairs<EPI, 2>(acc0, acc0, sc, p, out, task, row, ok, lane);
+    epi_apply_tile<EPI>(acc0, sc, p, out, task, row, ok, lane);
   } else {   // EPI_ARGMAX: per-row (max, arg max) over this tile's 16 outputs; lowest index wins ties
     float best = -INFINITY; int bi = 0x7fffffff;
 #pragma unroll
@@ -639,7 +676,11 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
   // constant, so none of them occupies a vector register (measured: 3-4 % at 24 and 32 row tiles)
   const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(lptr_t)&ring[0][0]) + 1024u * wave_s;
 #define ROWS_LDS(slot_, tile_) ((lptr_t)(size_t)(lds0 + 16u * ((slot_) * STAGE + (tile_) * 64)))
-  const u32x4* wsrc = (const u32x4*)W + (size_t)min(bx * WT + wave, ntiles - 1) * ktiles * 64 + lane;
+  constexpr int PT = EPI == EPI_SWIGLU || EPI == EPI_ROPE ? 2 : 1;      // tiles the epilogue takes at once
+  // (K shares leave their partial tiles as they lie in memory; so does the last of seven tiles, which has no partner here)
+  const bool paired = PT == 2 && gridDim.y == 1 && wave_s < (WT & ~1);
+  const u32x4* wsrc = (const u32x4*)W + (size_t)min(bx * WT + (paired ? (wave & ~1) + paired_tile(lane) : wave), ntiles - 1) * ktiles * 64 +
+                      (paired ? paired_unit(lane, wave) : lane);
   const u32x4* xsrc = (const u32x4*)A + (size_t)(((row0 + rbase) >> 4) + wave) * ktiles * 64 + act_unit(lane & 15, lane >> 4);
   // (weights: streaming hint)
 #define ROWS_REQUEST(slot_, kt_)                                                                              \
@@ -744,21 +785,35 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
     norm_request<TMW>(part, out.nin, row0 + rbase + mt_first * 16, MT_STEP, min(mt_own, TMW), 0, lane);
     norm_factors<TMW>(sc, part, out.nin, row0 + rbase + mt_first * 16, MT_STEP, min(mt_own, TMW), lane);
   }
-  constexpr int PT = EPI == EPI_SWIGLU || EPI == EPI_ROPE ? 2 : 1;      // tiles the epilogue takes at once
 #pragma unroll
   for (int t = 0; t < TN; t += PT) {
     const int task = nt0 + t;
     if (task >= ntiles || (WT < 2 * TN && nh && t == TN - 1)) continue;
-    const bool lone = PT == 2 && WT < 2 * TN && ((nh && t == TN - 2) || task + 1 >= ntiles);      // (the next tile is another workgroup's or none)
+    const bool lone = PT == 2 && WT < 2 * TN && nh && t == TN - 2;      // (the next tile is another workgroup's)
+    constexpr int RT = EPI == EPI_SWIGLU && TMW > 1 ? 2 : 1;            // row tiles it takes at once
+    const bool mine = PT == 1 || WT == 2 * TN || task + 1 < ntiles || lane < 32;      // (no next tile: only the lanes of the first one)
 #pragma unroll
-    for (int mt = 0; mt < TMW; ++mt) {
+    for (int mt = 0; mt < TMW; mt += RT) {
       const int m = (mt_first + mt * MT_STEP) * 16 + mc;
       if (mt_first + mt * MT_STEP >= mt_used) continue;
-      EpiPre pre;
-      epi_prefetch<EPI, 2 * PT>(pre, out, task, row0 + rbase + m, m < M, lane);
-      if (lone) epi_apply_pairs<EPI, 2>(acc[t][mt], acc[t][mt], sc[mt], pre, out, task, row0 + rbase + m, m < M, lane);
-      else if constexpr (PT == 2) epi_apply_pairs<EPI, 4>(acc[t][mt], acc[t + 1][mt], sc[mt], pre, out, task, row0 + rbase + m, m < M, lane);
-      else epi_apply<EPI>(acc[t][mt], sc[mt], pre, out, task, row0 + rbase + m, m < M, N, lane);
+      if constexpr (RT == 2) {
+        if (!lone && mt + 1 < TMW) {
+          const int m1 = m + 16 * MT_STEP;
+          epi_swiglu_two_rows(acc[t][mt], acc[t + 1][mt], sc[mt], acc[t][mt + 1], acc[t + 1][mt + 1], sc[mt + 1], out, task, row0 + rbase + m, m < M && mine,
+                              row0 + rbase + m1, m1 < M && mine, lane);
+          continue;
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        if (mt + r >= TMW || mt_first + (mt + r) * MT_STEP >= mt_used) continue;
+        const int mr = m + 16 * MT_STEP * r;
+        EpiPre pre;
+        epi_prefetch<EPI, 2 * PT>(pre, out, task, row0 + rbase + mr, mr < M, lane);
+        if (lone) epi_apply_tile<EPI>(acc[t][mt + r], sc[mt + r], pre, out, task, row0 + rbase + mr, mr < M, lane);
+        else if constexpr (PT == 2) epi_apply_pair<EPI>(acc[t][mt + r], acc[t + 1][mt + r], sc[mt + r], pre, out, task, row0 + rbase + mr, mr < M && mine, lane);
+        else epi_apply<EPI>(acc[t][mt + r], sc[mt + r], pre, out, task, row0 + rbase + mr, mr < M, N, lane);
+      }
     }
   }
 }
@@ -802,12 +857,14 @@ __device__ __forceinline__ void gemm_block_body(u32x4* ring, const uint4* __rest
   typedef const __attribute__((address_space(1))) void* gptr_t;
   typedef __attribute__((address_space(3))) void* lptr_t;
   const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(lptr_t)ring) + 1024u * wave_s;
+  constexpr int PT = EPI == EPI_SWIGLU || EPI == EPI_ROPE ? 2 : 1;      // tiles the epilogue takes at once
   const u32x4* src[NJ];
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
     const int t = wave_s + 8 * j;
-    const size_t tile = t < WT ? (size_t)min(bx * WT + t, ntiles - 1) : (size_t)(((row0 + rbase) >> 4) + t - WT);
-    src[j] = (t < WT ? (const u32x4*)W + lane : (const u32x4*)A + act_unit(lane & 15, lane >> 4)) + tile * ktiles * 64;
+    const int wt = PT == 2 ? (t & ~1) + paired_tile(lane) : t;
+    const size_t tile = t < WT ? (size_t)min(bx * WT + wt, ntiles - 1) : (size_t)(((row0 + rbase) >> 4) + t - WT);
+    src[j] = (t < WT ? (const u32x4*)W + (PT == 2 ? paired_unit(lane, t) : lane) : (const u32x4*)A + act_unit(lane & 15, lane >> 4)) + tile * ktiles * 64;
   }
   // requests of this wave per stage: its tiles that exist and, among the row tiles, hold rows (a prefix of its list)
   const int have = WT + mt_used;
@@ -874,19 +931,24 @@ __device__ __forceinline__ void gemm_block_body(u32x4* ring, const uint4* __rest
 #undef BLK_REQUEST
   __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
   const int mc = lane & 15;
-  constexpr int PT = EPI == EPI_SWIGLU || EPI == EPI_ROPE ? 2 : 1;      // tiles the epilogue takes at once
 #pragma unroll
   for (int t = 0; t < TN; t += PT) {
     const int task = nt0 + t;
     if (task >= ntiles) continue;
 #pragma unroll
-    for (int mt = 0; mt < TMW; ++mt) {
+    for (int mt = 0; mt < TMW; mt += EPI == EPI_SWIGLU ? 2 : 1) {
       const int m = (mt_first + mt * MT_STEP) * 16 + mc;
       if (mt_first + mt * MT_STEP >= mt_used) continue;
       const float sc = out.nin.inv_rms ? out.nin.inv_rms[rbase + min(m, M - 1)] : 1.0f;
+      if constexpr (EPI == EPI_SWIGLU) {
+        const int m1 = m + 16 * MT_STEP;
+        const float sc1 = out.nin.inv_rms ? out.nin.inv_rms[rbase + min(m1, M - 1)] : 1.0f;
+        epi_swiglu_two_rows(acc[t][mt], acc[t + 1][mt], sc, acc[t][mt + 1], acc[t + 1][mt + 1], sc1, out, task, row0 + rbase + m, m < M, row0 + rbase + m1, m1 < M, lane);
+        continue;
+      }
       EpiPre pre;
       epi_prefetch<EPI, 2 * PT>(pre, out, task, row0 + rbase + m, m < M, lane);
-      if constexpr (PT == 2) epi_apply_pairs<EPI, 4>(acc[t][mt], acc[t + 1][mt], sc, pre, out, task, row0 + rbase + m, m < M, lane);
+      if constexpr (PT == 2) epi_apply_pair<EPI>(acc[t][mt], acc[t + 1][mt], sc, pre, out, task, row0 + rbase + m, m < M, lane);
       else epi_apply<EPI>(acc[t][mt], sc, pre, out, task, row0 + rbase + m, m < M, N, lane);
     }
   }
