@@ -186,16 +186,18 @@ struct EpiPre {            // operands of the epilogue that do not depend on the
                            // EPI_ADD: r_a = row of the second destination
 };
 
-// Deals the pairs of one tile to all lanes: lo[i], hi[i] = output pair_feature<2> + i behind the tile's first feature and its partner.
-__device__ inline void pair_up(const f32x4& a, float sc, float (&lo)[2], float (&hi)[2]) {
+// Deals the pairs of one tile (NF = 2), or of two neighbouring ones (NF = 4: wider stores), to all lanes: lo[i], hi[i] = output
+// pair_feature<NF> + i behind the first tile's first feature and its partner.
+template <int NF>
+__device__ inline void pair_up(const f32x4& a, const f32x4& b, float sc, float (&lo)[NF], float (&hi)[NF]) {
   typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const u32x2_t r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a[i] * sc), __float_as_uint(a[2 + i] * sc), false, false);
+  for (int i = 0; i < NF; ++i) {
+    const u32x2_t r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a[i] * sc), __float_as_uint((NF == 2 ? a[2 + i] : b[i]) * sc), false, false);
     lo[i] = __uint_as_float(r[0]); hi[i] = __uint_as_float(r[1]);
   }
 }
-// The kernels that stage weight tiles in LDS need no such exchange: of a pair of tiles t and t + 1 they fetch the sixteen features into
+// Kernels that stage weight tiles in LDS can do without: of a pair of tiles t and t + 1 they fetch the sixteen features into
 // one slot and their partners into the next, so that a lane finds both in its two accumulators (QKV of 96 x 16 tiles at 512
 // rows 30.6 -> 28.4 us, 8B gate/up at 2048 with the stores below 374.8 -> 368.6).  Lane `lane` of slot `slot` fetches unit paired_unit of tile
 // (slot & ~1) + paired_tile:
@@ -344,12 +346,12 @@ __device__ inline void epi_store_pairs(float (&lo)[NF], float (&hi)[NF], const E
   }
 }
 
-// one tile as it lies in memory (eight features and their partners)
-template <int EPI>
-__device__ inline void epi_apply_tile(const f32x4& acc, float sc, const EpiPre& p, const GemmOut& out, int tile, int row, bool ok, int lane) {
-  float lo[2], hi[2];
-  pair_up(acc, sc, lo, hi);
-  if (ok) epi_store_pairs<EPI, 2>(lo, hi, p, out, tile, row, lane);
+// tiles as they lie in memory (eight features and their partners), NF as above (NF = 4: the next one's accumulators in acc1)
+template <int EPI, int NF>
+__device__ inline void epi_apply_tiles(const f32x4& acc0, const f32x4& acc1, float sc, const EpiPre& p, const GemmOut& out, int tile, int row, bool ok, int lane) {
+  float lo[NF], hi[NF];
+  pair_up<NF>(acc0, acc1, sc, lo, hi);
+  if (ok) epi_store_pairs<EPI, NF>(lo, hi, p, out, tile, row, lane);
 }
 // tiles `tile` and `tile` + 1, fetched as paired_unit says
 template <int EPI>
@@ -401,7 +403,7 @@ __device__ inline void epi_apply(const f32x4& acc0, float sc, const EpiPre& p, c
       else if (g == 0) out.nout.ssq[(size_t)task * out.nout.stride + row] = ss;
     }
   } else if (EPI == EPI_SWIGLU || EPI == EPI_ROPE) {
-    epi_apply_tile<EPI>(acc0, sc, p, out, task, row, ok, lane);
+    epi_apply_tiles<EPI, 2>(acc0, acc0, sc, p, out, task, row, ok, lane);
   } else {   // EPI_ARGMAX: per-row (max, arg max) over this tile's 16 outputs; lowest index wins ties
     float best = -INFINITY; int bi = 0x7fffffff;
 #pragma unroll
@@ -810,7 +812,7 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
         const int mr = m + 16 * MT_STEP * r;
         EpiPre pre;
         epi_prefetch<EPI, 2 * PT>(pre, out, task, row0 + rbase + mr, mr < M, lane);
-        if (lone) epi_apply_tile<EPI>(acc[t][mt + r], sc[mt + r], pre, out, task, row0 + rbase + mr, mr < M, lane);
+        if (lone) epi_apply_tiles<EPI, 2>(acc[t][mt + r], acc[t][mt + r], sc[mt + r], pre, out, task, row0 + rbase + mr, mr < M, lane);
         else if constexpr (PT == 2) epi_apply_pair<EPI>(acc[t][mt + r], acc[t + 1][mt + r], sc[mt + r], pre, out, task, row0 + rbase + mr, mr < M && mine, lane);
         else epi_apply<EPI>(acc[t][mt + r], sc[mt + r], pre, out, task, row0 + rbase + mr, mr < M, N, lane);
       }
@@ -862,9 +864,11 @@ __device__ __forceinline__ void gemm_block_body(u32x4* ring, const uint4* __rest
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
     const int t = wave_s + 8 * j;
-    const int wt = PT == 2 ? (t & ~1) + paired_tile(lane) : t;
+    // (QKV as it lies in memory: paired, 4096 rows took 202 us against 198 at the 8B width)
+    const bool paired = EPI == EPI_SWIGLU;
+    const int wt = paired ? (t & ~1) + paired_tile(lane) : t;
     const size_t tile = t < WT ? (size_t)min(bx * WT + wt, ntiles - 1) : (size_t)(((row0 + rbase) >> 4) + t - WT);
-    src[j] = (t < WT ? (const u32x4*)W + (PT == 2 ? paired_unit(lane, t) : lane) : (const u32x4*)A + act_unit(lane & 15, lane >> 4)) + tile * ktiles * 64;
+    src[j] = (t < WT ? (const u32x4*)W + (paired ? paired_unit(lane, t) : lane) : (const u32x4*)A + act_unit(lane & 15, lane >> 4)) + tile * ktiles * 64;
   }
   // requests of this wave per stage: its tiles that exist and, among the row tiles, hold rows (a prefix of its list)
   const int have = WT + mt_used;
@@ -948,7 +952,7 @@ __device__ __forceinline__ void gemm_block_body(u32x4* ring, const uint4* __rest
       }
       EpiPre pre;
       epi_prefetch<EPI, 2 * PT>(pre, out, task, row0 + rbase + m, m < M, lane);
-      if constexpr (PT == 2) epi_apply_pair<EPI>(acc[t][mt], acc[t + 1][mt], sc, pre, out, task, row0 + rbase + m, m < M, lane);
+      if constexpr (PT == 2) epi_apply_tiles<EPI, 4>(acc[t][mt], acc[t + 1][mt], sc, pre, out, task, row0 + rbase + m, m < M, lane);
       else epi_apply<EPI>(acc[t][mt], sc, pre, out, task, row0 + rbase + m, m < M, N, lane);
     }
   }
