@@ -131,7 +131,7 @@ def test_seven_weight_tiles_a_workgroup_match_oracle(batch):
 
 @pytest.mark.parametrize("row_tiles", [0, 4, 8, 16, 104, 108])
 def test_both_forms_of_the_narrow_projection_gemm_match_oracle(row_tiles):
-    """The narrow projections (O, down, QKV, adapters) of a call with more than 16 rows run either with K shares and
+    """The narrow projections (O, down, QKV, adapters) of a call with more than 32 rows run either with K shares and
     a reduction pass (0) or in blocks of row_tiles*16 rows (+100: eight weight tiles per workgroup): each form forced in turn on a case whose context build
     fills whole 512-row passes and ends in a ragged one, and whose verify calls hold 144 rows and 17..64 rows."""
     name, cfg, ctx, k, bonus = next(c for c in CASES if c[0] == "bf16_d128_heads_batch16")
@@ -150,8 +150,8 @@ def test_both_forms_of_the_narrow_projection_gemm_match_oracle(row_tiles):
 
 
 def test_more_than_512_rows_in_one_call():
-    """60 sequences x 9 block rows = 540 rows: beyond the row-tiled GEMM's 512, so the projections run as 64-row
-    passes of the skinny kernel.  With so many sequences some deciding row is always a near-tie, so every sequence
+    """60 sequences x 9 block rows = 540 rows: beyond the row-tiled GEMM's 512, so the projections run blocked or as 512 rows and the
+    rest.  With so many sequences some deciding row is always a near-tie, so every sequence
     is compared as far as its own rows clear the margin (and dropped once the two sides may have parted)."""
     cfg, k, tol = bf16_small(), 8, TOL["bf16"]
     ctx = [5 + (7 * i) % 60 for i in range(60)]
@@ -513,6 +513,31 @@ def test_17_to_32_rows_of_large_matrices_agree_with_a_row_alone(batch, shape):
     for alone, rows in zip(*got):
         assert max_rel(rows[0], alone[0].astype(np.float64)) <= TOL["bf16"]
         assert all(np.array_equal(rows[0], r) for r in rows[1:])       # (the same row in every slot)
+
+
+def test_forced_row_tiled_forms_reach_large_matrices_from_17_rows():
+    """18 rows of a model whose gate/up and head hold 128 MB and more: strips as the library runs them, and each forced form of the
+    row-tiled kernels, agree to bf16 accuracy; a forced form is another order of sums, so that some bits differ."""
+    import paper_2510_01336_amd as hs
+    cfg = bf16_small(n_layers=3, exit_draft=1, exit_inter=2, sigma=0.02, d_model=2720, d_ffn=14320, vocab=28632)
+    model = hs.Model(cfg, 58)
+    prompts = [synth.gen_prompt(cfg.vocab, 1, b) for b in range(18)]
+    got = {}
+    try:
+        for form in ("strips", "shares", "blocks"):
+            hs.ee_debug_gemm_row_blocks(0 if form == "shares" else -1)
+            hs.ee_debug_gemm_block_tiles(16 if form == "blocks" else 0)
+            sess = hs.Session(model, 18, 64, 12)
+            sess.enable_logits(True)
+            sess.prefill(prompts)
+            got[form] = sess.last_logits(18)
+            sess.close()
+    finally:
+        hs.ee_debug_gemm_row_blocks(-1); hs.ee_debug_gemm_block_tiles(0)
+    model.close()
+    for form in ("shares", "blocks"):
+        assert max_rel(got[form], got["strips"].astype(np.float64)) <= TOL["bf16"]
+        assert not np.array_equal(got[form], got["strips"])
 
 
 @pytest.mark.parametrize("pages", [136, 137, 648, 649])
