@@ -597,7 +597,8 @@ __global__ __launch_bounds__(64 * EE_MAX_WAVES) void gemm_skinny_kernel(const ui
 }
 
 // ---------------------------------------------------------------------------------------------
-// Row-tiled GEMM for a block of 16 < M <= 512 rows (up to 32 only where that is quicker than the skinny kernel, see strips_serve): weights cross HBM once per block, but every weight fragment now
+// Row-tiled GEMM for a block of 16 < M <= 512 rows (up to 32 only where that is quicker than the skinny kernel, see
+// strips_serve): weights cross HBM once per block, but every weight fragment now
 // meets up to 32 row tiles, so the kernel sits near the machine's ridge (M flop per weight byte).
 // Workgroup = 8 waves (two per SIMD: one wave alone does not keep a matrix pipe busy) on a group of
 // WT = 8 weight tiles (128 output features; 7 where that deals a wide matrix more evenly, see the launcher) and a share of K (grid.y); wave (rq, nh) owns 4 of the tiles and a

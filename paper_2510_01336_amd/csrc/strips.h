@@ -52,24 +52,26 @@ inline bool strips_serve(int ntiles, int ktiles, int M) {
 // K shares of a strip.  Below 128 MB they are a matter of the matrix alone: a row's sums then run over K in one order and are the same
 // bits however many rows are beside it (up to EE_STRIP_ROWS).  A large wide matrix is summed over the whole K by one wave up to 16 rows,
 // where a wave has one strip, and in eight shares beyond, where it has seven.
-//   Eight for some 256 strips with a long K, 8B down at 9 / 24 rows 20.9 / 27.1 us (four 22.0 / 26.5), else four, never of fewer than four
-//   k-tiles.
+//   Four, never of fewer than four k-tiles; eight on around 256 strips of 416 to 511 k-tiles, where single rows, most of a decoding
+//   step, gain more than 17..32 lose: us at 1 / 9 / 24 rows, eight and four, 256 x 448 (8B down) 19.8 / 21.1 / 27.2, 20.5 / 21.1 / 26.5;
+//   256 x 432 19.3 / 20.8 / 26.5, 19.6 / 20.9 / 25.5; but 256 x 344 17.9 / 18.9 / 22.2, 16.7 / 17.7 / 22.0; 256 x 400 18.8 / 20.2 / 24.7, 18.3 / 19.5 / 24.0;
+//   256 x 512 25.6 / 27.2 / 30.6, 25.4 / 27.2 / 31.1; 256 x 608 26.4 / 28.5 / 34.9, 25.6 / 27.3 / 34.4; 224 x 592 23.5 / 26.7 / 33.9, 22.6 / 25.9 / 32.9
 inline int strip_parts(int ntiles, int ktiles) {
   if (ntiles >= 768) return 1;
   if (ntiles > 512) return 8;
-  int parts = ntiles >= 200 && ntiles < 320 && ktiles >= 256 ? 8 : 4;
+  int parts = ntiles >= 200 && ntiles < 320 && ktiles >= 416 && ktiles < 512 ? 8 : 4;
   while (ntiles < 320 && parts > 1 && ktiles / parts < 4) parts >>= 1;
   return parts;
 }
 
-// Launch shape for M <= 32 rows, from sweeps over the matrices of the 8B and 70B widths with cold weights (us).  What bounds them is the memory path of a compute unit, which takes in weights and rows together at 35-50 GB/s,
-// so the shape has to give every compute unit the same share of the strips and, with several strips a wave, read the rows less
-// often.  `load`: strips on the busiest compute unit.
+// Launch shape for M <= 32 rows, from sweeps over the matrices of the 8B and 70B widths with cold weights (us).  What bounds them is
+// the memory path of a compute unit, which takes in weights and rows together at 35-50 GB/s, so the shape has to give every
+// compute unit the same share of the strips and, with several strips a wave, read the rows less often.  `load`: strips on the busiest compute unit.
 //   wide (>= 768 strips): a strip per wave, as many waves a workgroup as deal the strips most evenly: gate/up at 9 rows 8B 40.0
 //     with four waves on 224 units, 38.9 with seven on 256; 70B 148 / 141.  Of equal deals four waves, whose workgroups start and end
 //     sooner, where K is short (8016 x 64 at 9 rows 83.7, eight waves 92.0; 9496 x 80 120, 125; 5000 x 96 75.3, five 85.0), eight where
-//     it is long (8016 x 128 at 9 / 16 rows 163.7 / 166.1, four 164.7 / 167.9; 8016 x 256 309 / 311, four 321 / 329).  At 17..32 rows of a large matrix seven strips a wave and
-//     K over eight waves, see above.
+//     it is long (8016 x 128 at 9 / 16 rows 163.7 / 166.1, four 164.7 / 167.9; 8016 x 256 309 / 311, four 321 / 329).  At 17..32 rows of a
+//     large matrix seven strips a wave and K over eight waves, see above.
 //   narrow: K over four or eight waves.  Two or four strips a wave where that makes load * (1 + row tiles / strips) smaller: 70B
 //     QKV (640 strips) at 9 / 24 rows 32.8 / 37.9 with four, 35.1 / 41.6 with one; 70B down 70.2 / 74.4 with two, 77.4 / 92.6; 8B
 //     QKV (384) 13.3 / 15.5 with two, 13.8 / 16.6.  At one row tile, strips that fill the chip evenly and a K below 512 k-tiles stay

@@ -52,7 +52,7 @@ def test_calls_of_17_to_32_rows_get_the_quicker_kernel(strips_host, ntiles, ktil
 # the shapes that the GPU tests of the few-row GEMM are made for: weight tiles, k-tiles, at 8 and 18 rows (gate/up, then the large heads)
 @pytest.mark.parametrize("ntiles,ktiles,few,more", [
     (1792, 8, "1 7 1", "1 7 1"), (1788, 9, "1 7 1", "1 7 1"), (1794, 9, "1 4 1", "1 4 1"), (770, 9, "1 4 1", "1 4 1"), (642, 9, "4 8 8", "4 8 8"),
-    (386, 8, "2 4 4", "2 4 4"), (224, 256, "1 8 8", "1 8 8"), (512, 8, "1 4 4", "2 4 4"),
+    (386, 8, "2 4 4", "2 4 4"), (224, 256, "1 4 4", "1 4 4"), (256, 344, "1 4 4", "1 4 4"), (256, 448, "1 8 8", "1 8 8"), (512, 8, "1 4 4", "2 4 4"),
     (1790, 75, "1 7 1", "7 8 8"), (1790, 85, "1 7 1", "7 8 8"), (1790, 97, "1 7 1", "7 8 8"), (1376, 97, "1 6 1", "7 8 8"),
     (3584, 256, "1 7 1", "7 8 8"), (640, 256, "4 8 8", "rows"), (2000, 256, "1 8 1", "rows")])
 def test_shapes_of_the_gpu_tests(strips_host, ntiles, ktiles, few, more):
