@@ -824,8 +824,8 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
 // ---------------------------------------------------------------------------------------------
 // Blocked GEMM for calls of more than 256 rows (context build, large batches): the ring of direct global->LDS stages of
 // the kernel above, but the rows are cut into blocks of 256 and the weights into groups of 2*TN tiles, and one launch covers
-// all blocks.  blockIdx.x enumerates them so that every XCD (workgroup id mod 8) works on consecutive ones, row blocks
-// fastest: the row blocks of a weight group run side by side and read its weights from one L2.
+// all blocks.  blockIdx.x enumerates them so that every XCD (workgroup id mod 8) works on consecutive ones, a run of row blocks
+// fastest (block_place): the row blocks of a weight group run side by side and read its weights from one L2.
 // What bounds it: with sixteen weight tiles a k-tile is 1024 clocks of MFMAs per SIMD, 128 KiB of LDS traffic (1000 clocks)
 // and 32 KiB of requests, and the clock gives way under that load: 1361 TFLOP/s on the gate/up matrix at 4096 rows (707 us;
 // passes of 512 rows in the previous form 812 us), 1212-1245 at 2048 rows (386-397 us).  Narrow matrices take 12 or 8 weight tiles so that the
@@ -964,10 +964,11 @@ __global__ __launch_bounds__(512) void gemm_block_kernel(const uint4* __restrict
                                                          int row0, int M_all, int N, GemmOut out) {
   constexpr int TMT = 16, TILES = 2 * TN + TMT;
   __shared__ u32x4 ring[((160 / TILES) & ~1) * TILES * 64];
-  const int rblocks = (M_all + TMT * 16 - 1) / (TMT * 16), total = ((ntiles + 2 * TN - 1) / (2 * TN)) * rblocks;
+  const int rblocks = (M_all + TMT * 16 - 1) / (TMT * 16), cols = (ntiles + 2 * TN - 1) / (2 * TN), total = cols * rblocks;
   const int share = (total + 7) >> 3, i = blockIdx.x >> 3, b = (blockIdx.x & 7) * share + i;
   if (i >= share || b >= total) return;             // whole workgroup
-  const int bx = b / rblocks, rbase = (b % rblocks) * (TMT * 16), M = min(M_all - rbase, TMT * 16);
+  const BlockPlace at = block_place(b, cols, rblocks);
+  const int bx = at.col, rbase = at.row * (TMT * 16), M = min(M_all - rbase, TMT * 16);
   if (M > TMT * 16 - 16) gemm_block_body<EPI, TN, true>(ring, W, ktiles, ntiles, A, row0, rbase, M, N, out, bx);
   else gemm_block_body<EPI, TN, false>(ring, W, ktiles, ntiles, A, row0, rbase, M, N, out, bx);
 }

@@ -1,5 +1,5 @@
-// Host program behind test_strips_host.py: the launch shapes of the few-row GEMM (csrc/strips.h).
-//   strips_host                          every matrix of up to 4200 strips: prints the sizes whose shape breaks a rule
+// Host program behind test_strips_host.py: the launch shapes of the few-row GEMM and the order of the blocked one (csrc/strips.h).
+//   strips_host                          every matrix of up to 4200 strips: prints the sizes whose shape or order breaks a rule
 //   strips_host NTILES KTILES M          prints "strips-per-wave waves K-parts" of that call, or "rows": not a call of this kernel
 #include "../paper_2510_01336_amd/csrc/strips.h"
 #include <cstdio>
@@ -25,5 +25,13 @@ int main(int argc, char** argv) {
         // the K shares, and the shares of the norm's partial sums (one a wave), set the order of a row's sums
         if (!strips_large(nt, kt) && (s.ksplit != one.ksplit || s.nw != one.nw)) wrong(nt, kt, M, "sums in another order than one row alone");
       }
+  for (int rblocks = 1; rblocks <= 40; ++rblocks)      // every block of a blocked launch exactly once
+    for (int cols : {1, 2, 7, 32, 112}) {
+      std::vector<int> seen((size_t)rblocks * cols);
+      for (int b = 0; b < rblocks * cols; ++b) {
+        const BlockPlace p = block_place(b, cols, rblocks);
+        if (p.col < 0 || p.col >= cols || p.row < 0 || p.row >= rblocks || seen[(size_t)p.row * cols + p.col]++) wrong(cols, rblocks, b, "block out of place");
+      }
+    }
   return bad != 0;
 }
