@@ -303,7 +303,8 @@ int ee_debug_gemm_row_blocks(int row_tiles);
 
 /* Test support, process-wide: 8, 12 or 16 runs every projection of more than 16 rows (32 for matrices under 128 MB) in
  * blocks of 256 rows with that many 16-row weight tiles per workgroup (gate/up: 12 or 16, the exit head: 16), whatever
- * its size; 0 restores the built-in choice.  The three give bit-identical results.  EE_ERR_ARG for any other value. */
+ * its size; 808, 1208 and 1212 give QKV, O, down and adapters 8 or 12 weight tiles and blocks of 128 or 192 rows (row tiles
+ * times 100 in front); 0 restores the built-in choice.  All give bit-identical results.  EE_ERR_ARG for any other value. */
 int ee_debug_gemm_block_tiles(int weight_tiles);
 
 /* Test support, process-wide: by default the attention kernel of a call (KV splits with a merge, a wave per page, or

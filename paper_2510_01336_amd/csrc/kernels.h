@@ -92,7 +92,7 @@ extern LaunchEvents* g_launch_events;
 extern int g_attn_pages_override;   // <= 0: pages per KV split chosen from the call's shape; else that many (test hook: batch and solo runs then cut their contexts alike)
 extern int g_attn_form;              // -1: attention kernel chosen from the call's shape; else that one (ATTN_*) on every call (test hook)
 extern int g_rows_wide;              // 1: gate/up and exit head beyond 256 rows run in blocks of 256 rows; 0: in passes of up to 512 rows (test hook)
-extern int g_block_tiles;            // > 0: every call that the skinny kernel does not have to serve runs blocked with that many weight tiles per workgroup (test hook)
+extern int g_block_tiles;            // > 0: every call that the skinny kernel does not have to serve runs blocked with that many weight tiles per workgroup, plus 100 times the row tiles if not 16 (test hook)
 extern int g_rows_blocks_override;   // -1: built-in choice between K shares and row blocks; else 0, or row tiles per block (+100: eight weight tiles per workgroup)
 size_t bf16_gemm_rows_scratch_floats(int ntiles, int ktiles);
 // Whether bf16_gemm serves a call of M rows, else bf16_gemm_rows.  While a test hook forces a form of the latter, it gets every call of

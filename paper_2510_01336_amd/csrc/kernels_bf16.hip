@@ -824,8 +824,8 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
 // ---------------------------------------------------------------------------------------------
 // Blocked GEMM for calls of more than 256 rows (context build, large batches): the ring of direct global->LDS stages of
 // the kernel above, but the rows are cut into blocks of 256 and the weights into groups of 2*TN tiles, and one launch covers
-// all blocks.  blockIdx.x enumerates them so that every XCD (workgroup id mod 8) works on consecutive ones, a run of row blocks
-// fastest (block_place): the row blocks of a weight group run side by side and read its weights from one L2.
+// all blocks, each XCD on blocks that share weights and rows in its L2 (block_order).
+// (Blocks of 192 and 128 rows serve narrow matrices that would leave compute units idle, see kNarrowForms.)
 // What bounds it: with sixteen weight tiles a k-tile is 1024 clocks of MFMAs per SIMD, 128 KiB of LDS traffic (1000 clocks)
 // and 32 KiB of requests, and the clock gives way under that load: 1361 TFLOP/s on the gate/up matrix at 4096 rows (707 us;
 // passes of 512 rows in the previous form 812 us), 1212-1245 at 2048 rows (386-397 us).  Narrow matrices take 12 or 8 weight tiles so that the
@@ -836,10 +836,11 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
 // kernel a call gets.  Within the skinny kernel the order is the matrix's own below 128 MB, see strip_parts.)  K shares of the down projection measured 127 us against 154 at 1096 rows, nothing from 2048; shares
 // whose number follows the row count moved the full-depth comparison of a batch with its sequences alone past its bound.
 // ---------------------------------------------------------------------------------------------
-template <int EPI, int TN, bool FULL>
+template <int EPI, int TN, int TMT, bool FULL>
 __device__ __forceinline__ void gemm_block_body(u32x4* ring, const uint4* __restrict__ W, int ktiles, int ntiles, const uint4* __restrict__ A,
                                                 int row0, int rbase, int M, int N, const GemmOut& out, int bx) {
-  constexpr int TMT = 16, WT = 2 * TN, TMW = TMT / 4, TILES = WT + TMT, STAGE = TILES * 64;
+  constexpr int WT = 2 * TN, TMW = TMT / 4, TILES = WT + TMT, STAGE = TILES * 64;
+  static_assert(TMT % 4 == 0 && (EPI != EPI_SWIGLU || TMW % 2 == 0), "row tiles split four ways, and SwiGLU takes two at once");
   constexpr int S = (160 / TILES) & ~1;             // stages in the ring (even: fragments alternate between two register sets)
   constexpr int NJ = (TILES + 7) / 8;               // requests per wave and stage at most: tiles wave, wave + 8, ... (weights first)
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -868,7 +869,7 @@ __device__ __forceinline__ void gemm_block_body(u32x4* ring, const uint4* __rest
     // (QKV as it lies in memory: paired, 4096 rows took 202 us against 198 at the 8B width)
     const bool paired = EPI == EPI_SWIGLU;
     const int wt = paired ? (t & ~1) + paired_tile(lane) : t;
-    const size_t tile = t < WT ? (size_t)min(bx * WT + wt, ntiles - 1) : (size_t)(((row0 + rbase) >> 4) + t - WT);
+    const size_t tile = t < WT ? (size_t)min(bx * WT + wt, ntiles - 1) : (size_t)(((row0 + rbase) >> 4) + min(t - WT, (M - 1) >> 4));
     src[j] = (t < WT ? (const u32x4*)W + (paired ? paired_unit(lane, t) : lane) : (const u32x4*)A + act_unit(lane & 15, lane >> 4)) + tile * ktiles * 64;
   }
   // requests of this wave per stage: its tiles that exist and, among the row tiles, hold rows (a prefix of its list)
@@ -888,6 +889,7 @@ __device__ __forceinline__ void gemm_block_body(u32x4* ring, const uint4* __rest
     if ((FULL && TILES % 8 == 0) || nreq == NJ) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((stages_) * NJ)); \
     else if (FULL || nreq == NJ - 1) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((stages_) * (NJ - 1)));      \
     else if (nreq == NJ - 2) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((stages_) * (NJ - 2)));              \
+    else if (nreq == NJ - 3) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((stages_) * (NJ > 3 ? NJ - 3 : 0))); \
     else __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));                                                     \
   } while (0)
   static_assert((S - 1) * NJ < 64, "the load counter has six bits");
@@ -959,18 +961,16 @@ __device__ __forceinline__ void gemm_block_body(u32x4* ring, const uint4* __rest
   }
 }
 
-template <int EPI, int TN>
+template <int EPI, int TN, int TMT>
 __global__ __launch_bounds__(512) void gemm_block_kernel(const uint4* __restrict__ W, int ktiles, int ntiles, const uint4* __restrict__ A,
-                                                         int row0, int M_all, int N, GemmOut out) {
-  constexpr int TMT = 16, TILES = 2 * TN + TMT;
+                                                         int row0, int M_all, int N, GemmOut out, BlockOrder order) {
+  constexpr int TILES = 2 * TN + TMT;
   __shared__ u32x4 ring[((160 / TILES) & ~1) * TILES * 64];
-  const int rblocks = (M_all + TMT * 16 - 1) / (TMT * 16), cols = (ntiles + 2 * TN - 1) / (2 * TN), total = cols * rblocks;
-  const int share = (total + 7) >> 3, i = blockIdx.x >> 3, b = (blockIdx.x & 7) * share + i;
-  if (i >= share || b >= total) return;             // whole workgroup
-  const BlockPlace at = block_place(b, cols, rblocks);
+  const BlockPlace at = block_place(order, blockIdx.x);
+  if (at.col < 0) return;                           // whole workgroup
   const int bx = at.col, rbase = at.row * (TMT * 16), M = min(M_all - rbase, TMT * 16);
-  if (M > TMT * 16 - 16) gemm_block_body<EPI, TN, true>(ring, W, ktiles, ntiles, A, row0, rbase, M, N, out, bx);
-  else gemm_block_body<EPI, TN, false>(ring, W, ktiles, ntiles, A, row0, rbase, M, N, out, bx);
+  if (block_full((M + 15) >> 4, TMT)) gemm_block_body<EPI, TN, TMT, true>(ring, W, ktiles, ntiles, A, row0, rbase, M, N, out, bx);
+  else gemm_block_body<EPI, TN, TMT, false>(ring, W, ktiles, ntiles, A, row0, rbase, M, N, out, bx);
 }
 
 // Sums the K shares of a row tile and runs the epilogue, one wave per task.  Where the partial tiles are kept in the L2
@@ -1132,19 +1132,27 @@ static bool launch_gemm_rows_blocks(hipStream_t st, int epi, const uint4* W, int
   return true;
 }
 
-// Forms of the blocked kernel: weight tiles per workgroup (always sixteen row tiles), with the time of one k-tile and of
-// a block's start and end on a chip whose compute units are all busy, in units of 10 ns (from sweeps over 8B shapes on
-// random operands: gate/up at 4096 rows 705 us with 16 weight tiles, 798 with 12, 814 with 8; QKV at 2048 rows 106 / 95 /
-// 117; O 96 / 82 / 67; down 276 / 235 / 188).  Small blocks cost more per product but let narrow matrices fill the chip.
-struct BlockForm { int wt, step, ends; };
-static const BlockForm kBlockForms[3] = {{16, 74, 600}, {12, 62, 600}, {8, 41, 600}};
+// Forms of the blocked kernel: weight and row tiles per workgroup, with the time of one k-tile when all compute units are busy, the
+// share of it that is left when few are (%; the clock gives way under load), and the time of a block's start and end, in ns.
+// Gate/up and the head, whose 1536 and more weight tiles always fill the chip, from sweeps over 8B shapes on random operands (gate/up at
+// 4096 rows 705 us with 16 weight tiles, 798 with 12).  Their narrow blocks of rows lose: gate/up at 1096 rows 258 (16 x 16), 264 (16 x 8).
+// Narrow matrices (QKV, O, down, adapters) from 9 forms x 36 calls of 520 to 4096 rows at the 8B and 70B widths, which the model meets
+// within 2-4 %.  Small blocks cost more per product but let such a matrix fill the chip -- us with 16 x 16, 12 x 16 and 8 x 16 tiles alone,
+// and with all six: 8B O at 768 / 1024 / 1200 / 1536 rows 57.8 / 59.4 / 62.3 / 61.8, 43.3 / 44.1 / 52.4 / 55.1; 8B down at 900 / 1152 rows 171 / 174,
+// 117 / 152; 8B QKV at 600 / 960 / 1536 / 3072 rows 57 / 62 / 88 / 171, 43 / 55 / 73 / 145.
+struct BlockForm { int wt, rt, step, idle, ends; };
+static const BlockForm kWideForms[2] = {{16, 16, 740, 100, 6000}, {12, 16, 620, 100, 6000}};
+static const BlockForm kNarrowForms[6] = {{16, 16, 735, 45, 28400}, {12, 16, 588, 55, 22200}, {8, 16, 423, 59, 12600},
+                                          {12, 12, 446, 56, 15600}, {8, 12, 352, 59, 11200}, {8, 8, 250, 72, 9100}};
 constexpr int kCusPerXcd = 32;
 // Time of one launch by list scheduling of one XCD's blocks on its compute units (every XCD works on an equal run of
-// them, see the kernel); a partly filled row block costs its share of the MFMAs plus a third of a step.
+// them, see the kernel); a light row block costs two thirds of a step and its share of the rest (8B down, one row block of 8 x 16 tiles:
+// 122 / 126 / 151 / 178 us with 1 / 3 / 8 / 16 row tiles in use).
 static int block_cost(const BlockForm& f, int ntiles, int ktiles, int M) {
-  const int rblocks = ceil_div(M, 256), n = ceil_div(ceil_div(ntiles, f.wt) * rblocks, 8);
-  const int used = ceil_div(M - (rblocks - 1) * 256, 16);
-  const int full = ktiles * f.step + f.ends, part = ktiles * (f.step / 3 + f.step * 2 * used / 48) + f.ends;
+  const int rblocks = ceil_div(M, 16 * f.rt), n = ceil_div(ceil_div(ntiles, f.wt) * rblocks, 8);
+  const int used = ceil_div(M - (rblocks - 1) * 16 * f.rt, 16);
+  const int step = f.step * (f.idle + (100 - f.idle) * n / (kCusPerXcd * ceil_div(n, kCusPerXcd))) / 100;
+  const int full = ktiles * step + f.ends, part = block_full(used, f.rt) ? full : ktiles * (step * 2 / 3 + step * used / (3 * f.rt)) + f.ends;
   int free_at[kCusPerXcd] = {0}, end = 0;
   for (int i = 0; i < n; ++i) {
     int c = 0;
@@ -1155,33 +1163,45 @@ static int block_cost(const BlockForm& f, int ntiles, int ktiles, int M) {
   }
   return end;
 }
-// Weight tiles per workgroup of a blocked call: the cheapest of the forms (bit i: kBlockForms[i]) by the model above.  A pure
-// function of the sizes, remembered for the last few.
-static int choose_block(int ntiles, int ktiles, int M, int forms) {
-  struct Memo { int ntiles, ktiles, M, forms, wt; };
+// Form of a blocked call: the cheapest by the model above.  A pure function of the sizes, remembered for the last few.
+static const BlockForm& choose_block(int epi, int ntiles, int ktiles, int M) {
+  struct Memo { int ntiles, ktiles, M, kind; const BlockForm* form; };
   static thread_local Memo memo[8] = {};
   static thread_local unsigned next = 0;
+  if (epi == EPI_ARGMAX) return kWideForms[0];
+  const int kind = epi == EPI_SWIGLU ? 1 : 2;
   for (const Memo& m : memo)
-    if (m.ntiles == ntiles && m.ktiles == ktiles && m.M == M && m.forms == forms) return m.wt;
-  int wt = 0, least = 0;
-  for (int i = 0; i < 3; ++i) {
-    if (!(forms & (1 << i))) continue;
-    const int cost = block_cost(kBlockForms[i], ntiles, ktiles, M);
-    if (!wt || cost < least) { wt = kBlockForms[i].wt; least = cost; }
+    if (m.kind == kind && m.ntiles == ntiles && m.ktiles == ktiles && m.M == M) return *m.form;
+  const BlockForm* forms = kind == 1 ? kWideForms : kNarrowForms;
+  const BlockForm* best = forms;
+  int least = 0;
+  for (int i = 0; i < (kind == 1 ? 2 : 6); ++i) {
+    const int cost = block_cost(forms[i], ntiles, ktiles, M);
+    if (!i || cost < least) { best = forms + i; least = cost; }
   }
-  memo[next++ & 7] = Memo{ntiles, ktiles, M, forms, wt};
-  return wt;
+  memo[next++ & 7] = Memo{ntiles, ktiles, M, kind, best};
+  return *best;
+}
+// the form that the test hook names (weight tiles + 100 * row tiles, 16 of them if unnamed), as far as this epilogue is built with it
+static const BlockForm& forced_block(int epi, int tiles) {
+  const int wt = tiles % 100, rt = tiles >= 100 ? tiles / 100 : 16;
+  if (epi == EPI_ARGMAX) return kWideForms[0];
+  if (epi == EPI_SWIGLU) return kWideForms[wt == 16 ? 0 : 1];
+  for (const BlockForm& f : kNarrowForms)
+    if (f.wt == wt && f.rt == rt) return f;
+  return kNarrowForms[0];
 }
 
-template <int EPI, int TN>
+template <int EPI, int TN, int TMT>
 static void launch_block(hipStream_t st, const uint4* W, int ntiles, int ktiles, const uint4* A, int row0, int M, int N, const GemmOut& out) {
-  dim3 grid(8 * ceil_div(ceil_div(ntiles, 2 * TN) * ceil_div(M, 256), 8)), blk(512);
+  const BlockOrder order = block_order(ntiles, M, 2 * TN, TMT);
+  dim3 grid(8 * order.share), blk(512);
   LaunchEvents* ev = g_launch_events;
   g_launch_events = nullptr;
-  launch_timed(ev, gemm_block_kernel<EPI, TN>, grid, blk, st, W, ktiles, ntiles, A, row0, M, N, out);
+  launch_timed(ev, gemm_block_kernel<EPI, TN, TMT>, grid, blk, st, W, ktiles, ntiles, A, row0, M, N, out, order);
 }
 int g_rows_wide = 1;               // test and tuning hook: 0 keeps wide matrices in passes of up to 512 rows
-int g_block_tiles = 0;             // test hook: > 0 runs every call that reaches bf16_gemm_rows blocked, with so many weight tiles per workgroup
+int g_block_tiles = 0;             // test hook: > 0 runs every call that reaches bf16_gemm_rows blocked, in that form (forced_block)
 
 // Form of the launch above for a call of M rows: row tiles per block, plus 100 with eight weight tiles per workgroup
 // (TN = 4) instead of four; 0: use the K-share kernel (wide matrices, and shapes where it measured faster).
@@ -1206,17 +1226,17 @@ static int rows_blocks_form(int ntiles, int ktiles, int M) {
 //     slower); not where a third row block of up to 128 rows would cost most of a second round of workgroups (8B gate/up at
 //     520 / 608 / 640 rows: 164 / 169 / 170 us blocked, 146 / 150 / 154 as 512 rows and the rest; the 70B one, whose blocks
 //     fill more than two rounds anyway, 488 blocked, 542 in parts)
-//   narrow ones: from 513 rows where their blocks of 8 weight tiles fill the chip.  A long K (more k-tiles than weight tiles)
-//     on a part of the chip is quicker in K shares up to 1024 rows: down at 520 / 1024 rows, 8B 141 / 180 us blocked, 109 / 153
-//     in parts; 1B widths 83 / 90 and 58 / 83; 70B at 520 and 900 rows 349 / 395 and 300 / 426, the latter on 256 blocks.  Nor
-//     do a few rows beyond 512 pay for a third row block on less than half of the chip (8B O at 520 rows 51 us, 42 in parts).
+//   narrow ones: from 513 rows (8B O / QKV at 520 rows 35.9 / 39.3 us, in parts 40.0 / 54; 70B 92.9 / 102.8, 97.9 / 106.7).  A long K (more
+//     k-tiles than weight tiles) only where blocks of 8 weight tiles fill the chip, or lower ones fit one round of workgroups from 673
+//     rows: 8B down at 600 / 640 / 700 / 900 / 1024 rows 119 / 122 / 105 / 117 / 129 us in blocks, 102 / 105 / 110 / 141 / 145 as 512
+//     rows in K shares and the rest; 70B down at 520 / 700 / 900 rows 293 / 344 / 395 and 283 / 322 / 425.
 // The hooks that force another form keep the parts.
 static bool runs_blocked(bool wide, int ntiles, int ktiles, int M) {
   if (g_block_tiles > 0) return true;
   if (wide) return g_rows_wide && M > 256 && ntiles >= 1536 && !(M > 512 && M <= 640 && 3 * ceil_div(ntiles, 16) <= 512);
   if (M <= 512 || g_rows_blocks_override >= 0) return false;
-  const int blocks = ceil_div(ntiles, 8) * ceil_div(M, 256);
-  return ktiles <= ntiles ? M > 544 || blocks >= 128 : M > 1024 || blocks >= 256;
+  const int groups = ceil_div(ntiles, 8);
+  return ktiles <= ntiles || M > 1024 || groups * ceil_div(M, 256) >= 256 || (M > 672 && groups * ceil_div(M, 128) <= 256);
 }
 
 bool bf16_takes_strips(int ntiles, int ktiles, int M) {
@@ -1249,15 +1269,24 @@ int bf16_gemm_rows(hipStream_t st, int epi, const bf16_t* W, int ntiles, int kti
       out.nin.inv_rms = inv_rms;
     }
     if (blocked) {
-      const int forms = epi == EPI_ARGMAX ? 1 : (epi == EPI_SWIGLU ? 3 : 7);
-      const int wt = g_block_tiles > 0 ? g_block_tiles : choose_block(ntiles, ktiles, mc, forms);
-#define BLOCK_LAUNCH(E_, TN_) launch_block<E_, TN_>(st, Wc, ntiles, ktiles, Ac, m0, mc, N, out)
+      const BlockForm& f = g_block_tiles > 0 ? forced_block(epi, g_block_tiles) : choose_block(epi, ntiles, ktiles, mc);
+#define BLOCK_LAUNCH(E_, TN_, TMT_) launch_block<E_, TN_, TMT_>(st, Wc, ntiles, ktiles, Ac, m0, mc, N, out)
+#define BLOCK_NARROW(E_)                                        \
+  do {                                                          \
+    if (f.rt == 8) BLOCK_LAUNCH(E_, 4, 8);                      \
+    else if (f.rt == 12 && f.wt == 8) BLOCK_LAUNCH(E_, 4, 12);  \
+    else if (f.rt == 12) BLOCK_LAUNCH(E_, 6, 12);               \
+    else if (f.wt == 8) BLOCK_LAUNCH(E_, 4, 16);                \
+    else if (f.wt == 12) BLOCK_LAUNCH(E_, 6, 16);               \
+    else BLOCK_LAUNCH(E_, 8, 16);                               \
+  } while (0)
       switch (epi) {
-        case EPI_ARGMAX: BLOCK_LAUNCH(EPI_ARGMAX, 8); break;
-        case EPI_SWIGLU: if (wt == 16) BLOCK_LAUNCH(EPI_SWIGLU, 8); else BLOCK_LAUNCH(EPI_SWIGLU, 6); break;
-        case EPI_ROPE: if (wt == 16) BLOCK_LAUNCH(EPI_ROPE, 8); else if (wt == 12) BLOCK_LAUNCH(EPI_ROPE, 6); else BLOCK_LAUNCH(EPI_ROPE, 4); break;
-        default: if (wt == 16) BLOCK_LAUNCH(EPI_ADD, 8); else if (wt == 12) BLOCK_LAUNCH(EPI_ADD, 6); else BLOCK_LAUNCH(EPI_ADD, 4); break;
+        case EPI_ARGMAX: BLOCK_LAUNCH(EPI_ARGMAX, 8, 16); break;
+        case EPI_SWIGLU: if (f.wt == 16) BLOCK_LAUNCH(EPI_SWIGLU, 8, 16); else BLOCK_LAUNCH(EPI_SWIGLU, 6, 16); break;
+        case EPI_ROPE: BLOCK_NARROW(EPI_ROPE); break;
+        default: BLOCK_NARROW(EPI_ADD); break;
       }
+#undef BLOCK_NARROW
 #undef BLOCK_LAUNCH
       continue;
     }

@@ -1433,8 +1433,8 @@ extern "C" int ee_debug_gemm_row_blocks(int row_tiles) {
 }
 
 extern "C" int ee_debug_gemm_block_tiles(int weight_tiles) {
-  if (weight_tiles != 0 && weight_tiles != 8 && weight_tiles != 12 && weight_tiles != 16) {
-    ee_set_error("weight_tiles must be 0, 8, 12 or 16");
+  if (weight_tiles != 0 && weight_tiles != 8 && weight_tiles != 12 && weight_tiles != 16 && weight_tiles != 808 && weight_tiles != 1208 && weight_tiles != 1212) {
+    ee_set_error("weight_tiles must be 0, 8, 12 or 16, or 808, 1208 or 1212 (with row tiles)");
     return EE_ERR_ARG;
   }
   g_block_tiles = weight_tiles;

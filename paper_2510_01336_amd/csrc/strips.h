@@ -94,15 +94,31 @@ inline StripShape strip_shape(int ntiles, int ktiles, int M) {
   return StripShape{1, std::max(4, parts), parts};
 }
 
-// Which weight group and row block the b-th block of a blocked launch (gemm_block_kernel) is.  Row blocks come in runs of up to five, of
-// about equal length, that share a weight group before the next group follows.  The 32 blocks that an XCD works on side by side then
-// cover about as many weights as rows, which is the least its L2 has to fetch (sixteen row blocks by two groups fetch half as much
-// again), and moving tiles is what takes the clock away: without its requests the gate/up kernel at 4096 rows runs at 1.91 GHz instead
-// of 1.74.  All row blocks in one run / in runs of four, us: 4096 rows gate/up 702 / 688, QKV 212 / 197, O 130 / 121, down 373 / 363;
-// 2048 rows 386 / 385, 100 / 98.5, 65.5 / 65.4, 217 / 212.
-struct BlockPlace { int col, row; };
-__host__ __device__ inline BlockPlace block_place(int b, int cols, int rblocks) {
-  const int runs = (rblocks + 4) / 5, rows = (rblocks + runs - 1) / runs;
-  const int run = b / (cols * rows), left = b - run * cols * rows, wide = rblocks - run * rows < rows ? rblocks - run * rows : rows;
-  return BlockPlace{left / wide, run * rows + left % wide};
+// Whether a row block in which `used` of rt row tiles hold rows runs as a full one (tiles behind the last repeat it): one of its four wave
+// pairs has as many as in a full block either way, and the full form has no conditions (8B O, 9 of 12 row tiles used: 52 us, 59 with them)
+__host__ __device__ constexpr bool block_full(int used, int rt) { return used > rt - 4; }
+
+// Order of the blocks of a blocked launch (gemm_block_kernel): an XCD (workgroup id mod 8) gets consecutive blocks of an order in which
+// `run` row blocks share a weight group before the next group follows.  The 32 blocks that it works on side by side cover run row
+// blocks and 32 / run weight groups, and run is chosen so that they are the least its L2 has to fetch: moving tiles is what takes the
+// clock away (without its requests the gate/up kernel at 4096 rows runs at 1.91 GHz instead of 1.74).  All row blocks in one run / in runs
+// as chosen, us: 4096 rows gate/up 707 / 694, QKV 208 / 199, O 126 / 119; 2048 rows gate/up 388 / 390.  With a light last row block all are in
+// one run: else only some XCDs would get those (8B O at 1800 rows 62.4 / 65.0, 2400 rows 111 / 112).
+struct BlockOrder { int cols, rblocks, run, share; };      // weight groups, row blocks, row blocks of a run, blocks of an XCD
+inline BlockOrder block_order(int ntiles, int M, int wt, int rt) {
+  const int rblocks = ceil_div(M, 16 * rt);
+  BlockOrder o{ceil_div(ntiles, wt), rblocks, rblocks, ceil_div(ceil_div(ntiles, wt) * rblocks, 8)};
+  if (!block_full(ceil_div(M - (rblocks - 1) * 16 * rt, 16), rt)) return o;
+  for (int runs = 1, least = 0; runs <= rblocks; ++runs) {
+    const int g = ceil_div(rblocks, runs), tiles = g * rt + ceil_div(32 * wt, g);
+    if (runs == 1 || tiles < least) { least = tiles; o.run = g; }
+  }
+  return o;
+}
+struct BlockPlace { int col, row; };      // weight group (-1: no block), row block
+__host__ __device__ inline BlockPlace block_place(const BlockOrder& o, int id) {
+  const int b = (id & 7) * o.share + (id >> 3);
+  if ((id >> 3) >= o.share || b >= o.cols * o.rblocks) return BlockPlace{-1, 0};
+  const int at = b / (o.cols * o.run), left = b - at * o.cols * o.run, wide = o.rblocks - at * o.run < o.run ? o.rblocks - at * o.run : o.run;
+  return BlockPlace{left / wide, at * o.run + left % wide};
 }

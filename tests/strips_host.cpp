@@ -25,13 +25,20 @@ int main(int argc, char** argv) {
         // the K shares, and the shares of the norm's partial sums (one a wave), set the order of a row's sums
         if (!strips_large(nt, kt) && (s.ksplit != one.ksplit || s.nw != one.nw)) wrong(nt, kt, M, "sums in another order than one row alone");
       }
-  for (int rblocks = 1; rblocks <= 40; ++rblocks)      // every block of a blocked launch exactly once
-    for (int cols : {1, 2, 7, 32, 112}) {
-      std::vector<int> seen((size_t)rblocks * cols);
-      for (int b = 0; b < rblocks * cols; ++b) {
-        const BlockPlace p = block_place(b, cols, rblocks);
-        if (p.col < 0 || p.col >= cols || p.row < 0 || p.row >= rblocks || seen[(size_t)p.row * cols + p.col]++) wrong(cols, rblocks, b, "block out of place");
+  for (int M = 1; M <= 4096; M += M % 16 == 1 ? 15 : 1)      // every block of a blocked launch exactly once
+    for (int nt : {1, 16, 17, 128, 256, 384, 1546, 1792})
+      for (auto f : {BlockPlace{16, 16}, BlockPlace{12, 16}, BlockPlace{8, 16}, BlockPlace{12, 12}, BlockPlace{8, 12}, BlockPlace{8, 8}}) {
+        const BlockOrder o = block_order(nt, M, f.col, f.row);
+        const int rblocks = ceil_div(M, 16 * f.row), cols = ceil_div(nt, f.col);
+        std::vector<int> seen((size_t)rblocks * cols);
+        int n = 0;
+        for (int id = 0; id < 8 * o.share; ++id) {
+          const BlockPlace p = block_place(o, id);
+          if (p.col == -1) continue;
+          ++n;
+          if (p.col < 0 || p.col >= cols || p.row < 0 || p.row >= rblocks || seen[(size_t)p.row * cols + p.col]++) wrong(nt, f.col * 100 + f.row, M, "block out of place");
+        }
+        if (n != rblocks * cols) wrong(nt, f.col * 100 + f.row, M, "blocks missing");
       }
-    }
   return bad != 0;
 }

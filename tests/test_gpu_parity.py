@@ -817,7 +817,7 @@ _BLOCK_CFGS = {
 @pytest.mark.parametrize("rows", [40, 177, 256, 257, 497, 512, 785])
 @pytest.mark.parametrize("name", list(_BLOCK_CFGS))
 def test_blocked_gemm_in_every_form(name, rows):
-    """The blocked GEMM with 8, 12 and 16 weight tiles per workgroup, every epilogue in every form it is built with, at row
+    """The blocked GEMM with 8, 12 and 16 weight and 8, 12 and 16 row tiles per workgroup, every epilogue in every form it is built with, at row
     blocks that are full, partly filled and hold one row, groups of weight tiles that are not, and parts short enough for
     norm factors to be left to the consumer elsewhere: the forms sum K in one order, so logits, hidden rows and cached K and V
     are the same bits; against the row-tiled forms they agree to bf16 accuracy."""
@@ -832,7 +832,7 @@ def test_blocked_gemm_in_every_form(name, rows):
         got = {}
         hs.ee_debug_attention_split_pages(4)
         try:
-            for form in ("rows", 8, 12, 16):
+            for form in ("rows", 8, 12, 808, 1208, 1212, 16):
                 hs.ee_debug_gemm_block_tiles(0 if form == "rows" else form)
                 if form == "rows":
                     hs.ee_debug_gemm_row_blocks(0); hs.ee_debug_gemm_row_blocks(1000)
@@ -856,7 +856,7 @@ def test_blocked_gemm_in_every_form(name, rows):
             break
     else:
         raise AssertionError("no prompt whose first tokens are decided clearly")
-    for form in (8, 12):
+    for form in (8, 12, 808, 1208, 1212):
         for i, (x, y) in enumerate(zip(got[form][1], got[16][1])):
             assert np.array_equal(x, y), (form, i)
     for i, (x, y) in enumerate(zip(got[16][1], got["rows"][1])):
