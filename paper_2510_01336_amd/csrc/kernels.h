@@ -107,6 +107,9 @@ int bf16_gemm_rows(hipStream_t st, int epi, const bf16_t* W, int ntiles, int kti
                    const GemmOut& out, float* scratch, float* inv_rms, int inv_cap);
 // out row r (GEMM operand) <- RMSNorm of row idx[r] of X with gain g
 void bf16_rmsnorm(hipStream_t st, const float* X, const int* idx, const float* g, float eps, bf16_t* out, int ktiles, int M, int d);
+// Rows row_idx[0..M) of X to `rows`, and q-tiles qt_src[0..n_qt) of Q [kv head][total_qt tiles] to Qt [kv head][n_qt]
+void bf16_gather_tail(hipStream_t st, const float* X, const int* row_idx, int M, int d, float* rows, const bf16_t* Q, const int* qt_src, int n_qt,
+                      int total_qt, int Hkv, int D, bf16_t* Qt);
 // Opens a pass over layers in one launch: row r of X <- embedding of tok[r] (emb set), rows[row_idx[r]] (rows set) or
 // itself; out <- its RMSNorm with gain g as a GEMM operand; cs / rowinfo as f32_begin_pass fills them.
 void bf16_begin_pass(hipStream_t st, const bf16_t* emb, const int* tok, const float* rows, const int* row_idx, float* X,

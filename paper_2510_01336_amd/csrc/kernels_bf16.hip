@@ -158,6 +158,27 @@ void bf16_begin_pass(hipStream_t st, const bf16_t* emb, const int* tok, const fl
 #undef BEGIN_PASS
 }
 
+// Moves the rows of a context build's last layer that have a reader to the front (a workgroup per row or q-tile): plain copies, bound by
+// the launch (512 rows and 128 q-tiles of the 8B width, 12.6 MB read and written, 6.8 us).
+__global__ __launch_bounds__(256) void gather_tail_kernel(const float4* __restrict__ X, const int* __restrict__ row_idx, int M, int d4, float4* __restrict__ rows,
+                                                          const uint4* __restrict__ Q, const int* __restrict__ qt_src, int n_qt, int total_qt, int Hkv,
+                                                          int tile, uint4* __restrict__ Qt) {
+  const int r = blockIdx.x;
+  if (r < M) {
+    const float4* src = X + (size_t)row_idx[r] * d4;
+    for (int c = threadIdx.x; c < d4; c += 256) rows[(size_t)r * d4 + c] = src[c];
+  } else {
+    const int t = r - M, from = qt_src[t];
+    for (int i = threadIdx.x; i < Hkv * tile; i += 256)
+      Qt[((size_t)(i / tile) * n_qt + t) * tile + i % tile] = Q[((size_t)(i / tile) * total_qt + from) * tile + i % tile];
+  }
+}
+void bf16_gather_tail(hipStream_t st, const float* X, const int* row_idx, int M, int d, float* rows, const bf16_t* Q, const int* qt_src, int n_qt,
+                      int total_qt, int Hkv, int D, bf16_t* Qt) {
+  hipLaunchKernelGGL(gather_tail_kernel, dim3(M + n_qt), dim3(256), 0, st, (const float4*)X, row_idx, M, d / 4, (float4*)rows, (const uint4*)Q, qt_src, n_qt,
+                     total_qt, Hkv, D * 2, (uint4*)Qt);
+}
+
 // ---------------------------------------------------------------------------------------------
 // Skinny GEMM  Y[m][n] = sum_k X[m][k] W[n][k],  M <= 16*MT rows per launch, weights streamed once.
 // A strip is one 16-row weight tile over the whole K.  A wave takes NS strips and a share of K (ksplit waves of the workgroup share

@@ -353,6 +353,67 @@ static int upload_meta(ee_session* s, int si) {
   return EE_OK;
 }
 
+// Behind the last layer of a context-build pass only some rows have a reader: those that end a prompt, and the last 512-row piece that the
+// introspection calls report.  Of the other rows the layer has to leave K and V in the cache, nothing else.  The wanted rows are trailing
+// rows of their sequences, so the rest of the layer is a call of its own over fewer rows, packed anew.  Sequences keep whole q-tiles (rows
+// from a multiple of 16 on), and the reported piece starts at a row that is a multiple of 16 (rows in the gap in front of it hold copies).
+struct TailPlan {
+  bool on = false;
+  CallPlan p;                    // the wanted rows: M (0: none), total_qt, per-sequence rows and first positions
+  CallMeta mt;
+  const int* row_idx = nullptr;  // [M] row of the pass
+  const int* qt_src = nullptr;   // [total_qt] q-tile of the pass
+  int piece = 0;                 // first row of the reported piece
+  std::vector<int> row0;         // first row of every sequence
+};
+// keep[b]: wanted trailing rows of sequence b; piece0 >= 0: all rows from that row of the pass on are among them.  The tables lie behind the
+// n_src entries that row_src holds, where a context build has no rows to gather or scatter, and the rows are moved by way of LOGITS, which the
+// head fills later; off where either does not fit, or where a quarter of the rows is not saved.  Called between build_meta and upload_meta.
+static void plan_tail(ee_session* s, int si, const CallPlan& p, const std::vector<int>& keep, int piece0, int n_src, TailPlan& t) {
+  const ee_config& c = s->m->cfg;
+  const int B = s->B, rep = c.n_q_heads / c.n_kv_heads;
+  t = TailPlan();
+  t.p.m.assign(B, 0); t.p.p0.assign(B, 0); t.row0.assign(B, 0);
+  int row = 0, qt = 0;
+  for (int b = 0, first = 0; b < B; first += p.m[b], ++b) {
+    if (!keep[b]) continue;
+    const int skip = (p.m[b] - keep[b]) & ~15, m = p.m[b] - skip;
+    if (piece0 >= 0 && first <= piece0 && piece0 < first + p.m[b]) {       // the piece starts in this sequence
+      const int before = piece0 - first - skip;
+      t.piece = ceil_div(row + before, 16) * 16;
+      row = t.piece - before;
+    }
+    t.p.m[b] = m; t.p.p0[b] = p.p0[b] + skip; t.row0[b] = row;
+    t.p.max_m = std::max(t.p.max_m, m);
+    row += m; qt += ceil_div(m * rep, 16);
+  }
+  t.p.M = row; t.p.total_qt = qt;
+  auto pad = [](int n) { return (n + 3) / 4 * 4; };
+  const size_t moved = (size_t)row * c.d_model * sizeof(float) + (size_t)c.n_kv_heads * qt * 16 * c.head_dim * sizeof(bf16_t);
+  if (4 * row > 3 * p.M || pad(n_src) + pad(row) + 4 * pad(B) + 3 * pad(qt) > 2 * pad(p.M) ||
+      moved > (size_t)s->headM * c.vocab * sizeof(float)) return;
+  t.on = true;
+  int* h = s->slot[si].h;
+  size_t o = s->o_row_src + pad(n_src);
+  auto take = [&](int n) { const size_t r = o; o += pad(n); return r; };
+  const size_t o_idx = take(row), o_row0 = take(B), o_m = take(B), o_p0 = take(B), o_qt0 = take(B), o_qseq = take(qt), o_qloc = take(qt), o_qsrc = take(qt);
+  std::fill(h + o_idx, h + o_idx + row, 0);
+  qt = 0;
+  for (int b = 0, first = 0; b < B; first += p.m[b], ++b) {
+    const int m = t.p.m[b], skip = p.m[b] - m;
+    h[o_row0 + b] = t.row0[b]; h[o_m + b] = m; h[o_p0 + b] = t.p.p0[b]; h[o_qt0 + b] = qt;
+    for (int r = 0; r < m; ++r) h[o_idx + t.row0[b] + r] = first + skip + r;
+    for (int i = 0; i < ceil_div(m * rep, 16); ++i, ++qt) {
+      h[o_qseq + qt] = b; h[o_qloc + qt] = i; h[o_qsrc + qt] = h[s->o_seq_qt0 + b] + skip * rep / 16 + i;
+    }
+  }
+  const int* d = s->slot[si].d;
+  t.mt = meta_ptrs(s, d);
+  t.mt.seq_row0 = d + o_row0; t.mt.seq_m = d + o_m; t.mt.seq_p0 = d + o_p0; t.mt.seq_qt0 = d + o_qt0;
+  t.mt.qt_seq = d + o_qseq; t.mt.qt_local = d + o_qloc;
+  t.row_idx = d + o_idx; t.qt_src = d + o_qsrc;
+}
+
 // ---------------------------------------------------------------------------------------------
 // launch accounting
 // ---------------------------------------------------------------------------------------------
@@ -435,11 +496,13 @@ struct PassSink {
   float* rows = nullptr; const int* row_idx = nullptr; int add = 0;
 };
 
+// tail: the rows of the last layer that have a reader, where those are few (context builds of bf16 models)
 static void run_layers(ee_session* s, int l0, int l1, const CallPlan& p, const CallMeta& mt, int pos_add, const PassSource& src = PassSource(),
-                       const PassSink& sink = PassSink()) {
+                       const PassSink& sink = PassSink(), const TailPlan* tail = nullptr) {
   const ee_model* m = s->m;
   const ee_config& c = m->cfg;
-  const int d = c.d_model, D = c.head_dim, Hq = c.n_q_heads, Hkv = c.n_kv_heads, M = p.M;
+  const int d = c.d_model, D = c.head_dim, Hq = c.n_q_heads, Hkv = c.n_kv_heads;
+  int M = p.M;
   hipStream_t st = s->st;
   if (m->bf16) {
     // one launch: rows into the stream, the first layer's operand, the rotary table and the epilogue lookups
@@ -466,13 +529,29 @@ static void run_layers(ee_session* s, int l0, int l1, const CallPlan& p, const C
       nout.xn = (bf16_t*)s->XN; nout.ktiles = ceil_div(d, 32); nout.ssq = s->ssq; nout.stride = Mp;
       GemmOut o;
       if (l != l0) o.nin = nin;            // (the first layer's operand was normalised when the pass was opened)
-      RopeOut& R = o.rope;
-      R.cs = s->cs; R.rowinfo = s->rowinfo; R.Hq = Hq; R.Hkv = Hkv; R.D = D; R.layer = l;
-      R.n_pages = s->n_pages; R.total_qt = p.total_qt; R.Q = (bf16_t*)s->Qb; R.kv = (bf16_t*)s->kv;
+      RopeOut& ro = o.rope;
+      ro.cs = s->cs; ro.rowinfo = s->rowinfo; ro.Hq = Hq; ro.Hkv = Hkv; ro.D = D; ro.layer = l;
+      ro.n_pages = s->n_pages; ro.total_qt = p.total_qt; ro.Q = (bf16_t*)s->Qb; ro.kv = (bf16_t*)s->kv;
       KF(KF_GEMM_QKV, gemm(s, EPI_ROPE, L.qkv, (const bf16_t*)s->XN, M, o));
-      KF(KF_ATTN, bf16_attention(st, attn, (const bf16_t*)s->Qb, (const bf16_t*)s->kv, mt, pos_add, s->B, p.max_m, p.total_qt,
-                                 Hq, Hkv, D, l, s->n_pages, s->pps, scr, (bf16_t*)s->AO, L.o.ktiles()));
-      o = GemmOut(); o.Y = s->X; o.R = s->X; o.ldy = d; o.nout = nout; o.nout.g = g2;
+      const float* R = s->X;
+      if (l + 1 == l1 && tail) {
+        // K and V of all rows are in the cache; the rest of the layer runs over the wanted rows, moved to the front (their stream rows and Q
+        // tiles by way of LOGITS; H must keep the zeros behind d_ffn)
+        M = tail->p.M;
+        if (M == 0) break;
+        float* rows = s->LOGITS;
+        bf16_t* q = (bf16_t*)(rows + (size_t)M * d);
+        AttnScratch few;
+        const AttnPlan plan = attention_plan(s, tail->p, pos_add, few);
+        KF(KF_ATTN, bf16_gather_tail(st, s->X, tail->row_idx, M, d, rows, (const bf16_t*)s->Qb, tail->qt_src, tail->p.total_qt, p.total_qt, Hkv, D, q);
+                    bf16_attention(st, plan, q, (const bf16_t*)s->kv, tail->mt, pos_add, s->B, tail->p.max_m, tail->p.total_qt,
+                                   Hq, Hkv, D, l, s->n_pages, s->pps, few, (bf16_t*)s->AO, L.o.ktiles()));
+        R = rows;
+      } else {
+        KF(KF_ATTN, bf16_attention(st, attn, (const bf16_t*)s->Qb, (const bf16_t*)s->kv, mt, pos_add, s->B, p.max_m, p.total_qt,
+                                   Hq, Hkv, D, l, s->n_pages, s->pps, scr, (bf16_t*)s->AO, L.o.ktiles()));
+      }
+      o = GemmOut(); o.Y = s->X; o.R = R; o.ldy = d; o.nout = nout; o.nout.g = g2;
       KF(KF_GEMM_O, nin.n_part = gemm(s, EPI_ADD, L.o, (const bf16_t*)s->AO, M, o));
       o = GemmOut(); o.H = (bf16_t*)s->H; o.h_ktiles = L.down.ktiles(); o.nin = nin;
       KF(KF_GEMM_GU, gemm(s, EPI_SWIGLU, L.gu, (const bf16_t*)s->XN, M, o));
@@ -637,15 +716,30 @@ static int prefill_impl(ee_session* s, const int32_t* tokens, const int32_t* len
       if (done[b] + p.m[b] < lens[b]) last_pass = false;
       else if (p.m[b]) { end_seq[n_end] = b; end_row[n_end++] = row + p.m[b] - 1; }
     }
+    // The rows that end a prompt decide its first committed token: the head runs over them alone.  What the introspection
+    // calls report of a context build are the rows of its last 512-row piece; with logits kept these get a head as well.
+    int r0 = (p.M - 1) / 512 * 512;
+    const int piece_rows = p.M - r0, piece0 = r0;
+    TailPlan tail;
+    if (bf) {
+      std::vector<int> keep(s->B, 0);
+      for (int e = 0; e < n_end; ++e) keep[end_seq[e]] = 1;
+      if (last_pass)
+        for (int b = 0, first = 0; b < s->B; first += p.m[b], ++b)
+          if (first + p.m[b] > piece0) keep[b] = std::max(keep[b], std::min(p.m[b], first + p.m[b] - piece0));
+      plan_tail(s, si, p, keep, last_pass ? piece0 : -1, n_end, tail);
+      if (tail.on) {
+        r0 = last_pass ? tail.piece : 0;
+        for (int e = 0; e < n_end; ++e) end_row[e] = tail.row0[end_seq[e]] + tail.p.m[end_seq[e]] - 1;
+      }
+    }
     std::copy(end_row.begin(), end_row.begin() + n_end, s->slot[si].h + s->o_row_src);     // (no rows are gathered here: the list of ends)
     EE_TRY(upload_meta(s, si));
     CallMeta mt = meta_ptrs(s, s->slot[si].d);
     PassSource from_tokens; from_tokens.tok = mt.row_tok;
-    run_layers(s, 0, c.n_layers, p, mt, 0, from_tokens);
-    // The rows that end a prompt decide its first committed token: the head runs over them alone.  What the introspection
-    // calls report of a context build are the rows of its last 512-row piece; with logits kept these get a head as well.
+    run_layers(s, 0, c.n_layers, p, mt, 0, from_tokens, PassSink(), tail.on ? &tail : nullptr);
     if (bf && n_end) {
-      const int r0 = (p.M - 1) / 512 * 512, kept_piece = s->debug_logits && last_pass;
+      const bool kept_piece = s->debug_logits && last_pass;
       int early = 0;                                     // ends in front of that piece (all of them where it gets no head)
       while (early < n_end && !(kept_piece && end_row[early] >= r0)) ++early;
       if (early) {
@@ -653,11 +747,11 @@ static int prefill_impl(ee_session* s, const int32_t* tokens, const int32_t* len
         HIP_TRY(hipMemcpyAsync(s->out_host + n_first, s->vtok, early * sizeof(int), hipMemcpyDeviceToHost, s->st));
       }
       if (kept_piece) {
-        exit_head(s, p.M - r0, s->n_levels, r0);
+        exit_head(s, piece_rows, s->n_levels, r0);
         for (int e = early; e < n_end; ++e)
           HIP_TRY(hipMemcpyAsync(s->out_host + n_first + e, s->vtok + (end_row[e] - r0), sizeof(int), hipMemcpyDeviceToHost, s->st));
       }
-      s->last_rows = p.M - r0; s->last_row0 = r0;
+      s->last_rows = piece_rows; s->last_row0 = r0;
     } else if (n_end) {
       exit_head(s, p.M, s->n_levels);
       for (int e = 0; e < n_end; ++e)

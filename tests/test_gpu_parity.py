@@ -804,6 +804,65 @@ def test_context_build_in_blocks_matches_the_512_row_passes(name, rows):
     sess.close(); model.close()
 
 
+@pytest.mark.parametrize("lens,passes", [
+    ([700], 0), ([513], 0), ([1041], 0), ([527, 530], 0),                       # one sequence reaches into the reported piece
+    ([40, 600, 3, 530, 17], 0), ([5, 5, 509, 200], 0), ([1, 511, 1, 300], 0),     # prompts that end in front of it; a piece that starts with a sequence
+    ([300, 300, 200, 1], 0), ([100] * 7 + [900], 0),
+    ([700, 30, 1100], 512), ([1500, 9], 512),                                  # several passes, some of which end no prompt
+])
+@pytest.mark.parametrize("name", ["bf16_small", "bf16_rep3"])
+def test_last_layer_of_a_context_build_over_the_rows_that_are_read(name, lens, passes):
+    """A context build runs its last layer over the rows that end a prompt and the reported piece alone: first tokens and the reported
+    logits and hidden rows against the oracle, and every cached row of all layers through a decoding step behind it."""
+    import re
+
+    import paper_2510_01336_amd as hs
+    cfg = bf16_small(n_layers=3, exit_draft=1, exit_inter=2) if name == "bf16_small" else bf16_small(n_layers=3, exit_draft=1, exit_inter=2, n_q_heads=6)
+    W = synth.WeightStore(cfg, 41)
+    spec = eo.ModelSpec.from_config(cfg, round_mode="bf16")
+    m = eo.EEModel(spec, W)
+    hidden, firsts, prompts = [], [], []
+    for b, n in enumerate(lens):
+        for seed in range(40):
+            prompt = synth.gen_prompt(cfg.vocab, n, 900 + 50 * b + seed)
+            x = m.run_layers(range(cfg.n_layers), m.embed(prompt), np.arange(n), eo.KVCache(spec, n))
+            logits = m.exit_logits(x[-1:])
+            if eo.top2_margin(logits)[0] > 2 * MARGIN:
+                break
+        prompts.append(prompt); hidden.append(x); firsts.append(int(eo.argmax_rows(logits)[0]))
+    model = hs.Model(cfg, 41)
+    least = None
+    if passes:                                                 # the smallest arena: passes of 512 rows
+        with pytest.raises(hs.EEError) as e:
+            hs.Session(model, len(lens), max(lens) + 20, 8, arena_bytes=1 << 12)
+        least = int(re.search(r"< (\d+)", str(e.value)).group(1))
+    sess = hs.Session(model, len(lens), max(lens) + 20, 8, arena_bytes=least)
+    sess.enable_logits(True)
+    assert sess.prefill(prompts).tolist() == firsts
+    # rows of the last pass in packing order, the last 512-row piece of them
+    if not passes:
+        rows = np.concatenate(hidden)
+    else:
+        left, done = list(lens), [0] * len(lens)
+        while any(left):
+            room, rows = 512, []
+            for b in range(len(lens)):
+                n = min(left[b], room)
+                rows += list(hidden[b][done[b]:done[b] + n]); left[b] -= n; done[b] += n; room -= n
+        rows = np.array(rows)
+    want = rows[(len(rows) - 1) // 512 * 512:]
+    got = sess.last_hidden()
+    assert got.shape == want.shape
+    assert max_rel(got.astype(np.float64), want) <= TOL["bf16"]
+    assert max_rel(sess.last_logits().astype(np.float64), m.exit_logits(want)) <= TOL["bf16"]
+    sess.decode_ar(1)
+    step = sess.last_hidden(len(lens)).astype(np.float64)
+    for b, n in enumerate(lens):
+        x, _ = m.forward_nocache(list(prompts[b]) + [firsts[b]], cfg.n_layers)
+        assert max_rel(step[b:b + 1], x[-1:]) <= TOL["bf16"], b
+    sess.close(); model.close()
+
+
 _BLOCK_CFGS = {
     # weight tiles: QKV 48, O / down 16, gate/up 1546 (96 * 16 + 10); down over 387 k-tiles
     "long_k": lambda: bf16_small(d_ffn=12368, sigma=0.02),
