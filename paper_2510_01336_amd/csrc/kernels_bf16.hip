@@ -481,7 +481,7 @@ __device__ inline void mma_frags(f32x4 (&acc)[NS][MT], const Frags<MT, NS, U>& f
     }
 }
 
-template <int MT, int EPI, int NS, int U>
+template <int MT, int EPI, int NS, int U, bool HALF = false>
 __global__ __launch_bounds__(64 * EE_MAX_WAVES) void gemm_skinny_kernel(const uint4* __restrict__ W, int ktiles, int ntiles,
                                                                         const uint4* __restrict__ A, int row0, int M, int N,
                                                                         GemmOut out, int ksplit) {
@@ -493,6 +493,11 @@ __global__ __launch_bounds__(64 * EE_MAX_WAVES) void gemm_skinny_kernel(const ui
   // instructions ignore EXEC, so a masked-off MFMA would still add its product.
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
   const int tasks = nw / ksplit, task0 = blockIdx.x * tasks * NS, strip0 = task0 + wave / ksplit * NS, kpart = wave % ksplit;
+  // HALF: two workgroups of one XCD share 2 * NS - 1 strips, NS - 1 whole ones each and half of the last: four features and their partners,
+  // whose rows the lanes of the other four repeat.
+  static_assert(!HALF || (NS > 1 && EPI == EPI_ROPE), "whole strips and a half");
+  const int half = HALF ? half_of(blockIdx.x) : 0;
+  auto strip_at = [&](int i) { return HALF ? half_strip_at(blockIdx.x, i, NS) : task0 + i; };      // i-th strip of the workgroup
   const int per = (ktiles + ksplit - 1) / ksplit;
   const int kt0 = kpart * per, kt1 = min(ktiles, kt0 + per);
 
@@ -502,11 +507,12 @@ __global__ __launch_bounds__(64 * EE_MAX_WAVES) void gemm_skinny_kernel(const ui
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[s][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  const bool stream = strip0 < ntiles && kt0 < kt1;
+  const bool stream = (HALF ? strip_at(0) : strip0) < ntiles && kt0 < kt1;
   const int mc = lane & 15;
   const u32x4 *wp[NS], *ap[MT];
 #pragma unroll
-  for (int s = 0; s < NS; ++s) wp[s] = (const u32x4*)W + (size_t)min(strip0 + s, ntiles - 1) * ktiles * 64 + lane;
+  for (int s = 0; s < NS; ++s)
+    wp[s] = (const u32x4*)W + (size_t)min(HALF ? strip_at(s) : strip0 + s, ntiles - 1) * ktiles * 64 + (HALF && s == NS - 1 ? (lane & 0x3b) + 4 * half : lane);
   // (rows past the last repeat it: the quads behind the last row's are not fetched)
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) ap[mt] = (const u32x4*)A + (size_t)((row0 >> 4) + mt) * ktiles * 64 + act_unit(max(0, min(mc, M - 1 - 16 * mt)), lane >> 4);
@@ -517,15 +523,18 @@ __global__ __launch_bounds__(64 * EE_MAX_WAVES) void gemm_skinny_kernel(const ui
   const bool normed = out.nin.ssq != nullptr;
   const int np = normed ? out.nin.n_part : 0, cp = (np + nw - 1) / nw, cw = wave * cp, ce = min(np, cw + cp);
   // strip whose epilogue this wave runs first
-  const int own = ksplit == 1 ? strip0 : task0 + wave;
+  const int own = ksplit == 1 ? strip0 : strip_at(wave);
   const bool owner = own < ntiles && (ksplit == 1 || wave < tasks * NS);
+  // lane of the tile whose outputs this one holds (every second row of lanes of the half strip repeats the one before it: no results)
+  const int elane = HALF && wave == NS - 1 ? (lane & 0x2f) + 16 * half : lane;
+  const bool eok = !(HALF && wave == NS - 1 && (lane & 16));
   EpiPre pre[MT];
   NormPartials<MT> part;
   if (normed) norm_request<MT>(part, out.nin, row0, 1, MT, cw, lane);
   if (stream) load_frags<MT, NS, U>(cur, wp, ap, kt0, kt1 - 1);
   if (owner) {
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) epi_prefetch<EPI>(pre[mt], out, own, row0 + mt * 16 + mc, mt * 16 + mc < M, lane);
+    for (int mt = 0; mt < MT; ++mt) epi_prefetch<EPI>(pre[mt], out, own, row0 + mt * 16 + mc, eok && mt * 16 + mc < M, elane);
   }
 
   // Two register sets of fragments take turns: while one is multiplied the other is in flight, and the next request
@@ -604,15 +613,15 @@ __global__ __launch_bounds__(64 * EE_MAX_WAVES) void gemm_skinny_kernel(const ui
     return;
   }
   // the strips of the workgroup are dealt round its waves; the K parts of one are added in a fixed order
-  for (int i = wave; i < tasks * NS && task0 + i < ntiles; i += nw) {
+  for (int i = wave; i < tasks * NS && strip_at(i) < ntiles; i += nw) {      // (HALF: at most one strip a wave)
     const int w0 = i / NS * ksplit, s = i % NS;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
       const int m = mt * 16 + mc;
-      if (i != wave) epi_prefetch<EPI>(pre[mt], out, task0 + i, row0 + m, m < M, lane);
+      if (i != wave) epi_prefetch<EPI>(pre[mt], out, strip_at(i), row0 + m, m < M, lane);
       f32x4 sum = red[w0][s * MT + mt][lane];
       for (int w = 1; w < ksplit; ++w) sum += red[w0 + w][s * MT + mt][lane];
-      epi_apply<EPI>(sum, sc[mt], pre[mt], out, task0 + i, row0 + m, m < M, N, lane);
+      epi_apply<EPI>(sum, sc[mt], pre[mt], out, strip_at(i), row0 + m, eok && m < M, N, elane);
     }
   }
 }
@@ -1333,6 +1342,15 @@ int bf16_gemm_rows(hipStream_t st, int epi, const bf16_t* W, int ntiles, int kti
   return parts_left;
 }
 
+// QKV in whole strips and a half a workgroup (see strips_half)
+template <int MT, int NS, int U>
+static void launch_gemm_half(hipStream_t st, const uint4* W, int ntiles, int ktiles, const uint4* A, int row0, int M, int N, const GemmOut& out, int ksplit) {
+  LaunchEvents* ev = g_launch_events;
+  g_launch_events = nullptr;
+  launch_timed(ev, gemm_skinny_kernel<MT, EPI_ROPE, NS, U, true>, dim3(half_grid(ntiles, NS)), dim3(64 * ksplit), st, W, ktiles, ntiles,
+               A, row0, M, N, out, ksplit);
+}
+
 template <int MT, int NS, int U>
 static void launch_gemm_mt(hipStream_t st, int epi, const uint4* W, int ntiles, int ktiles, const uint4* A, int row0, int M, int N,
                            const GemmOut& out, int nw, int ksplit) {
@@ -1353,6 +1371,11 @@ void bf16_gemm(hipStream_t st, int epi, const bf16_t* W, int ntiles, int ktiles,
   const uint4* Wc = (const uint4*)W;
   const uint4* Ac = (const uint4*)A;
   const StripShape sh = strip_shape(ntiles, ktiles, M);
+  if (const int ns = epi == EPI_ROPE ? strips_half(ntiles, ktiles, M) : 0) {
+    if (ns == 3) launch_gemm_half<1, 3, 4>(st, Wc, ntiles, ktiles, Ac, row0, M, N, out, sh.ksplit);
+    else launch_gemm_half<1, 2, 4>(st, Wc, ntiles, ktiles, Ac, row0, M, N, out, sh.ksplit);
+    return;
+  }
 #define STRIPS(MT_, NS_, U_) launch_gemm_mt<MT_, NS_, U_>(st, epi, Wc, ntiles, ktiles, Ac, row0, M, N, out, sh.nw, sh.ksplit)
   if (M <= 16) {
     if (sh.ns == 4) STRIPS(1, 4, 4);

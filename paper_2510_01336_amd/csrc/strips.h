@@ -94,6 +94,26 @@ inline StripShape strip_shape(int ntiles, int ktiles, int M) {
   return StripShape{1, std::max(4, parts), parts};
 }
 
+// Strips of a workgroup of a QKV projection whose last one is half a strip, 0: whole strips only.  One and a half or two and a half, where
+// those are the even deal, by the waves that share out K and the norm's partial sums anyway, so that the sums stay the same bits.  Up to 16
+// rows (8B, 384 strips, at 1 / 9 / 16 rows 11.6 / 12.0 / 12.4 us, two whole strips 12.7 / 12.6 / 12.8, but at 32 rows 15.6, 15.1; 70B, 640 strips,
+// 30.0 / 30.5 / 31.0, four whole ones 30.6 / 31.6 / 32.3; 288 x 128 at 9 rows 10.6, 11.9; 560 x 64 9.7, 12.8; 352 x 160 13.3, 13.6).
+inline int strips_half(int ntiles, int ktiles, int M) {
+  const StripShape s = strip_shape(ntiles, ktiles, M);
+  if (M > 16 || ktiles < 64 || s.nw != s.ksplit) return 0;
+  if (ntiles > 256 && ntiles <= 384 && s.ksplit == 4) return 2;
+  if (ntiles > 512 && ntiles <= 640 && s.ksplit == 8) return 3;
+  return 0;
+}
+
+// Workgroups of such a launch, and the i-th of the ns strips of workgroup id: ids 8 apart, which run on one XCD, share 2 * ns - 1 strips and
+// halve the last one (half_of).
+inline int half_grid(int ntiles, int ns) { return 16 * ceil_div(ceil_div(ntiles, 2 * ns - 1), 8); }
+__host__ __device__ inline int half_of(int id) { return (id >> 3) & 1; }
+__host__ __device__ inline int half_strip_at(int id, int i, int ns) {
+  return ((id >> 4) * 8 + (id & 7)) * (2 * ns - 1) + (i < ns - 1 ? half_of(id) * (ns - 1) + i : 2 * (ns - 1));
+}
+
 // Whether a row block in which `used` of rt row tiles hold rows runs as a full one (tiles behind the last repeat it): one of its four wave
 // pairs has as many as in a full block either way, and the full form has no conditions (8B O, 9 of 12 row tiles used: 52 us, 59 with them)
 __host__ __device__ constexpr bool block_full(int used, int rt) { return used > rt - 4; }

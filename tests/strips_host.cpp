@@ -25,6 +25,19 @@ int main(int argc, char** argv) {
         // the K shares, and the shares of the norm's partial sums (one a wave), set the order of a row's sums
         if (!strips_large(nt, kt) && (s.ksplit != one.ksplit || s.nw != one.nw)) wrong(nt, kt, M, "sums in another order than one row alone");
       }
+  for (int nt = 1; nt <= 1024; ++nt)                        // half strips: every strip once, by the waves of the whole ones
+    for (int kt : {63, 64, 128, 448}) {
+      const int ns = strips_half(nt, kt, 9);
+      const StripShape w = strip_shape(nt, kt, 9);
+      if (!ns) continue;
+      if (w.nw != w.ksplit || ns > w.nw || kt < 64 || strips_half(nt, kt, 17)) wrong(nt, kt, 9, "half strips by other waves");
+      std::vector<int> seen(nt);
+      for (int id = 0; id < half_grid(nt, ns); ++id)
+        for (int i = 0; i < ns; ++i)
+          if (half_strip_at(id, i, ns) < nt) seen[half_strip_at(id, i, ns)] += i < ns - 1 ? 2 : 1;
+      for (int t = 0; t < nt; ++t)
+        if (seen[t] != 2) wrong(nt, kt, t, "strip not covered once");
+    }
   for (int M = 1; M <= 4096; M += M % 16 == 1 ? 15 : 1)      // every block of a blocked launch exactly once
     for (int nt : {1, 16, 17, 128, 256, 384, 1546, 1792})
       for (auto f : {BlockPlace{16, 16}, BlockPlace{12, 16}, BlockPlace{8, 16}, BlockPlace{12, 12}, BlockPlace{8, 12}, BlockPlace{8, 8}}) {

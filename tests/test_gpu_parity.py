@@ -863,6 +863,33 @@ def test_last_layer_of_a_context_build_over_the_rows_that_are_read(name, lens, p
     sess.close(); model.close()
 
 
+@pytest.mark.parametrize("rows", [2, 9, 16, 17, 32])
+@pytest.mark.parametrize("heads", [(60, 5), (120, 8)], ids=["280_strips", "544_strips"])
+def test_qkv_in_half_strips_matches_oracle(heads, rows):
+    """QKV matrices whose strips do not fill the compute units evenly: pairs of workgroups share 3 or 5 strips, the last pair fewer
+    (280 = 93 * 3 + 1, 544 = 108 * 5 + 4).  A block behind a short context, its logits and its cached K and V against the oracle."""
+    import paper_2510_01336_amd as hs
+    cfg = bf16_small(n_layers=3, exit_draft=1, exit_inter=2, d_model=2048, n_q_heads=heads[0], n_kv_heads=heads[1], d_ffn=256, sigma=0.02)
+    W = synth.WeightStore(cfg, 5)
+    m = eo.EEModel(eo.ModelSpec.from_config(cfg, round_mode="bf16"), W)
+    model = hs.Model(cfg, 5)
+    sess = hs.Session(model, 1, 128, 2 * rows + 4)
+    sess.enable_logits(True)
+    prompt = synth.gen_prompt(cfg.vocab, 21, 3)
+    c0 = int(sess.prefill([prompt])[0])
+    block = np.random.default_rng(rows).integers(0, cfg.vocab, (1, rows - 1)).astype(np.int32)
+    sess.draft_inject(block)
+    tokens = [int(t) for t in prompt] + [c0] + [int(t) for t in block[0]]
+    cache = eo.KVCache(m.spec, len(tokens))
+    x = m.run_layers(range(cfg.exit_inter), m.embed(tokens), np.arange(len(tokens)), cache)[len(prompt):]
+    gk, gv = sess.read_kv(0, 0, 0, len(tokens))
+    assert max_rel(gk, cache.K[0]) <= TOL["bf16"] and max_rel(gv, cache.V[0]) <= TOL["bf16"]
+    sess.verify_intermediate()
+    assert max_rel(sess.last_hidden().astype(np.float64), x) <= TOL["bf16"]
+    assert max_rel(sess.last_logits().astype(np.float64), m.exit_logits(x)) <= TOL["bf16"]
+    sess.close(); model.close()
+
+
 _BLOCK_CFGS = {
     # weight tiles: QKV 48, O / down 16, gate/up 1546 (96 * 16 + 10); down over 387 k-tiles
     "long_k": lambda: bf16_small(d_ffn=12368, sigma=0.02),

@@ -20,7 +20,7 @@ def strips_host(tmp_path_factory):
 
 
 def test_shapes_of_every_size_keep_their_rules(strips_host):
-    """Whole K shares to whole waves, and below 128 MB one order of a row's sums from 1 to 32 rows; every block of a blocked launch once."""
+    """Whole K shares to whole waves, and below 128 MB one order of a row's sums from 1 to 32 rows; half strips and every block of a blocked launch once."""
     run = subprocess.run([strips_host], stdout=subprocess.PIPE, text=True)
     assert run.returncode == 0, run.stdout
 
