@@ -9,6 +9,7 @@
 // wavefront fetches an operand tile as one fully coalesced 1 KiB load straight into registers; no
 // LDS staging or transposition is needed anywhere on the streaming path.
 #include "kernels.h"
+#include "norm_factor.h"
 #include <hip/hip_ext.h>
 #include <cmath>
 #include <type_traits>
@@ -265,8 +266,7 @@ __device__ inline void epi_prefetch(EpiPre& p, const GemmOut& out, int task, int
 
 // Deferred RMSNorm: row factors from the producer's partial sums of squares [partial][row], in a fixed order.  A lane loads four
 // rows (lane % 4) of every 16th partial (lane / 4); the sixteen lanes of a row quad then add up theirs.
-// sum over the lanes of equal lane % 4, delivered to all of them: the butterfly of norm_factor_kernel (neighbours first, so that
-// both add in one order)
+// sum over the lanes of equal lane % 4, delivered to all of them, neighbours first
 __device__ inline float quad_lane_sum(float x) {
   typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
   x += __shfl_xor(x, 4, 64);
@@ -1057,53 +1057,6 @@ __global__ __launch_bounds__(64 * EE_REDUCE_TASKS) void gemm_rows_reduce_kernel(
   }
 }
 
-// per-row factor rsqrt(mean(x^2) + eps) from the producer's per-tile partial sums of squares, in a fixed order: 64 chains (chain t takes
-// partials t, t + 64, t + 128, ... in turns of four), then a tree over neighbouring chains.  A workgroup takes 64 rows, a lane each, so that a
-// load is 256 bytes in a row, and its sixteen waves four chains each with all loads in flight: what bounds it is two trips to memory (a wave
-// per row, lanes along the partials, read sixteen bytes of every line: 4096 rows 8.7 us, 4.9 now; 2048 rows 5.8; 1096 rows 4.8, 4.6; the same bits).
-__global__ __launch_bounds__(1024) void norm_factor_kernel(const float* __restrict__ ssq, int n_part, int stride, float inv_d, float eps,
-                                                           float* __restrict__ inv_rms, int M) {
-  __shared__ float sum[16][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, row = blockIdx.x * 64 + lane;
-  const float* p = ssq + min(row, M - 1);
-  float s[4][4];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) s[c][0] = s[c][1] = s[c][2] = s[c][3] = 0.f;
-  int i0 = 4 * wave;
-  for (; i0 + 3 + 192 < n_part; i0 += 256) {
-    float x[4][4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) x[c][j] = p[(size_t)(i0 + c + 64 * j) * stride];
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) s[c][j] += x[c][j];
-  }
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    int i = i0 + c;
-    for (; i + 192 < n_part; i += 256) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) s[c][j] += p[(size_t)(i + 64 * j) * stride];
-    }
-    for (; i < n_part; i += 64) s[c][0] += p[(size_t)i * stride];
-    s[c][0] = (s[c][0] + s[c][1]) + (s[c][2] + s[c][3]);
-  }
-  sum[wave][lane] = (s[0][0] + s[1][0]) + (s[2][0] + s[3][0]);
-  __syncthreads();
-  if (wave || row >= M) return;
-  float t[16];
-#pragma unroll
-  for (int w = 0; w < 16; ++w) t[w] = sum[w][lane];
-#pragma unroll
-  for (int n = 8; n >= 1; n >>= 1)
-#pragma unroll
-    for (int w = 0; w < n; ++w) t[w] = t[2 * w] + t[2 * w + 1];
-  inv_rms[row] = 1.0f / sqrtf(t[0] * inv_d + eps);
-}
-
 size_t bf16_gemm_rows_scratch_floats(int ntiles, int ktiles) {
   const int ks = rows_ksplit(ntiles, ktiles);
   return ks > 1 ? (size_t)ks * ntiles * 32 * 256 : 0;       // [k share][weight tile][up to 32 row tiles][64 lanes x 4]
@@ -1322,7 +1275,7 @@ int bf16_gemm_rows(hipStream_t st, int epi, const bf16_t* W, int ntiles, int kti
     // beyond, too many workgroups would each read too many, and one launch reduces them to factors.  The blocked kernel reads
     // factors only, and a part of a blocked call may be as short as one row
     if (out.nin.ssq && (mc > 192 || blocked)) {
-      hipLaunchKernelGGL(norm_factor_kernel, dim3(ceil_div(mc, 64)), dim3(1024), 0, st, out.nin.ssq + m0, out.nin.n_part, out.nin.stride,
+      hipLaunchKernelGGL(norm_factor_kernel, dim3(ceil_div(mc, EE_NORM_ROWS)), dim3(1024), 0, st, out.nin.ssq + m0, out.nin.n_part, out.nin.stride,
                          out.nin.inv_d, out.nin.eps, inv_rms, mc);
       out.nin.inv_rms = inv_rms;
     }
