@@ -872,7 +872,7 @@ __device__ __forceinline__ void gemm_block_body(u32x4* ring, const uint4* __rest
   constexpr int WT = 2 * TN, TMW = TMT / 4, TILES = WT + TMT, STAGE = TILES * 64;
   static_assert(TMT % 4 == 0 && (EPI != EPI_SWIGLU || TMW % 2 == 0), "row tiles split four ways, and SwiGLU takes two at once");
   constexpr int S = (160 / TILES) & ~1;             // stages in the ring (even: fragments alternate between two register sets)
-  constexpr int NJ = (TILES + 7) / 8;               // requests per wave and stage at most: tiles wave, wave + 8, ... (weights first)
+  constexpr int NJ = block_requests(0, WT, TMT);    // requests per wave and stage at most
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   const int rq = wave_s >> 1, nh = wave_s & 1;
@@ -903,10 +903,11 @@ __device__ __forceinline__ void gemm_block_body(u32x4* ring, const uint4* __rest
     src[j] = (t < WT ? (const u32x4*)W + (paired ? paired_unit(lane, t) : lane) : (const u32x4*)A + act_unit(lane & 15, lane >> 4)) + tile * ktiles * 64;
   }
   // requests of this wave per stage: its tiles that exist and, among the row tiles, hold rows (a prefix of its list)
-  const int have = WT + mt_used;
-  int nreq = 0;
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) nreq += wave_s + 8 * j < have ? 1 : 0;
+  const int nreq = block_requests(wave_s, WT, mt_used);
+  // The wait chooses among the counts there are, no more: one branch more in every step of a light block (see block_full) costs 4-6 % of
+  // calls that end with one (8B gate/up in 12 x 16 tiles at 700 / 960 rows 161 / 238 us with it, 153 / 228 without, down in 16 x 16 at 900 rows 268 / 255).
+  constexpr int kLeast = block_requests(7, WT, FULL ? TMT : 1);
+  static_assert(kLeast >= 1 && NJ - kLeast <= 3, "waits for NJ, NJ - 1, NJ - 2 and kLeast requests a stage");
 #define BLK_REQUEST(slot_, kt_)                                                                               \
   do {                                                                                                        \
     const size_t k_ = (size_t)min(kt_, last) * 64;                                                            \
@@ -916,11 +917,10 @@ __device__ __forceinline__ void gemm_block_body(u32x4* ring, const uint4* __rest
   } while (0)
 #define BLK_WAIT(stages_)                                                                                     \
   do {                                                                                                        \
-    if ((FULL && TILES % 8 == 0) || nreq == NJ) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((stages_) * NJ)); \
-    else if (FULL || nreq == NJ - 1) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((stages_) * (NJ - 1)));      \
-    else if (nreq == NJ - 2) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((stages_) * (NJ - 2)));              \
-    else if (nreq == NJ - 3) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((stages_) * (NJ > 3 ? NJ - 3 : 0))); \
-    else __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));                                                     \
+    if (NJ == kLeast || nreq == NJ) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((stages_) * NJ));             \
+    else if (NJ - 1 == kLeast || nreq == NJ - 1) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((stages_) * (NJ - 1))); \
+    else if (NJ - 2 == kLeast || nreq == NJ - 2) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((stages_) * (NJ - 2))); \
+    else __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((stages_) * kLeast));                                    \
   } while (0)
   static_assert((S - 1) * NJ < 64, "the load counter has six bits");
   const u32x4* wl0 = ring + (nhv * TN) * 64 + lane;

@@ -118,6 +118,9 @@ __host__ __device__ inline int half_strip_at(int id, int i, int ns) {
 // pairs has as many as in a full block either way, and the full form has no conditions (8B O, 9 of 12 row tiles used: 52 us, 59 with them)
 __host__ __device__ constexpr bool block_full(int used, int rt) { return used > rt - 4; }
 
+// Tiles of a stage that a wave of such a block requests: wave, wave + 8, ... of the weight tiles and, behind them, the row tiles in use
+__host__ __device__ constexpr int block_requests(int wave, int wt, int used) { return (wt + used + 7 - wave) / 8; }
+
 // Order of the blocks of a blocked launch (gemm_block_kernel): an XCD (workgroup id mod 8) gets consecutive blocks of an order in which
 // `run` row blocks share a weight group before the next group follows.  The 32 blocks that it works on side by side cover run row
 // blocks and 32 / run weight groups, and run is chosen so that they are the least its L2 has to fetch: moving tiles is what takes the

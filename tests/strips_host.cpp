@@ -1,4 +1,4 @@
-// Host program behind test_strips_host.py: the launch shapes of the few-row GEMM and the order of the blocked one (csrc/strips.h).
+// Host program behind test_strips_host.py: the launch shapes of the few-row GEMM, the order and the requests of the blocked one (csrc/strips.h).
 //   strips_host                          every matrix of up to 4200 strips: prints the sizes whose shape or order breaks a rule
 //   strips_host NTILES KTILES M          prints "strips-per-wave waves K-parts" of that call, or "rows": not a call of this kernel
 #include "../paper_2510_01336_amd/csrc/strips.h"
@@ -37,6 +37,19 @@ int main(int argc, char** argv) {
           if (half_strip_at(id, i, ns) < nt) seen[half_strip_at(id, i, ns)] += i < ns - 1 ? 2 : 1;
       for (int t = 0; t < nt; ++t)
         if (seen[t] != 2) wrong(nt, kt, t, "strip not covered once");
+    }
+  // loads that the waves of a block wait for: every tile of a stage once, and no wave outside the counts that the kernel's waits know
+  for (auto f : {BlockPlace{16, 16}, BlockPlace{12, 16}, BlockPlace{8, 16}, BlockPlace{12, 12}, BlockPlace{8, 12}, BlockPlace{8, 8}})
+    for (int used = 1; used <= f.row; ++used) {
+      int n = 0;
+      for (int w = 0; w < 8; ++w) {
+        const int r = block_requests(w, f.col, used);
+        n += r;
+        if (w + 8 * (r - 1) >= f.col + used || w + 8 * r < f.col + used) wrong(f.col, f.row, used, "tile without a request, or a request without a tile");
+        if (r < block_requests(7, f.col, 1) || r > block_requests(0, f.col, f.row)) wrong(f.col, f.row, used, "a count that no wait is for");
+        if (used == f.row && r < block_requests(7, f.col, f.row)) wrong(f.col, f.row, used, "a count that no wait of a full block is for");
+      }
+      if (n != f.col + used) wrong(f.col, f.row, used, "requests");
     }
   for (int M = 1; M <= 4096; M += M % 16 == 1 ? 15 : 1)      // every block of a blocked launch exactly once
     for (int nt : {1, 16, 17, 128, 256, 384, 1546, 1792})
