@@ -1237,17 +1237,13 @@ static int rows_blocks_form(int ntiles, int ktiles, int M) {
 //     slower); not where a third row block of up to 128 rows would cost most of a second round of workgroups (8B gate/up at
 //     520 / 608 / 640 rows: 164 / 169 / 170 us blocked, 146 / 150 / 154 as 512 rows and the rest; the 70B one, whose blocks
 //     fill more than two rounds anyway, 488 blocked, 542 in parts)
-//   narrow ones: from 513 rows (8B O / QKV at 520 rows 35.9 / 39.3 us, in parts 40.0 / 54; 70B 92.9 / 102.8, 97.9 / 106.7).  A long K (more
-//     k-tiles than weight tiles) only where blocks of 8 weight tiles fill the chip, or lower ones fit one round of workgroups from 673
-//     rows: 8B down at 600 / 640 / 700 / 900 / 1024 rows 119 / 122 / 105 / 117 / 129 us in blocks, 102 / 105 / 110 / 141 / 145 as 512
-//     rows in K shares and the rest; 70B down at 520 / 700 / 900 rows 293 / 344 / 395 and 283 / 322 / 425.
+//   narrow ones: see blocks_serve_narrow
 // The hooks that force another form keep the parts.
 static bool runs_blocked(bool wide, int ntiles, int ktiles, int M) {
   if (g_block_tiles > 0) return true;
   if (wide) return g_rows_wide && M > 256 && ntiles >= 1536 && !(M > 512 && M <= 640 && 3 * ceil_div(ntiles, 16) <= 512);
   if (M <= 512 || g_rows_blocks_override >= 0) return false;
-  const int groups = ceil_div(ntiles, 8);
-  return ktiles <= ntiles || M > 1024 || groups * ceil_div(M, 256) >= 256 || (M > 672 && groups * ceil_div(M, 128) <= 256);
+  return blocks_serve_narrow(ntiles, ktiles, M);
 }
 
 bool bf16_takes_strips(int ntiles, int ktiles, int M) {

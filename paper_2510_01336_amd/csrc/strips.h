@@ -121,6 +121,25 @@ __host__ __device__ constexpr bool block_full(int used, int rt) { return used > 
 // Tiles of a stage that a wave of such a block requests: wave, wave + 8, ... of the weight tiles and, behind them, the row tiles in use
 __host__ __device__ constexpr int block_requests(int wave, int wt, int used) { return (wt + used + 7 - wave) / 8; }
 
+// Whether a narrow matrix (QKV, O, down, adapters) runs blocked at M > 512 rows, else as parts of 512 rows in K shares and the rest.  K up to N: always
+// (8B O / QKV at 520 rows 35.9 / 39.3 us, in parts 40.0 / 54; 70B 92.9 / 102.8, 97.9 / 106.7).  A longer K leaves few blocks with much to do: from 1025
+// rows, or where blocks of 8 weight tiles fill the chip; and where blocks of 128 rows fit one round, from the row count at which they are the
+// quicker ones.  They take the longer the more K exceeds N, and the less the emptier the last of them is (light: up to half), while K shares always
+// fill the chip.  Down, us, blocks / parts at 690, 736, 768, 784, 880, 928 rows:
+//   320 x 432 tiles  107 / 130, 123 / 136, 127 / 140
+//   192 x 256         62 / 71, 71 / 75, 74 / 77, 59 / 76, 74 / 82, 60 / 87
+//   256 x 448 (8B)   108 / 116, 124 / 122, 128 / 124, 104 / 126, 128 / 134, 111 / 140
+//   128 x 256         60 / 61, 70 / 64, 73 / 66, 57 / 66, 73 / 72, 57 / 75
+//   224 x 592        135 / 130, 156 / 134, 161 / 138, 134 / 140, 161 / 151, 133 / 157
+//   320 x 864        221 / 209, 230 / 216, 237 / 224; 70B down at 520 / 700 / 900 rows 293 / 283, 344 / 322, 395 / 425
+inline bool blocks_serve_narrow(int ntiles, int ktiles, int M) {
+  const int groups = ceil_div(ntiles, 8);
+  if (ktiles <= ntiles || M > 1024 || groups * ceil_div(M, 256) >= 256) return true;
+  const bool light = (M - 1) % 128 < 64;
+  const int first = 2 * ktiles <= 3 * ntiles ? 673 : ktiles < 2 * ntiles ? (light ? 673 : 769) : (light ? 769 : 897);
+  return M >= first && groups * ceil_div(M, 128) <= 256;
+}
+
 // Order of the blocks of a blocked launch (gemm_block_kernel): an XCD (workgroup id mod 8) gets consecutive blocks of an order in which
 // `run` row blocks share a weight group before the next group follows.  The 32 blocks that it works on side by side cover run row
 // blocks and 32 / run weight groups, and run is chosen so that they are the least its L2 has to fetch: moving tiles is what takes the

@@ -58,3 +58,20 @@ def test_calls_of_17_to_32_rows_get_the_quicker_kernel(strips_host, ntiles, ktil
 def test_shapes_of_the_gpu_tests(strips_host, ntiles, ktiles, few, more):
     got = [subprocess.run([strips_host, str(ntiles), str(ktiles), m], stdout=subprocess.PIPE, text=True, check=True).stdout.strip() for m in ("8", "18")]
     assert got == [few, more]
+
+
+# down projections of 600 to 1024 rows, the form that measured quicker
+@pytest.mark.parametrize("ntiles,ktiles,blocks,parts", [
+    (256, 448, [690, 784, 880, 928, 1024], [600, 736, 768]),
+    (320, 432, [690, 736, 768], [600]),
+    (192, 256, [690, 736, 768, 784, 880, 928], [600]),
+    (128, 256, [784, 832, 928, 1016], [600, 720, 736, 768]),
+    (224, 592, [784, 832, 928, 976], [600, 690, 720, 768, 880]),
+    (320, 864, [1025], [690, 736, 768, 1024]),
+    (512, 896, [900, 1024], [520, 700]),
+    (256, 128, [513, 1024], []),
+])
+def test_narrow_matrix_of_a_long_k_runs_in_the_quicker_form(strips_host, ntiles, ktiles, blocks, parts):
+    form = {rows: subprocess.run([strips_host, "narrow", str(ntiles), str(ktiles), str(rows)], stdout=subprocess.PIPE, text=True, check=True).stdout.strip()
+            for rows in blocks + parts}
+    assert form == {**{rows: "blocks" for rows in blocks}, **{rows: "parts" for rows in parts}}
