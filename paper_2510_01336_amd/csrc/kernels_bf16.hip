@@ -421,7 +421,7 @@ __device__ inline void epi_apply(const f32x4& acc0, float sc, const EpiPre& p, c
       ss += __shfl_xor(ss, 16, 64);
       ss += __shfl_xor(ss, 32, 64);
       if (ss_out) *ss_out = ss;                // (the caller adds up several tiles)
-      else if (g == 0) out.nout.ssq[(size_t)task * out.nout.stride + row] = ss;
+      else if (g == 0 && ok) out.nout.ssq[(size_t)task * out.nout.stride + row] = ss;      // (a full block may visit tiles without rows, see block_full)
     }
   } else if (EPI == EPI_SWIGLU || EPI == EPI_ROPE) {
     epi_apply_tiles<EPI, 2>(acc0, acc0, sc, p, out, task, row, ok, lane);
