@@ -812,8 +812,9 @@ def test_context_build_in_blocks_matches_the_512_row_passes(name, rows):
 ])
 @pytest.mark.parametrize("name", ["bf16_small", "bf16_rep3"])
 def test_last_layer_of_a_context_build_over_the_rows_that_are_read(name, lens, passes):
-    """A context build runs its last layer over the rows that end a prompt and the reported piece alone: first tokens and the reported
-    logits and hidden rows against the oracle, and every cached row of all layers through a decoding step behind it."""
+    """A context build runs its last layer over the rows that end a prompt and the reported piece alone: first tokens, the reported hidden
+    rows and every cached K and V row of all layers against the oracle, as a session is by default and once more with logits kept,
+    which are compared too, and a decoding step behind it."""
     import re
 
     import paper_2510_01336_amd as hs
@@ -821,15 +822,18 @@ def test_last_layer_of_a_context_build_over_the_rows_that_are_read(name, lens, p
     W = synth.WeightStore(cfg, 41)
     spec = eo.ModelSpec.from_config(cfg, round_mode="bf16")
     m = eo.EEModel(spec, W)
-    hidden, firsts, prompts = [], [], []
+    hidden, firsts, prompts, caches = [], [], [], []
     for b, n in enumerate(lens):
         for seed in range(40):
             prompt = synth.gen_prompt(cfg.vocab, n, 900 + 50 * b + seed)
-            x = m.run_layers(range(cfg.n_layers), m.embed(prompt), np.arange(n), eo.KVCache(spec, n))
+            cache = eo.KVCache(spec, n)
+            x = m.run_layers(range(cfg.n_layers), m.embed(prompt), np.arange(n), cache)
             logits = m.exit_logits(x[-1:])
             if eo.top2_margin(logits)[0] > 2 * MARGIN:
                 break
-        prompts.append(prompt); hidden.append(x); firsts.append(int(eo.argmax_rows(logits)[0]))
+        else:
+            raise AssertionError("no prompt whose first token is decided clearly")
+        caches.append(cache); prompts.append(prompt); hidden.append(x); firsts.append(int(eo.argmax_rows(logits)[0]))
     model = hs.Model(cfg, 41)
     least = None
     if passes:                                                 # the smallest arena: passes of 512 rows
@@ -837,8 +841,6 @@ def test_last_layer_of_a_context_build_over_the_rows_that_are_read(name, lens, p
             hs.Session(model, len(lens), max(lens) + 20, 8, arena_bytes=1 << 12)
         least = int(re.search(r"< (\d+)", str(e.value)).group(1))
     sess = hs.Session(model, len(lens), max(lens) + 20, 8, arena_bytes=least)
-    sess.enable_logits(True)
-    assert sess.prefill(prompts).tolist() == firsts
     # rows of the last pass in packing order, the last 512-row piece of them
     if not passes:
         rows = np.concatenate(hidden)
@@ -851,9 +853,16 @@ def test_last_layer_of_a_context_build_over_the_rows_that_are_read(name, lens, p
                 rows += list(hidden[b][done[b]:done[b] + n]); left[b] -= n; done[b] += n; room -= n
         rows = np.array(rows)
     want = rows[(len(rows) - 1) // 512 * 512:]
-    got = sess.last_hidden()
-    assert got.shape == want.shape
-    assert max_rel(got.astype(np.float64), want) <= TOL["bf16"]
+    for logits in (False, True):
+        sess.enable_logits(logits)
+        assert sess.prefill(prompts).tolist() == firsts
+        got = sess.last_hidden()
+        assert got.shape == want.shape
+        assert max_rel(got.astype(np.float64), want) <= TOL["bf16"]
+        for b, n in enumerate(lens):
+            for layer in range(cfg.n_layers):
+                gk, gv = sess.read_kv(b, layer, 0, n)
+                assert max_rel(gk, caches[b].K[layer]) <= TOL["bf16"] and max_rel(gv, caches[b].V[layer]) <= TOL["bf16"], (b, layer)
     assert max_rel(sess.last_logits().astype(np.float64), m.exit_logits(want)) <= TOL["bf16"]
     sess.decode_ar(1)
     step = sess.last_hidden(len(lens)).astype(np.float64)
