@@ -38,7 +38,7 @@ MODEL_SEED = 20251001
 # inside this script, so the line carries the figure of the committed profile of the same workload, named beside
 # it (`traffic_source`); a workload without such a profile reports null.
 MEASURED_TRAFFIC = {
-    "8b_b1_ctx2048_k8": (235_996_000, "profiles/hbm_traffic__8b_b1_ctx2048_k8.md"),
+    "8b_b1_ctx2048_k8": (236_010_000, "profiles/hbm_traffic__8b_b1_ctx2048_k8.md"),
 }
 CALIBRATION_COPY_BYTES = 1 << 30
 MFMA_TARGET_FRAC = 0.50          # the goal stated for the FFN / LM-head GEMMs at their compute-bound shapes

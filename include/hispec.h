@@ -297,7 +297,7 @@ int ee_debug_kernel_times(ee_session* s, int32_t* n_families, const char** names
  * rows and no K shares; row_tiles = 4, 8 or 16 forces the second form for every such call (104 and 108: blocks of 4
  * and 8 row tiles with eight instead of four weight tiles per workgroup), 0 the first, -1 restores the built-in
  * choice.  Values >= 0 also keep the narrow projections of calls beyond 512 rows in parts of 512 rows and the rest in
- * those forms; otherwise such calls run in blocks of 256 rows over the whole call where that is quicker.  Two more
+ * those forms; otherwise such calls run in blocks of 256, 192 or 128 rows over the whole call where that is quicker.  Two more
  * values choose the form of the wide projections (gate/up, exit head) beyond 256 rows: 1016 (the default) blocks of 256
  * rows where they are quicker, 1000 parts of up to 512 rows with eight weight tiles per workgroup.  Results of all forms agree to rounding order.
  * EE_ERR_ARG for any other value. */

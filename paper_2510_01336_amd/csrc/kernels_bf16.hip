@@ -853,17 +853,16 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(const uint4* __restrict_
 
 // ---------------------------------------------------------------------------------------------
 // Blocked GEMM for calls of more than 256 rows (context build, large batches): the ring of direct global->LDS stages of
-// the kernel above, but the rows are cut into blocks of 256 and the weights into groups of 2*TN tiles, and one launch covers
-// all blocks, each XCD on blocks that share weights and rows in its L2 (block_order).
-// (Blocks of 192 and 128 rows serve narrow matrices that would leave compute units idle, see kNarrowForms.)
+// the kernel above, but the rows are cut into blocks of 16*TMT and the weights into groups of 2*TN tiles, and one launch covers
+// all blocks, each XCD on blocks that share weights and rows in its L2 (block_order).  Gate/up and the exit head take blocks of 256 rows; narrow
+// matrices those of 256, 192 or 128 rows and 16, 12 or 8 weight tiles that fill the chip without K shares (kNarrowForms).
 // What bounds it: with sixteen weight tiles a k-tile is 1024 clocks of MFMAs per SIMD, 128 KiB of LDS traffic (1000 clocks)
-// and 32 KiB of requests, and the clock gives way under that load: 1361 TFLOP/s on the gate/up matrix at 4096 rows (707 us;
-// passes of 512 rows in the previous form 812 us), 1212-1245 at 2048 rows (386-397 us).  Narrow matrices take 12 or 8 weight tiles so that the
-// blocks of a pass fill the chip without K shares: QKV at 2048 rows 98 us (four passes of 512 rows 174), O 70 (127), down
-// 204 (300).
+// and 32 KiB of requests, and the clock gives way under that load: 8B gate/up at 4096 rows 672 us (1431 TFLOP/s), at 2048 rows 370 (1300), at
+// 512 rows in the row-tiled kernel 96 (1253).  (Layers without sampling or profiler on one card; under the profiler, and on other cards, up to 6 % longer.)
 // K is never shared out: among calls that run blocked a row's sums run over K in one order, whatever the form and the row
 // count.  (Between kernels they do not: skinny, row-tiled and K-share sums differ in order, and the row count decides which
-// kernel a call gets.  Within the skinny kernel the order is the matrix's own below 128 MB, see strip_parts.)  K shares of the down projection measured 127 us against 154 at 1096 rows, nothing from 2048; shares
+// kernel a call gets.  Within the skinny kernel the order is the matrix's own below 128 MB, see strip_parts.)  K shares of the down projection, tried at
+// 1096 rows, were a sixth quicker there and no quicker from 2048; shares
 // whose number follows the row count moved the full-depth comparison of a batch with its sequences alone past its bound.
 // ---------------------------------------------------------------------------------------------
 template <int EPI, int TN, int TMT, bool FULL>

@@ -178,8 +178,8 @@ static int shape_session(ee_session* s, const ee_model* m, int batch, int max_ct
   s->B = batch; s->max_ctx = max_ctx; s->max_rows = max_rows;
   s->pps = ceil_div(max_ctx, EE_PAGE);
   s->n_pages = total_pages > 0 ? total_pages : batch * s->pps;
-  // context-build rows per pass: 4096 give the blocked GEMM whole rounds of 256 x 256 blocks (gate/up at the 8B width: 1361
-  // TFLOP/s against 1212-1245 at 2048 rows and 1150 at 512); no more than the sequences and the page pool can hold
+  // context-build rows per pass: 4096 give the blocked GEMM whole rounds of blocks (gate/up at the 8B width: a tenth more products a second
+  // than at 2048 rows, see gemm_block_kernel); no more than the sequences and the page pool can hold
   const long held = std::min((long)batch * max_ctx, (long)s->n_pages * EE_PAGE);
   s->chunk = m->bf16 ? (int)std::max<long>(kLeastPassRows, std::min<long>(most_rows, (held + 511) / 512 * 512)) : 64;
   s->headM = std::max(batch * max_rows, m->bf16 ? 512 : 64);

@@ -144,8 +144,9 @@ inline bool blocks_serve_narrow(int ntiles, int ktiles, int M) {
 // `run` row blocks share a weight group before the next group follows.  The 32 blocks that it works on side by side cover run row
 // blocks and 32 / run weight groups, and run is chosen so that they are the least its L2 has to fetch: moving tiles is what takes the
 // clock away (without its requests the gate/up kernel at 4096 rows runs at 1.91 GHz instead of 1.74).  All row blocks in one run / in runs
-// as chosen, us: 4096 rows gate/up 707 / 694, QKV 208 / 199, O 126 / 119; 2048 rows gate/up 388 / 390.  With a light last row block all are in
-// one run: else only some XCDs would get those (8B O at 1800 rows 62.4 / 65.0, 2400 rows 111 / 112).
+// as chosen, 8B, us: 4096 rows gate/up 683 / 672, QKV 197 / 184, O 141 / 135, down 357 / 345; 3072 rows 544 / 541, 145 / 136, 116 / 110, 317 / 304; 2048
+// rows QKV 94 / 93, O 72 / 70, down 199 / 195 (gate/up stays in one run there).  With a light last row block all are in one run: else only some
+// XCDs would get those (8B O at 1800 rows 62.4 / 65.0, 2400 rows 111 / 112).
 struct BlockOrder { int cols, rblocks, run, share; };      // weight groups, row blocks, row blocks of a run, blocks of an XCD
 inline BlockOrder block_order(int ntiles, int M, int wt, int rt) {
   const int rblocks = ceil_div(M, 16 * rt);
