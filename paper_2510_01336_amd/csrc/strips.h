@@ -121,6 +121,52 @@ __host__ __device__ constexpr bool block_full(int used, int rt) { return used > 
 // Tiles of a stage that a wave of such a block requests: wave, wave + 8, ... of the weight tiles and, behind them, the row tiles in use
 __host__ __device__ constexpr int block_requests(int wave, int wt, int used) { return (wt + used + 7 - wave) / 8; }
 
+// Forms of the blocked kernel: weight and row tiles per workgroup, with the time of one k-tile when all compute units are busy, the
+// share of it that is left when few are (%; the clock gives way under load), and the time of a block's start and end, in ns.
+// Gate/up and the head, whose 1536 and more weight tiles always fill the chip, from sweeps over 8B shapes on random operands (gate/up at
+// 4096 rows 705 us with 16 weight tiles, 798 with 12).  Their narrow blocks of rows lose: gate/up at 1096 rows 258 (16 x 16), 264 (16 x 8).
+// Of 294 gate/up calls of six widths from 520 to 4096 rows the model names the quicker of the two forms or one within 3.5 % (0.05 % on average); with
+// a light row block at a third of a step and its share of the rest it took up to 18 % longer (8B at 1040 rows 208 us in 12 weight tiles, 224 in 16;
+// 70B at 576 rows 480 in 16, 530 in 12).
+// Narrow matrices (QKV, O, down, adapters) from six forms x 49 calls of 520 to 4096 rows at ten widths (1B to 70B).  The form it names takes 0.1 %
+// longer than the quickest one on average and 7 % at most, also on 80 further row counts.  (Fitted to the 8B and 70B widths alone: 26 % at most, 384 x 512
+// tiles at 2600 rows 591 us in 16 x 16, 467 in 12 x 12; 320 x 432 at 1300 rows 184 in 12 x 12, 176 in 8 x 16.)  Small blocks cost more per product but let
+// such a matrix fill the chip -- us with 16 x 16, 12 x 16 and 8 x 16 tiles alone, and with all six: 8B O at 768 / 1024 / 1200 / 1536 rows 57.8 / 59.4 / 62.3 / 61.8,
+// 43.3 / 44.1 / 52.4 / 55.1; 8B down at 900 / 1152 rows 171 / 174, 117 / 152; 8B QKV at 600 / 960 / 1536 / 3072 rows 57 / 62 / 88 / 171, 43 / 55 / 73 / 145.
+struct BlockForm { int wt, rt, step, idle, ends; };
+inline constexpr BlockForm kWideForms[2] = {{16, 16, 740, 100, 6000}, {12, 16, 620, 100, 6000}};
+inline constexpr BlockForm kNarrowForms[6] = {{16, 16, 727, 50, 27500}, {12, 16, 585, 63, 20600}, {8, 16, 413, 57, 14900},
+                                          {12, 12, 448, 58, 16600}, {8, 12, 344, 59, 12300}, {8, 8, 261, 53, 8400}};
+constexpr int kCusPerXcd = 32;
+// Time of one launch by list scheduling of one XCD's blocks on its compute units (every XCD works on an equal run of
+// them, see the kernel); a light row block costs three quarters of a step and its share of the rest.
+inline int block_cost(const BlockForm& f, int ntiles, int ktiles, int M) {
+  const int rblocks = ceil_div(M, 16 * f.rt), n = ceil_div(ceil_div(ntiles, f.wt) * rblocks, 8);
+  const int used = ceil_div(M - (rblocks - 1) * 16 * f.rt, 16);
+  const int step = f.step * (f.idle + (100 - f.idle) * n / (kCusPerXcd * ceil_div(n, kCusPerXcd))) / 100;
+  const int full = ktiles * step + f.ends, part = block_full(used, f.rt) ? full : ktiles * (step * 3 / 4 + step * used / (4 * f.rt)) + f.ends;
+  int free_at[kCusPerXcd] = {0}, end = 0;
+  for (int i = 0; i < n; ++i) {
+    int c = 0;
+    for (int k = 1; k < kCusPerXcd; ++k)
+      if (free_at[k] < free_at[c]) c = k;
+    free_at[c] += i % rblocks == rblocks - 1 ? part : full;
+    end = std::max(end, free_at[c]);
+  }
+  return end;
+}
+// Form of a blocked call: the cheapest by this model
+inline const BlockForm& block_form(bool wide, int ntiles, int ktiles, int M) {
+  const BlockForm* forms = wide ? kWideForms : kNarrowForms;
+  const BlockForm* best = forms;
+  int least = 0;
+  for (int i = 0; i < (wide ? 2 : 6); ++i) {
+    const int cost = block_cost(forms[i], ntiles, ktiles, M);
+    if (!i || cost < least) { best = forms + i; least = cost; }
+  }
+  return *best;
+}
+
 // Whether a narrow matrix (QKV, O, down, adapters) runs blocked at M > 512 rows, else as parts of 512 rows in K shares and the rest.  K up to N: always
 // (8B O / QKV at 520 rows 35.9 / 39.3 us, in parts 40.0 / 54; 70B 92.9 / 102.8, 97.9 / 106.7).  A longer K leaves few blocks with much to do: from 1025
 // rows, or where blocks of 8 weight tiles fill the chip; and where blocks of 128 rows fit one round, from the row count at which they are the

@@ -1,5 +1,6 @@
 // Host program behind test_strips_host.py: the launch shapes of the few-row GEMM, the order and the requests of the blocked one (csrc/strips.h).
 //   strips_host                          every matrix of up to 4200 strips: prints the sizes whose shape or order breaks a rule
+//   strips_host gateup|other NTILES KTILES M   prints "weight-tiles row-tiles" of a workgroup of that blocked call
 //   strips_host narrow NTILES KTILES M   prints "blocks" or "parts": form of a narrow matrix at more than 512 rows
 //   strips_host NTILES KTILES M          prints "strips-per-wave waves K-parts" of that call, or "rows": not a call of this kernel
 #include "../paper_2510_01336_amd/csrc/strips.h"
@@ -11,6 +12,11 @@ int main(int argc, char** argv) {
     const StripShape s = strip_shape(atoi(argv[1]), atoi(argv[2]), atoi(argv[3]));
     if (!strips_serve(atoi(argv[1]), atoi(argv[2]), atoi(argv[3]))) printf("rows\n");
     else printf("%d %d %d\n", s.ns, s.nw, s.ksplit);
+    return 0;
+  }
+  if (argc == 5 && argv[1][0] != 'n') {
+    const BlockForm& f = block_form(argv[1][0] == 'g', atoi(argv[2]), atoi(argv[3]), atoi(argv[4]));
+    printf("%d %d\n", f.wt, f.rt);
     return 0;
   }
   if (argc == 5) {

@@ -75,3 +75,15 @@ def test_narrow_matrix_of_a_long_k_runs_in_the_quicker_form(strips_host, ntiles,
     form = {rows: subprocess.run([strips_host, "narrow", str(ntiles), str(ktiles), str(rows)], stdout=subprocess.PIPE, text=True, check=True).stdout.strip()
             for rows in blocks + parts}
     assert form == {**{rows: "blocks" for rows in blocks}, **{rows: "parts" for rows in parts}}
+
+
+# blocked calls whose forms measured furthest apart: us in the form named here, and in the one that a model fitted to two widths named
+@pytest.mark.parametrize("kind,ntiles,ktiles,rows,want", [
+    ("gateup", 1792, 128, 1040, "12 16"),               # 208, 224
+    ("gateup", 3584, 256, 576, "16 16"),                # 480, 530
+    ("other", 384, 512, 2600, "12 12"),                 # 467, 591
+    ("other", 320, 432, 1300, "8 16"),                  # 176, 184
+    ("other", 256, 448, 1096, "8 12"), ("other", 256, 448, 2048, "8 16"), ("other", 384, 128, 2048, "12 16"), ("other", 256, 448, 4096, "16 16"),
+])
+def test_form_of_a_blocked_call(strips_host, kind, ntiles, ktiles, rows, want):
+    assert subprocess.run([strips_host, kind, str(ntiles), str(ktiles), str(rows)], stdout=subprocess.PIPE, text=True, check=True).stdout.strip() == want
